@@ -72,7 +72,7 @@ struct GemmEpilogue {
     void *C;             // output, row stride ldc elements
     int64_t ldc;
     int out_f32;         // 1: C is float, 0: C has the storage dtype
-    int out_f16;         // with out_f32 = 1 and no residual/table (persistent kernel only): the float32 results (scaled, biased) leave as
+    int out_f16;         // with out_f32 = 1 and no residual/table (large products only): the float32 results (scaled, biased) leave as
                          // IEEE half precision, C is a half array (row stride ldc elements): the classifier's logits for the selection
     const float *resid;  // float32 [M, stride ldr] residual stream, added to the product (may alias C)
     int64_t ldr;
@@ -83,7 +83,7 @@ struct GemmEpilogue {
     int act;             // ACT_*
     const int32_t *ctx_len;  // launch_gemm_vt only: valid rows per request (NULL = all)
     int vt_S;                // launch_gemm_vt only: rows per request
-    // RMSNorm folded into the projections around it (persistent kernel only; launch_gemm fails if it cannot honour them):
+    // RMSNorm folded into the projections around it (large products only; launch_gemm fails if it cannot honour them):
     // writer side (out_f32 with resid or table, N % 256 == 0): besides C, write norm_out[row, col] = C[row, col] * norm_gain[col]
     // in the storage dtype (row stride norm_ld) and norm_ss[row * (N / 64) + col / 64] = sum of C^2 over those 64 columns
     // (launch_row_inv turns them into 1/rms per row); reader side: scale row r of the product by row_inv[r] before anything
@@ -93,7 +93,7 @@ struct GemmEpilogue {
     int64_t norm_ld;
     float *norm_ss;
     const float *row_inv;
-    // persistent kernel only (ignored elsewhere): the rows of A are requests of skip_S rows each of which only the first
+    // matrix-core kernels only (ignored elsewhere): the rows of A are requests of skip_S rows each of which only the first
     // skip_len[b] are valid; output tiles whose rows all lie in one request's padding are not computed (their C is not written)
     const int32_t *skip_len;
     int skip_S;
@@ -105,7 +105,7 @@ struct GemmEpilogue {
 // A row stride lda, W row stride ldw (elements).  dtype: storage type of A, W (and C unless out_f32).
 int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                 const GemmEpilogue &epi, hipStream_t st);
-// true if launch_gemm would run this product on the persistent kernel (the one that supports the folded RMSNorm)
+// true if this product is one of the large class, which folds the RMSNorm and writes half-precision logits
 bool gemm_on_persistent_kernel(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                                const GemmEpilogue &epi);
 
@@ -115,7 +115,7 @@ int launch_gemm_f8(const void *A, int64_t lda, const float *a_scale, const void 
                    const GemmEpilogue &epi, hipStream_t st);
 bool gemm_f8_on_persistent_kernel(const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi);
 
-// batched small products (bf16 operands, 128x128 MFMA tiles): see gemm.hip
+// batched small products (bf16 operands): see gemm.hip
 int launch_gemm_batched(const void *A, int64_t lda, int64_t batch_a, const void *W, int64_t ldw, int64_t batch_w, void *C, int64_t ldc,
                         int64_t batch_c, int out_f32, int64_t M, int N, int K, int batch, const int32_t *batch_len, int len_bounds,
                         hipStream_t st);
@@ -194,7 +194,7 @@ int launch_select(const void *logits, int logits_f16, const float *cum, int B, i
 bool select_takes_f16(int V);
 
 // ---- optional per-kernel event timing ----------------------------------------
-enum KernelClass { KC_GEMM_256 = 0, KC_GEMM_128, KC_GEMM_SIMPLE, KC_XATTN_FLASH, KC_XATTN_SIMPLE, KC_SELF_STEP, KC_TRUNK_SELF,
+enum KernelClass { KC_GEMM_TILE = 0, KC_GEMM_SIMPLE, KC_XATTN_FLASH, KC_XATTN_SIMPLE, KC_SELF_STEP, KC_TRUNK_SELF,
                    KC_RMSNORM, KC_FUSE_GATE, KC_SELECT_ROWS, KC_SELECT_REQUEST, KC_GATHER, KC_BROADCAST, KC_V_TRANSPOSE, KC_GEMM_RING, KC_SOFTMAX, KC_GEMM_RING_F8, KC_QUANTIZE, KC_CONTEXT_ATTN, KC_COUNT };
 // Declared around a kernel launch: records an event before and (on scope exit) after it when timing is on.
 struct ProfScope {

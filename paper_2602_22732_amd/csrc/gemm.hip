@@ -7,9 +7,9 @@
 // ([out,in]), so both MFMA operands stream K-contiguous 16-byte chunks.
 //
 //  * gemm_simple<T>      64x64 tile, plain FMA, any shape; float32 path and fallback.
-//  * gemm_bf16_mfma<..>  bf16 operands, fp32 accumulation on the matrix cores with
-//                        v_mfma_f32_32x32x16_bf16; LDS double buffering with an
-//                        XOR swizzle of 16-byte chunks; XCD-aware tile order.
+//  * gemm_bf16_tile<..>  bf16 operands, fp32 accumulation on the matrix cores with
+//                        v_mfma_f32_32x32x16_bf16; 64x64 and 128x128 tiles for the
+//                        small and middle shapes, operands streamed into LDS.
 //  * gemm_bf16_ring<..>  the kernel of the large shapes: persistent, 256x256 tiles,
 //                        operands stream global -> LDS without passing registers.
 #include <string.h>
@@ -91,179 +91,15 @@ __global__ __launch_bounds__(256) void gemm_simple(const T *__restrict__ A, int6
         }
 }
 
-// ---------------------------------------------------------------------------
-// MFMA kernel (bf16)
-// ---------------------------------------------------------------------------
-// Block tile BM x BN, wave tile WM x WN, BK = 64 (one 128-byte row of bf16 per
-// tile row = 8 chunks of 16 bytes).  LDS holds two stages of (BM + BN) rows.
-// Chunk c of row r sits at slot c ^ ((r >> 1) & 7): the LDS serves 16 lanes x 16 bytes
-// per cycle from 64 banks, and the 16 rows such a group of lanes reads (or the 2 rows it
-// writes) then fall on 16 different 16-byte slots.  The next K tile travels
-// global -> registers while the current one is multiplied, then registers -> LDS.
-enum { EPI_STORE = 0, EPI_SILU, EPI_F32, EPI_F32_RESID, EPI_F32_TABLE, EPI_VT };  // EPI_VT: persistent kernel only
+// What a matrix-core kernel does with a product.  EPI_VT: transposed per request (context values); EPI_SILU / EPI_SILU_DIV: the
+// activation through the hardware reciprocal / through a division (they differ in the last bits; the row count of a product
+// decides, see launch_gemm, never the kernel that happens to run it).
+enum { EPI_STORE = 0, EPI_SILU, EPI_F32, EPI_F32_RESID, EPI_F32_TABLE, EPI_VT, EPI_SILU_DIV };
+__host__ __device__ constexpr bool kind_f32(int kind) { return kind == EPI_F32 || kind == EPI_F32_RESID || kind == EPI_F32_TABLE; }
 
 // bytes a bf16 GEMM must move once: both operands, the output, and the residual it adds
 static double gemm_bytes(int64_t M, int N, int K, bool out_f32, bool resid) {
     return 2.0 * ((double)M * K + (double)N * K) + (double)M * N * ((out_f32 ? 4 : 2) + (resid ? 4 : 0));
-}
-
-template <int BM, int BN, int WM, int WN, int KIND>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_bf16_mfma(const bf16 *__restrict__ A, int64_t lda,
-                                                                             const bf16 *__restrict__ W, int64_t ldw, int64_t M,
-                                                                             int N, int K, int64_t tiles_m, int tiles_n,
-                                                                             GemmEpilogue epi, int64_t batch_a, int64_t batch_w,
-                                                                             int64_t batch_c) {
-    // blockIdx.y: batch index; the operands and the output of batch i start batch_a/w/c elements further on
-    A += (int64_t)blockIdx.y * batch_a;
-    W += (int64_t)blockIdx.y * batch_w;
-    epi.C = (char *)epi.C + (int64_t)blockIdx.y * batch_c * (KIND >= EPI_F32 ? 4 : 2);
-    constexpr int WAVES_N = BN / WN;
-    constexpr int NT = (BM / WM) * (BN / WN) * 64;
-    constexpr int TM = WM / 32, TN = WN / 32;
-    constexpr int RPP = NT / 8;  // tile rows covered by one pass of all threads (8 threads per 128-byte row)
-    constexpr int A_PASSES = BM / RPP, W_PASSES = BN / RPP;
-    constexpr int STAGE_CHUNKS = (BM + BN) * 8;
-    static_assert(BM % RPP == 0 && BN % RPP == 0, "tile/threads mismatch");
-    extern __shared__ bf16x8 smem[];  // native vectors: arrays of them stay in registers
-
-    // XCD-aware order: consecutive workgroup ids land on different XCDs (each with
-    // its own L2), so give every XCD a contiguous range of tiles; inside the range
-    // the N index runs fastest so neighbouring tiles re-read the same rows of A.
-    const int64_t total = tiles_m * tiles_n;
-    const int64_t per_xcd = (total + 7) / 8;
-    const int64_t logical = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (logical >= total) return;
-    const int64_t m0 = (logical / tiles_n) * BM;
-    const int n0 = (int)(logical % tiles_n) * BN;
-    // batched launches may carry a valid length per batch: as a bound on N (columns from it on are never read by the
-    // consumer, so tiles wholly beyond it are skipped) or on K (the operands are zero from it on)
-    if (epi.batch_len) {
-        int len = epi.batch_len[blockIdx.y];
-        len = len < 1 ? 1 : len;
-        if (epi.len_bounds == 1 && n0 >= len) return;
-        if (epi.len_bounds == 2 && len < K) K = (len + 63) / 64 * 64;
-    }
-
-    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int lc = tid % 8, lr = tid / 8;
-
-    // global source of this thread's chunks (rows past the end re-read the last row; never stored)
-    const bf16 *a_src[A_PASSES];
-    const bf16 *w_src[W_PASSES];
-#pragma unroll
-    for (int i = 0; i < A_PASSES; i++) {
-        int64_t r = m0 + lr + i * RPP;
-        a_src[i] = A + (r < M ? r : M - 1) * lda + lc * 8;
-    }
-#pragma unroll
-    for (int i = 0; i < W_PASSES; i++) {
-        int64_t r = (int64_t)n0 + lr + i * RPP;
-        w_src[i] = W + (r < N ? r : N - 1) * ldw + lc * 8;
-    }
-    // LDS slot of this thread's chunks (same for every stage): row r, chunk lc ^ ((r >> 1) & 7); RPP is a multiple of 16
-    const int st_slot = lr * 8 + (lc ^ ((lr >> 1) & 7));
-
-    bf16x8 a_reg[A_PASSES], w_reg[W_PASSES];
-#pragma unroll
-    for (int i = 0; i < A_PASSES; i++) a_reg[i] = *(const bf16x8 *)(a_src[i]);
-#pragma unroll
-    for (int i = 0; i < W_PASSES; i++) w_reg[i] = *(const bf16x8 *)(w_src[i]);
-
-    floatx16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-#pragma unroll
-            for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
-
-    {
-        bf16x8 *sa = smem, *sw = smem + BM * 8;
-#pragma unroll
-        for (int i = 0; i < A_PASSES; i++) sa[st_slot + i * RPP * 8] = a_reg[i];
-#pragma unroll
-        for (int i = 0; i < W_PASSES; i++) sw[st_slot + i * RPP * 8] = w_reg[i];
-    }
-    __syncthreads();
-
-    const int frow = lane % 32, fhalf = lane / 32;
-    // fragment read slots: row r = base + frow, chunk (2*kk + fhalf) ^ ((r >> 1) & 7); tile bases are multiples of 32
-    int a_slot[TM], w_slot[TN];
-#pragma unroll
-    for (int i = 0; i < TM; i++) a_slot[i] = (wm * WM + i * 32 + frow) * 8;
-#pragma unroll
-    for (int j = 0; j < TN; j++) w_slot[j] = (BM + wn * WN + j * 32 + frow) * 8;
-    const int fx = (frow >> 1) & 7;
-
-    const int KT = K / 64;
-    for (int kt = 0; kt < KT; kt++) {
-        const bool more = kt + 1 < KT;
-        if (more) {
-            const int k0 = (kt + 1) * 64;
-#pragma unroll
-            for (int i = 0; i < A_PASSES; i++) a_reg[i] = *(const bf16x8 *)(a_src[i] + k0);
-#pragma unroll
-            for (int i = 0; i < W_PASSES; i++) w_reg[i] = *(const bf16x8 *)(w_src[i] + k0);
-        }
-        const bf16x8 *s = smem + (kt & 1) * STAGE_CHUNKS;
-#pragma unroll
-        for (int kk = 0; kk < 4; kk++) {
-            const int ch = (2 * kk + fhalf) ^ fx;
-            bf16x8 af[TM], wf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; i++) {
-                af[i] = s[a_slot[i] + ch];
-            }
-#pragma unroll
-            for (int j = 0; j < TN; j++) {
-                wf[j] = s[w_slot[j] + ch];
-            }
-#pragma unroll
-            for (int i = 0; i < TM; i++)
-#pragma unroll
-                for (int j = 0; j < TN; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], wf[j], acc[i][j], 0, 0, 0);
-        }
-        if (more) {
-            bf16x8 *sa = smem + ((kt + 1) & 1) * STAGE_CHUNKS, *sw = sa + BM * 8;
-#pragma unroll
-            for (int i = 0; i < A_PASSES; i++) sa[st_slot + i * RPP * 8] = a_reg[i];
-#pragma unroll
-            for (int i = 0; i < W_PASSES; i++) sw[st_slot + i * RPP * 8] = w_reg[i];
-        }
-        __syncthreads();
-    }
-
-    // Accumulator layout of the 32x32 MFMA: lane -> column lane%32, register v -> row 8*(v/4) + 4*(lane/32) + v%4.
-    // For one register the 32 lanes of a half-wave write 32 consecutive columns of one row.
-    const int64_t row_base = m0 + wm * WM + 4 * fhalf;
-    const int col_base = n0 + wn * WN + frow;
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-            const int col = col_base + j * 32;
-            if (col >= N) continue;
-            const float bias = (KIND == EPI_F32 && epi.bias) ? epi.bias[col] : 0.0f;
-#pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const int64_t row = row_base + i * 32 + 8 * (v / 4) + (v % 4);
-                if (row >= M) continue;
-                float x = acc[i][j][v];
-                if (KIND == EPI_STORE) {
-                    ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)x;
-                } else if (KIND == EPI_SILU) {
-                    ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)(x / (1.0f + __expf(-x)));
-                } else if (KIND == EPI_F32) {
-                    ((float *)epi.C)[row * epi.ldc + col] = x + bias;
-                } else if (KIND == EPI_F32_RESID) {
-                    ((float *)epi.C)[row * epi.ldc + col] = x + epi.resid[row * epi.ldr + col];
-                } else {
-                    const int64_t tr = epi.tok ? (int64_t)epi.tok[row] : 0;
-                    ((float *)epi.C)[row * epi.ldc + col] = x + epi.table[tr * N + col];
-                }
-            }
-        }
 }
 
 // ---------------------------------------------------------------------------
@@ -621,7 +457,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
         // ---- epilogue: slots sa (waves 0..3) and sa+1 (waves 4..7) are free, 8 KB per wave ----
         const int sw = sa + 1 >= RING_SLOTS ? sa + 1 - RING_SLOTS : sa + 1;
         {
-            constexpr bool OUT_F32 = KIND >= EPI_F32 && KIND != EPI_VT;
+            constexpr bool OUT_F32 = kind_f32(KIND);
             char *stage = (char *)(smem + (wave < 4 ? sa : sw) * SLOT_CHUNKS) + (wave % 4) * 8192;
             const int64_t wrow0 = m0 + wm * 128;
             const int wcol0 = n0 + wn * 64;
@@ -689,7 +525,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
 #pragma unroll
                                 for (int e = 0; e < 4; e++) {
                                     const float x = acc[pass * 2 + ii][j][4 * g + e];
-                                    pk[e] = (bf16)(KIND == EPI_SILU ? fast_silu(x) : x);
+                                    pk[e] = (bf16)(KIND == EPI_SILU ? fast_silu(x) : KIND == EPI_SILU_DIV ? x / (1.0f + __expf(-x)) : x);
                                 }
                                 const int c = j * 4 + g;
                                 *(bf16x4 *)(stage + r * 128 + ((c ^ (r & 7)) * 16) + hf * 8) = pk;
@@ -912,7 +748,7 @@ static int launch_ring_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t l
     {
         const double operand_bytes = F8 ? ((double)M * K + (double)N * K) : 0.0;  // FP8 operands are half the bytes gemm_bytes counts
         ProfScope ps(F8 ? KC_GEMM_RING_F8 : KC_GEMM_RING, st, 2.0 * (double)M * N * K,
-                     gemm_bytes(M, N, K, KIND >= EPI_F32 && KIND != EPI_VT && !epi.out_f16, KIND == EPI_F32_RESID) - operand_bytes);
+                     gemm_bytes(M, N, K, kind_f32(KIND) && !epi.out_f16, KIND == EPI_F32_RESID) - operand_bytes);
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), RING_LDS_BYTES, st, A, lda, W, ldw, M, N, K, tiles_m, tiles_n, 4, epi);
     }
     GR4AD_LAUNCH_CHECK();
@@ -922,7 +758,7 @@ static int launch_ring_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t l
 // The persistent kernel stores 16-byte pieces: it needs 16-byte aligned rows of C (and of what the epilogue adds),
 // at least three k-tiles, and row pitches whose byte offsets inside a 256-row block fit 32 bits.
 static bool ring_ok(int kind, int N, int K, int64_t lda, int64_t ldw, const GemmEpilogue &e) {
-    const bool f32 = kind >= EPI_F32;
+    const bool f32 = kind_f32(kind);
     if (e.skip_len && e.skip_S < 1) return false;
     if (K < 192 || lda >= (1 << 22) || ldw >= (1 << 22)) return false;
     if (e.out_f16 && kind != EPI_F32) return false;
@@ -938,6 +774,15 @@ static bool ring_ok(int kind, int N, int K, int64_t lda, int64_t ldw, const Gemm
     return true;
 }
 
+// the staged epilogue of the tile kernel stores 16-byte pieces like the persistent kernel's
+static bool tile_staged_ok(int kind, int N, const GemmEpilogue &e) {
+    const bool f32 = kind_f32(kind);
+    if (e.ldc % (f32 ? 4 : 8) || ((uintptr_t)e.C % 16) || N % (f32 ? 4 : 8)) return false;
+    if (kind == EPI_F32 && e.bias && ((uintptr_t)e.bias % 16)) return false;
+    if (kind == EPI_F32_RESID && (e.ldr % 4 || ((uintptr_t)e.resid % 16))) return false;
+    return kind != EPI_F32_TABLE || ((uintptr_t)e.table % 16) == 0;
+}
+
 static int launch_ring(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
                        hipStream_t st) {
     switch (kind) {
@@ -946,6 +791,7 @@ static int launch_ring(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, i
         case EPI_F32: return launch_ring_kind<EPI_F32>(A, lda, W, ldw, M, N, K, epi, st);
         case EPI_F32_RESID: return launch_ring_kind<EPI_F32_RESID>(A, lda, W, ldw, M, N, K, epi, st);
         case EPI_VT: return launch_ring_kind<EPI_VT>(A, lda, W, ldw, M, N, K, epi, st);
+        case EPI_SILU_DIV: return launch_ring_kind<EPI_SILU_DIV>(A, lda, W, ldw, M, N, K, epi, st);
         default: return launch_ring_kind<EPI_F32_TABLE>(A, lda, W, ldw, M, N, K, epi, st);
     }
 }
@@ -961,46 +807,416 @@ static int epilogue_kind(const GemmEpilogue &e) {
     return -1;
 }
 
-template <int BM, int BN, int WM, int WN, int KIND>
-static int launch_mfma_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi,
+// ---------------------------------------------------------------------------
+// MFMA kernel of the small and middle shapes: one output tile per workgroup, ring of ST k-tiles in LDS
+// ---------------------------------------------------------------------------
+// The persistent kernel needs about one 256x256 tile per compute unit; a decode of a few requests has products of 1 to a few
+// thousand rows, whose time is the latency of one tile.  So the tiles are small (32x32 to 128x128, one wave tile of WT x WT per
+// wavefront) to spread over the chip, and the operands of the next ST - 1 k-tiles (64 values of k) are always in flight, straight
+// from global memory into LDS (up to K = 64 * ST the whole operand slab is requested at once): one memory latency per tile instead
+// of one per k-tile.  Same LDS geometry as the persistent kernel: 128-byte rows, chunk c of row r at position c ^ ((r >> 1) & 7).
+// One barrier per k-tile, in its middle: the fragments of k-steps 2 and 3 have been read by then, so the slot is free for k-tile
+// kt + ST, and the first fragments of the next k-tile are read under the MFMAs of steps 2 and 3.  A product of one C element is the
+// same sequence of v_mfma_f32_32x32x16 over k as in the persistent kernel: the two give the same bits.
+// STAGED (WT = 64, N and C aligned): operands swapped, C leaves through LDS in 16-byte pieces of whole rows, with everything the
+// persistent kernel's epilogue offers.  Otherwise a lane stores the 16 rows of its column directly (64 or 128 bytes per half
+// wavefront and register), any N and pitch; EPI_VT swaps the operands so that these are 32 consecutive tokens of a column.
+template <int KIND, int TM>
+__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
+                                                const GemmEpilogue &epi, int lane) {
+    const int frow = lane % 32, hf = lane / 32;
+    if (epi.row_inv) {  // folded RMSNorm, reader side: a lane owns row frow of each 32-row block
+#pragma unroll
+        for (int i = 0; i < TM; i++) {
+            const int64_t row = wrow0 + i * 32 + frow;
+            const float f = epi.row_inv[row < M ? row : M - 1];
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) acc[i][j][v] *= f;
+        }
+    }
+    if (!kind_f32(KIND)) {
+        // passes of 64 rows x 64 columns: 128-byte rows of 8 chunks, chunk c of row r at position c ^ (r & 7)
+#pragma unroll
+        for (int pass = 0; pass < TM / 2; pass++) {
+#pragma unroll
+            for (int ii = 0; ii < 2; ii++) {
+                const int r = ii * 32 + frow;
+#pragma unroll
+                for (int j = 0; j < 2; j++)
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        bf16x4 pk;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            const float x = acc[pass * 2 + ii][j][4 * g + e];
+                            pk[e] = (bf16)(KIND == EPI_SILU ? fast_silu(x) : KIND == EPI_SILU_DIV ? x / (1.0f + __expf(-x)) : x);
+                        }
+                        const int c = j * 4 + g;
+                        *(bf16x4 *)(stage + r * 128 + ((c ^ (r & 7)) * 16) + hf * 8) = pk;
+                    }
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // wave-private region: no barrier needed
+            const char *rd = stage + (lane / 8) * 128 + (((lane % 8) ^ ((lane / 8) & 7)) * 16);
+            const int64_t row0 = wrow0 + pass * 64 + lane / 8;
+            const int col = wcol0 + (lane % 8) * 8;
+            bf16 *wr = (bf16 *)epi.C + row0 * epi.ldc + col;
+#pragma unroll
+            for (int it = 0; it < 8; it++)
+                if (row0 + it * 8 < M && col < N) *(bf16x8 *)(wr + (int64_t)(it * 8) * epi.ldc) = *(const bf16x8 *)(rd + it * 1024);
+            if (pass + 1 < TM / 2) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+    } else {
+        // passes of 32 rows x 64 columns: 256-byte rows of 16 chunks, chunk c of row r at position c ^ (r & 15)
+        const int erow = lane / 16, ecol = wcol0 + (lane % 16) * 4;
+        const bool emit = KIND != EPI_F32 && epi.norm_out != nullptr;  // folded RMSNorm, writer side (N % 256 == 0)
+        floatx4 bias4 = {0.0f, 0.0f, 0.0f, 0.0f}, gain4 = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (KIND == EPI_F32 && epi.bias && ecol < N) bias4 = *(const floatx4 *)(epi.bias + ecol);
+        if (emit) {
+            const bf16x4 g4 = *(const bf16x4 *)((const bf16 *)epi.norm_gain + ecol);
+#pragma unroll
+            for (int e = 0; e < 4; e++) gain4[e] = (float)g4[e];
+        }
+#pragma unroll
+        for (int pass = 0; pass < TM; pass++) {
+            floatx4 adds[8];
+#pragma unroll
+            for (int it = 0; it < 8; it++) {
+                const int64_t row = wrow0 + pass * 32 + it * 4 + erow;
+                adds[it] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (KIND != EPI_F32 && row < M && ecol < N) {
+                    if (KIND == EPI_F32_RESID) adds[it] = *(const floatx4 *)(epi.resid + row * epi.ldr + ecol);
+                    else adds[it] = *(const floatx4 *)(epi.table + (epi.tok ? (int64_t)epi.tok[row] : 0) * N + ecol);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) {
+                    floatx4 pk;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) pk[e] = acc[pass][j][4 * g + e];
+                    const int c = j * 8 + g * 2 + hf;
+                    *(floatx4 *)(stage + frow * 256 + ((c ^ (frow & 15)) * 16)) = pk;
+                }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int it = 0; it < 8; it++) {
+                const int rr = it * 4 + erow, c = lane % 16;
+                floatx4 x = *(const floatx4 *)(stage + rr * 256 + ((c ^ (rr & 15)) * 16));
+                const int64_t row = wrow0 + pass * 32 + rr;
+                if (KIND != EPI_F32) x += adds[it];
+                if (emit) {  // sum of squares over the row's 64 columns of this wavefront: the same tree as in the persistent kernel
+                    float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+                    sq += __shfl_xor(sq, 1, 64);
+                    sq += __shfl_xor(sq, 2, 64);
+                    sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x114, 0xf, 0xf, true));
+                    sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x118, 0xf, 0xf, true));
+                    if (lane % 16 == 15 && row < M) epi.norm_ss[row * (N / 64) + (wcol0 >> 6)] = sq;
+                }
+                if (row < M && ecol < N) {
+                    if (KIND == EPI_F32) x += bias4;
+                    if (KIND == EPI_F32 && epi.out_f16) {
+                        halfx4 hx;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) hx[e] = (_Float16)x[e];
+                        *(halfx4 *)((_Float16 *)epi.C + row * epi.ldc + ecol) = hx;
+                    } else {
+                        *(floatx4 *)((float *)epi.C + row * epi.ldc + ecol) = x;
+                    }
+                    if (emit) {
+                        bf16x4 nb;
+#pragma unroll
+                        for (int e = 0; e < 4; e++) nb[e] = (bf16)(x[e] * gain4[e]);
+                        *(bf16x4 *)((bf16 *)epi.norm_out + row * epi.norm_ld + ecol) = nb;
+                    }
+                }
+            }
+            if (pass < TM - 1) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+    }
+}
+
+// One wave tile of 32 x 32 accumulators at (row0, col0), operands in natural order (a lane owns column lane % 32 and, per register v,
+// row 8 * (v / 4) + 4 * (lane / 32) + v % 4); EPI_VT: swapped (a lane owns row lane % 32 and 16 columns).
+// What the epilogue adds to the 16 elements of a lane; rows and columns past the edge read inside the arrays and are dropped.
+template <int KIND>
+__device__ __forceinline__ void direct_addends(float (&add)[16], int64_t row0, int col0, int64_t M, int N, const GemmEpilogue &epi, int lane) {
+    if (KIND != EPI_F32_RESID && KIND != EPI_F32_TABLE) return;
+    const int hf = lane / 32, c = col0 + lane % 32, col = c < N ? c : N - 1;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+        const int64_t r = row0 + 4 * hf + 8 * (v / 4) + (v % 4), row = r < M ? r : M - 1;
+        if (KIND == EPI_F32_RESID) add[v] = epi.resid[row * epi.ldr + col];
+        else add[v] = epi.table[(epi.tok ? (int64_t)epi.tok[row] : 0) * N + col];
+    }
+}
+
+template <int KIND>
+__device__ __forceinline__ void direct_epilogue(const floatx16 &acc, const float (&add)[16], int64_t row0, int col0, int64_t M, int N,
+                                                const GemmEpilogue &epi, int lane) {
+    const int frow = lane % 32, hf = lane / 32;
+    if (KIND == EPI_VT) {
+        // out[(b*N + n) * ldc + s] for token s of request b: zero from the request's length on; where S is no multiple of 64, the
+        // request's first tokens also clear the padding columns S .. ldc - 1
+        const int64_t row = row0 + frow;
+        if (row >= M) return;
+        const int64_t b = row / epi.vt_S;
+        const int s = (int)(row - b * epi.vt_S);
+        int len = epi.ctx_len ? epi.ctx_len[b] : epi.vt_S;
+        len = len < 1 ? 1 : (len > epi.vt_S ? epi.vt_S : len);
+        const int pad = (int)epi.ldc - epi.vt_S;
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            const int col = col0 + 8 * (v / 4) + 4 * hf + v % 4;
+            if (col < N) {
+                bf16 *o = (bf16 *)epi.C + (b * N + col) * epi.ldc;
+                o[s] = s < len ? (bf16)acc[v] : (bf16)0.0f;
+                if (s < pad) o[epi.vt_S + s] = (bf16)0.0f;
+            }
+        }
+        return;
+    }
+    const int col = col0 + frow;
+    if (col >= N) return;
+    const float bias = (KIND == EPI_F32 && epi.bias) ? epi.bias[col] : 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+        const int64_t row = row0 + 4 * hf + 8 * (v / 4) + (v % 4);
+        if (row >= M) continue;
+        const float x = acc[v];
+        if (KIND == EPI_STORE) ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)x;
+        else if (KIND == EPI_SILU) ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)fast_silu(x);
+        else if (KIND == EPI_SILU_DIV) ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)(x / (1.0f + __expf(-x)));
+        else if (KIND == EPI_F32) ((float *)epi.C)[row * epi.ldc + col] = x + bias;
+        else ((float *)epi.C)[row * epi.ldc + col] = x + add[v];
+    }
+}
+
+template <int BM, int BN, int WT, int ST, int KIND, bool STAGED>
+__global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(const bf16 *__restrict__ A, int64_t lda, const bf16 *__restrict__ W,
+                                                                             int64_t ldw, int64_t M, int N, int K, int tiles_m, int tiles_n,
+                                                                             GemmEpilogue epi, int64_t batch_a, int64_t batch_w, int64_t batch_c) {
+    constexpr int WAVES_N = BN / WT, NW = (BM / WT) * WAVES_N, T = WT / 32;
+    constexpr int LPW = (BM + BN) / 8 / NW;           // loads of a wavefront per k-tile (1 KB each: 8 rows)
+    constexpr int STAGE = (BM + BN) * 128;            // bytes of a k-tile
+    constexpr bool SWAP = STAGED || KIND == EPI_VT;   // W fragment first
+    static_assert((BM + BN) / 8 % NW == 0 && (ST - 1) * LPW <= 63 && ST >= 2, "load counts");
+    static_assert(!STAGED || WT == 64, "the staged epilogue takes 64 x 64 wave tiles");
+    extern __shared__ bf16x8 smem[];
+    const int tid = threadIdx.x, lane = tid % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    // blockIdx.y: batch index; the operands and the output of batch i start batch_a/w/c elements further on
+    A += (int64_t)blockIdx.y * batch_a;
+    W += (int64_t)blockIdx.y * batch_w;
+    epi.C = (char *)epi.C + (int64_t)blockIdx.y * batch_c * (kind_f32(KIND) ? 4 : 2);
+    // XCD-aware order: consecutive workgroup ids land on different XCDs (each with its own L2), so every XCD gets a contiguous range
+    // of tiles, walked in groups of 8 row blocks (rows fastest): the tiles in flight on an XCD share their A and W blocks
+    const uint32_t total = (uint32_t)tiles_m * (uint32_t)tiles_n, per_xcd = (total + 7) / 8;
+    const uint32_t l = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || l >= total) return;
+    const uint32_t gsz = 8u * (uint32_t)tiles_n, grp = l / gsz, in = l - grp * gsz;
+    const uint32_t left = (uint32_t)tiles_m - grp * 8, gm = left < 8 ? left : 8;
+    const int64_t m0 = (int64_t)(grp * 8 + in % gm) * BM;
+    const int n0 = (int)(in / gm) * BN;
+    if (epi.batch_len) {  // a valid length per batch: bounds the columns of C that are needed (1) or K (2)
+        int len = epi.batch_len[blockIdx.y];
+        len = len < 1 ? 1 : len;
+        if (epi.len_bounds == 1 && n0 >= len) return;
+        if (epi.len_bounds == 2 && len < K) K = (len + 63) / 64 * 64;
+    }
+    if (epi.skip_len) {
+        // all rows of the tile in one request's padding, past the 64-row block of its last valid row: nobody reads the product
+        const uint32_t r0 = (uint32_t)m0, S = (uint32_t)epi.skip_S, b0 = r0 / S;
+        if (b0 == (r0 + BM - 1) / S) {
+            const int len = epi.skip_len[b0];
+            if (r0 - b0 * S >= (uint32_t)(len < 1 ? 64 : (len + 63) / 64 * 64)) return;
+        }
+    }
+    const int KT = K / 64;
+
+    // ---- loads: piece p = i * NW + wave fills rows 8p .. 8p+7 of the k-tile's BM rows of A and BN rows of W, lane -> row lane/8,
+    // position lane%8 (rows past the matrix edge re-read its last row) ----
+    const char *src[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; i++) {
+        const int p = i * NW + wave, r = p * 8 + lane / 8;
+        const int chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
+        if (p < BM / 8) {
+            const int64_t row = m0 + r;
+            src[i] = (const char *)(A + (row < M ? row : M - 1) * lda) + chunk * 16;
+        } else {
+            const int64_t row = (int64_t)n0 + r - BM;
+            src[i] = (const char *)(W + (row < N ? row : N - 1) * ldw) + chunk * 16;
+        }
+    }
+    auto issue = [&](int slot) {  // k-tiles are requested in ascending order
+#pragma unroll
+        for (int i = 0; i < LPW; i++) {
+            ring_dma16(src[i], (bf16x8 *)((char *)smem + slot * STAGE + (i * NW + wave) * 1024));
+            src[i] += 128;
+        }
+    };
+    // wait until at most `n` of this wavefront's k-tiles are in flight
+    auto wait_tiles = [&](int n) {
+        switch (n < ST - 1 ? n : ST - 1) {
+#define W_(x) case x: asm volatile("s_waitcnt vmcnt(%0)" ::"n"((x) * LPW > 63 ? 63 : (x) * LPW) : "memory"); break;
+            W_(1) W_(2) W_(3) W_(4) W_(5) W_(6) W_(7)
+#undef W_
+            default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+    };
+
+    // ---- fragments: lane reads row frow of a 32-row block, chunk 2s + hf of k-step s, i.e. position (hf ^ fx) ^ 2s ----
+    const int frow = lane % 32, hf = lane / 32, fx = (frow >> 1) & 7;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    const uint32_t a_lane = lds0 + (uint32_t)((wm * WT + frow) * 8 + (hf ^ fx)) * 16;
+    const uint32_t w_lane = lds0 + (uint32_t)((BM + wn * WT + frow) * 8 + (hf ^ fx)) * 16;
+    bf16x8 af[4][T], wf[4][T];
+    auto read = [&](int slot, int s) {
+        const uint32_t pa = (a_lane ^ (uint32_t)(s << 5)) + (uint32_t)(slot * STAGE), pw = (w_lane ^ (uint32_t)(s << 5)) + (uint32_t)(slot * STAGE);
+        asm volatile("ds_read_b128 %0, %1" : "=v"(af[s][0]) : "v"(pa));
+        if (T > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(af[s][T - 1]) : "v"(pa));
+        asm volatile("ds_read_b128 %0, %1" : "=v"(wf[s][0]) : "v"(pw));
+        if (T > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(wf[s][T - 1]) : "v"(pw));
+    };
+    auto wait_frags = [&](int s, int steps) {  // fragments of step s are there, those of `steps` later steps may still be on the way
+#define WF_(n) \
+    if constexpr (T == 2) asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(af[s][0]), "+v"(af[s][T - 1]), "+v"(wf[s][0]), "+v"(wf[s][T - 1]) : "n"((n) * 2 * T)); \
+    else asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(af[s][0]), "+v"(wf[s][0]) : "n"((n) * 2 * T))
+        if (steps == 0) { WF_(0); } else if (steps == 2) { WF_(2); } else { WF_(3); }
+#undef WF_
+    };
+    floatx16 acc[T][T];
+#pragma unroll
+    for (int i = 0; i < T; i++)
+#pragma unroll
+        for (int j = 0; j < T; j++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+    auto mma = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < T; i++)
+#pragma unroll
+            for (int j = 0; j < T; j++)
+                acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s][i], wf[s][j], acc[i][j], 0, 0, 0);
+    };
+
+#define SB __builtin_amdgcn_sched_barrier(0)
+    float add[16];
+    if (!STAGED && T == 1) direct_addends<KIND>(add, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);  // (on their way before the operands)
+    const int first = KT < ST ? KT : ST;
+    for (int t = 0; t < first; t++) issue(t);
+    wait_tiles(first - 1);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read(0, 0);
+    read(0, 1);
+    int slot = 0;
+    for (int kt = 0; kt < KT; kt++) {
+        SB; read(slot, 2); read(slot, 3);
+        wait_frags(0, 3); SB; mma(0); SB;
+        wait_frags(1, 2); SB; mma(1); SB;
+        wait_frags(2, 0); wait_frags(3, 0); SB;
+        const int next = slot + 1 == ST ? 0 : slot + 1;
+        if (kt + 1 < KT) {
+            wait_tiles(KT - 2 - kt < ST - 2 ? KT - 2 - kt : ST - 2);  // this wavefront's share of k-tile kt + 1 has landed
+            __builtin_amdgcn_s_barrier();                             // everybody's has, and everybody has read k-tile kt
+            asm volatile("" ::: "memory");
+            if (kt + ST < KT) issue(slot);
+            SB; read(next, 0); read(next, 1); SB;
+        }
+        mma(2); mma(3);
+        slot = next;
+    }
+#undef SB
+    if constexpr (STAGED) {
+        __builtin_amdgcn_s_barrier();  // every wavefront has read its last fragments: LDS becomes the staging area
+        asm volatile("" ::: "memory");
+        staged_epilogue<KIND, T>(acc, (char *)smem + wave * 8192, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
+    } else {
+#pragma unroll
+        for (int i = 0; i < T; i++)
+#pragma unroll
+            for (int j = 0; j < T; j++) {
+                if (T > 1) direct_addends<KIND>(add, m0 + wm * WT + i * 32, n0 + wn * WT + j * 32, M, N, epi, lane);
+                direct_epilogue<KIND>(acc[i][j], add, m0 + wm * WT + i * 32, n0 + wn * WT + j * 32, M, N, epi, lane);
+            }
+    }
+}
+
+template <int BM, int BN, int WT, int ST, int KIND, bool STAGED>
+static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi,
                             hipStream_t st, int batch = 1, int64_t batch_a = 0, int64_t batch_w = 0, int64_t batch_c = 0) {
-    constexpr int NT = (BM / WM) * (BN / WN) * 64;
-    constexpr size_t smem = 2 * (size_t)(BM + BN) * 128;
-    auto kern = gemm_bf16_mfma<BM, BN, WM, WN, KIND>;
+    constexpr int NT = (BM / WT) * (BN / WT) * 64;
+    constexpr size_t smem = (size_t)ST * (BM + BN) * 128;
+    auto kern = gemm_bf16_tile<BM, BN, WT, ST, KIND, STAGED>;
     static bool attr_done = false;  // one attribute call per instantiation is enough (value never changes)
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
-    int64_t tiles_m = ceil_div64(M, BM);
-    int tiles_n = (N + BN - 1) / BN;
-    int64_t total = tiles_m * tiles_n;
-    int64_t grid = ceil_div64(total, 8) * 8;
-    if (grid > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
+    const int64_t tiles_m = ceil_div64(M, BM), tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n;
+    if (total > 0x7ffffff0LL || batch < 1 || batch > 65535) return GR4AD_EUNSUPPORTED;
+    if (epi.skip_len && M > 0x7fffff00LL) return GR4AD_EUNSUPPORTED;
     {
-        if (batch < 1 || batch > 65535) return GR4AD_EUNSUPPORTED;
-        ProfScope ps(BM == 256 ? KC_GEMM_256 : KC_GEMM_128, st, 2.0 * (double)M * N * K * batch,
-                     batch * gemm_bytes(M, N, K, KIND >= EPI_F32, KIND == EPI_F32_RESID));
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)batch), dim3(NT), smem, st, A, lda, W, ldw, M, N, K, tiles_m, tiles_n, epi, batch_a,
-                           batch_w, batch_c);
+        ProfScope ps(KC_GEMM_TILE, st, 2.0 * (double)M * N * K * batch, batch * gemm_bytes(M, N, K, kind_f32(KIND) && !epi.out_f16, KIND == EPI_F32_RESID));
+        hipLaunchKernelGGL(kern, dim3((unsigned)(ceil_div64(total, 8) * 8), (unsigned)batch), dim3(NT), smem, st, A, lda, W, ldw, M, N, K, (int)tiles_m,
+                           (int)tiles_n, epi, batch_a, batch_w, batch_c);
     }
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
 
-template <int BM, int BN, int WM, int WN>
-static int launch_mfma(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
-                       hipStream_t st) {
+template <int BM, int BN, int WT, int ST, bool STAGED>
+static int launch_tile_cfg(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
+                           hipStream_t st, int batch, int64_t ba, int64_t bw, int64_t bc) {
+#define KIND_(k) case k: return launch_tile_kind<BM, BN, WT, ST, k, STAGED>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
     switch (kind) {
-        case EPI_STORE: return launch_mfma_kind<BM, BN, WM, WN, EPI_STORE>(A, lda, W, ldw, M, N, K, epi, st);
-        case EPI_SILU: return launch_mfma_kind<BM, BN, WM, WN, EPI_SILU>(A, lda, W, ldw, M, N, K, epi, st);
-        case EPI_F32: return launch_mfma_kind<BM, BN, WM, WN, EPI_F32>(A, lda, W, ldw, M, N, K, epi, st);
-        case EPI_F32_RESID: return launch_mfma_kind<BM, BN, WM, WN, EPI_F32_RESID>(A, lda, W, ldw, M, N, K, epi, st);
-        default: return launch_mfma_kind<BM, BN, WM, WN, EPI_F32_TABLE>(A, lda, W, ldw, M, N, K, epi, st);
+        KIND_(EPI_STORE) KIND_(EPI_SILU_DIV) KIND_(EPI_F32) KIND_(EPI_F32_RESID) KIND_(EPI_F32_TABLE)
+        case EPI_SILU: if constexpr (STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_SILU, STAGED>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+            return GR4AD_EUNSUPPORTED;
+        case EPI_VT: if constexpr (!STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_VT, STAGED>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+            return GR4AD_EUNSUPPORTED;
     }
+#undef KIND_
+    return GR4AD_EUNSUPPORTED;
 }
 
-// Batched product on the 128x128 MFMA kernel: for i < batch, C_i[M,N] = A_i[M,K] * W_i[N,K]^T with A_i = A + i*batch_a elements etc.
+// Which kernel runs a product, by an estimate of its time in microseconds (all give the same bits).  Measured on MI355X, 1 <= M <= 8192,
+// 512 <= N <= 8192, 512 <= K <= 4096, per k-tile of 64: a 64x64 tile takes 0.215 us alone on a compute unit (the latency of its
+// LDS reads, MFMA chain and barrier) and 0.19 us each when several share one; 128x128 tiles 0.56 us alone, 0.585 us each in
+// pairs; a wave of 256x256 tiles between 1.15 us (few of them) and 1.9 us (every unit busy: the clock falls); plus a fixed part for
+// epilogue and first loads.  Before (128x128 tiles below 8192 rows, register-staged), M = 512, K = 1024: N = 1024 17 us, now 7.2;
+// N = 4096 20 us, now 9.5.
+enum { RUN_TILE64 = 0, RUN_TILE128, RUN_RING };
+static int pick_kernel(int64_t M, int N, int K, int batch, bool tile64, bool tile128, bool ring) {
+    const float kt = (float)(K / 64);
+    auto rounds = [&](int tile) { return (float)ceil_div64(ceil_div64(M, tile) * ceil_div64(N, tile) * batch, 256); };
+    const float r64 = rounds(64), r128 = rounds(128);
+    const float t64 = r64 * 0.4f + kt * (r64 > 1.0f ? 0.19f * r64 : 0.215f);
+    const float t128 = r128 * 1.1f + kt * (r128 > 1.0f ? 0.585f * r128 : 0.56f);
+    const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256) * batch, full = tiles / 256;
+    const float rest = (float)(tiles % 256) / 256.0f;
+    const float tr = (float)(full + (rest > 0.0f)) * 1.3f + kt * (1.9f * (float)full + (rest > 0.0f ? 1.15f + 0.72f * rest * rest : 0.0f));
+    if (ring && (!tile128 || tr <= t128) && (!tile64 || tr <= t64)) return RUN_RING;
+    return tile128 && (!tile64 || t128 < t64) ? RUN_TILE128 : RUN_TILE64;
+}
+
+static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
+                       hipStream_t st, int batch = 1, int64_t ba = 0, int64_t bw = 0, int64_t bc = 0) {
+    if (run == RUN_TILE64) return launch_tile_cfg<64, 64, 32, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    if (kind == EPI_VT || !tile_staged_ok(kind, N, epi)) return launch_tile_cfg<128, 128, 64, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    // one tile per compute unit: three k-tiles in flight; more: two workgroups share a unit (64 KB of LDS each)
+    if (ceil_div64(M, 128) * ceil_div64(N, 128) * batch <= 256)
+        return launch_tile_cfg<128, 128, 64, 3, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    return launch_tile_cfg<128, 128, 64, 2, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+}
+
+// Batched product on the tile kernels: for i < batch, C_i[M,N] = A_i[M,K] * W_i[N,K]^T with A_i = A + i*batch_a elements etc.
 // bf16 operands; C bf16 or (out_f32) float.  Used by the lazy layers' cross-attention in absorbed form (many small products).
 // batch_len (may be NULL), len_bounds: 1 = batch i only needs columns n < batch_len[i] of C_i (the rest may stay unwritten),
 // 2 = A_i and W_i are zero from column batch_len[i] (rounded up to 64) on, so the K loop stops there.
@@ -1017,21 +1233,20 @@ int launch_gemm_batched(const void *A, int64_t lda, int64_t batch_a, const void 
     e.batch_len = batch_len;
     e.len_bounds = batch_len ? len_bounds : 0;
     const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
-    if (M <= 64) {  // few rows per batch: 64-row tiles waste no matrix-core work
-        if (out_f32) return launch_mfma_kind<64, 128, 32, 64, EPI_F32>(a, lda, w, ldw, M, N, K, e, st, batch, batch_a, batch_w, batch_c);
-        return launch_mfma_kind<64, 128, 32, 64, EPI_STORE>(a, lda, w, ldw, M, N, K, e, st, batch, batch_a, batch_w, batch_c);
-    }
-    if (out_f32) return launch_mfma_kind<128, 128, 64, 64, EPI_F32>(a, lda, w, ldw, M, N, K, e, st, batch, batch_a, batch_w, batch_c);
-    return launch_mfma_kind<128, 128, 64, 64, EPI_STORE>(a, lda, w, ldw, M, N, K, e, st, batch, batch_a, batch_w, batch_c);
+    const int kind = out_f32 ? EPI_F32 : EPI_STORE;
+    return launch_tile(pick_kernel(M, N, K, batch, true, true, false), a, lda, w, ldw, M, N, K, kind, e, st, batch, batch_a, batch_w, batch_c);
 }
 
 // Transposed-per-request product for the context values: out[(b*N + n) * ld_out + s] = sum_k A[b*S + s][k] * W[n][k] for
-// s < len_b, 0 for len_b <= s < S.  Only the persistent kernel does this; false = shape not covered (caller takes another route).
+// s < len_b, 0 for len_b <= s < ld_out (ld_out = S rounded up to 64).  false = shape not covered (caller takes another route).
+static bool ring_vt_ok(int64_t M, int N, int K, int S, int64_t lda, int64_t ldw) {
+    return K >= 192 && S % 64 == 0 && M >= 256 && N >= 256 && lda < (1 << 22) && ldw < (1 << 22);
+}
 bool gemm_vt_supported(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K, int S,
                        const void *out, int64_t ld_out) {
-    return dtype == GR4AD_BF16 && K % 64 == 0 && K >= 192 && S % 64 == 0 && M % S == 0 && M >= 256 && N >= 256 && lda % 8 == 0 && ldw % 8 == 0 &&
-           lda < (1 << 22) && ldw < (1 << 22) && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0 && ((uintptr_t)out % 16) == 0 &&
-           ld_out % 8 == 0 && ld_out >= S;
+    if (dtype != GR4AD_BF16 || K % 64 || M % S || lda % 8 || ldw % 8 || ((uintptr_t)A % 16) || ((uintptr_t)W % 16) || ((uintptr_t)out % 16)) return false;
+    // (the padding columns of a request are cleared by the lanes of its first tokens, see direct_epilogue)
+    return ld_out == (S + 63) / 64 * 64 && ld_out - S <= S && M <= 0x7fffff00LL;
 }
 int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K, int S, const int32_t *ctx_len, void *out,
                    int64_t ld_out, hipStream_t st) {
@@ -1044,7 +1259,9 @@ int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64
     e.vt_S = S;
     e.skip_len = ctx_len;  // key tiles beyond ceil(len / 64) * 64 are never read by the attention kernel
     e.skip_S = S;
-    return launch_ring((const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
+    const int run = pick_kernel(M, N, K, 1, true, true, ring_vt_ok(M, N, K, S, lda, ldw));
+    if (run == RUN_RING) return launch_ring((const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
+    return launch_tile(run, (const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1088,9 +1305,10 @@ int launch_gemm_f8(const void *A, int64_t lda, const float *a_scale, const void 
     return GR4AD_OK;
 }
 
-// Kernel choice by shape: bf16 products with 16-byte aligned, K-contiguous operands run on the matrix cores - the persistent
-// kernel from 8192 rows and 256 columns on (the 256x256 tile kernel where its epilogue does not cover the layout), 128x128
-// tiles below that - everything else on the plain kernel.
+// bf16 products with 16-byte aligned, K-contiguous operands run on the matrix cores, everything else on the plain kernel.  Products
+// of at least 8192 rows and 256 columns with aligned rows form a class of their own: they may fold the RMSNorm into their
+// epilogues, leave half-precision logits and use the hardware reciprocal in SiLU.  What a product computes depends on that class alone;
+// inside it (and below it) pick_kernel is free to choose.
 static bool mfma_ok(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int K, int kind) {
     return dtype == GR4AD_BF16 && kind >= 0 && K % 64 == 0 && lda % 8 == 0 && ldw % 8 == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0;
 }
@@ -1111,9 +1329,13 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
     if ((epi.norm_out || epi.row_inv || epi.out_f16) && !gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) return GR4AD_EUNSUPPORTED;
     if (mfma_ok(dtype, A, lda, W, ldw, K, kind)) {
         const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
-        if (gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) return launch_ring(a, lda, w, ldw, M, N, K, kind, epi, st);
-        if (M >= 8192 && N >= 256) return launch_mfma<256, 256, 128, 64>(a, lda, w, ldw, M, N, K, kind, epi, st);
-        return launch_mfma<128, 128, 64, 64>(a, lda, w, ldw, M, N, K, kind, epi, st);
+        if (gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) {
+            const int run = pick_kernel(M, N, K, 1, false, tile_staged_ok(kind, N, epi), true);
+            return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, kind, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, kind, epi, st);
+        }
+        const int k = kind == EPI_SILU ? EPI_SILU_DIV : kind;
+        const int run = pick_kernel(M, N, K, 1, true, true, N >= 256 && ring_ok(k, N, K, lda, ldw, epi));
+        return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, k, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, k, epi, st);
     }
     dim3 grid((unsigned)ceil_div64(M, 64), (unsigned)((N + 63) / 64));
     if (ceil_div64(M, 64) > 0x7fffffffLL || grid.y > 65535) return GR4AD_EUNSUPPORTED;

@@ -1,0 +1,28 @@
+"""Products at the edges of the GEMM kernels' tiles and of the rule that picks them, against a float64 reference."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_22732_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 64), (63, 65, 128), (65, 72, 192),      # one k-tile, fewer k-tiles than the ring of the 64x64 tiles, as many
+    (128, 1028, 1024), (1025, 200, 320),           # columns past the last tile, columns that are no multiple of 8
+    (2049, 3072, 192), (4100, 1000, 128),          # 128x128 tiles: paired and with a ragged edge
+    (4096, 4096, 192), (4500, 3080, 256),          # few and many 256x256 tiles below 8192 rows
+    (8200, 512, 192), (8192, 520, 256),            # the large class on 128x128 and on 256x256 tiles
+])
+def test_linear_at_tile_edges(M, N, K):
+    g = torch.Generator().manual_seed(M * 7 + N * 3 + K)
+    A, W = torch.randn(M, K, generator=g).bfloat16(), (torch.randn(N, K, generator=g) / K**0.5).bfloat16()
+    bias = torch.randn(N, generator=g)
+    rows = torch.unique(torch.cat([torch.arange(min(M, 70)), torch.arange(max(0, M - 70), M), torch.randint(0, M, (60,), generator=g)]))
+    ref = (A[rows].double() @ W.double().t()).numpy()
+    a, w = A.cuda(), W.cuda()
+    f32 = binding.op_linear(a, w, bias.cuda(), out_f32=True).cpu()[rows].double().numpy()
+    half = binding.op_linear(a, w).cpu()[rows].double().numpy()
+    np.testing.assert_allclose(f32, ref + bias.double().numpy(), atol=2e-5, rtol=1e-5)
+    np.testing.assert_allclose(half, ref, atol=1e-6 + 2.0**-8 * np.abs(ref).max(), rtol=2.0**-7)
