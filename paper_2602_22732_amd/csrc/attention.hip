@@ -42,6 +42,7 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
     const float scale = 1.0f / sqrtf((float)dh);
     for (int c = lane; c < dh; c += 64) sq[wv][c] = to_f(q[row * ldq + h * dh + c]) * scale;
     const T *kbase = kv + b * (int64_t)S * 2 * d + h * dh;  // key j at kbase + j*2d, value at + d
+    const bool vec = ((uintptr_t)kbase % 16) == 0 && (2 * d) % (16 / (int)sizeof(T)) == 0 && dh % (16 / (int)sizeof(T)) == 0;
     float m = -INFINITY, l = 0.0f, acc[2] = {0.0f, 0.0f};
     for (int j0 = 0; j0 < len; j0 += 64) {
         const int j = j0 + lane;
@@ -49,7 +50,17 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
         if (j < len) {
             const T *kr = kbase + (int64_t)j * 2 * d;
             s = 0.0f;
-            for (int c = 0; c < dh; c++) s = fmaf(sq[wv][c], to_f(kr[c]), s);
+            if (vec) {  // 16 bytes per load, same order of additions
+                constexpr int E = 16 / sizeof(T);
+#pragma unroll 4
+                for (int c = 0; c < dh; c += E) {
+                    const uint4 raw = *(const uint4 *)(kr + c);
+#pragma unroll
+                    for (int e = 0; e < E; e++) s = fmaf(sq[wv][c + e], to_f(((const T *)&raw)[e]), s);
+                }
+            } else {
+                for (int c = 0; c < dh; c++) s = fmaf(sq[wv][c], to_f(kr[c]), s);
+            }
         }
         const float mnew = fmaxf(m, wave_max(s));
         const float p = (j < len) ? __expf(s - mnew) : 0.0f;
@@ -60,11 +71,21 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
         acc[0] *= alpha;
         acc[1] *= alpha;
         const int cnt = (len - j0) < 64 ? (len - j0) : 64;
-        for (int jj = 0; jj < cnt; jj++) {
-            const float pj = sp[wv][jj];
-            const T *vr = kbase + (int64_t)(j0 + jj) * 2 * d + d;
-            if (lane < dh) acc[0] = fmaf(pj, to_f(vr[lane]), acc[0]);
-            if (lane + 64 < dh) acc[1] = fmaf(pj, to_f(vr[lane + 64]), acc[1]);
+        // values: loads of 16 keys in flight (keys past the tile's last re-read it with weight zero: adding 0 * v changes nothing)
+        for (int j1 = 0; j1 < cnt; j1 += 16) {
+            float v0[16], v1[16];
+#pragma unroll
+            for (int u = 0; u < 16; u++) {
+                const T *vr = kbase + (int64_t)(j0 + (j1 + u < cnt ? j1 + u : cnt - 1)) * 2 * d + d;
+                v0[u] = lane < dh ? to_f(vr[lane]) : 0.0f;
+                v1[u] = lane + 64 < dh ? to_f(vr[lane + 64]) : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < 16; u++) {
+                const float pj = j1 + u < cnt ? sp[wv][j1 + u] : 0.0f;
+                acc[0] = fmaf(pj, v0[u], acc[0]);
+                acc[1] = fmaf(pj, v1[u], acc[1]);
+            }
         }
     }
     const float inv = 1.0f / l;

@@ -26,3 +26,14 @@ def test_linear_at_tile_edges(M, N, K):
     half = binding.op_linear(a, w).cpu()[rows].double().numpy()
     np.testing.assert_allclose(f32, ref + bias.double().numpy(), atol=2e-5, rtol=1e-5)
     np.testing.assert_allclose(half, ref, atol=1e-6 + 2.0**-8 * np.abs(ref).max(), rtol=2.0**-7)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 1, 4), (17, 33, 20), (16, 16, 512), (65, 130, 516),  # 16x16 tiles, K split over four wavefronts: empty and ragged shares
+    (1024, 1024, 64), (2100, 520, 68),                       # 64x64 tiles
+])
+def test_f32_linear_at_tile_edges(M, N, K):
+    g = torch.Generator().manual_seed(M + N + K)
+    A, W, bias = torch.randn(M, K, generator=g), torch.randn(N, K, generator=g) / K**0.5, torch.randn(N, generator=g)
+    out = binding.op_linear(A.cuda(), W.cuda(), bias.cuda(), out_f32=True).cpu().double()
+    np.testing.assert_allclose(out.numpy(), (A.double() @ W.double().t() + bias.double()).numpy(), atol=1e-5, rtol=1e-6)
