@@ -6,11 +6,12 @@
 // (appendix A.2) describes: every beam row first keeps its own min(b_t, V_t)
 // best tokens, then the request keeps the b_t best of those.  Both stages are
 // exact selections, so the result equals a full sort of all candidates.
-// The per-row cut is tightened by a bound per request: the request's first row
-// holds its best beam, and that row's own cut already has b_t candidates, so no
-// candidate below the worst of them can survive.  The other rows write only what
-// reaches that bound (at most their own cut), compacted per request; with beams
-// of unequal scores that is a fraction of b_t per row.
+// The per-row cut is tightened by a bound per request: b_t candidates that are known
+// to exist put a floor under the survivors.  The first R rows hold the best beams, and
+// their ceil(b_t / R) best candidates each are b_t candidates, so nothing below the worst
+// of those can survive; the tightest of R = 1, 2, 4, ... is used (one row where the beams'
+// scores fall off steeply, many where they are level).  All rows write only what
+// reaches that bound (at most their own cut), compacted per request.
 //
 // Candidates travel between the stages as unique 64-bit keys
 //     (order-preserving bits of the fp32 score) << 32 | (0xFFFFFFFF - flat index)
@@ -18,8 +19,15 @@
 // scores resolve deterministically and the final order is a plain key sort.
 #include <stdlib.h>
 
-#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
+
+// The running candidate count of a request sits on a cache line of its own where there is room (select_plan): the rows of all requests
+// count at once, and atomics on one line are served one after the other, about 20 ns each.  Measured: 64 requests of 256 rows of 4096
+// half-precision logits, 157 us with the counts side by side, 40 us apart.
+#define COUNT_PITCH_MAX 32
+#define BOUND_ROWS_MAX 32  // rows per request that go into its bound
 
 __device__ __forceinline__ uint32_t score_key(float f) {
     f += 0.0f;  // -0 -> +0 so equal scores have equal keys
@@ -298,6 +306,136 @@ __global__ __launch_bounds__(256) void select_rows(const float *__restrict__ log
     for (int i = tid; i < m; i += 256) dst[i] = out_stage[i];
 }
 
+template <typename LT> struct LogitPiece;  // one 16-byte piece of a row of logits as floats
+template <> struct LogitPiece<float> {
+    static constexpr int E = 4;
+    static __device__ __forceinline__ void unpack(const uint4 &r, float *o) {
+        o[0] = __uint_as_float(r.x); o[1] = __uint_as_float(r.y); o[2] = __uint_as_float(r.z); o[3] = __uint_as_float(r.w);
+    }
+};
+template <> struct LogitPiece<_Float16> {
+    static constexpr int E = 8;
+    static __device__ __forceinline__ void unpack(const uint4 &r, float *o) {
+        const halfx8 v = __builtin_bit_cast(halfx8, r);
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = (float)v[e];
+    }
+};
+
+// ---------------------------------------------------------------------------
+// request bounds
+// ---------------------------------------------------------------------------
+// One workgroup per row r < R of a request (R a power of two): the scores below which the row has its ceil(m / Q) best candidates, for every
+// power of two Q in (r, R], go to rb[b * 2R + Q + r].  A bound may lie below the exact value (that only lets a few more candidates
+// through), so a histogram of the logits is enough: the lower edge of the bin that holds the ranked value, a margin above the error of
+// bin and log-sum-exp (the sweep computes its own).  Q = 1 is ranked exactly inside its bin and its logit kept too (slot 0 of the
+// request): the first row takes the threshold from that, since the margin would let it over its m slots now and then.
+template <int ITEMS, typename LT>
+__global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits, const float *__restrict__ cum, int n, int V, int m, int R,
+                                                  float *__restrict__ rb, int *__restrict__ req_count, int count_pitch, int *__restrict__ todo_count) {
+    __shared__ RowShared sh;
+    const int tid = threadIdx.x, r = blockIdx.x % R;
+    const int64_t b = blockIdx.x / R, row = b * n + r;
+    if (blockIdx.x == 0 && tid == 0) *todo_count = 0;
+    if (r == 0 && tid == 0) req_count[b * count_pitch] = 0;
+    for (int i = tid; i < ROW_BINS; i += 256) sh.hist[i] = 0;
+    if (tid == 0) sh.list_n = 0;
+    const uint4 *z = (const uint4 *)(logits + row * (int64_t)V);
+    constexpr int E = LogitPiece<LT>::E, G = ITEMS / E;
+    float x[ITEMS];
+    float mx = -INFINITY, mn = INFINITY;
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        const bool ok = (g * 256 + tid) * E < V;  // V % E == 0
+        if (ok) LogitPiece<LT>::unpack(z[g * 256 + tid], &x[g * E]);
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            if (!ok) x[g * E + e] = -INFINITY;
+            mx = fmaxf(mx, x[g * E + e]);
+            if (ok) mn = fminf(mn, x[g * E + e]);
+        }
+    }
+    mx = block_max_256(mx, sh, 0);
+    mn = -block_max_256(-mn, sh, 1);
+    float sum = 0.0f;
+#pragma unroll
+    for (int j = 0; j < ITEMS; j++) sum += __expf(x[j] - mx);
+    const float lse = mx + __logf(block_sum_256(sum, sh, 2));
+    const float inv_w = mx > mn && mx - mn < INFINITY ? (float)ROW_BINS / (mx - mn) : 0.0f;
+    auto bin_of = [&](float v) { return min((int)fmaxf((v - mn) * inv_w, 0.0f), ROW_BINS - 1); };  // (NaN: bin 0)
+#pragma unroll
+    for (int g = 0; g < G; g++)
+        if ((g * 256 + tid) * E < V)
+#pragma unroll
+            for (int e = 0; e < E; e++) atomicAdd(&sh.hist[bin_of(x[g * E + e])], 1);
+    __syncthreads();
+    // thread t owns bins 1023-4t .. 1020-4t; inclusive scan from the top bin down
+    const int b0 = ROW_BINS - 1 - 4 * tid;
+    const int h[4] = {sh.hist[b0], sh.hist[b0 - 1], sh.hist[b0 - 2], sh.hist[b0 - 3]};
+    const int incl = block_scan_256(h[0] + h[1] + h[2] + h[3], sh.wave_tot);
+    const int excl = incl - (h[0] + h[1] + h[2] + h[3]);
+    const float c = cum ? cum[row] : 0.0f;
+    auto put = [&](int Q, float v) {
+        const float sc = c + (v - lse), low = sc - (1e-5f + 4e-7f * (fabsf(c) + fabsf(v) + fabsf(lse)));
+        rb[b * (2 * R) + Q + r] = low == low ? low : -INFINITY;
+    };
+    for (int Q = 1; Q <= R; Q <<= 1) {
+        if (Q <= r) continue;
+        const int rank = (m + Q - 1) / Q;
+        if (excl < rank && incl >= rank) {
+            int above = excl, i = 0;
+            while (above + h[i] < rank) above += h[i++];
+            if (Q == 1) {
+                sh.sel_bin = b0 - i;
+                sh.sel_krem = rank - above;
+                sh.sel_cnt = h[i];
+            } else {
+                put(Q, inv_w > 0.0f ? mn + ((float)(b0 - i) - 0.01f) / inv_w : mn);
+            }
+        }
+    }
+    if (r != 0) return;
+    __syncthreads();
+    const int T = sh.sel_bin, krem = sh.sel_krem, cnt = sh.sel_cnt;
+    if (cnt > ROW_LIST || !(inv_w > 0.0f)) {  // crowded bin (degenerate rows): its edge will do
+        if (tid == 0) {
+            put(1, inv_w > 0.0f ? mn + ((float)T - 0.01f) / inv_w : mn);
+            rb[b * (2 * R)] = -INFINITY;
+        }
+        return;
+    }
+    float *list = (float *)sh.list;
+#pragma unroll
+    for (int g = 0; g < G; g++)
+        if ((g * 256 + tid) * E < V)
+#pragma unroll
+            for (int e = 0; e < E; e++)
+                if (bin_of(x[g * E + e]) == T) list[atomicAdd(&sh.list_n, 1)] = x[g * E + e];
+    __syncthreads();
+    for (int i = tid; i < cnt; i += 256) {
+        const float v = list[i];
+        int gt = 0, ge = 0;
+        for (int q = 0; q < cnt; q++) { gt += list[q] > v ? 1 : 0; ge += list[q] >= v ? 1 : 0; }
+        if (gt < krem && ge >= krem) {  // (equal values write the same)
+            put(1, v);
+            rb[b * (2 * R)] = v;
+        }
+    }
+}
+
+// The request's bound by one wavefront, v: slot `lane` of the request's scores (anything past them).  Slots [Q, 2Q) hold the rows of
+// Q, an aligned group of lanes: the minimum of every group, then the best group.
+__device__ __forceinline__ float request_bound(float v, int R, int lane) {
+#pragma unroll
+    for (int s = 1; s < BOUND_ROWS_MAX; s <<= 1) {
+        const float o = __shfl_xor(v, s, 64);
+        if (lane >= 2 * s) v = fminf(v, o);
+    }
+    return wave_max_dpp(lane >= 1 && lane < 2 * R ? v : -INFINITY);
+}
+// the same for the request's first row, whose own m-th best logit x0 (slot 0) is known
+__device__ __forceinline__ float first_row_bound(float x0, float bound, float c, float lse) { return fmaxf(bound, c + (x0 - lse)); }
+
 // ---------------------------------------------------------------------------
 // stage A, wavefront form: one wavefront per beam row (V <= 8192)
 // ---------------------------------------------------------------------------
@@ -305,11 +443,11 @@ __global__ __launch_bounds__(256) void select_rows(const float *__restrict__ log
 // registers per lane, read as 16-byte pieces of E = 4 float32 or E = 8 half-precision values (lane l, piece g holds tokens
 // (g*64 + l)*E .. +E-1; V % E == 0), every reduction is a wave reduction, and the histogram, the threshold-bin list and the
 // staged output live in a private LDS region per wavefront.  The kernel is bound by vector instructions per logit, so the
-// common case is kept to a maximum, one exp2 and one comparison per logit: with a request-level bound in force the row is
-// swept in the logit domain against a threshold a hair below the exact one, and only the few logits that pass it are turned
-// into scores and tested exactly.  Rows that need their own cut (more than m candidates at the bound, or no bound) turn all
-// logits into scores, histogram them and rank the threshold bin exactly; score bits are staged raw and turned into sortable
-// keys only for the survivors on the way out.
+// common case, select_rows_sweep, is kept to a maximum, one exp2 and one comparison per logit: with a request-level bound in
+// force the row is swept in the logit domain against a threshold a hair below the exact one, and only the few logits that pass it
+// are turned into scores and tested exactly.  Rows that need their own cut (select_rows_wave: more than m candidates at the bound,
+// or no bound) turn all logits into scores, histogram them and rank the threshold bin exactly; score bits are staged raw and
+// turned into sortable keys only for the survivors on the way out.
 #define WROW_BINS 1024
 #define WROW_LIST 512  // threshold-bin candidates ranked exactly; the list reuses the histogram's 4 KB
 
@@ -394,22 +532,6 @@ __device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], i
         }
     }
 }
-
-template <typename LT> struct LogitPiece;  // one 16-byte piece of a row of logits as floats
-template <> struct LogitPiece<float> {
-    static constexpr int E = 4;
-    static __device__ __forceinline__ void unpack(const uint4 &r, float *o) {
-        o[0] = __uint_as_float(r.x); o[1] = __uint_as_float(r.y); o[2] = __uint_as_float(r.z); o[3] = __uint_as_float(r.w);
-    }
-};
-template <> struct LogitPiece<_Float16> {
-    static constexpr int E = 8;
-    static __device__ __forceinline__ void unpack(const uint4 &r, float *o) {
-        const halfx8 v = __builtin_bit_cast(halfx8, r);
-#pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = (float)v[e];
-    }
-};
 
 // The row's own top-m cut.  x[i]: the logit of token wave_tok<E>(i, lane), padding -inf; mx, lse: the row's maximum and
 // log-sum-exp; the m best (score, token) pairs go to dst.
@@ -507,84 +629,13 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
     for (int i = lane; i < m; i += 64) dst[i] = staged_to_key(stage[i]);
 }
 
-// One row of logits, already in registers (x[i]: token wave_tok<E>(i, lane); padding -inf), through the cut.  Returns when the
-// row's candidates are written.
-template <int VEC, bool FULL, int E>
-__device__ __forceinline__ void select_one_row_wave(float (&x)[VEC * 4], int64_t vrow, int64_t row, const float *__restrict__ cum, int n, int V,
-                                                    int m, unsigned long long *__restrict__ cand, const unsigned long long *__restrict__ bound,
-                                                    int *__restrict__ req_count, unsigned long long *list, int lane, int64_t dst_at) {
-    constexpr int NX = VEC * 4;
-    unsigned long long *stage = list + 512;
-    const float c = cum ? cum[row] : 0.0f;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < NX; i++) mx = fmaxf(mx, x[i]);
-    mx = wave_max_dpp(mx);
-    const float mxl = mx * 1.4426950408889634f;
-    float sum = 0.0f;
-#pragma unroll
-    for (int i = 0; i < NX; i++) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(x[i], 1.4426950408889634f, -mxl));  // padding gives 0
-    const float lse = mx + __logf(wave_sum_dpp(sum));
-
-    unsigned long long *dst = cand + (dst_at >= 0 ? dst_at : vrow * (int64_t)m);  // dst_at: where a listed row reserved its m slots
-    const uint32_t flat0 = (uint32_t)((row % n) * (int64_t)V);
-    // low word of a staged candidate: 0xFFFFFFFF - (flat0 + token)
-    const uint32_t nflat = 0xFFFFFFFFu - flat0 - (uint32_t)lane * (uint32_t)E;
-    if (bound) {
-        // Request-level bound: the request's first row alone has m candidates at or above `bound`, so nothing below it can
-        // survive the request's selection.  Rows that have at most m candidates there write exactly those - usually far
-        // fewer than m - and skip the histogram; the others fall through to the row's own top-m cut.
-        const int64_t req = row / n;
-        const float sstar = key_score((uint32_t)(bound[req] >> 32));
-        // score(x) = c + (x - lse) >= sstar is tested exactly, but only on the logits that pass a threshold in the logit domain
-        // placed a few roundings below the exact one (every candidate at or above the bound passes it)
-        const float t0 = (sstar - c) + lse;
-        const float thr = t0 - 1e-6f * (fabsf(sstar) + fabsf(c) + fabsf(lse) + fabsf(t0));
-        int cnt = 0;
-        constexpr int CH = 16;  // logits per test: one wave-uniform branch per CH elements, taken for the few chunks that hold a candidate
-#pragma unroll
-        for (int i0 = 0; i0 < NX; i0 += CH) {
-            unsigned long long any = 0;
-#pragma unroll
-            for (int u = 0; u < CH; u++) any |= __ballot(x[i0 + u] >= thr);  // padding is -inf
-            if (any != 0) {
-#pragma unroll
-                for (int u = 0; u < CH; u++) {
-                    const int i = i0 + u;
-                    const float sc = c + (x[i] - lse);
-                    const bool hit = sc >= sstar;
-                    const unsigned long long mk = __ballot(hit);
-                    const unsigned long long st = ((unsigned long long)__float_as_uint(sc + 0.0f) << 32) | (nflat - (uint32_t)((i / E) * 64 * E + (i % E)));
-                    const int at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0));
-                    if (hit && at < m) stage[at] = st;
-                    cnt += __popcll(mk);
-                }
-            }
-        }
-        const int take = cnt <= m ? cnt : m;
-        int base = 0;
-        if (lane == 0) base = atomicAdd(&req_count[req], take);
-        base = __shfl(base, 0, 64);
-        dst = cand + req * ((int64_t)n * m) + base;
-        if (cnt <= m) {
-            for (int i = lane; i < cnt; i += 64) dst[i] = staged_to_key(stage[i]);
-            return;
-        }
-    }
-    select_row_own_cut<VEC, FULL, E>(x, c, mx, lse, dst, flat0, nflat, V, m, list, lane);
-}
-
 // FULL: V == VEC*256, every register holds a token (the validity tests fold away).
-// row_step: the launch visits rows 0, row_step, 2 row_step, ... of the logits (row_step = n: the first beam of every request).
-// bound / req_count (both or neither): per request, a key no survivor can lie below; the launch then writes only
-// the candidates that reach it (at most the row's m best), compacted per request behind a running count.
-// todo / todo_count (both or neither; then without bound): the launch visits only the listed rows {row, slot}; each gets its
+// todo / todo_count (both or neither): the launch visits only the listed rows {row, slot}; each gets its
 // own cut, written at slot `slot` of its request's segment.  Wavefronts walk their rows with the launch's stride.
 template <int VEC, bool FULL, typename LT>
 __global__ __launch_bounds__(256, 3) void select_rows_wave(const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V,
-                                                          int m, unsigned long long *__restrict__ cand, int64_t row_step,
-                                                          const unsigned long long *__restrict__ bound, int *__restrict__ req_count,
-                                                          const int2 *__restrict__ todo, const int *__restrict__ todo_count) {
+                                                          int m, unsigned long long *__restrict__ cand, const int2 *__restrict__ todo,
+                                                          const int *__restrict__ todo_count) {
     constexpr int E = LogitPiece<LT>::E, NX = VEC * 4, G = NX / E;
     extern __shared__ unsigned long long wave_lds[];  // per wavefront: 512 slots of histogram / list, then m slots of staged output
     const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
@@ -599,7 +650,7 @@ __global__ __launch_bounds__(256, 3) void select_rows_wave(const LT *__restrict_
             vrow = t.x;
             dst_at = (vrow / n) * ((int64_t)n * m) + t.y;
         }
-        const uint4 *z = (const uint4 *)(logits + vrow * row_step * (int64_t)V);
+        const uint4 *z = (const uint4 *)(logits + vrow * (int64_t)V);
         float x[NX];
 #pragma unroll
         for (int g = 0; g < G; g++) {
@@ -610,42 +661,62 @@ __global__ __launch_bounds__(256, 3) void select_rows_wave(const LT *__restrict_
                 for (int e = 0; e < E; e++) x[g * E + e] = -INFINITY;
             }
         }
-        select_one_row_wave<VEC, FULL, E>(x, vrow, vrow * row_step, cum, n, V, m, cand, bound, req_count, list, lane, dst_at);
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NX; i++) mx = fmaxf(mx, x[i]);
+        mx = wave_max_dpp(mx);
+        const float mxl = mx * 1.4426950408889634f;
+        float sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NX; i++) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(x[i], 1.4426950408889634f, -mxl));  // padding gives 0
+        const float lse = mx + __logf(wave_sum_dpp(sum));
+        const uint32_t flat0 = (uint32_t)((vrow % n) * (int64_t)V);
+        // low word of a staged candidate: 0xFFFFFFFF - (flat0 + token)
+        const uint32_t nflat = 0xFFFFFFFFu - flat0 - (uint32_t)lane * (uint32_t)E;
+        select_row_own_cut<VEC, FULL, E>(x, cum ? cum[vrow] : 0.0f, mx, lse, cand + (dst_at >= 0 ? dst_at : vrow * (int64_t)m), flat0, nflat, V, m, list,
+                                         lane);
     }
 }
 
-// The bounded pass over half-precision logits.  A row stays packed (raw[g]: tokens (g*64 + lane)*8 .. +7; pieces past V
-// hold -inf): maximum, log-sum-exp and the sweep for candidates at or above the request's bound read the halves in
-// place, and each wavefront asks for its next row before it works on the current one, so the memory latency hides behind the
-// arithmetic.  A row with more than m candidates at the bound reserves m slots and is put on the list for
-// select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
-template <int VEC, bool FULL>
-__global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void select_rows_sweep_f16(
-    const _Float16 *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V, int m, unsigned long long *__restrict__ cand,
-    const unsigned long long *__restrict__ bound, int *__restrict__ req_count, int2 *__restrict__ todo, int *__restrict__ todo_count) {
-    constexpr int NX = VEC * 4, E = 8, G = NX / E;
-    extern __shared__ unsigned long long wave_lds[];  // per wavefront: m slots of staged output
+// The bounded pass.  A row stays in registers as it was read (raw[g]: tokens (g*64 + lane)*E .. +E-1; pieces past V hold -inf): maximum,
+// log-sum-exp and the sweep for candidates at or above the request's bound read it in place.  Each wavefront walks rows_per
+// consecutive rows; half-precision rows are half the registers, so it asks for the next one before it works on the current one and
+// the memory latency hides behind the arithmetic.  The candidates of its rows gather in LDS and leave with one reservation in the
+// request's segment per SWEEP_SLACK candidates or request.  A row with more than m candidates at the bound reserves m slots and is
+// put on the list for select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
+#define SWEEP_SLACK 128
+template <int VEC, bool FULL, typename LT>
+__global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void select_rows_sweep(
+    const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V, int m, unsigned long long *__restrict__ cand,
+    const float *__restrict__ rb, int R, int *__restrict__ req_count, int count_pitch, int2 *__restrict__ todo, int *__restrict__ todo_count, int rows_per) {
+    constexpr bool HALF = sizeof(LT) == 2;
+    constexpr int NX = VEC * 4, E = LogitPiece<LT>::E, G = NX / E;
+    extern __shared__ unsigned long long wave_lds[];  // per wavefront: m + SWEEP_SLACK slots of staged output
     // The row index is made a scalar of the wavefront (rows < 2^31, checked by the host): its cumulative score and bound then
     // come through scalar loads, which do not queue behind the vector loads of the next row.
     const int lane = threadIdx.x % 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const uint32_t nwaves = gridDim.x * 4u;
-    uint32_t row = blockIdx.x * 4u + (uint32_t)wv;
-    if (row >= (uint64_t)rows) return;  // whole wavefronts leave; nothing below synchronises across wavefronts
-    unsigned long long *stage = wave_lds + (size_t)wv * m;
+    const uint64_t row0 = (uint64_t)(blockIdx.x * 4u + (uint32_t)wv) * (uint32_t)rows_per;
+    if (row0 >= (uint64_t)rows) return;  // whole wavefronts leave; nothing below synchronises across wavefronts
+    uint32_t row = (uint32_t)row0;
+    const uint32_t row_end = (uint32_t)(row0 + (uint32_t)rows_per < (uint64_t)rows ? row0 + (uint32_t)rows_per : (uint64_t)rows);
+    unsigned long long *stage = wave_lds + (size_t)wv * (m + SWEEP_SLACK);
+    int held = 0;  // candidates of earlier rows of this request in `stage`, at most SWEEP_SLACK at the start of a row
     auto request_row = [&](uint32_t r, uint4 (&raw)[G]) {
         const uint4 *z = (const uint4 *)(logits + (int64_t)r * V);
 #pragma unroll
         for (int g = 0; g < G; g++) {
             if (FULL || (g * 64 + lane) * E < V) raw[g] = z[g * 64 + lane];
-            else raw[g] = make_uint4(0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u);  // halves of -inf
+            else raw[g] = HALF ? make_uint4(0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u, 0xFC00FC00u)  // -inf
+                               : make_uint4(0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u);
         }
     };
-    // per row: request, beam, cumulative score and the bound's score, fetched one row ahead like the logits
-    auto row_scalars = [&](uint32_t r, uint32_t &req, uint32_t &beam, float &c, float &sstar) {
+    // per row: request, beam, cumulative score and this lane's slot of the request's bound, fetched one row ahead like the logits
+    // (the slot by a vector load, so before them: loads return in order)
+    auto row_scalars = [&](uint32_t r, uint32_t &req, uint32_t &beam, float &c, float &rbv) {
         req = r / (uint32_t)n;
         beam = r % (uint32_t)n;
         c = cum ? cum[r] : 0.0f;
-        sstar = key_score((uint32_t)(bound[req] >> 32));
+        rbv = rb[(int64_t)req * (2 * R) + (lane < 2 * R ? lane : 0)];
     };
     auto pk_max = [](halfx2 a, halfx2 b) {  // (the plain instruction: the generic maximum first quiets both operands)
         halfx2 r;
@@ -653,44 +724,62 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         return r;
     };
     uint4 raw[G];
-    request_row(row, raw);
     uint32_t req, beam;
-    float c, sstar;
-    row_scalars(row, req, beam, c, sstar);
+    float c, rbv;
+    row_scalars(row, req, beam, c, rbv);
+    request_row(row, raw);
     for (;;) {
-        const uint64_t next = (uint64_t)row + nwaves;
-        const bool more = next < (uint64_t)rows;
-        const uint32_t ahead = more ? (uint32_t)next : row;
-        uint4 nxt[G];
-        // (unconditional - the last row is asked for twice: a branch here would make the compiler wait for these loads at the
+        const bool more = row + 1 < row_end;
+        const uint32_t ahead = more ? row + 1 : row;
+        uint4 nxt[HALF ? G : 1];
+        // (half precision: unconditional - the last row is asked for twice: a branch here would make the compiler wait for these loads at the
         // first use of the current row, as if they had been skipped)
-        request_row(ahead, nxt);
         uint32_t req_n, beam_n;
-        float c_n, sstar_n;
-        row_scalars(ahead, req_n, beam_n, c_n, sstar_n);
+        float c_n, rbv_n;
+        row_scalars(ahead, req_n, beam_n, c_n, rbv_n);
+        if constexpr (HALF) request_row(ahead, nxt);
         __builtin_amdgcn_sched_barrier(0);  // the loads go out here, not where the instruction scheduler finds the registers cheapest
 
-        halfx2 pmax[G];  // per piece: the maximum of its even and of its odd tokens
+        typename std::conditional<HALF, halfx2, float>::type pmax[G];  // per piece: the maximum (half precision: of its even and of its odd tokens)
+        float lane_mx;
+        auto piece_max = [&](int g) {
+            if constexpr (HALF) return fmaxf((float)pmax[g][0], (float)pmax[g][1]);
+            else return pmax[g];
+        };
+        if constexpr (HALF) {
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            const halfx8 v = __builtin_bit_cast(halfx8, raw[g]);
-            const halfx2 p0 = {v[0], v[1]}, p1 = {v[2], v[3]}, p2 = {v[4], v[5]}, p3 = {v[6], v[7]};
-            pmax[g] = pk_max(pk_max(p0, p1), pk_max(p2, p3));
+            for (int g = 0; g < G; g++) {
+                const halfx8 v = __builtin_bit_cast(halfx8, raw[g]);
+                const halfx2 p0 = {v[0], v[1]}, p1 = {v[2], v[3]}, p2 = {v[4], v[5]}, p3 = {v[6], v[7]};
+                pmax[g] = pk_max(pk_max(p0, p1), pk_max(p2, p3));
+            }
+            halfx2 rm = pmax[0];
+#pragma unroll
+            for (int g = 1; g < G; g++) rm = pk_max(rm, pmax[g]);
+            lane_mx = fmaxf((float)rm[0], (float)rm[1]);
+        } else {
+            lane_mx = -INFINITY;
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                float v[E];
+                LogitPiece<LT>::unpack(raw[g], v);
+                pmax[g] = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+                lane_mx = fmaxf(lane_mx, pmax[g]);
+            }
         }
-        halfx2 rm = pmax[0];
-#pragma unroll
-        for (int g = 1; g < G; g++) rm = pk_max(rm, pmax[g]);
-        const float lane_mx = fmaxf((float)rm[0], (float)rm[1]);
         const float mx = wave_max_dpp(lane_mx);
         const float mxl = mx * 1.4426950408889634f;
         float sum = 0.0f;
 #pragma unroll
         for (int g = 0; g < G; g++) {
-            const halfx8 v = __builtin_bit_cast(halfx8, raw[g]);
+            float v[E];
+            LogitPiece<LT>::unpack(raw[g], v);
 #pragma unroll
-            for (int e = 0; e < E; e++) sum += __builtin_amdgcn_exp2f(__builtin_fmaf((float)v[e], 1.4426950408889634f, -mxl));  // padding gives 0
+            for (int e = 0; e < E; e++) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(v[e], 1.4426950408889634f, -mxl));  // padding gives 0
         }
         const float lse = mx + __logf(wave_sum_dpp(sum));
+        float sstar = request_bound(rbv, R, lane);
+        if (beam == 0) sstar = first_row_bound(__shfl(rbv, 0, 64), sstar, c, lse);
         // (opaque to the compiler: otherwise it keeps the NX widened logits of the sum above in registers for the sweep below)
 #pragma unroll
         for (int g = 0; g < G; g++) asm volatile("" : "+v"(raw[g].x), "+v"(raw[g].y), "+v"(raw[g].z), "+v"(raw[g].w));
@@ -706,40 +795,48 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         if (__ballot(lane_mx >= thr) != 0) {
 #pragma unroll
             for (int g = 0; g < G; g++) {
-                const unsigned long long any = __ballot(fmaxf((float)pmax[g][0], (float)pmax[g][1]) >= thr);
+                const unsigned long long any = __ballot(piece_max(g) >= thr);
                 if (any != 0) {
-                    const halfx8 v = __builtin_bit_cast(halfx8, raw[g]);
+                    float v[E];
+                    LogitPiece<LT>::unpack(raw[g], v);
 #pragma unroll
                     for (int e = 0; e < E; e++) {
-                        const float sc = c + ((float)v[e] - lse);
+                        const float sc = c + (v[e] - lse);
                         const bool hit = sc >= sstar;
                         const unsigned long long mk = __ballot(hit);
                         const unsigned long long st = ((unsigned long long)__float_as_uint(sc + 0.0f) << 32) | (nflat - (uint32_t)(g * 64 * E + e));
                         const int at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0));
-                        if (hit && at < m) stage[at] = st;
+                        if (hit && at < m) stage[held + at] = st;
                         cnt += __popcll(mk);
                     }
                 }
             }
         }
-        if (cnt > 0) {  // (wavefront-uniform)
-            const int take = cnt <= m ? cnt : m;
-            int base = 0;
+        if (cnt > m) {  // (wavefront-uniform) its m slots are filled by the listed pass
             if (lane == 0) {
-                base = atomicAdd(&req_count[req], take);
-                if (cnt > m) todo[atomicAdd(todo_count, 1)] = make_int2((int)row, base);  // its m slots are filled by the listed pass
+                const int base = atomicAdd(&req_count[(int64_t)req * count_pitch], m);
+                todo[atomicAdd(todo_count, 1)] = make_int2((int)row, base);
             }
+        } else {
+            held += cnt;
+        }
+        if (held > 0 && (held > SWEEP_SLACK || !more || req_n != req)) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&req_count[(int64_t)req * count_pitch], held);
             base = __shfl(base, 0, 64);
-            if (cnt <= m) {
-                unsigned long long *dst = cand + (int64_t)req * ((int64_t)n * m) + base;
-                for (int i = lane; i < cnt; i += 64) dst[i] = staged_to_key(stage[i]);
-            }
+            unsigned long long *dst = cand + (int64_t)req * ((int64_t)n * m) + base;
+            for (int i = lane; i < held; i += 64) dst[i] = staged_to_key(stage[i]);
+            held = 0;
         }
         if (!more) break;
+        row++;
+        if constexpr (HALF) {
 #pragma unroll
-        for (int g = 0; g < G; g++) raw[g] = nxt[g];
-        row = (uint32_t)next;
-        req = req_n; beam = beam_n; c = c_n; sstar = sstar_n;
+            for (int g = 0; g < G; g++) raw[g] = nxt[g];
+        } else {
+            request_row(row, raw);
+        }
+        req = req_n; beam = beam_n; c = c_n; rbv = rbv_n;
     }
 }
 
@@ -749,19 +846,68 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
 #define SELB_THREADS 1024
 #define SELB_SORT_MAX 4096
 
-__device__ __forceinline__ void bitonic_sort_desc(unsigned long long *s, int n_pow2) {
-    for (int k = 2; k <= n_pow2; k <<= 1)
+// Bitonic sort, descending, of np keys (a power of two, np <= E * SELB_THREADS; the registers past np hold nothing).  Element
+// i = tid * E + e sits in v[e]: exchanges over less than 64 * E elements stay inside a lane or a wavefront, the ten
+// or so longer ones go through LDS.  (All 55 steps of 1024 keys through LDS with a barrier each: about 10 us of this kernel's
+// former 29 us at 256 x 4096 logits, k = 512.)
+template <int E>
+__device__ __forceinline__ void sort_desc(unsigned long long (&v)[E], int np, unsigned long long *lds) {
+    const int tid = threadIdx.x;
+    for (int k = 2; k <= np; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < n_pow2; i += SELB_THREADS) {
-                int ixj = i ^ j;
-                if (ixj > i) {
-                    unsigned long long a = s[i], b = s[ixj];
-                    bool desc = (i & k) == 0;
-                    if (desc ? (a < b) : (a > b)) { s[i] = b; s[ixj] = a; }
+            if (j < E) {
+#pragma unroll
+                for (int e = 0; e < E; e++)
+#pragma unroll
+                    for (int q = 1; q < E; q <<= 1)
+                        if (q == j && !(e & q)) {
+                            const bool desc = ((tid * E + e) & k) == 0;
+                            const unsigned long long a = v[e], b = v[e | q];
+                            if (desc ? a < b : a > b) { v[e] = b; v[e | q] = a; }
+                        }
+            } else {
+                const int x = j / E;
+                unsigned long long o[E];
+                if (x < 64) {
+#pragma unroll
+                    for (int e = 0; e < E; e++) o[e] = __shfl_xor(v[e], x, 64);
+                } else {
+                    __syncthreads();
+#pragma unroll
+                    for (int e = 0; e < E; e++) lds[e * SELB_THREADS + tid] = v[e];
+                    __syncthreads();
+#pragma unroll
+                    for (int e = 0; e < E; e++) o[e] = lds[e * SELB_THREADS + (tid ^ x)];
+                }
+                const bool low = (tid & x) == 0;
+#pragma unroll
+                for (int e = 0; e < E; e++) {
+                    const bool desc = ((tid * E + e) & k) == 0, take_max = desc == low;
+                    v[e] = (o[e] > v[e]) == take_max ? o[e] : v[e];
                 }
             }
-            __syncthreads();
         }
+}
+
+// sorts the `count` keys of lds (count <= SELB_SORT_MAX, a power of two np >= count of them are keys or zero) in place
+template <int E>
+__device__ __forceinline__ void sort_keys_lds(unsigned long long *lds, int np) {
+    const int tid = threadIdx.x;
+    unsigned long long v[E];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; e++) v[e] = tid * E + e < np ? lds[tid * E + e] : 0ull;
+    sort_desc<E>(v, np, lds);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; e++)
+        if (tid * E + e < np) lds[tid * E + e] = v[e];
+    __syncthreads();
+}
+__device__ __forceinline__ void bitonic_sort_desc(unsigned long long *lds, int np) {
+    if (np <= SELB_THREADS) sort_keys_lds<1>(lds, np);
+    else if (np <= 2 * SELB_THREADS) sort_keys_lds<2>(lds, np);
+    else sort_keys_lds<4>(lds, np);
 }
 
 // every key of a request's candidate list, 16 bytes per lane and four loads in flight (the list is streamed several times)
@@ -846,7 +992,7 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
 }
 
 __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned long long *__restrict__ cand, int64_t req_stride,
-                                                               const int *__restrict__ req_count, int V, int k,
+                                                               const int *__restrict__ req_count, int count_pitch, int V, int k,
                                                                int32_t *__restrict__ parent, int32_t *__restrict__ tok,
                                                                float *__restrict__ score, const int32_t *__restrict__ sid_old,
                                                                int32_t *__restrict__ sid_new, const int32_t *__restrict__ anc_old,
@@ -858,11 +1004,12 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
     const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
     const int64_t b = blockIdx.x;
     const unsigned long long *src = cand + b * req_stride;  // the request's candidates: the first req_count[b] keys of its segment
-    const int64_t ncand = req_count[b];
+    const int64_t ncand = req_count[b * count_pitch];
     int kp = 1;
     while (kp < k) kp <<= 1;
 
-    if (ncand <= SELB_SORT_MAX) {
+    // few enough to sort them all (a cut down to about k keys costs two sweeps, about as much as sorting 1024 keys)
+    if (ncand <= SELB_THREADS || ncand <= kp) {
         int np = 1;
         while (np < ncand) np <<= 1;
         for (int i = tid; i < np; i += SELB_THREADS) skeys[i] = i < ncand ? src[i] : 0ull;
@@ -952,8 +1099,10 @@ struct RowsLaunch {
     const float *cum;
     int n, V, m;
     unsigned long long *cand;
-    const unsigned long long *bound;
+    float *rb;  // scores behind the request bounds, R rows per request
+    int R;
     int *req_count;
+    int count_pitch;
     int2 *todo;
     int *todo_count;
 };
@@ -967,9 +1116,9 @@ static int compute_units() {
     }
     return n_cu;
 }
-// mode 0: every row (stride row_step) its own cut or, with a bound, the bounded cut; mode 1: the listed rows' own cuts
+// mode 0: every row its own cut; mode 1: the listed rows' own cuts
 template <int VEC, bool FULL, typename LT>
-static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int64_t row_step, int mode) {
+static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int mode) {
     auto kern = select_rows_wave<VEC, FULL, LT>;
     static bool attr_done = false;
     if (!attr_done) {
@@ -983,78 +1132,90 @@ static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int64_t row_
         if (!n_cu) return GR4AD_EHIP;
         if (grid > (int64_t)n_cu * 4) grid = (int64_t)n_cu * 4;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows, a.n, a.V, a.m, a.cand, row_step,
-                       mode == 1 ? nullptr : a.bound, mode == 1 ? nullptr : a.req_count, mode == 1 ? (const int2 *)a.todo : nullptr,
-                       mode == 1 ? (const int *)a.todo_count : nullptr);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows, a.n, a.V, a.m, a.cand,
+                       mode == 1 ? (const int2 *)a.todo : nullptr, mode == 1 ? (const int *)a.todo_count : nullptr);
     return GR4AD_OK;
 }
-// mode 2: the bounded pass over packed half-precision logits, which lists the rows that need their own cut
-template <int VEC, bool FULL>
+// mode 2: the bounded pass, which lists the rows that need their own cut
+template <int VEC, bool FULL, typename LT>
 static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
-    auto kern = select_rows_sweep_f16<VEC, FULL>;
+    auto kern = select_rows_sweep<VEC, FULL, LT>;
     static bool attr_done = false;
     if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * GR4AD_MAX_BEAM * 8) != hipSuccess) return GR4AD_EHIP;
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (GR4AD_MAX_BEAM + SWEEP_SLACK) * 8) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
     const int n_cu = compute_units();
     if (!n_cu) return GR4AD_EHIP;
-    // wavefronts walk the rows with the launch's stride
-    const size_t lds = 4 * (size_t)a.m * sizeof(unsigned long long);
-    // About 8 rows per wavefront: measured at a million rows of 8192 logits, 3.6 ms against 4.3 ms with 128 rows per wavefront
-    // (as many workgroups as fit the chip at once) and 3.8 ms with one row per wavefront (no next-row prefetch at all).
-    int64_t grid = ceil_div64(rows, 32);
-    if (grid < (int64_t)n_cu * 16) grid = std::min<int64_t>(ceil_div64(rows, 4), (int64_t)n_cu * 16);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const _Float16 *)a.logits, a.cum, rows,
-                       a.n, a.V, a.m, a.cand, a.bound, a.req_count, a.todo, a.todo_count);
+    const size_t lds = 4 * (size_t)(a.m + SWEEP_SLACK) * sizeof(unsigned long long);
+    // Up to eight rows per wavefront, but 64 wavefronts per compute unit come first.  Measured at a million rows of 8192 halves: 3.6 ms,
+    // 4.3 ms with 128 rows per wavefront, 3.8 ms with one; at 16384 rows of 4096: 35 us with one row per wavefront, 44 with four.
+    int64_t rows_per = rows / ((int64_t)n_cu * 64);
+    rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
+    const int64_t grid = ceil_div64(ceil_div64(rows, rows_per), 4);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows,
+                       a.n, a.V, a.m, a.cand, (const float *)a.rb, a.R, a.req_count, a.count_pitch, a.todo, a.todo_count, (int)rows_per);
+    return GR4AD_OK;
+}
+// the request bounds: R rows of every request
+template <int ITEMS>
+static int launch_row_bounds(const RowsLaunch &a, int B) {
+    const dim3 grid((unsigned)((int64_t)B * a.R));
+    if (a.logits_f16)
+        hipLaunchKernelGGL((row_bounds<ITEMS, _Float16>), grid, dim3(256), 0, a.st, (const _Float16 *)a.logits, a.cum, a.n, a.V, a.m, a.R, a.rb,
+                           a.req_count, a.count_pitch, a.todo_count);
+    else
+        hipLaunchKernelGGL((row_bounds<ITEMS, float>), grid, dim3(256), 0, a.st, (const float *)a.logits, a.cum, a.n, a.V, a.m, a.R, a.rb, a.req_count,
+                           a.count_pitch, a.todo_count);
     return GR4AD_OK;
 }
 template <int VEC>
-static int launch_rows_vec(const RowsLaunch &a, int64_t rows, int64_t row_step, int mode) {
+static int launch_rows_vec(const RowsLaunch &a, int64_t rows, int mode) {
     const bool full = a.V == VEC * 256;
-    if (mode == 2) return full ? launch_rows_sweep_kind<VEC, true>(a, rows) : launch_rows_sweep_kind<VEC, false>(a, rows);
-    if (a.logits_f16)
-        return full ? launch_rows_wave_kind<VEC, true, _Float16>(a, rows, row_step, mode) : launch_rows_wave_kind<VEC, false, _Float16>(a, rows, row_step, mode);
-    return full ? launch_rows_wave_kind<VEC, true, float>(a, rows, row_step, mode) : launch_rows_wave_kind<VEC, false, float>(a, rows, row_step, mode);
+    if (mode == 3) return launch_row_bounds<(VEC < 8 ? 8 : VEC)>(a, (int)rows);
+    if (mode == 2) {
+        if (a.logits_f16) return full ? launch_rows_sweep_kind<VEC, true, _Float16>(a, rows) : launch_rows_sweep_kind<VEC, false, _Float16>(a, rows);
+        return full ? launch_rows_sweep_kind<VEC, true, float>(a, rows) : launch_rows_sweep_kind<VEC, false, float>(a, rows);
+    }
+    if (a.logits_f16) return full ? launch_rows_wave_kind<VEC, true, _Float16>(a, rows, mode) : launch_rows_wave_kind<VEC, false, _Float16>(a, rows, mode);
+    return full ? launch_rows_wave_kind<VEC, true, float>(a, rows, mode) : launch_rows_wave_kind<VEC, false, float>(a, rows, mode);
 }
-static int launch_rows(const RowsLaunch &a, int64_t rows, int64_t row_step, int mode) {
-    if (a.V <= 1024) return launch_rows_vec<4>(a, rows, row_step, mode);
-    if (a.V <= 2048) return launch_rows_vec<8>(a, rows, row_step, mode);
-    if (a.V <= 4096) return launch_rows_vec<16>(a, rows, row_step, mode);
-    return launch_rows_vec<32>(a, rows, row_step, mode);
+// mode 3: the request bounds (rows = requests)
+static int launch_rows(const RowsLaunch &a, int64_t rows, int mode) {
+    if (a.V <= 1024) return launch_rows_vec<4>(a, rows, mode);
+    if (a.V <= 2048) return launch_rows_vec<8>(a, rows, mode);
+    if (a.V <= 4096) return launch_rows_vec<16>(a, rows, mode);
+    return launch_rows_vec<32>(a, rows, mode);
 }
 
 // Half-precision logits are taken by the wavefront kernel only: 16-byte pieces of 8 values.
 bool select_takes_f16(int V) { return V >= 8 && V <= 8192 && V % 8 == 0; }
 
-// bound[b] = smallest of the m keys the first row of request b kept (wavefront per request); count[b] = 0; list count = 0
-__global__ __launch_bounds__(256) void request_bound_kernel(const unsigned long long *__restrict__ cand0, int m, int B,
-                                                            unsigned long long *__restrict__ bound, int *__restrict__ req_count,
-                                                            int *__restrict__ todo_count) {
-    const int lane = threadIdx.x % 64;
-    const int b = blockIdx.x * 4 + threadIdx.x / 64;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *todo_count = 0;  // the list of rows that need their own cut starts empty
-    if (b >= B) return;
-    unsigned long long mn = ~0ull;
-    for (int i = lane; i < m; i += 64) { const unsigned long long k = cand0[(int64_t)b * m + i]; mn = k < mn ? k : mn; }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { const unsigned long long t = __shfl_xor(mn, o, 64); mn = t < mn ? t : mn; }
-    if (lane == 0) { bound[b] = mn; req_count[b] = 0; }
-}
-__global__ __launch_bounds__(256) void fill_count_kernel(int *__restrict__ req_count, int B, int v) {
+__global__ __launch_bounds__(256) void fill_count_kernel(int *__restrict__ req_count, int count_pitch, int B, int v) {
     const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b < B) req_count[b] = v;
+    if (b < B) req_count[(int64_t)b * count_pitch] = v;
 }
 
-// workspace: candidates [B][n*m] keys, then the first rows' cuts [B][m], the request bounds [B], the request counts [B], the
-// count of listed rows (one int in 256 bytes) and the list {row, slot} [B*n]
-static inline size_t sel_ws_cand(int B, int n, int m) { return align256((size_t)B * n * m * sizeof(unsigned long long)); }
-static inline size_t sel_ws_cand0(int B, int m) { return align256((size_t)B * m * sizeof(unsigned long long)); }
-size_t select_workspace_bytes(int B, int n, int V, int k) {
-    int m = k < V ? k : V;
-    return sel_ws_cand(B, n, m) + sel_ws_cand0(B, m) + align256((size_t)B * sizeof(unsigned long long)) + align256((size_t)B * sizeof(int)) + 256 +
-           align256((size_t)B * n * sizeof(int2));
+// Workspace: candidates [B][n*m] keys, the request counts, the scores behind the bounds [B][2R], the count of listed rows (one int in 256
+// bytes) and the list {row, slot} [B*n].  Counts and scores together take at most 8 * m bytes per request.
+struct SelectPlan {
+    int R, count_pitch;
+    size_t counts, scores, todo_count, todo, total;
+};
+static SelectPlan select_plan(int B, int n, int V, int k) {
+    SelectPlan p;
+    const int m = k < V ? k : V;
+    p.R = 1;
+    while (p.R < BOUND_ROWS_MAX && p.R * 32 <= n && p.R * 4 <= m) p.R <<= 1;  // at most one row in sixteen is read for the bound
+    p.count_pitch = m < COUNT_PITCH_MAX ? m : COUNT_PITCH_MAX;
+    p.counts = align256((size_t)B * n * m * sizeof(unsigned long long));
+    p.scores = p.counts + align256((size_t)B * p.count_pitch * sizeof(int));
+    p.todo_count = p.scores + align256((size_t)B * 2 * p.R * sizeof(float));
+    p.todo = p.todo_count + 256;
+    p.total = p.todo + align256((size_t)B * n * sizeof(int2));
+    return p;
 }
+size_t select_workspace_bytes(int B, int n, int V, int k) { return select_plan(B, n, V, k).total; }
 
 int launch_select(const void *logits_any, int logits_f16, const float *cum, int B, int n, int V, int k, void *ws, size_t ws_bytes, int32_t *parent,
                   int32_t *tok, float *score, const int32_t *sid_old, int32_t *sid_new, const int32_t *anc_old, int32_t *anc_new, int T, int level,
@@ -1067,44 +1228,28 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
     const int m = k < V ? k : V;
     const int64_t rows = (int64_t)B * n;
     if (rows > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
+    const SelectPlan p = select_plan(B, n, V, k);
     unsigned long long *cand = (unsigned long long *)ws;
-    unsigned long long *cand0 = (unsigned long long *)((char *)ws + sel_ws_cand(B, n, m));
-    unsigned long long *bound = (unsigned long long *)((char *)cand0 + sel_ws_cand0(B, m));
-    int *req_count = (int *)((char *)bound + align256((size_t)B * sizeof(unsigned long long)));
-    int *todo_count = (int *)((char *)req_count + align256((size_t)B * sizeof(int)));
-    int2 *todo = (int2 *)((char *)todo_count + 256);
+    int *req_count = (int *)((char *)ws + p.counts), *todo_count = (int *)((char *)ws + p.todo_count);
     const bool wave_path = V <= 8192 && V % 4 == 0 && ((uintptr_t)logits % 16) == 0;
-    // Request-level bound (several rows per request, cut smaller than the row): the first row of a request holds its best
-    // beam; the m-th best candidate of that row is a score no survivor of the request can lie below.
-    const bool bounded = wave_path && n > 1 && k <= V;
+    // Request-level bound (a cut smaller than the row): see row_bounds
+    const bool bounded = wave_path && k <= V;
     {
         // algorithmic bytes: every logit once; the candidates written depend on the data (between k per request and m per row):
         // the lower bound is counted when the request-level bound is in use
         ProfScope ps(KC_SELECT_ROWS, st, 0.0, (double)rows * V * (logits_f16 ? 2 : 4) + (bounded ? (double)B * k : (double)rows * m) * 8);
         if (wave_path) {
-            const RowsLaunch a = {st, logits_any, logits_f16, cum, n, V, m, nullptr, bound, req_count, todo, todo_count};
-            RowsLaunch first = a, all = a;
-            first.cand = cand0;
-            first.bound = nullptr;
-            first.req_count = nullptr;
-            all.cand = cand;
+            const RowsLaunch a = {st, logits_any, logits_f16, cum, n, V, m, cand, (float *)((char *)ws + p.scores), p.R, req_count, p.count_pitch,
+                            (int2 *)((char *)ws + p.todo), todo_count};
             int s;
             if (bounded) {
-                if ((s = launch_rows(first, B, n, 0))) return s;  // the first row of every request, cut on its own
+                if ((s = launch_rows(a, B, 3))) return s;
                 GR4AD_LAUNCH_CHECK();
-                hipLaunchKernelGGL(request_bound_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, st, cand0, m, B, bound, req_count, todo_count);
+                if ((s = launch_rows(a, rows, 2))) return s;
                 GR4AD_LAUNCH_CHECK();
-                if (logits_f16) {
-                    if ((s = launch_rows(all, rows, 1, 2))) return s;
-                    GR4AD_LAUNCH_CHECK();
-                    if ((s = launch_rows(all, rows, 1, 1))) return s;
-                } else {
-                    if ((s = launch_rows(all, rows, 1, 0))) return s;
-                }
-            } else {
-                all.bound = nullptr;
-                all.req_count = nullptr;
-                if ((s = launch_rows(all, rows, 1, 0))) return s;
+                if ((s = launch_rows(a, rows, 1))) return s;
+            } else if ((s = launch_rows(a, rows, 0))) {
+                return s;
             }
         } else {
             const size_t stage_bytes = (size_t)m * sizeof(unsigned long long);  // <= 32 KB (GR4AD_MAX_BEAM)
@@ -1119,12 +1264,12 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
         }
         GR4AD_LAUNCH_CHECK();
         if (!bounded) {  // every row wrote its m: the request's candidates are the n*m keys of its rows
-            hipLaunchKernelGGL(fill_count_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, req_count, B, n * m);
+            hipLaunchKernelGGL(fill_count_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, req_count, p.count_pitch, B, n * m);
             GR4AD_LAUNCH_CHECK();
         }
     }
     ProfScope ps(KC_SELECT_REQUEST, st, 0.0, (bounded ? (double)B * k : (double)rows * m) * 8 + (double)B * k * 12);  // (same convention)
-    hipLaunchKernelGGL(select_request, dim3((unsigned)B), dim3(SELB_THREADS), 0, st, (const unsigned long long *)ws, (int64_t)n * m, req_count, V, k,
+    hipLaunchKernelGGL(select_request, dim3((unsigned)B), dim3(SELB_THREADS), 0, st, (const unsigned long long *)ws, (int64_t)n * m, req_count, p.count_pitch, V, k,
                        parent, tok, score, sid_old, sid_new, anc_old, anc_new, n, T, level);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
