@@ -679,28 +679,25 @@ __global__ __launch_bounds__(256, 3) void select_rows_wave(const LT *__restrict_
 }
 
 // The bounded pass.  A row stays in registers as it was read (raw[g]: tokens (g*64 + lane)*E .. +E-1; pieces past V hold -inf): maximum,
-// log-sum-exp and the sweep for candidates at or above the request's bound read it in place.  Each wavefront walks rows_per
-// consecutive rows; half-precision rows are half the registers, so it asks for the next one before it works on the current one and
-// the memory latency hides behind the arithmetic.  The candidates of its rows gather in LDS and leave with one reservation in the
-// request's segment per SWEEP_SLACK candidates or request.  A row with more than m candidates at the bound reserves m slots and is
+// log-sum-exp and the sweep for candidates at or above the request's bound read it in place.  Wavefronts walk the rows with the launch's
+// stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
+// candidates, were 15 % slower); half-precision rows are half the registers, so a wavefront asks for its next row before it works
+// on the current one and the memory latency hides behind the arithmetic.  A row with more than m candidates at the bound reserves m slots and is
 // put on the list for select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
-#define SWEEP_SLACK 128
 template <int VEC, bool FULL, typename LT>
 __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void select_rows_sweep(
     const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V, int m, unsigned long long *__restrict__ cand,
-    const float *__restrict__ rb, int R, int *__restrict__ req_count, int count_pitch, int2 *__restrict__ todo, int *__restrict__ todo_count, int rows_per) {
+    const float *__restrict__ rb, int R, int *__restrict__ req_count, int count_pitch, int2 *__restrict__ todo, int *__restrict__ todo_count) {
     constexpr bool HALF = sizeof(LT) == 2;
     constexpr int NX = VEC * 4, E = LogitPiece<LT>::E, G = NX / E;
-    extern __shared__ unsigned long long wave_lds[];  // per wavefront: m + SWEEP_SLACK slots of staged output
+    extern __shared__ unsigned long long wave_lds[];  // per wavefront: m slots of staged output
     // The row index is made a scalar of the wavefront (rows < 2^31, checked by the host): its cumulative score and bound then
     // come through scalar loads, which do not queue behind the vector loads of the next row.
     const int lane = threadIdx.x % 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const uint64_t row0 = (uint64_t)(blockIdx.x * 4u + (uint32_t)wv) * (uint32_t)rows_per;
-    if (row0 >= (uint64_t)rows) return;  // whole wavefronts leave; nothing below synchronises across wavefronts
-    uint32_t row = (uint32_t)row0;
-    const uint32_t row_end = (uint32_t)(row0 + (uint32_t)rows_per < (uint64_t)rows ? row0 + (uint32_t)rows_per : (uint64_t)rows);
-    unsigned long long *stage = wave_lds + (size_t)wv * (m + SWEEP_SLACK);
-    int held = 0;  // candidates of earlier rows of this request in `stage`, at most SWEEP_SLACK at the start of a row
+    const uint32_t nwaves = gridDim.x * 4u;
+    uint32_t row = blockIdx.x * 4u + (uint32_t)wv;
+    if (row >= (uint64_t)rows) return;  // whole wavefronts leave; nothing below synchronises across wavefronts
+    unsigned long long *stage = wave_lds + (size_t)wv * m;
     auto request_row = [&](uint32_t r, uint4 (&raw)[G]) {
         const uint4 *z = (const uint4 *)(logits + (int64_t)r * V);
 #pragma unroll
@@ -729,8 +726,9 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
     row_scalars(row, req, beam, c, rbv);
     request_row(row, raw);
     for (;;) {
-        const bool more = row + 1 < row_end;
-        const uint32_t ahead = more ? row + 1 : row;
+        const uint64_t next = (uint64_t)row + nwaves;
+        const bool more = next < (uint64_t)rows;
+        const uint32_t ahead = more ? (uint32_t)next : row;
         uint4 nxt[HALF ? G : 1];
         // (half precision: unconditional - the last row is asked for twice: a branch here would make the compiler wait for these loads at the
         // first use of the current row, as if they had been skipped)
@@ -806,30 +804,27 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
                         const unsigned long long mk = __ballot(hit);
                         const unsigned long long st = ((unsigned long long)__float_as_uint(sc + 0.0f) << 32) | (nflat - (uint32_t)(g * 64 * E + e));
                         const int at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0));
-                        if (hit && at < m) stage[held + at] = st;
+                        if (hit && at < m) stage[at] = st;
                         cnt += __popcll(mk);
                     }
                 }
             }
         }
-        if (cnt > m) {  // (wavefront-uniform) its m slots are filled by the listed pass
-            if (lane == 0) {
-                const int base = atomicAdd(&req_count[(int64_t)req * count_pitch], m);
-                todo[atomicAdd(todo_count, 1)] = make_int2((int)row, base);
-            }
-        } else {
-            held += cnt;
-        }
-        if (held > 0 && (held > SWEEP_SLACK || !more || req_n != req)) {
+        if (cnt > 0) {  // (wavefront-uniform)
+            const int take = cnt <= m ? cnt : m;
             int base = 0;
-            if (lane == 0) base = atomicAdd(&req_count[(int64_t)req * count_pitch], held);
+            if (lane == 0) {
+                base = atomicAdd(&req_count[(int64_t)req * count_pitch], take);
+                if (cnt > m) todo[atomicAdd(todo_count, 1)] = make_int2((int)row, base);  // its m slots are filled by the listed pass
+            }
             base = __shfl(base, 0, 64);
-            unsigned long long *dst = cand + (int64_t)req * ((int64_t)n * m) + base;
-            for (int i = lane; i < held; i += 64) dst[i] = staged_to_key(stage[i]);
-            held = 0;
+            if (cnt <= m) {
+                unsigned long long *dst = cand + (int64_t)req * ((int64_t)n * m) + base;
+                for (int i = lane; i < cnt; i += 64) dst[i] = staged_to_key(stage[i]);
+            }
         }
         if (!more) break;
-        row++;
+        row = (uint32_t)next;
         if constexpr (HALF) {
 #pragma unroll
             for (int g = 0; g < G; g++) raw[g] = nxt[g];
@@ -1142,19 +1137,19 @@ static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
     auto kern = select_rows_sweep<VEC, FULL, LT>;
     static bool attr_done = false;
     if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (GR4AD_MAX_BEAM + SWEEP_SLACK) * 8) != hipSuccess) return GR4AD_EHIP;
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * GR4AD_MAX_BEAM * 8) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
     const int n_cu = compute_units();
     if (!n_cu) return GR4AD_EHIP;
-    const size_t lds = 4 * (size_t)(a.m + SWEEP_SLACK) * sizeof(unsigned long long);
+    const size_t lds = 4 * (size_t)a.m * sizeof(unsigned long long);
     // Up to eight rows per wavefront, but 64 wavefronts per compute unit come first.  Measured at a million rows of 8192 halves: 3.6 ms,
     // 4.3 ms with 128 rows per wavefront, 3.8 ms with one; at 16384 rows of 4096: 35 us with one row per wavefront, 44 with four.
     int64_t rows_per = rows / ((int64_t)n_cu * 64);
     rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
     const int64_t grid = ceil_div64(ceil_div64(rows, rows_per), 4);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows,
-                       a.n, a.V, a.m, a.cand, (const float *)a.rb, a.R, a.req_count, a.count_pitch, a.todo, a.todo_count, (int)rows_per);
+                       a.n, a.V, a.m, a.cand, (const float *)a.rb, a.R, a.req_count, a.count_pitch, a.todo, a.todo_count);
     return GR4AD_OK;
 }
 // the request bounds: R rows of every request
@@ -1206,7 +1201,7 @@ static SelectPlan select_plan(int B, int n, int V, int k) {
     SelectPlan p;
     const int m = k < V ? k : V;
     p.R = 1;
-    while (p.R < BOUND_ROWS_MAX && p.R * 32 <= n && p.R * 4 <= m) p.R <<= 1;  // at most one row in sixteen is read for the bound
+    while (p.R < BOUND_ROWS_MAX && p.R * 64 <= n && p.R * 4 <= m) p.R <<= 1;  // at most one row in 32 is read for the bound
     p.count_pitch = m < COUNT_PITCH_MAX ? m : COUNT_PITCH_MAX;
     p.counts = align256((size_t)B * n * m * sizeof(unsigned long long));
     p.scores = p.counts + align256((size_t)B * p.count_pitch * sizeof(int));

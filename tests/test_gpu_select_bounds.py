@@ -1,0 +1,31 @@
+"""Selections whose request bound comes from several rows (one more power of two of rows per 64 beams), on both logit types."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_common import judge_selection
+from paper_2602_22732_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("spread", ["level", "steep", "best_row_last", "equal_logits"])
+@pytest.mark.parametrize("B,n,V,k", [(3, 1, 1024, 7), (2, 127, 264, 64), (2, 128, 264, 65), (1, 512, 1032, 1032), (1, 2048, 64, 60)])
+def test_select_bound_from_several_rows(B, n, V, k, spread, half):
+    rng = np.random.default_rng([B, n, V, k, half])
+    logits = rng.standard_normal((B, n, V)).astype(np.float16 if half else np.float32)
+    if spread == "equal_logits":
+        logits[:] = 0.25
+    cum = (-3.0 - 0.02 * rng.random((B, n))).astype(np.float32)
+    if spread == "steep":
+        cum -= 2.5 * np.arange(n, dtype=np.float32)
+    if spread == "best_row_last":
+        cum[:, :-1] -= 4.0
+    parent, tok, score = (t.cpu().numpy() for t in binding.op_select(torch.from_numpy(logits).cuda(), torch.from_numpy(cum).cuda(), k))
+    for b in range(B):
+        allsc = cum[b].astype(np.float64)[:, None] + np.stack([oracle.prim_log_softmax(logits[b, i].astype(np.float32)) for i in range(n)])
+        flat = parent[b].astype(np.int64) * V + tok[b]
+        assert len(np.unique(flat)) == k
+        judge_selection(allsc, flat, score[b], k, tol=3e-5, margin=2e-5, what="select b=%d" % b)
