@@ -900,8 +900,28 @@ static int epilogue_kind(const GemmEpilogue &e) {
 // STAGED (WT = 64, N and C aligned): operands swapped, C leaves through LDS in 16-byte pieces of whole rows, with everything the
 // persistent kernel's epilogue offers.  Otherwise a lane stores the 16 rows of its column directly (64 or 128 bytes per half
 // wavefront and register), any N and pitch; EPI_VT swaps the operands so that these are 32 consecutive tokens of a column.
+// The addends of a wave tile in the read-back layout of the staged epilogue: piece it of pass p is row p*32 + it*4 + lane/16, columns
+// (lane%16)*4 .. +3 (zero outside C).  Requested before the operands, they arrive under the main loop; requested in the epilogue
+// each pass waits for them (8192 x 512 x 512: 14.2 us, now 11).
 template <int KIND, int TM>
-__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
+__device__ __forceinline__ void staged_addends(floatx4 (&adds)[TM][8], int64_t wrow0, int wcol0, int64_t M, int N, const GemmEpilogue &epi, int lane) {
+    if (KIND != EPI_F32_RESID && KIND != EPI_F32_TABLE) return;
+    const int ecol = wcol0 + (lane % 16) * 4;
+#pragma unroll
+    for (int pass = 0; pass < TM; pass++)
+#pragma unroll
+        for (int it = 0; it < 8; it++) {
+            const int64_t row = wrow0 + pass * 32 + it * 4 + lane / 16;
+            adds[pass][it] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (row < M && ecol < N) {
+                if (KIND == EPI_F32_RESID) adds[pass][it] = *(const floatx4 *)(epi.resid + row * epi.ldr + ecol);
+                else adds[pass][it] = *(const floatx4 *)(epi.table + (epi.tok ? (int64_t)epi.tok[row] : 0) * N + ecol);
+            }
+        }
+}
+
+template <int KIND, int TM>
+__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], const floatx4 (&adds)[TM][8], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
                                                 const GemmEpilogue &epi, int lane) {
     const int frow = lane % 32, hf = lane / 32;
     if (epi.row_inv) {  // folded RMSNorm, reader side: a lane owns row frow of each 32-row block
@@ -959,16 +979,6 @@ __device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], char *st
         }
 #pragma unroll
         for (int pass = 0; pass < TM; pass++) {
-            floatx4 adds[8];
-#pragma unroll
-            for (int it = 0; it < 8; it++) {
-                const int64_t row = wrow0 + pass * 32 + it * 4 + erow;
-                adds[it] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-                if (KIND != EPI_F32 && row < M && ecol < N) {
-                    if (KIND == EPI_F32_RESID) adds[it] = *(const floatx4 *)(epi.resid + row * epi.ldr + ecol);
-                    else adds[it] = *(const floatx4 *)(epi.table + (epi.tok ? (int64_t)epi.tok[row] : 0) * N + ecol);
-                }
-            }
 #pragma unroll
             for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -985,7 +995,7 @@ __device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], char *st
                 const int rr = it * 4 + erow, c = lane % 16;
                 floatx4 x = *(const floatx4 *)(stage + rr * 256 + ((c ^ (rr & 15)) * 16));
                 const int64_t row = wrow0 + pass * 32 + rr;
-                if (KIND != EPI_F32) x += adds[it];
+                if (KIND != EPI_F32) x += adds[pass][it];
                 if (emit) {  // sum of squares over the row's 64 columns of this wavefront: the same tree as in the persistent kernel
                     float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
                     sq += __shfl_xor(sq, 1, 64);
@@ -1131,12 +1141,13 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
             src[i] = (const char *)(W + (row < N ? row : N - 1) * ldw) + chunk * 16;
         }
     }
-    auto issue = [&](int slot) {  // k-tiles are requested in ascending order
+    auto issue1 = [&](int slot, int i) {  // k-tiles are requested in ascending order
+        ring_dma16(src[i], (bf16x8 *)((char *)smem + slot * STAGE + (i * NW + wave) * 1024));
+        src[i] += 128;
+    };
+    auto issue = [&](int slot) {
 #pragma unroll
-        for (int i = 0; i < LPW; i++) {
-            ring_dma16(src[i], (bf16x8 *)((char *)smem + slot * STAGE + (i * NW + wave) * 1024));
-            src[i] += 128;
-        }
+        for (int i = 0; i < LPW; i++) issue1(slot, i);
     };
     // wait until at most `n` of this wavefront's k-tiles are in flight
     auto wait_tiles = [&](int n) {
@@ -1175,18 +1186,23 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
         for (int j = 0; j < T; j++)
 #pragma unroll
             for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
+    auto mma1 = [&](int s, int i, int j) {
+        acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s][i], wf[s][j], acc[i][j], 0, 0, 0);
+    };
     auto mma = [&](int s) {
 #pragma unroll
         for (int i = 0; i < T; i++)
 #pragma unroll
-            for (int j = 0; j < T; j++)
-                acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0)
-                                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s][i], wf[s][j], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < T; j++) mma1(s, i, j);
     };
 
 #define SB __builtin_amdgcn_sched_barrier(0)
     float add[16];
-    if (!STAGED && T == 1) direct_addends<KIND>(add, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);  // (on their way before the operands)
+    floatx4 adds[T][8];
+    // (on their way before the operands)
+    if constexpr (STAGED) staged_addends<KIND, T>(adds, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
+    else if (T == 1) direct_addends<KIND>(add, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
     const int first = KT < ST ? KT : ST;
     for (int t = 0; t < first; t++) issue(t);
     wait_tiles(first - 1);
@@ -1215,7 +1231,7 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     if constexpr (STAGED) {
         __builtin_amdgcn_s_barrier();  // every wavefront has read its last fragments: LDS becomes the staging area
         asm volatile("" ::: "memory");
-        staged_epilogue<KIND, T>(acc, (char *)smem + wave * 8192, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
+        staged_epilogue<KIND, T>(acc, adds, (char *)smem + wave * 8192, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
     } else {
 #pragma unroll
         for (int i = 0; i < T; i++)
