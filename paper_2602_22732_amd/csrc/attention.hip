@@ -12,6 +12,7 @@
 //                           (keys = values = the raw context rows, one query of
 //                           width d per (position, head)): one pass over the
 //                           context, MFMA, online softmax.
+//  * context_scores / context_sums  the same for few requests, tiles side by side.
 //  * self_attn_step<T>      autoregressive self-attention of the new position over
 //                           the beam path's earlier positions (at most T keys), read
 //                           in place from the buffers their levels wrote, through
@@ -723,21 +724,306 @@ static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ct
     return GR4AD_OK;
 }
 
+// ---------------------------------------------------------------------------
+// The same for few requests: the tiles of a request side by side.  One workgroup per request leaves most of the chip idle below some
+// hundred requests and walks its tiles one after the other, 2.9 us each (8 requests of 1024 rows: 93 us).  Here context_scores
+// computes the scores of every tile at once, one workgroup per (request, tile), and context_sums gives every request D / 128 (one
+// query tile: D / 256) workgroups, one per slice of the columns of z: they repeat the cheap part, the running maxima over the tile
+// maxima and the exponentials, and walk the tiles only for their product.  Every sum keeps the order of the one-pass kernel (partial
+// scores of the same slices of D, the lazily refreshed maximum tile by tile, the normaliser per half wavefront, z over the rows), so
+// the two give the same bits.  8 requests of up to 1024 rows, d = 1024, 64 queries: 93 us before, now 29; one of 512 rows, d = 512: 40, now 15.
+// ---------------------------------------------------------------------------
+#define CTX_CHUNK 8  // tiles whose probabilities are formed together
+#define CTX_STAGE (32 * 1024)
+
+// sc: [B][ntiles][QT][4][64 lanes][4] raw scores as a wavefront holds them; mxs: [B][ntiles][QT][32] scaled maximum of each tile's valid rows
+template <int D, int QT>
+__global__ __launch_bounds__(512) void context_scores(const bf16 *__restrict__ qp, const bf16 *__restrict__ x, const int32_t *__restrict__ ctx_len,
+                                                      float *__restrict__ sc, float *__restrict__ mxs, int RQ, int rq_stride, int S, float scale_log2e) {
+    constexpr int KSPLIT = 8 / QT, KSL = D / KSPLIT, KSTEPS = KSL / 16;
+    __shared__ __attribute__((aligned(16))) char part[QT * (KSPLIT - 1) * 4096];
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int tile = blockIdx.x, ntiles = gridDim.x, b = blockIdx.y;
+    const int r32 = lane % 32, g = lane / 32, kq = wave % KSPLIT, qh = wave / KSPLIT;
+    int len = ctx_len ? ctx_len[b] : S;
+    len = len < 1 ? 1 : (len > S ? S : len);
+    if (tile * 32 >= len) return;
+    const int row = tile * 32 + r32 < len ? tile * 32 + r32 : len - 1, qrow = qh * 32 + r32 < RQ ? qh * 32 + r32 : RQ - 1;
+    const bf16 *xr = x + ((int64_t)b * S + row) * D + kq * KSL + 8 * g;
+    const bf16 *qr = qp + ((int64_t)b * rq_stride + qrow) * D + kq * KSL + 8 * g;
+    bf16x8 xf[KSTEPS], qf[KSTEPS];
+#pragma unroll
+    for (int st = 0; st < KSTEPS; st++) { xf[st] = *(const bf16x8 *)(xr + 16 * st); qf[st] = *(const bf16x8 *)(qr + 16 * st); }
+    __builtin_amdgcn_sched_barrier(0);  // (every load on its way before the first product: one latency)
+    floatx16 s;
+#pragma unroll
+    for (int v = 0; v < 16; v++) s[v] = 0.0f;
+#pragma unroll
+    for (int st = 0; st < KSTEPS; st++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[st], qf[st], s, 0, 0, 0);
+    if (kq > 0) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            floatx4 pk;
+#pragma unroll
+            for (int e = 0; e < 4; e++) pk[e] = s[4 * i + e];
+            *(floatx4 *)(part + (qh * (KSPLIT - 1) + kq - 1) * 4096 + (i * 64 + lane) * 16) = pk;
+        }
+    }
+    __syncthreads();
+    if (kq > 0) return;
+#pragma unroll
+    for (int k = 0; k < KSPLIT - 1; k++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const floatx4 pk = *(const floatx4 *)(part + (qh * (KSPLIT - 1) + k) * 4096 + (i * 64 + lane) * 16);
+#pragma unroll
+            for (int e = 0; e < 4; e++) s[4 * i + e] += pk[e];
+        }
+    const int64_t unit = ((int64_t)b * ntiles + tile) * QT + qh;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        floatx4 pk;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            pk[e] = s[4 * i + e];
+            if (tile * 32 + 8 * i + 4 * g + e < len) mx = fmaxf(mx, pk[e]);
+        }
+        *(floatx4 *)(sc + unit * 1024 + (i * 64 + lane) * 4) = pk;
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;
+    if (g == 0) mxs[unit * 32 + r32] = mx;
+}
+
+template <int D, int QT>
+__global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, const int32_t *__restrict__ ctx_len, const float *__restrict__ sc,
+                                                    const float *__restrict__ mxs, bf16 *__restrict__ z, int RQ, int rq_stride, int S, int nt_max,
+                                                    float scale_log2e) {
+    constexpr int COLS = 256 / QT, ROWB = COLS * 2, CH = COLS / 8;  // columns of this workgroup, bytes and 16-byte pieces of a staged row
+    constexpr int TS = CTX_STAGE / (32 * ROWB);                     // tiles per stage (4, or 2 with one query tile)
+    constexpr int UPW = CTX_CHUNK * QT / 8;                         // (tile, query tile) units of probabilities per wavefront and chunk
+    constexpr int PB = 3 * CTX_STAGE, MB = PB + CTX_CHUNK * QT * 2048, AB = MB + CTX_CHUNK * QT * 128, LB = AB + 2 * CTX_CHUNK * QT * 128,
+                  IB = LB + CTX_CHUNK * QT * 256;
+    extern __shared__ __attribute__((aligned(16))) char ctx_lds[];  // 3 stages | P | maxima in use | rescale factors (two chunks) | sums | 1/l
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int b = blockIdx.y, slice = blockIdx.x;
+    const int r32 = lane % 32, g = lane / 32;
+    int len = ctx_len ? ctx_len[b] : S;
+    len = len < 1 ? 1 : (len > S ? S : len);
+    const int ntiles = (len + 31) / 32, nstages = (ntiles + TS - 1) / TS;
+    const bf16 *xb = x + (int64_t)b * S * D + slice * COLS;
+    const float *scb = sc + (int64_t)b * nt_max * QT * 1024, *mxb = mxs + (int64_t)b * nt_max * QT * 32;
+
+    auto issue_stage = [&](int st) {  // rows st*TS*32 .. of this workgroup's columns (past the length: the last valid row again)
+        char *dst = ctx_lds + (st % 3) * CTX_STAGE;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int id = (i * 8 + wave) * 64 + lane, r = id / CH, pos = id % CH;
+            int row = st * TS * 32 + r;
+            if (row > len - 1) row = len - 1;
+            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(xb + (int64_t)row * D + (pos ^ ctx_swz(r)) * 8),
+                                             (void __attribute__((address_space(3))) *)(dst + (i * 8 + wave) * 1024), 16, 0, 0);
+        }
+    };
+    // scores of this wavefront's units and, in the first QT wavefronts, the tile maxima of the chunk from tile c0 on, a chunk ahead
+    floatx4 sreg[UPW][4];
+    float mreg[CTX_CHUNK];
+    auto load_chunk = [&](int c0) {
+#pragma unroll
+        for (int k = 0; k < UPW; k++) {
+            const int u = wave + k * 8;
+            int t = c0 + u / QT;
+            if (t > ntiles - 1) t = ntiles - 1;
+#pragma unroll
+            for (int i = 0; i < 4; i++) sreg[k][i] = *(const floatx4 *)(scb + ((int64_t)t * QT + u % QT) * 1024 + (i * 64 + lane) * 4);
+        }
+        if (wave < QT) {
+#pragma unroll
+            for (int t = 0; t < CTX_CHUNK; t++) mreg[t] = mxb[((c0 + t < ntiles ? c0 + t : ntiles - 1) * QT + wave) * 32 + r32];
+        }
+    };
+    load_chunk(0);
+    issue_stage(0);
+    if (nstages > 1) issue_stage(1);
+
+    float m_run = -INFINITY, l_run = 0.0f, areg[CTX_CHUNK];  // (first QT wavefronts: lane = query r32, half g)
+    const int qt = wave / (8 / QT), ct = wave % (8 / QT);    // second product: query tile, 32 columns
+    floatx16 o;
+#pragma unroll
+    for (int v = 0; v < 16; v++) o[v] = 0.0f;
+    // transposing reads: see context_attn_flash_bf16
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)ctx_lds;
+    const int i16 = lane % 16, piece = ct * 4 + 2 * ((lane / 16) & 1) + (i16 % 4) / 2;
+    uint32_t tr_off[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int sr = 8 * g + 4 * h + i16 / 4;
+        tr_off[h] = (uint32_t)(sr * ROWB + (i16 & 1) * 8 + ((piece ^ ctx_swz(sr)) * 16));
+    }
+    int par = 0;
+    for (int c0 = 0; c0 < ntiles; c0 += CTX_CHUNK, par ^= 1) {
+        float *mA = (float *)(ctx_lds + MB), *aA = (float *)(ctx_lds + AB) + par * CTX_CHUNK * QT * 32, *lS = (float *)(ctx_lds + LB);
+        // ---- the maximum in use at every tile of the chunk ----
+        if (wave < QT) {
+#pragma unroll
+            for (int t = 0; t < CTX_CHUNK; t++) {
+                const float mx = mreg[t];
+                float alpha = 1.0f;
+                if (c0 + t < ntiles && mx > m_run + 8.0f) {
+                    alpha = __builtin_amdgcn_exp2f(m_run - mx);
+                    m_run = mx;
+                }
+                areg[t] = alpha;
+                if (g == 0) { mA[(t * QT + wave) * 32 + r32] = m_run; aA[(t * QT + wave) * 32 + r32] = alpha; }
+            }
+        }
+        __syncthreads();
+        // ---- probabilities ----
+#pragma unroll
+        for (int k = 0; k < UPW; k++) {
+            const int u = wave + k * 8, t = u / QT, q = (u % QT) * 32 + r32;
+            if (c0 + t < ntiles) {
+                const float neg_m = -mA[u * 32 + r32];
+                float lsum = 0.0f;
+                char *p_w = ctx_lds + PB + t * (QT * 2048) + q * 64 + g * 8;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    bf16x4 pk;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const float s = (c0 + t) * 32 + 8 * i + 4 * g + e < len ? sreg[k][i][e] : -INFINITY;
+                        const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s, scale_log2e, neg_m));
+                        lsum += pv;
+                        pk[e] = (bf16)pv;
+                    }
+                    *(bf16x4 *)(p_w + ((i ^ ((q >> 2) & 3)) * 16)) = pk;
+                }
+                lS[u * 64 + lane] = lsum;
+            }
+        }
+        __syncthreads();
+        if (wave < QT) {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int t = 0; t < CTX_CHUNK; t++)
+                if (c0 + t < ntiles) {
+                    l_run *= areg[t];
+                    l_run += lS[(t * QT + wave) * 64 + lane];
+                }
+        }
+        if (c0 + CTX_CHUNK < ntiles) load_chunk(c0 + CTX_CHUNK);
+        // ---- z^T += x^T P^T over the chunk's stages ----
+#pragma unroll 1
+        for (int st = c0 / TS; st < (c0 + CTX_CHUNK) / TS && st < nstages; st++) {
+            // this wavefront's share of the stage has landed (the next stage's loads, and younger ones, may be in flight); after the
+            // barrier everybody's has, and the stage before it is read out: its buffer takes stage st + 2
+            if (st + 1 < nstages) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (st + 2 < nstages) issue_stage(st + 2);
+#pragma unroll
+            for (int tt = 0; tt < TS; tt++) {
+                const int tile = st * TS + tt, t = tile - c0;
+                if (tile < ntiles) {
+                    const float a = aA[(t * QT + qt) * 32 + r32];
+                    if (__builtin_amdgcn_ballot_w64(a != 1.0f) != 0) {
+#pragma unroll
+                        for (int v = 0; v < 16; v++) o[v] *= a;
+                    }
+                    intx2 w[2][2];
+                    bf16x8 pf[2];
+#pragma unroll
+                    for (int ks = 0; ks < 2; ks++) {
+                        const int q = qt * 32 + r32;
+                        pf[ks] = *(const bf16x8 *)(ctx_lds + PB + t * (QT * 2048) + q * 64 + (((2 * ks + g) ^ ((q >> 2) & 3)) * 16));
+#pragma unroll
+                        for (int h = 0; h < 2; h++)
+                            asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(w[ks][h]) : "v"(lds0 + (st % 3) * CTX_STAGE + (tt * 32 + ks * 16) * ROWB + tr_off[h]));
+                    }
+                    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0][0]), "+v"(w[0][1]), "+v"(w[1][0]), "+v"(w[1][1]));
+#pragma unroll
+                    for (int ks = 0; ks < 2; ks++) {
+                        const intx4 both = __builtin_shufflevector(w[ks][0], w[ks][1], 0, 1, 2, 3);
+                        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[ks], o, 0, 0, 0);
+                    }
+                }
+            }
+        }
+    }
+    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    float *inv_l = (float *)(ctx_lds + IB);
+    if (wave < QT && g == 0) inv_l[wave * 32 + r32] = 1.0f / l_tot;
+    __syncthreads();
+    const int q = qt * 32 + r32;
+    if (q < RQ) {
+        const float inv = inv_l[q];
+        bf16 *zr = z + ((int64_t)b * rq_stride + q) * D + slice * COLS + ct * 32 + 4 * g;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            bf16x4 pk;
+#pragma unroll
+            for (int e = 0; e < 4; e++) pk[e] = (bf16)(o[4 * i + e] * inv);
+            *(bf16x4 *)(zr + 8 * i) = pk;
+        }
+    }
+}
+
+// Requests up to which the tiles run side by side: 128 at d = 512, 64 at d = 1024.  Their cost grows with the requests (each tile reads the
+// request's queries again: 1.7 us a request at d = 1024 and 64 queries, 0.27 us at d = 512 and 24), the one-pass kernel's only
+// from 256 requests on (111 us and 53 us there).
+static bool context_split(int B, int d) { return (int64_t)B * d <= 65536; }
+size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S, int d) {
+    if (!context_attention_covers(dtype, RQ, d) || !context_split(B, d)) return 0;
+    return (size_t)B * ((S + 31) / 32) * (RQ > 32 ? 2 : 1) * (1024 + 32) * sizeof(float);
+}
+
+template <int D, int QT>
+static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
+                                float *ws, hipStream_t st) {
+    auto sums = context_sums<D, QT>;
+    constexpr int LDS_BYTES = 3 * CTX_STAGE + CTX_CHUNK * QT * (2048 + 128 + 256 + 256) + QT * 128;
+    static_assert(LDS_BYTES <= 160 * 1024, "the workgroup's LDS");
+    static bool attr_done = false;
+    if (!attr_done) {
+        if (hipFuncSetAttribute((const void *)sums, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess) return GR4AD_EHIP;
+        attr_done = true;
+    }
+    const int nt = (S + 31) / 32;
+    float *mxs = ws + (size_t)B * nt * QT * 1024;
+    ProfScope ps(KC_CONTEXT_ATTN, st, 4.0 * B * (double)RQ * S * D, (2.0 * B * (double)RQ * D + B * (double)S * D) * sizeof(bf16));
+    hipLaunchKernelGGL((context_scores<D, QT>), dim3(nt, B), dim3(512), 0, st, qp, x, ctx_len, ws, mxs, RQ, rq_stride, S, scale * 1.4426950408889634f);
+    GR4AD_LAUNCH_CHECK();
+    hipLaunchKernelGGL(sums, dim3(D * QT / 256, B), dim3(512), LDS_BYTES, st, x, ctx_len, (const float *)ws, (const float *)mxs, z, RQ, rq_stride, S, nt,
+                       scale * 1.4426950408889634f);
+    GR4AD_LAUNCH_CHECK();
+    return GR4AD_OK;
+}
+
 // z [B, RQ, d] = attention of the queries qp [B, RQ, d] over the context rows x [B, S, d] as keys and values (above).
 int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, const int32_t *ctx_len, void *z, int B, int RQ, int S, int d,
-                             float scale, hipStream_t st) {
+                             float scale, void *ws, hipStream_t st) {
     if (!context_attention_covers(dtype, RQ, d) || B < 1 || S < 1) return GR4AD_EUNSUPPORTED;
-    if (!qp || !x || !z || ((uintptr_t)qp % 16) || ((uintptr_t)x % 16) || ((uintptr_t)z % 8)) return GR4AD_EINVAL;
+    if (!qp || !x || !z || ((uintptr_t)qp % 16) || ((uintptr_t)x % 16) || ((uintptr_t)z % 8) || ((uintptr_t)ws % 16)) return GR4AD_EINVAL;
     const bf16 *xx = (const bf16 *)x;
     for (int q0 = 0; q0 < RQ; q0 += 64) {  // 64 queries of every request per launch
         const bf16 *q = (const bf16 *)qp + (int64_t)q0 * d;
         bf16 *zz = (bf16 *)z + (int64_t)q0 * d;
         const int nq = RQ - q0 < 64 ? RQ - q0 : 64;
         int s;
-        if (d == 1024) s = nq > 32 ? launch_context_flash<1024, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st)
-                                   : launch_context_flash<1024, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st);
-        else s = nq > 32 ? launch_context_flash<512, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st)
-                         : launch_context_flash<512, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st);
+        if (ws && context_split(B, d)) {
+            float *w = (float *)ws;
+            if (d == 1024) s = nq > 32 ? launch_context_split<1024, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st)
+                                       : launch_context_split<1024, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st);
+            else s = nq > 32 ? launch_context_split<512, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st)
+                             : launch_context_split<512, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st);
+        } else if (d == 1024) {
+            s = nq > 32 ? launch_context_flash<1024, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st)
+                        : launch_context_flash<1024, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st);
+        } else {
+            s = nq > 32 ? launch_context_flash<512, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st)
+                        : launch_context_flash<512, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st);
+        }
         if (s) return s;
     }
     return GR4AD_OK;

@@ -172,8 +172,10 @@ int launch_masked_softmax(const float *sc, void *p, const int32_t *ctx_len, int6
 // (qp [B, RQ, d], x [B, S, d], bf16; 64 queries of every request per launch).  GR4AD_EUNSUPPORTED for shapes
 // context_attention_covers() refuses.
 bool context_attention_covers(gr4ad_dtype dtype, int RQ, int d);
+// ws: scratch of context_attention_workspace_bytes() bytes with which few requests run their tiles side by side, or NULL
+size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S, int d);
 int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, const int32_t *ctx_len, void *z, int B, int RQ, int S, int d,
-                             float scale, hipStream_t st);
+                             float scale, void *ws, hipStream_t st);
 // autoregressive self-attention of position `pos` for rows (b*n+i).  qkv [rows,3d] holds q, k, v of the new position;
 // the keys and values of position p < pos are columns d..3d of row anc[row*T + p] of prev.p[p] (the [*,3d] q/k/v buffer
 // that level wrote): the beam reorder is the ancestor table, no rows are moved.

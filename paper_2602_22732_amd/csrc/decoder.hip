@@ -138,7 +138,7 @@ Plan make_plan(const gr4ad_decoder *dec, int64_t B, int64_t S, const int32_t *be
         p.xt = take(two_pass ? (size_t)B * d * Spad * e : 0);
         p.qp = take((size_t)B * RQ * d * e);
         p.zb = take((size_t)B * RQ * d * e);
-        p.sc = take(two_pass ? (size_t)B * RQ * Spad * sizeof(float) : 0);
+        p.sc = take(two_pass ? (size_t)B * RQ * Spad * sizeof(float) : context_attention_workspace_bytes(dec->dtype, (int)B, (int)RQ, (int)S, dec->d));
         p.pb = take(two_pass ? (size_t)B * RQ * Spad * e : 0);
     }
     p.ss = take((size_t)p.rows_max * (d / 64 + 1) * sizeof(float));  // partial sums of squares of the folded RMSNorm
@@ -608,7 +608,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         if ((s = launch_gemm_batched(q, d, dh, lw.wkT_x, dh, (int64_t)d * dh, qp, (int64_t)H * d, d, 0, rows, d, dh, H, nullptr, 0, st))) return s;
         if (one_pass) {
             // scores, softmax and z in one kernel that reads the request's context rows once (widths and query counts it covers)
-            if ((s = launch_context_attention(dt, qp, ctx, ctx_len, zb, B, (int)RQ, S, d, 1.0f / sqrtf((float)dh), st))) return s;
+            if ((s = launch_context_attention(dt, qp, ctx, ctx_len, zb, B, (int)RQ, S, d, 1.0f / sqrtf((float)dh), sc, st))) return s;
         } else {
             // raw scores[b][(t,h)][s] = q'[b][(t,h)] . x[b][s]         (batch = request; columns beyond the length are not needed)
             if ((s = launch_gemm_batched(qp, d, RQ * d, ctx, d, (int64_t)S * d, sc, Spad, RQ * Spad, 1, RQ, S, d, B, ctx_len, 1, st))) return s;
@@ -787,7 +787,7 @@ int gr4ad_op_cross_attention(gr4ad_dtype dtype, const void *q, const void *kv, c
 int gr4ad_op_context_attention(gr4ad_dtype dtype, const void *q, const void *x, const int32_t *ctx_len, void *out, int32_t B, int32_t RQ,
                                int32_t S, int32_t d, float scale, void *hip_stream) {
     if (!q || !x || !out || B < 1 || RQ < 1 || S < 1 || d < 1 || !(scale > 0.0f)) return GR4AD_EINVAL;
-    return launch_context_attention(dtype, q, x, ctx_len, out, B, RQ, S, d, scale, (hipStream_t)hip_stream);
+    return launch_context_attention(dtype, q, x, ctx_len, out, B, RQ, S, d, scale, nullptr, (hipStream_t)hip_stream);
 }
 
 int gr4ad_op_gather_rows(gr4ad_dtype dtype, const void *src, const int32_t *parent, void *dst, int32_t B, int32_t n, int32_t k,
