@@ -68,39 +68,45 @@ int gr4ad_set_thread_error(int code, const char *fmt, ...) __attribute__((format
 
 // ---- GEMM: C[M,N] = A[M,K] * W[N,K]^T with a fused epilogue -----------------
 enum { ACT_NONE = 0, ACT_SILU = 1 };
+// (Kernel arguments are read from memory that is cold at every launch, a 64-byte line at a time: what the small products read - the
+// fields up to skip_len - shares the first two lines with the operands.)
 struct GemmEpilogue {
     void *C;             // output, row stride ldc elements
     int64_t ldc;
-    int out_f32;         // 1: C is float, 0: C has the storage dtype
-    int out_f16;         // with out_f32 = 1 and no residual/table (large products only): the float32 results (scaled, biased) leave as
-                         // IEEE half precision, C is a half array (row stride ldc elements): the classifier's logits for the selection
     const float *resid;  // float32 [M, stride ldr] residual stream, added to the product (may alias C)
     int64_t ldr;
     const float *bias;   // [N] float, added per column
     const float *table;  // float32 [*, N]: row tok[row] (or row 0 if tok == NULL) added per row
     const int32_t *tok;  // [M] row selector of `table`
-    const void *rowmul;  // unused by the GEMM (reserved)
+    // matrix-core kernels only (ignored elsewhere): the rows of A are requests of skip_S rows each of which only the first
+    // skip_len[b] are valid; output tiles whose rows all lie in one request's padding are not computed (their C is not written)
+    const int32_t *skip_len;
+    int skip_S;
+    int out_f32;         // 1: C is float, 0: C has the storage dtype
+    int out_f16;         // with out_f32 = 1 and no residual/table (large products only): the float32 results (scaled, biased) leave as
+                         // IEEE half precision, C is a half array (row stride ldc elements): the classifier's logits for the selection
     int act;             // ACT_*
     const int32_t *ctx_len;  // launch_gemm_vt only: valid rows per request (NULL = all)
     int vt_S;                // launch_gemm_vt only: rows per request
+    int len_bounds;            // launch_gemm_batched only, 1: batch_len bounds the columns of C that are needed, 2: it bounds K
+    const int32_t *batch_len;  // launch_gemm_batched only: valid length per batch (NULL = none)
     // RMSNorm folded into the projections around it (large products only; launch_gemm fails if it cannot honour them):
     // writer side (out_f32 with resid or table, N % 256 == 0): besides C, write norm_out[row, col] = C[row, col] * norm_gain[col]
     // in the storage dtype (row stride norm_ld) and norm_ss[row * (N / 64) + col / 64] = sum of C^2 over those 64 columns
     // (launch_row_inv turns them into 1/rms per row); reader side: scale row r of the product by row_inv[r] before anything
     // else the epilogue does (activation, bias).
+    const float *row_inv;
     const void *norm_gain;
     void *norm_out;
     int64_t norm_ld;
     float *norm_ss;
-    const float *row_inv;
-    // matrix-core kernels only (ignored elsewhere): the rows of A are requests of skip_S rows each of which only the first
-    // skip_len[b] are valid; output tiles whose rows all lie in one request's padding are not computed (their C is not written)
-    const int32_t *skip_len;
-    int skip_S;
     const float *a_scale;      // launch_gemm_f8 only (set by it): per-row scale of the FP8 A operand
     float w_scale;             // launch_gemm_f8 only (set by it): scale of the FP8 W operand
-    const int32_t *batch_len;  // launch_gemm_batched only: valid length per batch (NULL = none)
-    int len_bounds;            // 1: the length bounds the columns of C that are needed, 2: it bounds K
+    // The A operand is RMSNorm(pre_x) with gain pre_gain: pre_x float32 [M, K] (row stride K); A (row stride K) is where its rows go if they
+    // have to be formed by the norm kernel.  Small float32 products normalise in their own prologue instead.
+    float pre_eps;
+    const float *pre_x;
+    const void *pre_gain;
 };
 // A row stride lda, W row stride ldw (elements).  dtype: storage type of A, W (and C unless out_f32).
 int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,

@@ -487,7 +487,8 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     // stream x (residual update or Fuse) and one that reads norm(x).  On launches that run on the persistent kernel the
     // writer also stores gain * x (storage dtype, into xn) and per-row partial sums of x^2, and the reader scales its
     // product rows by 1/rms(x) - (gain * x / rms) W^T = (1/rms) (gain * x) W^T - so the norm kernel and its pass over
-    // the stream disappear.  Elsewhere (small launches, float32, widths the kernel does not cover) the norm kernel runs.
+    // the stream disappear.  Elsewhere (small launches, float32, widths the kernel does not cover) the reader forms its operand itself
+    // (GemmEpilogue::pre_x).
     const int nparts = d / 64;
     float *ss = (float *)(ws + p.ss), *rinv = ss + (size_t)p.rows_max * nparts;  // partial sums of x^2; 1/rms per row
     bool fold = false;             // set per phase: this row count and these widths run on the persistent kernel
@@ -518,6 +519,8 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     auto gemm8 = [&](int64_t M, const void *W8, float wscale, int N, int Kdim, const GemmEpilogue &epi) {
         return launch_gemm_f8(aq, Kdim, ascale, W8, Kdim, wscale, M, N, Kdim, epi, st);
     };
+    const float *pre_x = nullptr;
+    const void *pre_gain = nullptr;
     auto norm = [&](void *x, const void *gain, int64_t rows) -> int {
         if (f8) {
             emitted = nullptr;
@@ -531,10 +534,18 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         }
         emitted = nullptr;
         scaled = false;
-        return launch_rmsnorm(dt, x, gain, xn, rows, d, dec->eps, st);
+        pre_x = (const float *)x;  // formed by the product that reads it: in its prologue, or by the norm kernel into xn
+        pre_gain = gain;
+        return GR4AD_OK;
     };
-    auto reads_norm = [&](GemmEpilogue g) {  // reader side: the A operand is xn
-        if (scaled) g.row_inv = rinv;
+    auto reads_norm = [&](GemmEpilogue g) {  // reader side: the A operand is xn (every norm has one reader)
+        if (scaled) {
+            g.row_inv = rinv;
+        } else {
+            g.pre_x = pre_x;
+            g.pre_gain = pre_gain;
+            g.pre_eps = dec->eps;
+        }
         return g;
     };
 

@@ -117,6 +117,25 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
     const float *a = A + (ar < M ? ar : M - 1) * lda + k4, *w = W + (int64_t)(wr < N ? wr : N - 1) * ldw + k4;  // (rows past the edge: never stored)
     typedef typename std::conditional<T == 16, floatx4, floatx16>::type Acc;
     Acc acc = {};
+    __shared__ float rinv[16];
+    if constexpr (T == 16) {
+        if (epi.pre_x) {  // A = RMSNorm(pre_x): 1/rms of the tile's rows, four per wavefront (the loads below take the gain)
+            float ss[4] = {};
+            for (int k = lane * 4; k < K; k += 256)
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    const int64_t r = m0 + wave + 4 * q;
+                    const floatx4 v = *(const floatx4 *)(epi.pre_x + (r < M ? r : M - 1) * lda + k);
+                    ss[q] += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+                }
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                ss[q] = wave_sum_dpp(ss[q]);
+                if (lane == 0) rinv[wave + 4 * q] = 1.0f / sqrtf(ss[q] / (float)K + epi.pre_eps);
+            }
+            __syncthreads();
+        }
+    }
     const int nb = (K + KB - 1) / KB;                              // blocks of KB values of k
     const int per = T == 16 ? (nb + 3) / 4 : nb, b0 = T == 16 ? wave * per : 0, b1 = b0 + per < nb ? b0 + per : nb;
     for (int b = b0; b < b1; b += UN) {
@@ -128,6 +147,8 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
             if (b + u < b1 && k < K) {
                 av[u] = *(const floatx4 *)(a + (int64_t)(b + u) * KB);
                 wv[u] = *(const floatx4 *)(w + (int64_t)(b + u) * KB);
+                if constexpr (T == 16)
+                    if (epi.pre_x) av[u] = *(const floatx4 *)((const float *)epi.pre_gain + k) * av[u] * rinv[lane % 16];
             }
         }
 #pragma unroll
@@ -158,9 +179,11 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
     }
 }
 
+// 64x64 tiles once they give every compute unit one (below that the finer tiles and the split of K win)
+static bool f32_big_tiles(int64_t M, int N) { return ceil_div64(M, 64) * ceil_div64(N, 64) >= 256; }
+
 static int launch_f32(const float *A, int64_t lda, const float *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi, hipStream_t st) {
-    // 64x64 tiles once they give every compute unit one (below that the finer tiles and the split of K win)
-    const bool big = ceil_div64(M, 64) * ceil_div64(N, 64) >= 256;
+    const bool big = f32_big_tiles(M, N);
     const int64_t gx = ceil_div64(M, big ? 64 : 16), gy = ceil_div64(N, big ? 64 : 16);
     if (gx > 0x7fffffffLL || gy > 65535) return GR4AD_EUNSUPPORTED;
     ProfScope ps(KC_GEMM_SIMPLE, st, 2.0 * (double)M * N * K);
@@ -1083,7 +1106,7 @@ __device__ __forceinline__ void direct_epilogue(const floatx16 &acc, const float
     }
 }
 
-template <int BM, int BN, int WT, int ST, int KIND, bool STAGED>
+template <int BM, int BN, int WT, int ST, int KIND, bool STAGED, bool BATCHED>
 __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(const bf16 *__restrict__ A, int64_t lda, const bf16 *__restrict__ W,
                                                                              int64_t ldw, int64_t M, int N, int K, int tiles_m, int tiles_n,
                                                                              GemmEpilogue epi, int64_t batch_a, int64_t batch_w, int64_t batch_c) {
@@ -1098,9 +1121,11 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     // blockIdx.y: batch index; the operands and the output of batch i start batch_a/w/c elements further on
-    A += (int64_t)blockIdx.y * batch_a;
-    W += (int64_t)blockIdx.y * batch_w;
-    epi.C = (char *)epi.C + (int64_t)blockIdx.y * batch_c * (kind_f32(KIND) ? 4 : 2);
+    if (BATCHED) {
+        A += (int64_t)blockIdx.y * batch_a;
+        W += (int64_t)blockIdx.y * batch_w;
+        epi.C = (char *)epi.C + (int64_t)blockIdx.y * batch_c * (kind_f32(KIND) ? 4 : 2);
+    }
     // XCD-aware order: consecutive workgroup ids land on different XCDs (each with its own L2), so every XCD gets a contiguous range
     // of tiles, walked in groups of 8 row blocks (rows fastest): the tiles in flight on an XCD share their A and W blocks
     const uint32_t total = (uint32_t)tiles_m * (uint32_t)tiles_n, per_xcd = (total + 7) / 8;
@@ -1110,13 +1135,13 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     const uint32_t left = (uint32_t)tiles_m - grp * 8, gm = left < 8 ? left : 8;
     const int64_t m0 = (int64_t)(grp * 8 + in % gm) * BM;
     const int n0 = (int)(in / gm) * BN;
-    if (epi.batch_len) {  // a valid length per batch: bounds the columns of C that are needed (1) or K (2)
+    if (BATCHED && epi.batch_len) {  // a valid length per batch: bounds the columns of C that are needed (1) or K (2)
         int len = epi.batch_len[blockIdx.y];
         len = len < 1 ? 1 : len;
         if (epi.len_bounds == 1 && n0 >= len) return;
         if (epi.len_bounds == 2 && len < K) K = (len + 63) / 64 * 64;
     }
-    if (epi.skip_len) {
+    if (!BATCHED && (KIND == EPI_STORE || KIND == EPI_VT) && epi.skip_len) {
         // all rows of the tile in one request's padding, past the 64-row block of its last valid row: nobody reads the product
         const uint32_t r0 = (uint32_t)m0, S = (uint32_t)epi.skip_S, b0 = r0 / S;
         if (b0 == (r0 + BM - 1) / S) {
@@ -1243,12 +1268,12 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     }
 }
 
-template <int BM, int BN, int WT, int ST, int KIND, bool STAGED>
+template <int BM, int BN, int WT, int ST, int KIND, bool STAGED, bool BATCHED = false>
 static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi,
                             hipStream_t st, int batch = 1, int64_t batch_a = 0, int64_t batch_w = 0, int64_t batch_c = 0) {
     constexpr int NT = (BM / WT) * (BN / WT) * 64;
     constexpr size_t smem = (size_t)ST * (BM + BN) * 128;
-    auto kern = gemm_bf16_tile<BM, BN, WT, ST, KIND, STAGED>;
+    auto kern = gemm_bf16_tile<BM, BN, WT, ST, KIND, STAGED, BATCHED>;
     static bool attr_done = false;  // one attribute call per instantiation is enough (value never changes)
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return GR4AD_EHIP;
@@ -1269,12 +1294,17 @@ static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t l
 template <int BM, int BN, int WT, int ST, bool STAGED>
 static int launch_tile_cfg(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
                            hipStream_t st, int batch, int64_t ba, int64_t bw, int64_t bc) {
-#define KIND_(k) case k: return launch_tile_kind<BM, BN, WT, ST, k, STAGED>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+#define KIND_(k) case k: return launch_tile_kind<BM, BN, WT, ST, k, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
+    if (batch > 1) {
+        if (kind == EPI_STORE) return launch_tile_kind<BM, BN, WT, ST, EPI_STORE, STAGED, true>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+        if (kind == EPI_F32) return launch_tile_kind<BM, BN, WT, ST, EPI_F32, STAGED, true>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+        return GR4AD_EUNSUPPORTED;
+    }
     switch (kind) {
         KIND_(EPI_STORE) KIND_(EPI_SILU_DIV) KIND_(EPI_F32) KIND_(EPI_F32_RESID) KIND_(EPI_F32_TABLE)
-        case EPI_SILU: if constexpr (STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_SILU, STAGED>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+        case EPI_SILU: if constexpr (STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_SILU, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
             return GR4AD_EUNSUPPORTED;
-        case EPI_VT: if constexpr (!STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_VT, STAGED>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+        case EPI_VT: if constexpr (!STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_VT, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
             return GR4AD_EUNSUPPORTED;
     }
 #undef KIND_
@@ -1400,6 +1430,10 @@ int launch_gemm_f8(const void *A, int64_t lda, const float *a_scale, const void 
     return GR4AD_OK;
 }
 
+static bool f32_mfma_ok(const void *A, int64_t lda, const void *W, int64_t ldw, int K) {
+    return K % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0;
+}
+
 // bf16 products with 16-byte aligned, K-contiguous operands run on the matrix cores, everything else on the plain kernel.  Products
 // of at least 8192 rows and 256 columns with aligned rows form a class of their own: they may fold the RMSNorm into their
 // epilogues, leave half-precision logits and use the hardware reciprocal in SiLU.  What a product computes depends on that class alone;
@@ -1422,6 +1456,16 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
     const int kind = epilogue_kind(epi);
     // only the persistent kernel folds the RMSNorm or writes half-precision logits: never drop such a request silently
     if ((epi.norm_out || epi.row_inv || epi.out_f16) && !gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) return GR4AD_EUNSUPPORTED;
+    if (epi.pre_x) {
+        if (lda != K || !epi.pre_gain) return GR4AD_EINVAL;
+        if (dtype == GR4AD_F32 && !f32_big_tiles(M, N) && f32_mfma_ok(epi.pre_x, lda, W, ldw, K) && ((uintptr_t)epi.pre_gain % 16) == 0)
+            return launch_f32(epi.pre_x, lda, (const float *)W, ldw, M, N, K, epi, st);
+        const int s = launch_rmsnorm(dtype, epi.pre_x, epi.pre_gain, (void *)A, M, K, epi.pre_eps, st);
+        if (s) return s;
+        GemmEpilogue plain = epi;
+        plain.pre_x = nullptr;
+        return launch_gemm(dtype, A, lda, W, ldw, M, N, K, plain, st);
+    }
     if (mfma_ok(dtype, A, lda, W, ldw, K, kind)) {
         const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
         if (gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) {
@@ -1432,7 +1476,7 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
         const int run = pick_kernel(M, N, K, 1, true, true, N >= 256 && ring_ok(k, N, K, lda, ldw, epi));
         return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, k, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, k, epi, st);
     }
-    if (dtype == GR4AD_F32 && K % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0)
+    if (dtype == GR4AD_F32 && f32_mfma_ok(A, lda, W, ldw, K))
         return launch_f32((const float *)A, lda, (const float *)W, ldw, M, N, K, epi, st);
     dim3 grid((unsigned)ceil_div64(M, 64), (unsigned)((N + 63) / 64));
     if (ceil_div64(M, 64) > 0x7fffffffLL || grid.y > 65535) return GR4AD_EUNSUPPORTED;
