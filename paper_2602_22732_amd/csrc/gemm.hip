@@ -1114,7 +1114,7 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     constexpr int LPW = (BM + BN) / 8 / NW;           // loads of a wavefront per k-tile (1 KB each: 8 rows)
     constexpr int STAGE = (BM + BN) * 128;            // bytes of a k-tile
     constexpr bool SWAP = STAGED || KIND == EPI_VT;   // W fragment first
-    static_assert((BM + BN) / 8 % NW == 0 && (ST - 1) * LPW <= 63 && ST >= 2, "load counts");
+    static_assert((BM + BN) / 8 % NW == 0 && (ST - 1) * LPW <= 63 && ST >= 2 && ST <= 4, "load counts");
     static_assert(!STAGED || WT == 64, "the staged epilogue takes 64 x 64 wave tiles");
     extern __shared__ bf16x8 smem[];
     const int tid = threadIdx.x, lane = tid % 64;
@@ -1153,36 +1153,24 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
 
     // ---- loads: piece p = i * NW + wave fills rows 8p .. 8p+7 of the k-tile's BM rows of A and BN rows of W, lane -> row lane/8,
     // position lane%8 (rows past the matrix edge re-read its last row) ----
-    const char *src[LPW];
+    // A lane's byte offset in its operand block stays, the two block addresses move on: no vector arithmetic per k-tile.
+    const char *base_a = (const char *)(A + m0 * lda), *base_w = (const char *)(W + (int64_t)n0 * ldw);
+    uint32_t off[LPW];
 #pragma unroll
     for (int i = 0; i < LPW; i++) {
-        const int p = i * NW + wave, r = p * 8 + lane / 8;
-        const int chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
-        if (p < BM / 8) {
-            const int64_t row = m0 + r;
-            src[i] = (const char *)(A + (row < M ? row : M - 1) * lda) + chunk * 16;
-        } else {
-            const int64_t row = (int64_t)n0 + r - BM;
-            src[i] = (const char *)(W + (row < N ? row : N - 1) * ldw) + chunk * 16;
-        }
+        const int p = i * NW + wave, r = p * 8 + lane / 8, chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
+        if (p < BM / 8) off[i] = (uint32_t)(m0 + r < M ? r : M - 1 - m0) * ((uint32_t)lda * 2) + chunk * 16;
+        else off[i] = (uint32_t)(n0 + r - BM < N ? r - BM : N - 1 - n0) * ((uint32_t)ldw * 2) + chunk * 16;
     }
-    auto issue1 = [&](int slot, int i) {  // k-tiles are requested in ascending order
-        ring_dma16(src[i], (bf16x8 *)((char *)smem + slot * STAGE + (i * NW + wave) * 1024));
-        src[i] += 128;
-    };
-    auto issue = [&](int slot) {
+    auto issue = [&](uint32_t at) {  // k-tiles are requested in ascending order; at: byte offset of the slot
 #pragma unroll
-        for (int i = 0; i < LPW; i++) issue1(slot, i);
+        for (int i = 0; i < LPW; i++)
+            ring_dma16(((i * NW + wave) < BM / 8 ? base_a : base_w) + off[i], (bf16x8 *)((char *)smem + at + (i * NW + wave) * 1024));
+        base_a += 128;
+        base_w += 128;
     };
-    // wait until at most `n` of this wavefront's k-tiles are in flight
-    auto wait_tiles = [&](int n) {
-        switch (n < ST - 1 ? n : ST - 1) {
-#define W_(x) case x: asm volatile("s_waitcnt vmcnt(%0)" ::"n"((x) * LPW > 63 ? 63 : (x) * LPW) : "memory"); break;
-            W_(1) W_(2) W_(3) W_(4) W_(5) W_(6) W_(7)
-#undef W_
-            default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-    };
+    // wait until at most n of this wavefront's k-tiles are in flight
+    auto wait_tiles = [&](auto n) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n.value * LPW) : "memory"); };
 
     // ---- fragments: lane reads row frow of a 32-row block, chunk 2s + hf of k-step s, i.e. position (hf ^ fx) ^ 2s ----
     const int frow = lane % 32, hf = lane / 32, fx = (frow >> 1) & 7;
@@ -1190,8 +1178,8 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     const uint32_t a_lane = lds0 + (uint32_t)((wm * WT + frow) * 8 + (hf ^ fx)) * 16;
     const uint32_t w_lane = lds0 + (uint32_t)((BM + wn * WT + frow) * 8 + (hf ^ fx)) * 16;
     bf16x8 af[4][T], wf[4][T];
-    auto read = [&](int slot, int s) {
-        const uint32_t pa = (a_lane ^ (uint32_t)(s << 5)) + (uint32_t)(slot * STAGE), pw = (w_lane ^ (uint32_t)(s << 5)) + (uint32_t)(slot * STAGE);
+    auto read = [&](uint32_t at, int s) {
+        const uint32_t pa = (a_lane ^ (uint32_t)(s << 5)) + at, pw = (w_lane ^ (uint32_t)(s << 5)) + at;
         asm volatile("ds_read_b128 %0, %1" : "=v"(af[s][0]) : "v"(pa));
         if (T > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(af[s][T - 1]) : "v"(pa));
         asm volatile("ds_read_b128 %0, %1" : "=v"(wf[s][0]) : "v"(pw));
@@ -1229,29 +1217,40 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
     if constexpr (STAGED) staged_addends<KIND, T>(adds, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
     else if (T == 1) direct_addends<KIND>(add, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
     const int first = KT < ST ? KT : ST;
-    for (int t = 0; t < first; t++) issue(t);
-    wait_tiles(first - 1);
+    for (int t = 0; t < first; t++) issue((uint32_t)(t * STAGE));
+    if (KT < ST) wait_tiles(std::integral_constant<int, 0>());
+    else wait_tiles(std::integral_constant<int, ST - 1>());
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     read(0, 0);
     read(0, 1);
-    int slot = 0;
-    for (int kt = 0; kt < KT; kt++) {
-        SB; read(slot, 2); read(slot, 3);
+    uint32_t at = 0;
+    // One k-tile.  ahead: k-tiles that may be in flight beyond the next one (-1: this is the last); refill: k-tile kt + ST goes into its slot.
+    // Everything the loop would branch on is known at compile time: in a product that is one latency chain the scalar
+    // branches of a wait by count cost as much as the MFMAs (0.16 us per k-tile without any memory traffic, now 0.13).
+    auto step = [&](auto ahead, auto refill) {
+        SB; read(at, 2); read(at, 3);
         wait_frags(0, 3); SB; mma(0); SB;
         wait_frags(1, 2); SB; mma(1); SB;
         wait_frags(2, 0); wait_frags(3, 0); SB;
-        const int next = slot + 1 == ST ? 0 : slot + 1;
-        if (kt + 1 < KT) {
-            wait_tiles(KT - 2 - kt < ST - 2 ? KT - 2 - kt : ST - 2);  // this wavefront's share of k-tile kt + 1 has landed
-            __builtin_amdgcn_s_barrier();                             // everybody's has, and everybody has read k-tile kt
+        if constexpr (ahead.value >= 0) {
+            wait_tiles(ahead);             // this wavefront's share of the next k-tile has landed
+            __builtin_amdgcn_s_barrier();  // everybody's has, and everybody has read this one
             asm volatile("" ::: "memory");
-            if (kt + ST < KT) issue(slot);
+            const uint32_t next = at + STAGE == (uint32_t)(ST * STAGE) ? 0u : at + (uint32_t)STAGE;
+            if constexpr (refill.value) issue(at);
             SB; read(next, 0); read(next, 1); SB;
+            at = next;
         }
         mma(2); mma(3);
-        slot = next;
-    }
+    };
+    for (int kt = ST; kt < KT; kt++) step(std::integral_constant<int, ST - 2>(), std::true_type());
+    if constexpr (ST >= 4)
+        if (KT >= 4) step(std::integral_constant<int, 2>(), std::false_type());
+    if constexpr (ST >= 3)
+        if (KT >= 3) step(std::integral_constant<int, 1>(), std::false_type());
+    if (KT >= 2) step(std::integral_constant<int, 0>(), std::false_type());
+    step(std::integral_constant<int, -1>(), std::false_type());
 #undef SB
     if constexpr (STAGED) {
         __builtin_amdgcn_s_barrier();  // every wavefront has read its last fragments: LDS becomes the staging area
@@ -1280,7 +1279,7 @@ static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t l
         attr_done = true;
     }
     const int64_t tiles_m = ceil_div64(M, BM), tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n;
-    if (total > 0x7ffffff0LL || batch < 1 || batch > 65535) return GR4AD_EUNSUPPORTED;
+    if (total > 0x7ffffff0LL || batch < 1 || batch > 65535 || lda >= (1 << 23) || ldw >= (1 << 23)) return GR4AD_EUNSUPPORTED;
     if (epi.skip_len && M > 0x7fffff00LL) return GR4AD_EUNSUPPORTED;
     {
         ProfScope ps(KC_GEMM_TILE, st, 2.0 * (double)M * N * K * batch, batch * gemm_bytes(M, N, K, kind_f32(KIND) && !epi.out_f16, KIND == EPI_F32_RESID));
@@ -1311,19 +1310,19 @@ static int launch_tile_cfg(const bf16 *A, int64_t lda, const bf16 *W, int64_t ld
     return GR4AD_EUNSUPPORTED;
 }
 
-// Which kernel runs a product, by an estimate of its time in microseconds (all give the same bits).  Measured on MI355X, 1 <= M <= 8192,
-// 512 <= N <= 8192, 512 <= K <= 4096, per k-tile of 64: a 64x64 tile takes 0.215 us alone on a compute unit (the latency of its
-// LDS reads, MFMA chain and barrier) and 0.19 us each when several share one; 128x128 tiles 0.56 us alone, 0.585 us each in
+// Which kernel runs a product, by an estimate of its time in microseconds (all give the same bits).  Measured on MI355X, 1 <= M <= 16384,
+// 512 <= N <= 8192, 512 <= K <= 4096, per k-tile of 64: a 64x64 tile takes 0.19 us alone on a compute unit (the latency of its
+// LDS reads, MFMA chain and barrier) and as much each when several share one; 128x128 tiles 0.50 us alone, 0.585 us each in
 // pairs; a wave of 256x256 tiles between 1.15 us (few of them) and 1.9 us (every unit busy: the clock falls); plus a fixed part for
-// epilogue and first loads.  Before (128x128 tiles below 8192 rows, register-staged), M = 512, K = 1024: N = 1024 17 us, now 7.2;
+// epilogue and first loads.  Before (128x128 tiles below 8192 rows, register-staged), M = 512, K = 1024: N = 1024 17 us, now 6.2;
 // N = 4096 20 us, now 9.5.
 enum { RUN_TILE64 = 0, RUN_TILE128, RUN_RING };
 static int pick_kernel(int64_t M, int N, int K, int batch, bool tile64, bool tile128, bool ring) {
     const float kt = (float)(K / 64);
     auto rounds = [&](int tile) { return (float)ceil_div64(ceil_div64(M, tile) * ceil_div64(N, tile) * batch, 256); };
     const float r64 = rounds(64), r128 = rounds(128);
-    const float t64 = r64 * 0.4f + kt * (r64 > 1.0f ? 0.19f * r64 : 0.215f);
-    const float t128 = r128 * 1.1f + kt * (r128 > 1.0f ? 0.585f * r128 : 0.56f);
+    const float t64 = r64 * (0.4f + 0.19f * kt);
+    const float t128 = r128 * 1.1f + kt * (r128 > 1.0f ? 0.585f * r128 : 0.5f);
     const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256) * batch, full = tiles / 256;
     const float rest = (float)(tiles % 256) / 256.0f;
     const float tr = (float)(full + (rest > 0.0f)) * 1.3f + kt * (1.9f * (float)full + (rest > 0.0f ? 1.15f + 0.72f * rest * rest : 0.0f));
@@ -1333,7 +1332,14 @@ static int pick_kernel(int64_t M, int N, int K, int batch, bool tile64, bool til
 
 static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
                        hipStream_t st, int batch = 1, int64_t ba = 0, int64_t bw = 0, int64_t bc = 0) {
-    if (run == RUN_TILE64) return launch_tile_cfg<64, 64, 32, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    if (run == RUN_TILE64) {
+        // at most one 32x64 tile per compute unit: the smaller tiles (0.18 us per k-tile); at most one 64x64 tile: four k-tiles in LDS; else
+        // three, so that three workgroups fit a unit
+        const int64_t cols = ceil_div64(N, 64) * batch;
+        if (ceil_div64(M, 32) * cols <= 256) return launch_tile_cfg<32, 64, 32, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        if (ceil_div64(M, 64) * cols <= 256) return launch_tile_cfg<64, 64, 32, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        return launch_tile_cfg<64, 64, 32, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    }
     if (kind == EPI_VT || !tile_staged_ok(kind, N, epi)) return launch_tile_cfg<128, 128, 64, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
     // one tile per compute unit: three k-tiles in flight; more: two workgroups share a unit (64 KB of LDS each)
     if (ceil_div64(M, 128) * ceil_div64(N, 128) * batch <= 256)
@@ -1439,7 +1445,7 @@ static bool f32_mfma_ok(const void *A, int64_t lda, const void *W, int64_t ldw, 
 // epilogues, leave half-precision logits and use the hardware reciprocal in SiLU.  What a product computes depends on that class alone;
 // inside it (and below it) pick_kernel is free to choose.
 static bool mfma_ok(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int K, int kind) {
-    return dtype == GR4AD_BF16 && kind >= 0 && K % 64 == 0 && lda % 8 == 0 && ldw % 8 == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0;
+    return dtype == GR4AD_BF16 && kind >= 0 && K % 64 == 0 && lda % 8 == 0 && ldw % 8 == 0 && lda < (1 << 23) && ldw < (1 << 23) && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0;
 }
 
 bool gemm_on_persistent_kernel(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
