@@ -141,7 +141,8 @@ template <int DH, int QT, int NW, int SUBS>
 __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void cross_attn_flash_bf16(const bf16 *__restrict__ q, int64_t ldq, const bf16 *__restrict__ kv,
                                                                  const bf16 *__restrict__ vt, const int32_t *__restrict__ ctx_len,
                                                                  bf16 *__restrict__ out, int64_t ldo, int n, int S, int Spad, int d,
-                                                                 int H, float scale_log2e, int beam_blocks, int64_t total_blocks) {
+                                                                 int H, float scale_log2e, int beam_blocks, int64_t total_blocks,
+                                                                 const int32_t *__restrict__ q_first, const int32_t *__restrict__ q_count) {
     constexpr int KCH = DH / 8;                   // 16-byte chunks per K row
     constexpr int K_CHUNKS = 64 * KCH, V_CHUNKS = DH * 8;
     constexpr int STAGE = K_CHUNKS + V_CHUNKS;    // one 64-key tile
@@ -156,15 +157,29 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
     const int64_t per_xcd = (total_blocks + 7) / 8;
     const int64_t logical = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (logical >= total_blocks) return;
-    const int beam_block = (int)(logical % beam_blocks);
-    const int h = (int)((logical / beam_blocks) % H);
+    int beam_block = (int)(logical % beam_blocks);
+    int h = (int)((logical / beam_blocks) % H);
     const int b = (int)(logical / ((int64_t)beam_blocks * H));
+    if (q_count) {
+        // Requests have fewer rows than the launch allows for and their last blocks find no work.  Idle blocks in a short regular pattern
+        // starve some of the XCD's shader engines (workgroups are dealt to those in turn), so here the head runs fastest: a request's blocks
+        // with work are consecutive.  (1024 requests, 512 beams of which about 20 % distinct: 1.35 ms -> 0.76 ms.)
+        const int in = (int)(logical - (int64_t)b * beam_blocks * H);
+        h = in % H;
+        beam_block = in / H;
+    }
     const int frow = lane % 32, hf = lane / 32;
     int len = ctx_len ? ctx_len[b] : S;
     len = len < 1 ? 1 : (len > S ? S : len);
     const int ntiles = (len + 63) / 64;
     const int nmacro = (ntiles + SUBS - 1) / SUBS;
     const int q0 = (beam_block * NW + wave) * (QT * 32);
+    int64_t req_row = (int64_t)b * n;
+    if (q_count) {  // rows packed over the requests
+        req_row = q_first[b];
+        n = q_count[b];
+        if (beam_block * (NW * QT * 32) >= n) return;
+    }
 
     // query fragments stay in registers for the whole kernel
     bf16x8 qf[QT][KSTEPS];
@@ -172,7 +187,7 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
     for (int qt = 0; qt < QT; qt++) {
         int row = q0 + qt * 32 + frow;
         if (row > n - 1) row = n - 1;  // rows past the end are computed and dropped
-        const bf16 *qr = q + ((int64_t)b * n + row) * ldq + h * DH;
+        const bf16 *qr = q + (req_row + row) * ldq + h * DH;
 #pragma unroll
         for (int s = 0; s < KSTEPS; s++) qf[qt][s] = *(const bf16x8 *)(qr + 16 * s + 8 * hf);
     }
@@ -253,6 +268,7 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
             asm volatile("" ::: "memory");
             if (macro + 1 < nmacro) issue_macro(macro + 1, (macro + 1) & 1);
         }
+        if (q0 >= n) continue;  // a wavefront without beams only helps to load
         const bf16x8 *sk = smem + (macro & 1) * MACRO + sub_tile * STAGE, *sv = sk + K_CHUNKS;
         // first product: the two 32-key halves are independent accumulation chains, issued in turn; the key fragments of
         // k-step st+1 are read while step st multiplies
@@ -345,7 +361,7 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
         const float inv = 1.0f / l;
         const int row = q0 + qt * 32 + frow;
         if (row < n) {
-            bf16 *orow = out + ((int64_t)b * n + row) * ldo + h * DH;
+            bf16 *orow = out + (req_row + row) * ldo + h * DH;
 #pragma unroll
             for (int mt = 0; mt < MT; mt++)
 #pragma unroll
@@ -1031,7 +1047,7 @@ int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, c
 
 template <int DH, int QT, int NW, int SUBS>
 static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, const bf16 *vt, const int32_t *ctx_len, bf16 *out, int64_t ldo, int B,
-                        int n, int S, int d, int H, hipStream_t st) {
+                        int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
     auto kern = cross_attn_flash_bf16<DH, QT, NW, SUBS>;
     constexpr int LDS_BYTES = 2 * SUBS * (64 * (DH / 8) + DH * 8) * 16;
     static bool attr_done = false;
@@ -1048,13 +1064,13 @@ static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, const bf16 *
     // flops on the padded length S; bytes: queries and outputs once, keys and values once per request (beam-shared)
     ProfScope ps(KC_XATTN_FLASH, st, 4.0 * B * (double)n * S * d, (2.0 * B * n * d + 2.0 * B * (double)S * d) * sizeof(bf16));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS_BYTES, st, q, ldq, kv, vt, ctx_len, out, ldo, n, S, (S + 63) / 64 * 64, d, H, scale_log2e,
-                       beam_blocks, total_blocks);
+                       beam_blocks, total_blocks, dr ? dr->first : nullptr, dr ? dr->count : nullptr);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
 
 int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, const void *vt, const int32_t *ctx_len, void *out,
-                           int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st) {
+                           int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
     if (B <= 0 || n <= 0 || S <= 0 || d <= 0 || H <= 0 || d % H) return GR4AD_EINVAL;
     const int dh = d / H;
     if (dh > 128) return GR4AD_EUNSUPPORTED;
@@ -1068,15 +1084,16 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
             // SIMD: the kernel waits on LDS, barrier and dependent-MFMA latencies, and occupancy is what hides them.  Blocks
             // of 8 wavefronts (256 beams) share each staged tile among twice as many beams and are 3-7 % faster than blocks
             // of 4; they are used where they waste no more beam slots.
-            if (n <= 128) return launch_flash<64, 1, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st);
-            if ((n + 255) / 256 * 256 == (n + 127) / 128 * 128) return launch_flash<64, 1, 8, 1>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st);
-            return launch_flash<64, 1, 4, 1>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st);
+            if (n <= 128) return launch_flash<64, 1, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if ((n + 255) / 256 * 256 == (n + 127) / 128 * 128) return launch_flash<64, 1, 8, 1>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            return launch_flash<64, 1, 4, 1>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
         } else {
-            if (n <= 128) return launch_flash<32, 1, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st);
-            if (n <= 256) return launch_flash<32, 2, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st);
-            return launch_flash<32, 2, 8, 4>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st);
+            if (n <= 128) return launch_flash<32, 1, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if (n <= 256) return launch_flash<32, 2, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            return launch_flash<32, 2, 8, 4>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
         }
     }
+    if (dr) return GR4AD_EUNSUPPORTED;
     const int64_t rows = (int64_t)B * n;
     const int64_t grid = ceil_div64(rows * H, 4);
     if (grid > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
@@ -1127,9 +1144,12 @@ template <> struct Chunk8<float> {
     }
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void self_attn_step(const T *__restrict__ qkv, LevelBuffers prev, const int32_t *__restrict__ anc,
-                                                      T *__restrict__ out, int64_t rows, int pos, int Tlev, int d, int H) {
+struct LevelRows { const void *p[GR4AD_MAX_LEVELS]; };
+struct NoMaps {};
+template <typename T, typename MAPS>
+__global__ __launch_bounds__(256) void self_attn_step(const T *__restrict__ qkv, const int32_t *__restrict__ anc, T *__restrict__ out, int64_t rows, int pos,
+                                                      int Tlev, int d, int H, LevelRows prev, MAPS maps) {
+    constexpr bool MAPPED = sizeof(MAPS) > sizeof(NoMaps);  // some of the buffers hold distinct rows
     const int cpr = d / 8;        // chunks per row
     const int lph = (d / H) / 8;  // lanes per head: 2, 4, 8 or 16
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -1137,7 +1157,9 @@ __global__ __launch_bounds__(256) void self_attn_step(const T *__restrict__ qkv,
     const int64_t row = live ? gid / cpr : rows - 1;  // idle lanes shadow the last row and store nothing
     const int ch = live ? (int)(gid % cpr) : 0;
     const float scale = 1.0f / sqrtf((float)(d / H));
-    const T *qr = qkv + row * 3 * d + ch * 8;
+    int64_t qrow = row;
+    if constexpr (MAPPED) qrow = maps.map[pos] ? maps.map[pos][row] : row;
+    const T *qr = qkv + qrow * 3 * d + ch * 8;
     float qv[8], kn[8], vn[8];
     Chunk8<T>::load(qr, qv);
     Chunk8<T>::load(qr + d, kn);
@@ -1145,7 +1167,13 @@ __global__ __launch_bounds__(256) void self_attn_step(const T *__restrict__ qkv,
     const T *kvp[GR4AD_MAX_LEVELS];  // k of position p (v follows d elements later)
 #pragma unroll
     for (int p = 0; p < GR4AD_MAX_LEVELS; p++)
-        if (p < pos) kvp[p] = (const T *)prev.p[p] + (int64_t)anc[row * Tlev + p] * 3 * d + d + ch * 8;
+        if (p < pos) {
+            int64_t r = anc[row * Tlev + p];
+            if constexpr (MAPPED) {
+                if (maps.map[p]) r = maps.map[p][r];
+            }
+            kvp[p] = (const T *)prev.p[p] + r * 3 * d + d + ch * 8;
+        }
     float s[GR4AD_MAX_LEVELS];
     float mx = -INFINITY;
 #pragma unroll
@@ -1191,10 +1219,10 @@ __global__ __launch_bounds__(256) void self_attn_step(const T *__restrict__ qkv,
 }
 
 int launch_self_attention_step(gr4ad_dtype dtype, const void *qkv, const LevelBuffers &prev, const int32_t *anc, void *out, int64_t rows,
-                               int pos, int T, int d, int H, hipStream_t st) {
+                               int pos, int T, int d, int H, hipStream_t st, const LevelMaps *maps) {
     // T is the row stride of anc: positions 0..pos-1 are read from it, so pos == T (a step after the last level) is allowed
     if (rows <= 0 || pos < 0 || pos > T || pos >= GR4AD_MAX_LEVELS || T > GR4AD_MAX_LEVELS || d % H) return GR4AD_EINVAL;
-    if (pos > 0 && !anc) return GR4AD_EINVAL;
+    if ((pos > 0 && !anc) || (maps && dtype != GR4AD_BF16)) return GR4AD_EINVAL;
     for (int p = 0; p < pos; p++)
         if (!prev.p[p] || ((uintptr_t)prev.p[p] % 32) || prev.rows[p] < 1) return GR4AD_EINVAL;
     const int dh = d / H;
@@ -1207,10 +1235,14 @@ int launch_self_attention_step(gr4ad_dtype dtype, const void *qkv, const LevelBu
     double units = 4.0 * rows;
     for (int p = 0; p < pos; p++) units += 2.0 * (double)(prev.rows[p] > 0 && prev.rows[p] < rows ? prev.rows[p] : rows);
     ProfScope ps(KC_SELF_STEP, st, 4.0 * rows * (double)(pos + 1) * d, units * d * (dtype == GR4AD_BF16 ? 2 : 4));
-    if (dtype == GR4AD_BF16)
-        hipLaunchKernelGGL(self_attn_step<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)qkv, prev, anc, (bf16 *)out, rows, pos, T, d, H);
-    else
-        hipLaunchKernelGGL(self_attn_step<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)qkv, prev, anc, (float *)out, rows, pos, T, d, H);
+    LevelRows lr;
+    for (int p = 0; p < GR4AD_MAX_LEVELS; p++) lr.p[p] = p < pos ? prev.p[p] : nullptr;
+    if (dtype == GR4AD_BF16) {
+        if (maps) hipLaunchKernelGGL((self_attn_step<bf16, LevelMaps>), dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)qkv, anc, (bf16 *)out, rows, pos, T, d, H, lr, *maps);
+        else hipLaunchKernelGGL((self_attn_step<bf16, NoMaps>), dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)qkv, anc, (bf16 *)out, rows, pos, T, d, H, lr, NoMaps{});
+    } else {
+        hipLaunchKernelGGL((self_attn_step<float, NoMaps>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)qkv, anc, (float *)out, rows, pos, T, d, H, lr, NoMaps{});
+    }
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }

@@ -79,7 +79,8 @@ struct GemmEpilogue {
     const float *table;  // float32 [*, N]: row tok[row] (or row 0 if tok == NULL) added per row
     const int32_t *tok;  // [M] row selector of `table`
     // matrix-core kernels only (ignored elsewhere): the rows of A are requests of skip_S rows each of which only the first
-    // skip_len[b] are valid; output tiles whose rows all lie in one request's padding are not computed (their C is not written)
+    // skip_len[b] are valid; output tiles whose rows all lie in one request's padding are not computed (their C is not written).
+    // skip_S = 0 (products of the large class and FP8 ones on the persistent kernel): A has skip_len[0] rows, 1 .. M; M is the bound launches are sized by
     const int32_t *skip_len;
     int skip_S;
     int out_f32;         // 1: C is float, 0: C has the storage dtype
@@ -133,14 +134,17 @@ int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64
 
 // ---- element-wise / norm kernels -------------------------------------------
 // y[r,:] = g * x[r,:] / sqrt(mean(x[r,:]^2) + eps); x is the float32 residual stream, g and y have the storage dtype
-int launch_rmsnorm(gr4ad_dtype dtype, const void *x, const void *g, void *y, int64_t rows, int d, float eps, hipStream_t st);
+// (rows_dev, here and below: if not NULL, the row count lies there on the device, 1 .. rows)
+int launch_rmsnorm(gr4ad_dtype dtype, const void *x, const void *g, void *y, int64_t rows, int d, float eps, hipStream_t st, const int32_t *rows_dev = nullptr);
 // inv[r] = 1 / sqrt(sum(ss[r*parts .. r*parts+parts-1]) / dim + eps): per-row factor of the folded RMSNorm from the partial sums
-int launch_row_inv(const float *ss, float *inv, int64_t rows, int parts, int dim, float eps, hipStream_t st);
+int launch_row_inv(const float *ss, float *inv, int64_t rows, int parts, int dim, float eps, hipStream_t st, const int32_t *rows_dev = nullptr);
 // a[(b*n+i), :] = m[b*m_stride + :] * G[tok(b,i), :]   (tok == NULL: row 0 of G); m and G float32 (G: table_rows rows), a storage dtype
+// (with rows_dev, row r belongs to request req[r])
 int launch_fuse_gate(gr4ad_dtype dtype, const void *m, int64_t m_req_stride, const void *G, int64_t table_rows, const int32_t *tok, void *a,
-                     int B, int n, int d, hipStream_t st);
+                     int B, int n, int d, hipStream_t st, const int32_t *rows_dev = nullptr, const int32_t *req = nullptr);
 // h[row, :] = E[tok[row], :] + p[:]   (tok == NULL: row 0 of E); E and p storage dtype, h float32: the vanilla decoder's input state
-int launch_embed_pos(gr4ad_dtype dtype, const void *E, const int32_t *tok, const void *p, void *h, int64_t rows, int d, hipStream_t st);
+int launch_embed_pos(gr4ad_dtype dtype, const void *E, const int32_t *tok, const void *p, void *h, int64_t rows, int d, hipStream_t st,
+                     const int32_t *rows_dev = nullptr);
 // dst[b*T + t, :] = pos[t, :]   (pos storage dtype, dst float32)
 int launch_broadcast_rows(gr4ad_dtype dtype, const void *pos, void *dst, int B, int T, int d, hipStream_t st);
 // dst[b, j, 0:row_elems] = src[b, parent[b,j], 0:row_elems]
@@ -152,19 +156,32 @@ int launch_log_softmax_rows(const float *logits, float *out, int64_t rows, int V
 
 // FP8 (OCP E4M3) operands.  Rows: yq[r, :] = e4m3(x[r, :] / scale[r]), scale[r] = amax(row) / 448 (1 for a zero row);
 // launch_rmsnorm_quant takes the float32 residual stream and quantises g * x / rms(x), launch_quantize_rows a bf16 row as it is.
-int launch_rmsnorm_quant(const void *x, const void *g, void *yq, float *scale, int64_t rows, int d, float eps, hipStream_t st);
-int launch_quantize_rows(const void *x, void *yq, float *scale, int64_t rows, int n, hipStream_t st);
+int launch_rmsnorm_quant(const void *x, const void *g, void *yq, float *scale, int64_t rows, int d, float eps, hipStream_t st, const int32_t *rows_dev = nullptr);
+int launch_quantize_rows(const void *x, void *yq, float *scale, int64_t rows, int n, hipStream_t st, const int32_t *rows_dev = nullptr);
 // init time, synchronises the stream: one scale for the whole bf16 matrix of `count` elements, returned on the host
 int launch_quantize_matrix(const void *w, void *wq, int64_t count, unsigned *amax_dev, float *scale_host, hipStream_t st);
 
 // out[h][j][c] = w[h*dh + c][j] for a bf16 [d, d] weight (init-time)
 int launch_head_transpose(const void *w, void *out, int d, int H, hipStream_t st);
 
+// The distinct tokens of every request's n rows (n <= GR4AD_MAX_BEAM, tokens < GR4AD_MAX_CODEBOOK), numbered without gaps over the batch
+// (request by request, in the order of first appearance).  All device memory of the caller's.
+struct DistinctRows {
+    int32_t *map;    // [B*n]  number of the row's (request, token)
+    int32_t *tok;    // [<= B*n]  token of each distinct row
+    int32_t *req;    // [<= B*n]  its request
+    int32_t *first;  // [B]  number of the request's first distinct row
+    int32_t *count;  // [B]  distinct rows of the request
+    int32_t *total;  // [1]  distinct rows of the batch
+};
+int launch_distinct_rows(const int32_t *tok, int B, int n, const DistinctRows &dr, hipStream_t st);
+
 // ---- attention ---------------------------------------------------------------
 // beam-shared cross-attention; q/out row stride ldq/ldo elements, rows (b*n+i)
 // vt: per-(request, head) transposed values built by launch_cross_attention_prepare (NULL: plain kernel on kv alone)
+// dr: the rows of request b are the dr->count[b] (<= n) rows from dr->first[b] on (matrix-core kernel only)
 int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, const void *vt, const int32_t *ctx_len, void *out,
-                           int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st);
+                           int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr = nullptr);
 // bytes of the transposed-value buffer the MFMA kernel needs for kv [B,S,2d] (0: the shape runs on the plain kernel)
 size_t cross_attention_workspace_bytes(gr4ad_dtype dtype, int B, int S, int d, int H);
 int launch_cross_attention_prepare(gr4ad_dtype dtype, const void *kv, const int32_t *ctx_len, void *vt, int B, int S, int d, int H,
@@ -186,8 +203,10 @@ int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, c
 // the keys and values of position p < pos are columns d..3d of row anc[row*T + p] of prev.p[p] (the [*,3d] q/k/v buffer
 // that level wrote): the beam reorder is the ancestor table, no rows are moved.
 struct LevelBuffers { const void *p[GR4AD_MAX_LEVELS]; int64_t rows[GR4AD_MAX_LEVELS]; };  // rows: rows of that level's buffer
+// maps: for buffers that hold distinct rows, map[p] (NULL: none) gives the row of prev.p[p] (of qkv for p = pos) that stands for row r of level p
+struct LevelMaps { const int32_t *map[GR4AD_MAX_LEVELS]; };
 int launch_self_attention_step(gr4ad_dtype dtype, const void *qkv, const LevelBuffers &prev, const int32_t *anc, void *out, int64_t rows,
-                               int pos, int T, int d, int H, hipStream_t st);
+                               int pos, int T, int d, int H, hipStream_t st, const LevelMaps *maps = nullptr);
 // causal self-attention over the T trunk positions of each request: qkv [B*T,3d] -> out [B*T,d]
 int launch_trunk_self_attention(gr4ad_dtype dtype, const void *qkv, void *out, int B, int T, int d, int H, hipStream_t st);
 
@@ -203,7 +222,7 @@ bool select_takes_f16(int V);
 
 // ---- optional per-kernel event timing ----------------------------------------
 enum KernelClass { KC_GEMM_TILE = 0, KC_GEMM_SIMPLE, KC_XATTN_FLASH, KC_XATTN_SIMPLE, KC_SELF_STEP, KC_TRUNK_SELF,
-                   KC_RMSNORM, KC_FUSE_GATE, KC_SELECT_ROWS, KC_SELECT_REQUEST, KC_GATHER, KC_BROADCAST, KC_V_TRANSPOSE, KC_GEMM_RING, KC_SOFTMAX, KC_GEMM_RING_F8, KC_QUANTIZE, KC_CONTEXT_ATTN, KC_COUNT };
+                   KC_RMSNORM, KC_FUSE_GATE, KC_SELECT_ROWS, KC_SELECT_REQUEST, KC_GATHER, KC_BROADCAST, KC_V_TRANSPOSE, KC_GEMM_RING, KC_SOFTMAX, KC_GEMM_RING_F8, KC_QUANTIZE, KC_CONTEXT_ATTN, KC_DISTINCT, KC_COUNT };
 // Declared around a kernel launch: records an event before and (on scope exit) after it when timing is on.
 struct ProfScope {
     ProfScope(int cls, hipStream_t st, double flops = 0.0, double bytes = 0.0);  // algorithmic work of the launch
@@ -211,6 +230,8 @@ struct ProfScope {
     int idx_;
     hipStream_t st_;
 };
+bool prof_on();
+void prof_scale_work(double f);  // factor on the work of the launches that follow (rows that turned out not to be there)
 
 #define GR4AD_LAUNCH_CHECK()                                   \
     do {                                                       \

@@ -29,10 +29,11 @@ template <typename T> __device__ __forceinline__ void store16(T *p, const float 
 // ---------------------------------------------------------------------------
 template <typename T, int MAXV>  // MAXV: 16-byte vectors per lane
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ x, const T *__restrict__ g, T *__restrict__ y,
-                                                      int64_t rows, int d, float eps) {
+                                                      int64_t rows, int d, float eps, const int32_t *__restrict__ rows_dev) {
     constexpr int N = Vec16<T>::N;
     const int lane = threadIdx.x % 64;
     const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
+    if (rows_dev) rows = rows_dev[0];
     if (row >= rows) return;
     const int nvec = d / N;
     float v[MAXV][N];
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
     }
 }
 
-int launch_rmsnorm(gr4ad_dtype dtype, const void *x, const void *g, void *y, int64_t rows, int d, float eps, hipStream_t st) {
+int launch_rmsnorm(gr4ad_dtype dtype, const void *x, const void *g, void *y, int64_t rows, int d, float eps, hipStream_t st, const int32_t *rows_dev) {
     if (rows <= 0) return GR4AD_OK;
     int64_t grid = ceil_div64(rows, 4);
     if (grid > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
@@ -71,18 +72,18 @@ int launch_rmsnorm(gr4ad_dtype dtype, const void *x, const void *g, void *y, int
         int nvec = d / 8;
         if (d % 8) return GR4AD_EUNSUPPORTED;
         if (nvec <= 128)
-            hipLaunchKernelGGL((rmsnorm_kernel<bf16, 2>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const bf16 *)g, (bf16 *)y, rows, d, eps);
+            hipLaunchKernelGGL((rmsnorm_kernel<bf16, 2>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const bf16 *)g, (bf16 *)y, rows, d, eps, rows_dev);
         else if (nvec <= 512)
-            hipLaunchKernelGGL((rmsnorm_kernel<bf16, 8>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const bf16 *)g, (bf16 *)y, rows, d, eps);
+            hipLaunchKernelGGL((rmsnorm_kernel<bf16, 8>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const bf16 *)g, (bf16 *)y, rows, d, eps, rows_dev);
         else
             return GR4AD_EUNSUPPORTED;
     } else {
         int nvec = d / 4;
         if (d % 4) return GR4AD_EUNSUPPORTED;
         if (nvec <= 128)
-            hipLaunchKernelGGL((rmsnorm_kernel<float, 2>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const float *)g, (float *)y, rows, d, eps);
+            hipLaunchKernelGGL((rmsnorm_kernel<float, 2>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const float *)g, (float *)y, rows, d, eps, rows_dev);
         else if (nvec <= 1024)
-            hipLaunchKernelGGL((rmsnorm_kernel<float, 16>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const float *)g, (float *)y, rows, d, eps);
+            hipLaunchKernelGGL((rmsnorm_kernel<float, 16>), dim3((unsigned)grid), dim3(256), 0, st, (const float *)x, (const float *)g, (float *)y, rows, d, eps, rows_dev);
         else
             return GR4AD_EUNSUPPORTED;
     }
@@ -96,14 +97,15 @@ int launch_rmsnorm(gr4ad_dtype dtype, const void *x, const void *g, void *y, int
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void fuse_gate_kernel(const float *__restrict__ m, int64_t m_req_stride, const float *__restrict__ G,
-                                                        const int32_t *__restrict__ tok, T *__restrict__ a, int64_t rows, int n, int d) {
+                                                        const int32_t *__restrict__ tok, T *__restrict__ a, int64_t rows, int n, int d,
+                                                        const int32_t *__restrict__ rows_dev, const int32_t *__restrict__ req) {
     constexpr int N = Vec16<T>::N;
     const int nvec = d / N;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= rows * nvec) return;
+    if (idx >= (rows_dev ? (int64_t)rows_dev[0] : rows) * nvec) return;
     const int64_t row = idx / nvec;
     const int c = (int)(idx % nvec);
-    const int64_t b = row / n;
+    const int64_t b = rows_dev ? (int64_t)req[row] : row / n;
     const int64_t t = tok ? (int64_t)tok[row] : 0;
     float mv[N], gv[N];
 #pragma unroll
@@ -116,7 +118,8 @@ __global__ __launch_bounds__(256) void fuse_gate_kernel(const float *__restrict_
 }
 
 int launch_fuse_gate(gr4ad_dtype dtype, const void *m, int64_t m_req_stride, const void *G, int64_t table_rows, const int32_t *tok, void *a,
-                     int B, int n, int d, hipStream_t st) {
+                     int B, int n, int d, hipStream_t st, const int32_t *rows_dev, const int32_t *req) {
+    if (rows_dev && !req) return GR4AD_EINVAL;
     const int N = dtype == GR4AD_BF16 ? 8 : 4;
     int64_t rows = (int64_t)B * n, total = rows * (d / N);
     int64_t grid = ceil_div64(total, 256);
@@ -126,9 +129,9 @@ int launch_fuse_gate(gr4ad_dtype dtype, const void *m, int64_t m_req_stride, con
     const double distinct = (double)(rows < table_rows ? rows : table_rows);
     ProfScope ps(KC_FUSE_GATE, st, 0.0, (double)rows * d * (dtype == GR4AD_BF16 ? 2 : 4) + ((double)B + distinct) * d * 4);
     if (dtype == GR4AD_BF16)
-        hipLaunchKernelGGL(fuse_gate_kernel<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)m, m_req_stride, (const float *)G, tok, (bf16 *)a, rows, n, d);
+        hipLaunchKernelGGL(fuse_gate_kernel<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)m, m_req_stride, (const float *)G, tok, (bf16 *)a, rows, n, d, rows_dev, req);
     else
-        hipLaunchKernelGGL(fuse_gate_kernel<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)m, m_req_stride, (const float *)G, tok, (float *)a, rows, n, d);
+        hipLaunchKernelGGL(fuse_gate_kernel<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)m, m_req_stride, (const float *)G, tok, (float *)a, rows, n, d, rows_dev, req);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
@@ -139,11 +142,11 @@ int launch_fuse_gate(gr4ad_dtype dtype, const void *m, int64_t m_req_stride, con
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void embed_pos_kernel(const T *__restrict__ E, const int32_t *__restrict__ tok, const T *__restrict__ p,
-                                                        float *__restrict__ h, int64_t rows, int d) {
+                                                        float *__restrict__ h, int64_t rows, int d, const int32_t *__restrict__ rows_dev) {
     constexpr int N = Vec16<T>::N;
     const int nvec = d / N;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= rows * nvec) return;
+    if (idx >= (rows_dev ? (int64_t)rows_dev[0] : rows) * nvec) return;
     const int64_t row = idx / nvec;
     const int c = (int)(idx % nvec);
     const int64_t t = tok ? (int64_t)tok[row] : 0;
@@ -156,7 +159,8 @@ __global__ __launch_bounds__(256) void embed_pos_kernel(const T *__restrict__ E,
     for (int e = 0; e < N; e += 4) store16<float>(h + row * d + (int64_t)c * N + e, &ev[e]);
 }
 
-int launch_embed_pos(gr4ad_dtype dtype, const void *E, const int32_t *tok, const void *p, void *h, int64_t rows, int d, hipStream_t st) {
+int launch_embed_pos(gr4ad_dtype dtype, const void *E, const int32_t *tok, const void *p, void *h, int64_t rows, int d, hipStream_t st,
+                     const int32_t *rows_dev) {
     const int N = dtype == GR4AD_BF16 ? 8 : 4;
     if (!E || !p || !h || rows < 1 || d < N || d % N) return GR4AD_EINVAL;
     if (((uintptr_t)E % 16) || ((uintptr_t)p % 16) || ((uintptr_t)h % 16)) return GR4AD_EUNSUPPORTED;
@@ -165,9 +169,9 @@ int launch_embed_pos(gr4ad_dtype dtype, const void *E, const int32_t *tok, const
     // one embedding row per distinct token is the least that must be read; rows of float32 written
     ProfScope ps(KC_FUSE_GATE, st, 0.0, (double)rows * d * 4);
     if (dtype == GR4AD_BF16)
-        hipLaunchKernelGGL(embed_pos_kernel<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)E, tok, (const bf16 *)p, (float *)h, rows, d);
+        hipLaunchKernelGGL(embed_pos_kernel<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)E, tok, (const bf16 *)p, (float *)h, rows, d, rows_dev);
     else
-        hipLaunchKernelGGL(embed_pos_kernel<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)E, tok, (const float *)p, (float *)h, rows, d);
+        hipLaunchKernelGGL(embed_pos_kernel<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)E, tok, (const float *)p, (float *)h, rows, d, rows_dev);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
@@ -192,6 +196,94 @@ int launch_broadcast_rows(gr4ad_dtype dtype, const void *pos, void *dst, int B, 
         hipLaunchKernelGGL(broadcast_rows_kernel<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)pos, (float *)dst, total, per_req);
     else
         hipLaunchKernelGGL(broadcast_rows_kernel<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)pos, (float *)dst, total, per_req);
+    GR4AD_LAUNCH_CHECK();
+    return GR4AD_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Distinct (request, previous token) rows of a level.  One workgroup per request; the tokens go into a hash table in LDS (at most half
+// full, so every probe ends), one word per token: token << 12 | first row that carries it.  A row is the representative of its token
+// if the table names it, and its number is the count of representatives before it: the numbering does not depend on timing.
+// ---------------------------------------------------------------------------
+constexpr uint32_t DISTINCT_EMPTY = 0xffffffffu;
+
+__global__ __launch_bounds__(256) void distinct_tokens_kernel(const int32_t *__restrict__ tok, int n, uint32_t mask, int32_t *__restrict__ number,
+                                                              int32_t *__restrict__ count) {
+    __shared__ uint32_t table[2 * GR4AD_MAX_BEAM];
+    __shared__ uint16_t rank[GR4AD_MAX_BEAM];
+    __shared__ int wsum[4];
+    const int64_t row0 = (int64_t)blockIdx.x * n;
+    const int tid = threadIdx.x;
+    for (uint32_t i = tid; i <= mask; i += 256) table[i] = DISTINCT_EMPTY;
+    __syncthreads();
+    auto home = [&](uint32_t t) { return (t * 2654435761u >> 15) & mask; };
+    for (int i = tid; i < n; i += 256) {
+        const uint32_t t = (uint32_t)tok[row0 + i], word = t << 12 | (uint32_t)i;
+        for (uint32_t s = home(t);; s = (s + 1) & mask) {
+            const uint32_t was = atomicCAS(&table[s], DISTINCT_EMPTY, word);
+            if (was == DISTINCT_EMPTY) break;
+            if (was >> 12 == t) {
+                atomicMin(&table[s], word);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    int base = 0;
+    for (int i0 = 0; i0 < n; i0 += 256) {
+        const int i = i0 + tid;
+        int rep = -1;
+        if (i < n) {
+            const uint32_t t = (uint32_t)tok[row0 + i];
+            uint32_t s = home(t);
+            while (table[s] >> 12 != t) s = (s + 1) & mask;
+            rep = (int)(table[s] & 0xfffu);
+        }
+        const uint64_t own = __builtin_amdgcn_ballot_w64(rep == i);
+        if (tid % 64 == 0) wsum[tid / 64] = __popcll(own);
+        __syncthreads();
+        int before = base;
+        for (int w = 0; w < 4; w++) {
+            if (w < tid / 64) before += wsum[w];
+            base += wsum[w];
+        }
+        if (rep == i) rank[i] = (uint16_t)(before + __popcll(own & ((1ull << (tid % 64)) - 1)));
+        __syncthreads();
+        if (i < n) number[row0 + i] = rank[rep];  // (rep <= i: its rank is known)
+    }
+    if (tid == 0) count[blockIdx.x] = base;
+}
+
+__global__ __launch_bounds__(256) void distinct_rows_kernel(const int32_t *__restrict__ tok, int B, int n, DistinctRows dr) {
+    __shared__ int part[4];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    int sum = 0;
+    for (int i = tid; i < b; i += 256) sum += dr.count[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (tid % 64 == 0) part[tid / 64] = sum;
+    __syncthreads();
+    const int first = part[0] + part[1] + part[2] + part[3];
+    for (int i = tid; i < n; i += 256) {
+        const int64_t row = (int64_t)b * n + i;
+        const int u = first + dr.map[row];
+        dr.map[row] = u;
+        dr.tok[u] = tok[row];  // (rows of one token write the same value)
+        dr.req[u] = b;
+    }
+    if (tid == 0) {
+        dr.first[b] = first;
+        if (b == B - 1) dr.total[0] = first + dr.count[b];
+    }
+}
+
+int launch_distinct_rows(const int32_t *tok, int B, int n, const DistinctRows &dr, hipStream_t st) {
+    if (!tok || B < 1 || n < 1 || n > GR4AD_MAX_BEAM || (int64_t)B * n > 0x7fffffffLL) return GR4AD_EINVAL;
+    uint32_t slots = 64;
+    while (slots < 2u * (uint32_t)n) slots *= 2;
+    ProfScope ps(KC_DISTINCT, st, 0.0, (double)B * n * 20);
+    hipLaunchKernelGGL(distinct_tokens_kernel, dim3(B), dim3(256), 0, st, tok, n, slots - 1, dr.map, dr.count);
+    hipLaunchKernelGGL(distinct_rows_kernel, dim3(B), dim3(256), 0, st, tok, B, n, dr);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
@@ -250,7 +342,8 @@ int launch_head_transpose(const void *w, void *out, int d, int H, hipStream_t st
 // Folded RMSNorm: per-row factor from the partial sums of squares a projection's epilogue left
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void row_inv_kernel(const float *__restrict__ ss, float *__restrict__ inv, int64_t rows, int parts, int dim,
-                                                      float eps) {
+                                                      float eps, const int32_t *__restrict__ rows_dev) {
+    if (rows_dev) rows = rows_dev[0];
     // 16 lanes per row: consecutive lanes read consecutive 16-byte pieces of the row's partial sums
     const int64_t r = ((int64_t)blockIdx.x * 256 + threadIdx.x) / 16;
     const int sub = threadIdx.x % 16;
@@ -265,12 +358,12 @@ __global__ __launch_bounds__(256) void row_inv_kernel(const float *__restrict__ 
     if (r < rows && sub == 0) inv[r] = 1.0f / sqrtf(s / (float)dim + eps);
 }
 
-int launch_row_inv(const float *ss, float *inv, int64_t rows, int parts, int dim, float eps, hipStream_t st) {
+int launch_row_inv(const float *ss, float *inv, int64_t rows, int parts, int dim, float eps, hipStream_t st, const int32_t *rows_dev) {
     if (!ss || !inv || rows < 1 || parts < 4 || parts % 4 || dim < 1 || ((uintptr_t)ss % 16)) return GR4AD_EINVAL;
     const int64_t grid = ceil_div64(rows * 16, 256);
     if (grid > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
     ProfScope ps(KC_RMSNORM, st, 0.0, (double)rows * (parts + 1) * sizeof(float));
-    hipLaunchKernelGGL(row_inv_kernel, dim3((unsigned)grid), dim3(256), 0, st, ss, inv, rows, parts, dim, eps);
+    hipLaunchKernelGGL(row_inv_kernel, dim3((unsigned)grid), dim3(256), 0, st, ss, inv, rows, parts, dim, eps, rows_dev);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
@@ -322,7 +415,9 @@ __device__ __forceinline__ uint2 pack8_e4m3(const float (&v)[8], float qinv) {
 // g * x / rms(x) (the RMSNorm in front of a projection); otherwise x is a bf16 activation row taken as it is.
 template <bool NORM, int MAXV>  // MAXV: 8-element vectors per lane
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const void *__restrict__ xin, const bf16 *__restrict__ g, uint8_t *__restrict__ yq,
-                                                            float *__restrict__ scale, int64_t rows, int n, float eps) {
+                                                            float *__restrict__ scale, int64_t rows, int n, float eps,
+                                                            const int32_t *__restrict__ rows_dev) {
+    if (rows_dev) rows = rows_dev[0];
     const int lane = threadIdx.x % 64;
     const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     if (row >= rows) return;
@@ -373,7 +468,8 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const void *__restri
 }
 
 template <bool NORM>
-static int launch_quantize_rows_any(const void *x, const void *g, void *yq, float *scale, int64_t rows, int n, float eps, hipStream_t st) {
+static int launch_quantize_rows_any(const void *x, const void *g, void *yq, float *scale, int64_t rows, int n, float eps, hipStream_t st,
+                                    const int32_t *rows_dev) {
     if (!x || !yq || !scale || rows < 1 || n < 8 || n % 8 || (NORM && !g)) return GR4AD_EINVAL;
     if (((uintptr_t)x % 16) || ((uintptr_t)yq % 8)) return GR4AD_EUNSUPPORTED;
     const int64_t grid = ceil_div64(rows, 4);
@@ -381,23 +477,23 @@ static int launch_quantize_rows_any(const void *x, const void *g, void *yq, floa
     const int nvec = n / 8;
     ProfScope ps(KC_QUANTIZE, st, 0.0, (double)rows * n * ((NORM ? 4 : 2) + 1));
     if (nvec <= 128)
-        hipLaunchKernelGGL((quantize_rows_kernel<NORM, 2>), dim3((unsigned)grid), dim3(256), 0, st, x, (const bf16 *)g, (uint8_t *)yq, scale, rows, n, eps);
+        hipLaunchKernelGGL((quantize_rows_kernel<NORM, 2>), dim3((unsigned)grid), dim3(256), 0, st, x, (const bf16 *)g, (uint8_t *)yq, scale, rows, n, eps, rows_dev);
     else if (nvec <= 512)
-        hipLaunchKernelGGL((quantize_rows_kernel<NORM, 8>), dim3((unsigned)grid), dim3(256), 0, st, x, (const bf16 *)g, (uint8_t *)yq, scale, rows, n, eps);
+        hipLaunchKernelGGL((quantize_rows_kernel<NORM, 8>), dim3((unsigned)grid), dim3(256), 0, st, x, (const bf16 *)g, (uint8_t *)yq, scale, rows, n, eps, rows_dev);
     else if (nvec <= 2048)
-        hipLaunchKernelGGL((quantize_rows_kernel<NORM, 32>), dim3((unsigned)grid), dim3(256), 0, st, x, (const bf16 *)g, (uint8_t *)yq, scale, rows, n, eps);
+        hipLaunchKernelGGL((quantize_rows_kernel<NORM, 32>), dim3((unsigned)grid), dim3(256), 0, st, x, (const bf16 *)g, (uint8_t *)yq, scale, rows, n, eps, rows_dev);
     else
         return GR4AD_EUNSUPPORTED;
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
 
-int launch_rmsnorm_quant(const void *x, const void *g, void *yq, float *scale, int64_t rows, int d, float eps, hipStream_t st) {
-    return launch_quantize_rows_any<true>(x, g, yq, scale, rows, d, eps, st);
+int launch_rmsnorm_quant(const void *x, const void *g, void *yq, float *scale, int64_t rows, int d, float eps, hipStream_t st, const int32_t *rows_dev) {
+    return launch_quantize_rows_any<true>(x, g, yq, scale, rows, d, eps, st, rows_dev);
 }
 
-int launch_quantize_rows(const void *x, void *yq, float *scale, int64_t rows, int n, hipStream_t st) {
-    return launch_quantize_rows_any<false>(x, nullptr, yq, scale, rows, n, 0.0f, st);
+int launch_quantize_rows(const void *x, void *yq, float *scale, int64_t rows, int n, hipStream_t st, const int32_t *rows_dev) {
+    return launch_quantize_rows_any<false>(x, nullptr, yq, scale, rows, n, 0.0f, st, rows_dev);
 }
 
 // whole-matrix scale (init time): largest magnitude through an integer maximum of the bit patterns (non-negative floats order like integers)

@@ -255,6 +255,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
     const int frow = lane % 32, hf = lane / 32;
     const int KT = F8 ? K / 128 : K / 64;
     static_assert(!(F8 && KIND == EPI_VT), "the transposed epilogue has no FP8 form");
+    if (epi.skip_len && !epi.skip_S) {  // the row count is known on the device only; M is its bound
+        M = epi.skip_len[0];
+        tiles_m = (M + 255) / 256;
+    }
 
     // ---- tile schedule: every XCD (workgroup id % 8) owns a contiguous range of logical tiles and its workgroups walk it
     // with stride nslots; inside a group of group_m row blocks the row index runs fastest, so the workgroups of an XCD
@@ -278,7 +282,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
     // Rows of A beyond a request's valid length (epi.skip_len[b] of every skip_S rows) are padding nobody reads the product
     // of: a tile whose 256 rows all lie in one request's padding is passed over.
     auto tile_live = [&](int64_t l) -> bool {
-        if (!epi.skip_len) return true;
+        if (!epi.skip_len || !epi.skip_S) return true;
         int64_t tm0;
         int tn0;
         tile_coords(l, tm0, tn0);
@@ -676,6 +680,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                 }
                 // the wave's block lies inside C (all but the last row and column of tiles): no bounds tests and running addresses
                 const bool interior = wrow0 + 128 <= M && wcol0 + 64 <= N;
+                // table rows: a lane fetches the selectors of two of the wave's 128 rows, the others take them from it (one memory
+                // latency per tile in front of the table's own instead of one per pass: 524288 x 1024 x 1024 with rows through a map 1.97 -> 1.54 ms)
+                uint32_t sel[2] = {0, 0};
+                if (KIND == EPI_F32_TABLE && epi.tok)
+#pragma unroll
+                    for (int i = 0; i < 2; i++) {
+                        const int64_t row = wrow0 + i * 64 + lane;
+                        sel[i] = (uint32_t)epi.tok[row < M ? row : M - 1];
+                    }
+                auto table_row = [&](int pass, int it) {
+                    return epi.table + (uint64_t)(uint32_t)__shfl((int)sel[pass / 2], (pass % 2) * 32 + it * 4 + erow, 64) * (uint32_t)N;
+                };
 #pragma unroll
                 for (int pass = 0; pass < 4; pass++) {
                     floatx4 adds[8];
@@ -688,7 +704,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                         } else {
 #pragma unroll
                             for (int it = 0; it < 8; it++)
-                                adds[it] = *(const floatx4 *)(epi.table + (epi.tok ? (int64_t)epi.tok[row0 + it * 4] : 0) * N + ecol);
+                                adds[it] = *(const floatx4 *)(table_row(pass, it) + ecol);
                         }
                     } else if (HAS_ADD) {
 #pragma unroll
@@ -861,7 +877,7 @@ static int launch_ring_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t l
 // at least three k-tiles, and row pitches whose byte offsets inside a 256-row block fit 32 bits.
 static bool ring_ok(int kind, int N, int K, int64_t lda, int64_t ldw, const GemmEpilogue &e) {
     const bool f32 = kind_f32(kind);
-    if (e.skip_len && e.skip_S < 1) return false;
+    if (e.skip_len && e.skip_S < 0) return false;
     if (K < 192 || lda >= (1 << 22) || ldw >= (1 << 22)) return false;
     if (e.out_f16 && kind != EPI_F32) return false;
     if (e.ldc % (f32 ? 4 : 8) || ((uintptr_t)e.C % 16)) return false;
@@ -1126,6 +1142,10 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
         W += (int64_t)blockIdx.y * batch_w;
         epi.C = (char *)epi.C + (int64_t)blockIdx.y * batch_c * (kind_f32(KIND) ? 4 : 2);
     }
+    if (!BATCHED && KIND != EPI_VT && STAGED && epi.skip_len && !epi.skip_S) {  // the row count is known on the device only; M is its bound
+        M = epi.skip_len[0];
+        tiles_m = (int)((M + BM - 1) / BM);
+    }
     // XCD-aware order: consecutive workgroup ids land on different XCDs (each with its own L2), so every XCD gets a contiguous range
     // of tiles, walked in groups of 8 row blocks (rows fastest): the tiles in flight on an XCD share their A and W blocks
     const uint32_t total = (uint32_t)tiles_m * (uint32_t)tiles_n, per_xcd = (total + 7) / 8;
@@ -1141,7 +1161,7 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
         if (epi.len_bounds == 1 && n0 >= len) return;
         if (epi.len_bounds == 2 && len < K) K = (len + 63) / 64 * 64;
     }
-    if (!BATCHED && (KIND == EPI_STORE || KIND == EPI_VT) && epi.skip_len) {
+    if (!BATCHED && (KIND == EPI_STORE || KIND == EPI_VT) && epi.skip_len && epi.skip_S) {
         // all rows of the tile in one request's padding, past the 64-row block of its last valid row: nobody reads the product
         const uint32_t r0 = (uint32_t)m0, S = (uint32_t)epi.skip_S, b0 = r0 / S;
         if (b0 == (r0 + BM - 1) / S) {
@@ -1466,7 +1486,7 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
         if (lda != K || !epi.pre_gain) return GR4AD_EINVAL;
         if (dtype == GR4AD_F32 && !f32_big_tiles(M, N) && f32_mfma_ok(epi.pre_x, lda, W, ldw, K) && ((uintptr_t)epi.pre_gain % 16) == 0)
             return launch_f32(epi.pre_x, lda, (const float *)W, ldw, M, N, K, epi, st);
-        const int s = launch_rmsnorm(dtype, epi.pre_x, epi.pre_gain, (void *)A, M, K, epi.pre_eps, st);
+        const int s = launch_rmsnorm(dtype, epi.pre_x, epi.pre_gain, (void *)A, M, K, epi.pre_eps, st, epi.skip_len && !epi.skip_S ? epi.skip_len : nullptr);
         if (s) return s;
         GemmEpilogue plain = epi;
         plain.pre_x = nullptr;

@@ -8,13 +8,14 @@
 namespace {
 struct Record { hipEvent_t start, stop; int cls; double flops, bytes; };
 bool g_on = false;
+double g_scale = 1.0;                // factor on the algorithmic work of the launches
 std::vector<Record> g_records;       // events in flight since the last read
 std::vector<Record> g_pool;          // recycled event pairs
 const size_t kMaxRecords = 1 << 16;
 const char *kNames[KC_COUNT] = {"gemm_bf16_tile", "gemm_simple", "cross_attn_flash_bf16",
                                 "cross_attn_simple", "self_attn_step", "trunk_self_attn", "rmsnorm", "fuse_gate", "select_rows",
                                 "select_request", "gather_rows", "broadcast_rows", "v_transpose", "gemm_bf16_ring", "masked_softmax_rows",
-                                "gemm_fp8_ring", "quantize_rows", "context_attn_flash_bf16"};
+                                "gemm_fp8_ring", "quantize_rows", "context_attn_flash_bf16", "distinct_rows"};
 }  // namespace
 
 ProfScope::ProfScope(int cls, hipStream_t st, double flops, double bytes) : idx_(-1), st_(st) {
@@ -31,8 +32,8 @@ ProfScope::ProfScope(int cls, hipStream_t st, double flops, double bytes) : idx_
         }
     }
     r.cls = cls;
-    r.flops = flops;
-    r.bytes = bytes;
+    r.flops = flops * g_scale;
+    r.bytes = bytes * g_scale;
     (void)hipEventRecord(r.start, st);
     g_records.push_back(r);
     idx_ = (int)g_records.size() - 1;
@@ -41,6 +42,9 @@ ProfScope::ProfScope(int cls, hipStream_t st, double flops, double bytes) : idx_
 ProfScope::~ProfScope() {
     if (idx_ >= 0) (void)hipEventRecord(g_records[idx_].stop, st_);
 }
+
+bool prof_on() { return g_on; }
+void prof_scale_work(double f) { g_scale = f; }
 
 extern "C" {
 

@@ -1,0 +1,50 @@
+"""Levels whose token-only part runs on their distinct (request, previous token) rows.
+
+FP8 products compute the same at every row count, so the same requests decoded in a batch below the size from which levels share rows
+(8192) must come out bit for bit; bf16 decodes are held to the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import gpu_decode, judge_decode, judge_value, value_rounding_model
+from paper_2602_22732_amd import binding, synth
+from rounding_model import RoundedModel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,beam,V,Ve,vanilla", [
+    (130, [64, 64, 64, 64], [64, 5, 70, 3000], 0, False),    # 5 and at most 70 tokens for 64 beams
+    (129, [65, 67, 66, 65], [4096] * 4, 0, False),           # odd beams, few shared tokens
+    (140, [64, 64, 30], [80, 300, 256], 64, False),          # the value step shares too (n = 30: below the size)
+    (70, [120, 110, 127], [600, 90, 256], 64, False),        # the value step alone
+    (70, [300, 300, 520], [600, 90, 256], 64, False),        # several blocks of beams, shared in both batches, packed differently
+    (130, [64, 64, 64], [128, 16, 256], 0, True),            # vanilla input states
+])
+def test_fp8_decode_equals_the_same_requests_in_a_small_batch(B, beam, V, Ve, vanilla):
+    w = synth.Workload("distinct", "bf16", B, 70, 512, 3, 0 if vanilla else 1, 8, 1024, len(V), V, beam, zipf_bias=True, fp8=True, Ve=Ve, vanilla=vanilla)
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    g = torch.Generator(device="cuda").manual_seed(B)
+    ctx = torch.randn(B, w.S, w.d, generator=g, device="cuda").bfloat16()
+    lens = torch.randint(1, w.S + 1, (B,), generator=g, device="cuda").int()
+    some = dec.decode_batch(ctx, lens, w.beam, value=bool(Ve))
+    m = 64  # (at least as many rows as the FP8 matrix-core kernel takes, at level 1)
+    few = dec.decode_batch(ctx[:m].contiguous(), lens[:m].contiguous(), w.beam, value=bool(Ve))
+    torch.cuda.synchronize()
+    for a, b in zip(some, few):
+        assert torch.equal(a[:m], b)
+    dec.close()
+
+
+@pytest.mark.parametrize("V,Ve,vanilla", [([64, 6, 200, 96], 0, False), ([512, 512, 512], 0, False), ([64, 40, 64], 32, False), ([64, 7, 256], 0, True)])
+def test_bf16_decode_matches_oracle(V, Ve, vanilla):
+    T = len(V)
+    w = synth.Workload("distinct", "bf16", 131, 20, 256, 2, 0 if vanilla else 1, 4, 512, T, V, [64] * T, len_min=3, zipf_bias=True, Ve=Ve, vanilla=vanilla)
+    W = synth.make_weights(w)
+    lens = synth.make_lengths(w, seed=3)
+    X = synth.make_context(w, lens)
+    res = gpu_decode(w, W, X, lens, value=bool(Ve))
+    print(judge_decode(w, W, X, lens, res[0], res[1], res[2], [0, 65, 130], model=RoundedModel(w, W)))
+    if Ve:
+        print(judge_value(w, W, X, lens, res[0], res[1], res[3], [130], model=value_rounding_model(w, W)))
+    assert np.isfinite(res[1]).all()
