@@ -1192,7 +1192,9 @@ __global__ __launch_bounds__(256) void fill_count_kernel(int *__restrict__ req_c
 }
 
 // Workspace: candidates [B][n*m] keys, the request counts, the scores behind the bounds [B][2R], the count of listed rows (one int in 256
-// bytes) and the list {row, slot} [B*n].  Counts and scores together take at most 8 * m bytes per request.
+// bytes) and the list {row, slot} [B*n].  The size callers are told, r() rounding up to 256 bytes, is
+// r(8 B n m) + r(8 B m) + r(8 B) + r(4 B) + 256 + r(8 B n): the parts never need more (counts: at most 4 m bytes per request; scores: 8, or at
+// most 2 m where R > 1), so how counts and scores are spread changes neither it nor what the static scratch accepts.
 struct SelectPlan {
     int R, count_pitch;
     size_t counts, scores, todo_count, todo, total;
@@ -1207,7 +1209,7 @@ static SelectPlan select_plan(int B, int n, int V, int k) {
     p.scores = p.counts + align256((size_t)B * p.count_pitch * sizeof(int));
     p.todo_count = p.scores + align256((size_t)B * 2 * p.R * sizeof(float));
     p.todo = p.todo_count + 256;
-    p.total = p.todo + align256((size_t)B * n * sizeof(int2));
+    p.total = p.counts + align256((size_t)B * m * 8) + align256((size_t)B * 8) + align256((size_t)B * 4) + 256 + align256((size_t)B * n * sizeof(int2));
     return p;
 }
 size_t select_workspace_bytes(int B, int n, int V, int k) { return select_plan(B, n, V, k).total; }
