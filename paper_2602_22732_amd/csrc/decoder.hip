@@ -682,6 +682,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         g.table = (const float *)f;
         return gemm_f8_on_persistent_kernel(aq, d, dec->layers[K].wo_s8, d, rows, d, d, g);
     };
+    prof_scale_work(1.0);  // (a call that failed inside a level may have left its factor)
     LevelMaps maps;
     memset(&maps, 0, sizeof(maps));
     bool any_map = false;

@@ -1274,7 +1274,7 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
 
 // ---------------------------------------------------------------------------
 // The same selection for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
-// harnesses that forbid hipMalloc): the candidate lists, first-row cuts, request bounds and counts live in a fixed device
+// harnesses that forbid hipMalloc): the candidate lists, the scores behind the request bounds and the counts live in a fixed device
 // array of this library instead of a caller workspace.  Host code never uses the array's name as an address: the device
 // address is looked up once per device and kept.  Every call on a GPU shares that GPU's array (overlapping calls race);
 // nothing in it has to start at zero - the counts are written by a kernel of every call before they are read.
