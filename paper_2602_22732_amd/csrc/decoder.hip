@@ -716,7 +716,9 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             maps.map[t] = dr.map;
             any_map = true;
             distinct = dr.total;
-            if (prof_on()) {  // the timing attributes work to launches: let it know how many rows there are
+            hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+            if (prof_on()) HIP_TRY(dec, hipStreamIsCapturing(st, &capturing));
+            if (prof_on() && capturing == hipStreamCaptureStatusNone) {  // the timing attributes work to launches: let it know how many rows there are
                 int32_t u = 0;
                 HIP_TRY(dec, hipMemcpyAsync(&u, dr.total, sizeof(u), hipMemcpyDeviceToHost, st));
                 HIP_TRY(dec, hipStreamSynchronize(st));

@@ -48,3 +48,32 @@ def test_bf16_decode_matches_oracle(V, Ve, vanilla):
     if Ve:
         print(judge_value(w, W, X, lens, res[0], res[1], res[3], [130], model=value_rounding_model(w, W)))
     assert np.isfinite(res[1]).all()
+
+
+def test_captured_replays_match_eager_calls():
+    """The number of distinct rows is read on the device, so a captured decode follows new contexts."""
+    w = synth.Workload("distinct", "bf16", 131, 20, 256, 2, 1, 4, 512, 3, [512, 512, 512], [64] * 3, len_min=3, zipf_bias=True)
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    ctx = torch.randn(w.B, w.S, w.d, generator=g, device="cuda").bfloat16()
+    ws = torch.empty(dec.workspace_bytes(w.B, w.S, w.beam), dtype=torch.uint8, device="cuda")
+    sid = torch.empty(w.B, 64, 3, dtype=torch.int32, device="cuda")
+    lp = torch.empty(w.B, 64, dtype=torch.float32, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        dec.decode_batch(ctx, None, w.beam, workspace=ws, out_sid=sid, out_logprob=lp)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        dec.decode_batch(ctx, None, w.beam, workspace=ws, out_sid=sid, out_logprob=lp)
+    for _ in range(3):
+        ctx.copy_(torch.randn(w.B, w.S, w.d, generator=g, device="cuda"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = sid.clone(), lp.clone()
+        want = dec.decode_batch(ctx, None, w.beam)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    dec.close()
