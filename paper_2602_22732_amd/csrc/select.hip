@@ -94,6 +94,11 @@ __device__ __forceinline__ float block_sum_256(float v, RowShared &sh, int slot)
     return (sh.f[slot][0] + sh.f[slot][1]) + (sh.f[slot][2] + sh.f[slot][3]);
 }
 
+// Every score of the row is a number.  False: a NaN or +inf logit or nothing but -inf (the log-sum-exp is no number then), or a cumulative
+// score of NaN or +inf.  NaN passes no comparison, so such a row takes no part in the bounded pass: it is cut by the order of its keys,
+// like every row of a selection without a bound (a NaN key ranks above all numbers).
+__device__ __forceinline__ bool row_is_numbers(float c, float lse) { return fabsf(lse) < INFINITY && c < INFINITY; }
+
 __device__ __forceinline__ unsigned long long pack_candidate(float score, uint32_t flat) {
     return ((unsigned long long)score_key(score) << 32) | (0xFFFFFFFFu - flat);
 }
@@ -361,6 +366,15 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) sum += __expf(x[j] - mx);
     const float lse = mx + __logf(block_sum_256(sum, sh, 2));
+    const float c = cum ? cum[row] : 0.0f;
+    if (!row_is_numbers(c, lse)) {  // bounds nothing
+        if (tid == 0) {
+            for (int Q = 1; Q <= R; Q <<= 1)
+                if (Q > r) rb[b * (2 * R) + Q + r] = -INFINITY;
+            if (r == 0) rb[b * (2 * R)] = -INFINITY;
+        }
+        return;
+    }
     const float inv_w = mx > mn && mx - mn < INFINITY ? (float)ROW_BINS / (mx - mn) : 0.0f;
     auto bin_of = [&](float v) { return min((int)fmaxf((v - mn) * inv_w, 0.0f), ROW_BINS - 1); };  // (NaN: bin 0)
 #pragma unroll
@@ -374,7 +388,6 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
     const int h[4] = {sh.hist[b0], sh.hist[b0 - 1], sh.hist[b0 - 2], sh.hist[b0 - 3]};
     const int incl = block_scan_256(h[0] + h[1] + h[2] + h[3], sh.wave_tot);
     const int excl = incl - (h[0] + h[1] + h[2] + h[3]);
-    const float c = cum ? cum[row] : 0.0f;
     auto put = [&](int Q, float v) {
         const float sc = c + (v - lse), low = sc - (1e-5f + 4e-7f * (fabsf(c) + fabsf(v) + fabsf(lse)));
         rb[b * (2 * R) + Q + r] = low == low ? low : -INFINITY;
@@ -788,8 +801,9 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         uint32_t nflat = 0xFFFFFFFFu - beam * (uint32_t)V - (uint32_t)lane * (uint32_t)E;
         asm volatile("" : "+v"(nflat));  // (opaque: keeps the compiler from carrying NX row-independent parts of the token words across rows)
         const float t0 = (sstar - c) + lse;
-        const float thr = t0 - 1e-6f * (fabsf(sstar) + fabsf(c) + fabsf(lse) + fabsf(t0));
-        int cnt = 0;
+        // (no bound: everything passes, also where the scores are -inf and t0 is NaN)
+        const float thr = sstar > -INFINITY ? t0 - 1e-6f * (fabsf(sstar) + fabsf(c) + fabsf(lse) + fabsf(t0)) : -INFINITY;
+        int cnt = row_is_numbers(c, lse) ? 0 : m + 1;  // (to the list, whatever the sweep finds)
         if (__ballot(lane_mx >= thr) != 0) {
 #pragma unroll
             for (int g = 0; g < G; g++) {
@@ -1007,7 +1021,7 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
     if (ncand <= SELB_THREADS || ncand <= kp) {
         int np = 1;
         while (np < ncand) np <<= 1;
-        for (int i = tid; i < np; i += SELB_THREADS) skeys[i] = i < ncand ? src[i] : 0ull;
+        for (int i = tid; i < (np > kp ? np : kp); i += SELB_THREADS) skeys[i] = i < ncand ? src[i] : 0ull;
         __syncthreads();
         bitonic_sort_desc(skeys, np);
     } else if (select_request_binned(src, ncand, k, skeys, hist, wave_tot, &sel_digit, &sel_krem, &sel_cnt, &out_cnt)) {
@@ -1068,7 +1082,8 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
     for (int j = tid; j < k; j += SELB_THREADS) {
         const unsigned long long key = skeys[j];
         const uint32_t flat = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
-        const int par = (int)(flat / (uint32_t)V), tk = (int)(flat % (uint32_t)V);
+        // (a request lists at least k candidates; the clamp keeps what is read through the parent inside the batch whatever the keys hold)
+        const int par = min((int)(flat / (uint32_t)V), n - 1), tk = (int)(flat % (uint32_t)V);
         parent[b * k + j] = par;
         tok[b * k + j] = tk;
         score[b * k + j] = key_score((uint32_t)(key >> 32));

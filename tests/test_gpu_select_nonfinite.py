@@ -1,0 +1,78 @@
+"""Selections with scores that are no numbers: every request still gets k distinct candidates with tokens and parents in range, ranked as a
+selection without a bound ranks them (the order of the score keys, in which a NaN lies above or below all numbers by its sign)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_common import judge_selection
+from paper_2602_22732_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def unbounded(logits, cum, k):
+    """The selection of the workgroup kernel, which knows no bound: float32 logits that are not 16-byte aligned."""
+    buf = torch.empty(logits.size + 1, device="cuda")[1:]
+    z = buf.view(logits.shape).copy_(torch.from_numpy(logits.astype(np.float32)))
+    assert z.data_ptr() % 16
+    return (t.cpu().numpy() for t in binding.op_select(z, torch.from_numpy(cum).cuda(), k))
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("kind", ["nan", "all_nan", "inf", "all_neg_inf", "cum_neg_inf", "cum_nan", "cum_inf"])
+@pytest.mark.parametrize("where", ["first", "last", "every"])
+@pytest.mark.parametrize("B,n,V,k", [(2, 1, 1024, 1024), (3, 1, 264, 7), (2, 3, 8192, 600), (2, 130, 264, 264)])
+def test_select_of_scores_that_are_no_numbers(B, n, V, k, where, kind, half):
+    rng = np.random.default_rng([B, n, V, k, half])
+    logits = rng.standard_normal((B, n, V)).astype(np.float16 if half else np.float32)
+    cum = (-2.0 * rng.random((B, n))).astype(np.float32)
+    rows = {"first": [0], "last": [n - 1], "every": range(n)}[where]
+    for i in rows:  # (the last request keeps numbers, where there is more than one)
+        z, c = logits[:B - 1, i], cum[:B - 1, i]
+        if kind == "nan":
+            z[:, 5] = np.nan
+        elif kind == "all_nan":
+            z[:] = np.nan
+        elif kind == "inf":
+            z[:, V - 3] = np.inf
+        elif kind == "all_neg_inf":
+            z[:] = -np.inf
+        else:
+            c[:] = {"cum_neg_inf": -np.inf, "cum_nan": np.nan, "cum_inf": np.inf}[kind]
+    print(kind, where, "half", half, "B n V k", B, n, V, k, flush=True)
+    parent, tok, score = (t.cpu().numpy() for t in binding.op_select(torch.from_numpy(logits).cuda(), torch.from_numpy(cum).cuda(), k))
+    u_parent, u_tok, u_score = unbounded(logits, cum, k)
+    assert (parent >= 0).all() and (parent < n).all() and (tok >= 0).all() and (tok < V).all()
+    for b in range(B):
+        flat, u_flat = parent[b].astype(np.int64) * V + tok[b], u_parent[b].astype(np.int64) * V + u_tok[b]
+        assert len(np.unique(flat)) == k
+        number = np.abs(score[b]) < np.inf
+        assert np.array_equal(number, np.abs(u_score[b]) < np.inf)
+        assert np.array_equal(flat[~number], u_flat[~number]) and np.array_equal(score[b][~number], u_score[b][~number], equal_nan=True)
+        lp = np.full((n, V), np.nan)
+        for i in range(n):
+            z = logits[b, i].astype(np.float32)
+            if not np.isnan(z).any() and np.abs(z).max() < np.inf:
+                lp[i] = oracle.prim_log_softmax(z)
+        want = cum[b].astype(np.float64)[:, None] + lp
+        if number.any():
+            judge_selection(np.where(np.isfinite(want), want, -1e30), flat[number], score[b][number], int(number.sum()), tol=3e-5, margin=2e-5, what="request %d" % b)
+
+
+@pytest.mark.parametrize("dtype,B,d", [("f32", 5, 128), ("bf16", 140, 256)])
+def test_request_of_nan_contexts_leaves_the_others_alone(dtype, B, d):
+    w = synth.Workload("poisoned", dtype, B, 24, d, 3, 1, 4, 2 * d, 3, [264, 96, 512], [64, 64, 64])
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    g = torch.Generator(device="cuda").manual_seed(d)
+    ctx = torch.randn(B, w.S, d, generator=g, device="cuda").to(binding.torch_dtype(dtype))
+    want_sid, want_lp = dec.decode_batch(ctx, None, w.beam)
+    ctx[2] = float("nan")
+    sid, lp = dec.decode_batch(ctx, None, w.beam)
+    torch.cuda.synchronize()
+    others = [b for b in range(B) if b != 2]
+    assert torch.equal(sid[others], want_sid[others]) and torch.equal(lp[others], want_lp[others])
+    V = torch.tensor(w.V, device="cuda")
+    assert (sid >= 0).all() and (sid < V).all()
+    assert len(torch.unique(sid[2].cpu(), dim=0)) == w.beam[-1]
+    dec.close()
