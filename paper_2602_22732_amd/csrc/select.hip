@@ -38,6 +38,7 @@ __device__ __forceinline__ float key_score(uint32_t k) {
     uint32_t u = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
     return __uint_as_float(u);
 }
+#define LAST_KEY 0x003FFFFFu  // score_key of the NaN that ranks below all numbers
 
 // inclusive scan over a 256-thread block (4 wavefronts)
 __device__ __forceinline__ int block_scan_256(int v, int *wave_tot /*[4] LDS*/) {
@@ -95,8 +96,7 @@ __device__ __forceinline__ float block_sum_256(float v, RowShared &sh, int slot)
 }
 
 // Every score of the row is a number.  False: a NaN or +inf logit or nothing but -inf (the log-sum-exp is no number then), or a cumulative
-// score of NaN or +inf.  NaN passes no comparison, so such a row takes no part in the bounded pass: it is cut by the order of its keys,
-// like every row of a selection without a bound (a NaN key ranks above all numbers).
+// score of NaN or +inf.  NaN passes no comparison, so such a row takes no part in the bounded pass; see select_rows_wave.
 __device__ __forceinline__ bool row_is_numbers(float c, float lse) { return fabsf(lse) < INFINITY && c < INFINITY; }
 
 __device__ __forceinline__ unsigned long long pack_candidate(float score, uint32_t flat) {
@@ -686,8 +686,15 @@ __global__ __launch_bounds__(256, 3) void select_rows_wave(const LT *__restrict_
         const uint32_t flat0 = (uint32_t)((vrow % n) * (int64_t)V);
         // low word of a staged candidate: 0xFFFFFFFF - (flat0 + token)
         const uint32_t nflat = 0xFFFFFFFFu - flat0 - (uint32_t)lane * (uint32_t)E;
-        select_row_own_cut<VEC, FULL, E>(x, cum ? cum[vrow] : 0.0f, mx, lse, cand + (dst_at >= 0 ? dst_at : vrow * (int64_t)m), flat0, nflat, V, m, list,
-                                         lane);
+        const float c = cum ? cum[vrow] : 0.0f;
+        unsigned long long *dst = cand + (dst_at >= 0 ? dst_at : vrow * (int64_t)m);
+        if (todo && (lse != lse || c != c)) {
+            // No score of the row is a number (a beam whose tokens are all masked, say).  Its tokens rank below every number, -inf too, so they
+            // survive only where the request has fewer than k numbers.  (m <= V)
+            for (int i = lane; i < m; i += 64) dst[i] = (unsigned long long)LAST_KEY << 32 | (0xFFFFFFFFu - (flat0 + (uint32_t)i));
+            continue;
+        }
+        select_row_own_cut<VEC, FULL, E>(x, c, mx, lse, dst, flat0, nflat, V, m, list, lane);
     }
 }
 

@@ -1,5 +1,6 @@
-"""Selections with scores that are no numbers: every request still gets k distinct candidates with tokens and parents in range, ranked as a
-selection without a bound ranks them (the order of the score keys, in which a NaN lies above or below all numbers by its sign)."""
+"""Selections with scores that are no numbers: every request still gets k distinct candidates with tokens and parents in range.  With several
+rows per request a row without numbers ranks below all numbers; a request of one row ranks as a selection without a bound does (the
+order of the score keys, in which a NaN lies above or below all numbers by its sign)."""
 import numpy as np
 import pytest
 import torch
@@ -45,19 +46,29 @@ def test_select_of_scores_that_are_no_numbers(B, n, V, k, where, kind, half):
     u_parent, u_tok, u_score = unbounded(logits, cum, k)
     assert (parent >= 0).all() and (parent < n).all() and (tok >= 0).all() and (tok < V).all()
     for b in range(B):
-        flat, u_flat = parent[b].astype(np.int64) * V + tok[b], u_parent[b].astype(np.int64) * V + u_tok[b]
+        flat = parent[b].astype(np.int64) * V + tok[b]
         assert len(np.unique(flat)) == k
-        number = np.abs(score[b]) < np.inf
-        assert np.array_equal(number, np.abs(u_score[b]) < np.inf)
-        assert np.array_equal(flat[~number], u_flat[~number]) and np.array_equal(score[b][~number], u_score[b][~number], equal_nan=True)
-        lp = np.full((n, V), np.nan)
-        for i in range(n):
-            z = logits[b, i].astype(np.float32)
-            if not np.isnan(z).any() and np.abs(z).max() < np.inf:
-                lp[i] = oracle.prim_log_softmax(z)
-        want = cum[b].astype(np.float64)[:, None] + lp
-        if number.any():
-            judge_selection(np.where(np.isfinite(want), want, -1e30), flat[number], score[b][number], int(number.sum()), tol=3e-5, margin=2e-5, what="request %d" % b)
+        with np.errstate(invalid="ignore"):
+            want = cum[b].astype(np.float64)[:, None] + np.stack([oracle.prim_log_softmax(z) if np.abs(z).max() < np.inf else np.full(V, np.nan)
+                                                                  for z in logits[b].astype(np.float32)])
+        want = want.ravel()
+        # +inf, then numbers, -inf and what is no number; ties in the order of the candidates
+        up, numbers, down, none = (np.flatnonzero(w) for w in (want == np.inf, np.isfinite(want), want == -np.inf, np.isnan(want)))
+        assert len(none) == 0 or n == 1 or len(up) + len(numbers) + len(down) >= k or where == "every"
+        if n == 1 and len(none):
+            u_flat = u_parent[b].astype(np.int64) * V + u_tok[b]
+            assert np.array_equal(flat, u_flat) and np.array_equal(score[b], u_score[b], equal_nan=True)
+            continue
+        take = [len(up[:k])]
+        for part in (numbers, down, none):
+            take.append(len(part[:k - sum(take)]))
+        at = np.cumsum(take)
+        assert np.array_equal(flat[:at[0]], up[:k]) and (score[b, :at[0]] == np.inf).all()
+        if take[1]:
+            judge_selection(np.where(np.isfinite(want), want, -1e30).reshape(n, V), flat[at[0]:at[1]], score[b, at[0]:at[1]], take[1], tol=3e-5, margin=2e-5,
+                            what="request %d" % b)
+        assert np.array_equal(flat[at[1]:at[2]], down[:take[2]]) and (score[b, at[1]:at[2]] == -np.inf).all()
+        assert np.array_equal(flat[at[2]:], none[:take[3]]) and np.isnan(score[b, at[2]:]).all()
 
 
 @pytest.mark.parametrize("dtype,B,d", [("f32", 5, 128), ("bf16", 140, 256)])
