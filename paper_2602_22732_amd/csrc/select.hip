@@ -335,6 +335,9 @@ template <> struct LogitPiece<_Float16> {
 // through), so a histogram of the logits is enough: the lower edge of the bin that holds the ranked value, a margin above the error of
 // bin and log-sum-exp (the sweep computes its own).  Q = 1 is ranked exactly inside its bin and its logit kept too (slot 0 of the
 // request): the first row takes the threshold from that, since the margin would let it over its m slots now and then.
+// Masked tokens must not cost the request its bound: -inf stays out of the histogram (a row with fewer numbers than a rank has no bound
+// there), and where finite masks (-1e4, -65504) press the others into the top bins, the histogram is taken again over those bins alone, at
+// most twice (masks of two magnitudes).  64 requests of 128 rows of 4096 halves of which 1024 are not masked, k = 512: MASKED_TIMES
 template <int ITEMS, typename LT>
 __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits, const float *__restrict__ cum, int n, int V, int m, int R,
                                                   float *__restrict__ rb, int *__restrict__ req_count, int count_pitch, int *__restrict__ todo_count) {
@@ -348,7 +351,7 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
     const uint4 *z = (const uint4 *)(logits + row * (int64_t)V);
     constexpr int E = LogitPiece<LT>::E, G = ITEMS / E;
     float x[ITEMS];
-    float mx = -INFINITY, mn = INFINITY;
+    float mx = -INFINITY, lo = INFINITY;
 #pragma unroll
     for (int g = 0; g < G; g++) {
         const bool ok = (g * 256 + tid) * E < V;  // V % E == 0
@@ -357,11 +360,11 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
         for (int e = 0; e < E; e++) {
             if (!ok) x[g * E + e] = -INFINITY;
             mx = fmaxf(mx, x[g * E + e]);
-            if (ok) mn = fminf(mn, x[g * E + e]);
+            if (x[g * E + e] > -INFINITY) lo = fminf(lo, x[g * E + e]);
         }
     }
     mx = block_max_256(mx, sh, 0);
-    mn = -block_max_256(-mn, sh, 1);
+    lo = -block_max_256(-lo, sh, 1);
     float sum = 0.0f;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) sum += __expf(x[j] - mx);
@@ -375,55 +378,79 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
         }
         return;
     }
-    const float inv_w = mx > mn && mx - mn < INFINITY ? (float)ROW_BINS / (mx - mn) : 0.0f;
-    auto bin_of = [&](float v) { return min((int)fmaxf((v - mn) * inv_w, 0.0f), ROW_BINS - 1); };  // (NaN: bin 0)
+    // (from here on the logits are numbers or -inf, and some are numbers)
+    auto rank_of = [&](int q) { return (m + (1 << q) - 1) >> q; };  // ceil(m / Q), Q = 1 << q
+    const int q0 = 32 - __clz(r), rank_max = rank_of(q0);           // the smallest Q above r: the row's lowest rank
+    const int b0 = ROW_BINS - 1 - 4 * tid;  // thread t owns bins 1023-4t .. 1020-4t
+    float inv_w;
+    int h[4], incl, excl;
+    auto bin_of = [&](float v) { return (int)fminf((v - lo) * inv_w, (float)(ROW_BINS - 1)); };  // of a logit from lo on
+    auto find = [&](int rank, int &above, int &cnt) {  // the bin of a rank in (excl, incl], how many values lie above it and in it
+        int at = 0;
+        above = excl;
+        cnt = h[0];
 #pragma unroll
-    for (int g = 0; g < G; g++)
-        if ((g * 256 + tid) * E < V)
+        for (int i = 0; i < 3; i++)
+            if (at == i && above + h[i] < rank) { above += h[i]; cnt = h[i + 1]; at = i + 1; }
+        return b0 - at;
+    };
+    for (int pass = 0;; pass++) {
+        inv_w = mx > lo && mx - lo < INFINITY ? (float)ROW_BINS / (mx - lo) : 0.0f;
 #pragma unroll
-            for (int e = 0; e < E; e++) atomicAdd(&sh.hist[bin_of(x[g * E + e])], 1);
-    __syncthreads();
-    // thread t owns bins 1023-4t .. 1020-4t; inclusive scan from the top bin down
-    const int b0 = ROW_BINS - 1 - 4 * tid;
-    const int h[4] = {sh.hist[b0], sh.hist[b0 - 1], sh.hist[b0 - 2], sh.hist[b0 - 3]};
-    const int incl = block_scan_256(h[0] + h[1] + h[2] + h[3], sh.wave_tot);
-    const int excl = incl - (h[0] + h[1] + h[2] + h[3]);
+        for (int j = 0; j < ITEMS; j++)
+            if (x[j] >= lo) atomicAdd(&sh.hist[bin_of(x[j])], 1);
+        if (tid == 0) sh.sel_bin = -1;
+        __syncthreads();
+        // inclusive scan from the top bin down
+#pragma unroll
+        for (int i = 0; i < 4; i++) h[i] = sh.hist[b0 - i];
+        incl = block_scan_256(h[0] + h[1] + h[2] + h[3], sh.wave_tot);
+        excl = incl - (h[0] + h[1] + h[2] + h[3]);
+        if (excl < rank_max && incl >= rank_max) {
+            int above, cnt;
+            sh.sel_bin = find(rank_max, above, cnt);
+            sh.sel_krem = rank_max - above;
+            sh.sel_cnt = cnt;
+        }
+        __syncthreads();
+        const int T = sh.sel_bin, cnt = sh.sel_cnt;
+        // (a rank in the top 16 of 1024 bins: they say little about the ranked values)
+        if (pass == 2 || T < 0 || !(inv_w > 0.0f) || !(cnt > ROW_LIST || (cnt > 8 && T >= ROW_BINS - 16))) break;
+        float from = INFINITY;
+#pragma unroll
+        for (int j = 0; j < ITEMS; j++)
+            if (x[j] >= lo && bin_of(x[j]) >= T) from = fminf(from, x[j]);
+        from = -block_max_256(-from, sh, 1);
+        if (from == lo) break;
+        lo = from;
+        for (int i = tid; i < ROW_BINS; i += 256) sh.hist[i] = 0;
+        __syncthreads();
+    }
     auto put = [&](int Q, float v) {
         const float sc = c + (v - lse), low = sc - (1e-5f + 4e-7f * (fabsf(c) + fabsf(v) + fabsf(lse)));
         rb[b * (2 * R) + Q + r] = low == low ? low : -INFINITY;
     };
-    for (int Q = 1; Q <= R; Q <<= 1) {
-        if (Q <= r) continue;
-        const int rank = (m + Q - 1) / Q;
-        if (excl < rank && incl >= rank) {
-            int above = excl, i = 0;
-            while (above + h[i] < rank) above += h[i++];
-            if (Q == 1) {
-                sh.sel_bin = b0 - i;
-                sh.sel_krem = rank - above;
-                sh.sel_cnt = h[i];
-            } else {
-                put(Q, inv_w > 0.0f ? mn + ((float)(b0 - i) - 0.01f) / inv_w : mn);
-            }
-        }
+    // the value at the lower edge of a bin
+    auto edge = [&](int bin) { return inv_w > 0.0f ? lo + ((float)bin - 0.01f) / inv_w : lo; };
+    for (int q = q0; (1 << q) <= R; q++) {
+        const int rank = rank_of(q);
+        int above, cnt;
+        if (q > 0 && excl < rank && incl >= rank) put(1 << q, edge(find(rank, above, cnt)));
+        if (tid == 255 && incl < rank) put(1 << q, -INFINITY);  // fewer numbers than that
     }
     if (r != 0) return;
-    __syncthreads();
     const int T = sh.sel_bin, krem = sh.sel_krem, cnt = sh.sel_cnt;
-    if (cnt > ROW_LIST || !(inv_w > 0.0f)) {  // crowded bin (degenerate rows): its edge will do
+    if (T < 0 || cnt > ROW_LIST || !(inv_w > 0.0f)) {  // no such rank, or a crowded bin (degenerate rows): its edge will do
         if (tid == 0) {
-            put(1, inv_w > 0.0f ? mn + ((float)T - 0.01f) / inv_w : mn);
+            if (T >= 0) put(1, edge(T));
             rb[b * (2 * R)] = -INFINITY;
         }
         return;
     }
     float *list = (float *)sh.list;
 #pragma unroll
-    for (int g = 0; g < G; g++)
-        if ((g * 256 + tid) * E < V)
-#pragma unroll
-            for (int e = 0; e < E; e++)
-                if (bin_of(x[g * E + e]) == T) list[atomicAdd(&sh.list_n, 1)] = x[g * E + e];
+    for (int j = 0; j < ITEMS; j++)
+        if (x[j] >= lo && bin_of(x[j]) == T) list[atomicAdd(&sh.list_n, 1)] = x[j];
     __syncthreads();
     for (int i = tid; i < cnt; i += 256) {
         const float v = list[i];
