@@ -337,7 +337,8 @@ template <> struct LogitPiece<_Float16> {
 // request): the first row takes the threshold from that, since the margin would let it over its m slots now and then.
 // Masked tokens must not cost the request its bound: -inf stays out of the histogram (a row with fewer numbers than a rank has no bound
 // there), and where finite masks (-1e4, -65504) press the others into the top bins, the histogram is taken again over those bins alone, at
-// most twice (masks of two magnitudes).  64 requests of 128 rows of 4096 halves of which 1024 are not masked, k = 512: MASKED_TIMES
+// most twice (masks of two magnitudes).  64 requests of 128 float32 rows of 4096 of which 1024 are not masked, level scores, k = 512: 55 us
+// masked with -inf and 60 with -1e4, as against 560 and 350 with bounds lost to the masks; 55 without a mask.
 template <int ITEMS, typename LT>
 __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits, const float *__restrict__ cum, int n, int V, int m, int R,
                                                   float *__restrict__ rb, int *__restrict__ req_count, int count_pitch, int *__restrict__ todo_count) {
