@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
         acc[0] *= alpha;
         acc[1] *= alpha;
         const int cnt = (len - j0) < 64 ? (len - j0) : 64;
-        // values: loads of 16 keys in flight (keys past the tile's last re-read it with weight zero: adding 0 * v changes nothing)
+        // values: loads of 16 keys in flight (keys past the tile's last re-read it and count as zero: 0 * v is no zero where v is infinite)
         for (int j1 = 0; j1 < cnt; j1 += 16) {
             float v0[16], v1[16];
 #pragma unroll
@@ -80,6 +80,11 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
                 const T *vr = kbase + (int64_t)(j0 + (j1 + u < cnt ? j1 + u : cnt - 1)) * 2 * d + d;
                 v0[u] = lane < dh ? to_f(vr[lane]) : 0.0f;
                 v1[u] = lane + 64 < dh ? to_f(vr[lane + 64]) : 0.0f;
+            }
+            if (j1 + 16 > cnt) {
+#pragma unroll
+                for (int u = 0; u < 16; u++)
+                    if (j1 + u >= cnt) v0[u] = v1[u] = 0.0f;
             }
 #pragma unroll
             for (int u = 0; u < 16; u++) {

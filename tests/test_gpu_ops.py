@@ -206,6 +206,20 @@ def test_cross_attention_matches_oracle(dtype, B, n, S, d, H):
         np.testing.assert_allclose(out[b], ref, atol=2e-5 if dtype == "f32" else 1.5e-2)
 
 
+@pytest.mark.parametrize("d,H,S,n_keys", [(64, 1, 40, 37), (96, 1, 17, 17), (64, 2, 70, 65)])
+def test_cross_attention_keeps_infinite_values(d, H, S, n_keys):
+    """An infinite value at the last key makes its column infinite, not NaN: keys past the last one carry no weight (float32 kernel)."""
+    q = RNG.standard_normal((1, 3, d)).astype(np.float32)
+    kv = RNG.standard_normal((1, S, 2 * d)).astype(np.float32)
+    clean = kv.copy()
+    kv[0, n_keys - 1, d + 1], kv[0, n_keys - 1, 2 * d - 1] = np.inf, -np.inf
+    lens = torch.tensor([n_keys], dtype=torch.int32, device="cuda")
+    out, want = (binding.op_cross_attention(torch.from_numpy(q).cuda(), torch.from_numpy(x).cuda(), lens, H).cpu().numpy() for x in (kv, clean))
+    assert (out[..., 1] == np.inf).all() and (out[..., d - 1] == -np.inf).all()
+    rest = [c for c in range(d) if c not in (1, d - 1)]
+    np.testing.assert_array_equal(out[..., rest], want[..., rest])
+
+
 def context_attention_bound(xv):
     """What bf16 storage allows: the kernel rounds every probability that enters the product (8 significand bits: relative
     error up to 2^-8; the normaliser sums the unrounded ones) and the weighted sum itself (2^-8), so an output is off by at
