@@ -51,6 +51,8 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
     v += dpp_move<0x143, 0xC>(0.0f, v);  // row_bcast:31 into rows 2 and 3
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
+// four values' part of a sum of squares (spelled out: kernels that must agree to the bit leave the contraction to nobody)
+__device__ __forceinline__ float sum_sq4(float a, float b, float c, float d) { return fmaf(b, b, a * a) + fmaf(d, d, c * c); }
 __device__ __forceinline__ float wave_max_dpp(float v) {
     v = fmaxf(v, dpp_move<0x128, 0xF>(v, v));
     v = fmaxf(v, dpp_move<0x124, 0xF>(v, v));

@@ -44,11 +44,16 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
         if (c < nvec) {
 #pragma unroll
             for (int e = 0; e < N; e += 4) load16<float>(x + row * d + (int64_t)c * N + e, &v[i][e]);
+            if constexpr (N == 4) {
+                ss += sum_sq4(v[i][0], v[i][1], v[i][2], v[i][3]);
+            } else {
 #pragma unroll
-            for (int e = 0; e < N; e++) ss += v[i][e] * v[i][e];
+                for (int e = 0; e < N; e++) ss += v[i][e] * v[i][e];
+            }
         }
     }
-    ss = wave_sum(ss);
+    // (float32: the sum of gemm_f32_mfma's prologue, so that a row is normalised alike in every batch)
+    ss = N == 4 ? wave_sum_dpp(ss) : wave_sum(ss);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
     for (int i = 0; i < MAXV; i++) {

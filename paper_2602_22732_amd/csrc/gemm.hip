@@ -102,31 +102,38 @@ __global__ __launch_bounds__(256) void gemm_simple(const T *__restrict__ A, int6
 // L1 serves the sharing), with all loads of an unrolled block in flight.  T = 16: a workgroup owns a 16x16 tile and its four
 // wavefronts split K, joined through LDS in a fixed order - 12 x 512 x 128 runs on 32 compute units for a chain of 8 MFMAs.
 // T = 32: four wavefronts own a 64x64 tile, 32x32 each, for shapes with enough tiles to fill the chip (twice the flops per byte).
+// A request's result must not depend on its batch, so both add in one order: the same instruction (v_mfma_f32_16x16x4_f32: T = 32 has four
+// accumulators per wavefront, at the rate of one v_mfma_f32_32x32x2_f32) over the same quarters of K, joined in the same way; a wavefront with
+// 32x32 elements walks the quarters in turn.
 // Replaces 64x64 FMA tiles staged through LDS value by value: 27 us on average for the products of a decode of 4 requests at d = 128,
 // now 3 to 4 us.  Needs K % 4 == 0 and 16-byte aligned rows.
 template <int T>
 __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A, int64_t lda, const float *__restrict__ W, int64_t ldw, int64_t M,
                                                      int N, int K, GemmEpilogue epi) {
-    constexpr int KL = 64 / T, KB = KL * 4;       // k values of one MFMA; k values of one 16-byte load per lane
-    constexpr int UN = T == 16 ? 8 : 4;           // loads of A (and of W) in flight per lane
+    constexpr int G = T / 16, KB = 16;            // 16x16 tiles of a wavefront each way; k values of one 16-byte load per lane
+    constexpr int UN = T == 16 ? 8 : 2;           // blocks of KB whose loads are in flight (2 UN G per lane)
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const int64_t m0 = T == 16 ? (int64_t)blockIdx.x * 16 : (int64_t)blockIdx.x * 64 + (wave / 2) * 32;
     const int n0 = T == 16 ? blockIdx.y * 16 : blockIdx.y * 64 + (wave % 2) * 32;
-    const int64_t ar = m0 + lane % T;
-    const int wr = n0 + lane % T, k4 = (lane / T) * 4;
-    const float *a = A + (ar < M ? ar : M - 1) * lda + k4, *w = W + (int64_t)(wr < N ? wr : N - 1) * ldw + k4;  // (rows past the edge: never stored)
-    typedef typename std::conditional<T == 16, floatx4, floatx16>::type Acc;
-    Acc acc = {};
+    const int k4 = (lane / 16) * 4;
+    const float *a[G], *w[G];
+#pragma unroll
+    for (int g = 0; g < G; g++) {  // (rows past the edge: never stored)
+        const int64_t ar = m0 + g * 16 + lane % 16;
+        const int wr = n0 + g * 16 + lane % 16;
+        a[g] = A + (ar < M ? ar : M - 1) * lda + k4;
+        w[g] = W + (int64_t)(wr < N ? wr : N - 1) * ldw + k4;
+    }
     __shared__ float rinv[16];
     if constexpr (T == 16) {
-        if (epi.pre_x) {  // A = RMSNorm(pre_x): 1/rms of the tile's rows, four per wavefront (the loads below take the gain)
+        if (epi.pre_x) {  // A = RMSNorm(pre_x): 1/rms of the tile's rows, four per wavefront (the loads below take the gain), as rmsnorm_kernel has it
             float ss[4] = {};
             for (int k = lane * 4; k < K; k += 256)
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
                     const int64_t r = m0 + wave + 4 * q;
                     const floatx4 v = *(const floatx4 *)(epi.pre_x + (r < M ? r : M - 1) * lda + k);
-                    ss[q] += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+                    ss[q] += sum_sq4(v[0], v[1], v[2], v[3]);
                 }
 #pragma unroll
             for (int q = 0; q < 4; q++) {
@@ -136,46 +143,75 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
             __syncthreads();
         }
     }
-    const int nb = (K + KB - 1) / KB;                              // blocks of KB values of k
-    const int per = T == 16 ? (nb + 3) / 4 : nb, b0 = T == 16 ? wave * per : 0, b1 = b0 + per < nb ? b0 + per : nb;
-    for (int b = b0; b < b1; b += UN) {
-        floatx4 av[UN], wv[UN];
+    const int nb = (K + KB - 1) / KB, per = (nb + 3) / 4;  // blocks of KB values of k; blocks in a quarter
+    auto quarter = [&](int s, floatx4 (&acc)[G][G]) {
+        const int b0 = s * per, b1 = b0 + per < nb ? b0 + per : nb;
 #pragma unroll
-        for (int u = 0; u < UN; u++) {
-            const int k = (b + u) * KB + k4;
-            av[u] = wv[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (b + u < b1 && k < K) {
-                av[u] = *(const floatx4 *)(a + (int64_t)(b + u) * KB);
-                wv[u] = *(const floatx4 *)(w + (int64_t)(b + u) * KB);
-                if constexpr (T == 16)
-                    if (epi.pre_x) av[u] = *(const floatx4 *)((const float *)epi.pre_gain + k) * av[u] * rinv[lane % 16];
+        for (int i = 0; i < G; i++)
+#pragma unroll
+            for (int j = 0; j < G; j++) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = b0; b < b1; b += UN) {
+            floatx4 av[UN][G], wv[UN][G];
+#pragma unroll
+            for (int u = 0; u < UN; u++) {
+                const int k = (b + u) * KB + k4;
+#pragma unroll
+                for (int g = 0; g < G; g++) {
+                    av[u][g] = wv[u][g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if (b + u < b1 && k < K) {
+                        av[u][g] = *(const floatx4 *)(a[g] + (int64_t)(b + u) * KB);
+                        wv[u][g] = *(const floatx4 *)(w[g] + (int64_t)(b + u) * KB);
+                        if constexpr (T == 16)
+                            if (epi.pre_x) av[u][g] = *(const floatx4 *)((const float *)epi.pre_gain + k) * av[u][g] * rinv[lane % 16];
+                    }
+                }
             }
+#pragma unroll
+            for (int u = 0; u < UN; u++)
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+#pragma unroll
+                    for (int i = 0; i < G; i++)
+#pragma unroll
+                        for (int j = 0; j < G; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], wv[u][j][e], acc[i][j], 0, 0, 0);
         }
-#pragma unroll
-        for (int u = 0; u < UN; u++)
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                if constexpr (T == 16) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][e], wv[u][e], acc, 0, 0, 0);
-                else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u][e], wv[u][e], acc, 0, 0, 0);
-            }
-    }
-    // accumulators: column lane % T; T = 16: row 4 * (lane / 16) + v, T = 32: row 8 * (v / 4) + 4 * (lane / 32) + v % 4
+    };
+    floatx4 acc[G][G];
+    // accumulators: column lane % 16, row 4 * (lane / 16) + v
     if constexpr (T == 16) {
+        quarter(wave, acc);
         __shared__ float part[4][256];
 #pragma unroll
-        for (int v = 0; v < 4; v++) part[wave][(4 * (lane / 16) + v) * 16 + lane % 16] = acc[v];
+        for (int v = 0; v < 4; v++) part[wave][(4 * (lane / 16) + v) * 16 + lane % 16] = acc[0][0][v];
         __syncthreads();
         const int t = threadIdx.x;
         const int64_t row = m0 + t / 16;
         const int col = n0 + t % 16;
         if (row < M && col < N) epilogue_store<float>(epi, row, col, N, (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]));
     } else {
+        floatx4 low[G][G], high[G][G];
+        auto join = [&](floatx4 (&sum)[G][G]) {
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-            const int64_t row = m0 + 8 * (v / 4) + 4 * (lane / 32) + v % 4;
-            const int col = n0 + lane % 32;
-            if (row < M && col < N) epilogue_store<float>(epi, row, col, N, acc[v]);
-        }
+            for (int i = 0; i < G; i++)
+#pragma unroll
+                for (int j = 0; j < G; j++) sum[i][j] += acc[i][j];
+        };
+        quarter(0, low);
+        quarter(1, acc);
+        join(low);
+        quarter(2, high);
+        quarter(3, acc);
+        join(high);
+#pragma unroll
+        for (int i = 0; i < G; i++)
+#pragma unroll
+            for (int j = 0; j < G; j++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const int64_t row = m0 + i * 16 + 4 * (lane / 16) + v;
+                    const int col = n0 + j * 16 + lane % 16;
+                    if (row < M && col < N) epilogue_store<float>(epi, row, col, N, low[i][j][v] + high[i][j][v]);
+                }
     }
 }
 

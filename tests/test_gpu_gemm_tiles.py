@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2602_22732_amd import binding
+from paper_2602_22732_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,27 @@ def test_f32_linear_at_tile_edges(M, N, K):
     A, W, bias = torch.randn(M, K, generator=g), torch.randn(N, K, generator=g) / K**0.5, torch.randn(N, generator=g)
     out = binding.op_linear(A.cuda(), W.cuda(), bias.cuda(), out_f32=True).cpu().double()
     np.testing.assert_allclose(out.numpy(), (A.double() @ W.double().t() + bias.double()).numpy(), atol=1e-5, rtol=1e-6)
+
+
+@pytest.mark.parametrize("N,K", [(1024, 4), (1040, 68), (1024, 132), (1032, 516), (1024, 1024)])
+def test_f32_rows_do_not_depend_on_the_row_count(N, K):
+    """Enough rows for the 64x64 tiles and few of them alone: the same bits."""
+    g = torch.Generator().manual_seed(N + K)
+    a, w = torch.randn(1100, K, generator=g).cuda(), torch.randn(N, K, generator=g).cuda()
+    many = binding.op_linear(a, w, out_f32=True)
+    for first, rows in ((0, 1), (37, 64), (1000, 100)):
+        assert torch.equal(binding.op_linear(a[first:first + rows].contiguous(), w, out_f32=True), many[first:first + rows])
+
+
+@pytest.mark.parametrize("d,H", [(128, 4), (384, 3)])
+def test_f32_requests_do_not_depend_on_their_batch(d, H):
+    """Products, norms and attention of one request alone and inside a batch whose products run on the larger tiles."""
+    w = synth.Workload("batch", "f32", 40, 33, d, 3, 1, H, 2 * d, 3, [512, 264, 1024], [64, 64, 64], len_min=5)
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    lens = synth.make_lengths(w, seed=1)
+    ctx, cl = torch.from_numpy(synth.make_context(w, lens)).cuda(), torch.from_numpy(lens).int().cuda()
+    sid, lp = dec.decode_batch(ctx, cl, w.beam)
+    for b in (0, 39):
+        one = dec.decode_batch(ctx[b:b + 1].contiguous(), cl[b:b + 1].contiguous(), w.beam)
+        assert torch.equal(one[0][0], sid[b]) and torch.equal(one[1][0], lp[b])
+    dec.close()
