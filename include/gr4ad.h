@@ -119,6 +119,8 @@ int gr4ad_decode_init(const gr4ad_model_desc *desc, const gr4ad_weights *weights
 /*
  * gr4ad_decode_workspace_bytes -- bytes of device workspace decode_batch needs
  * for B requests of S context tokens with beam widths beam[T] (host array).
+ * The size of a larger batch need not serve a smaller one (levels of 8192
+ * rows and more keep half-precision logits): ask for the sizes of each call.
  * Returns 0 if the arguments are invalid for this decoder.
  */
 size_t gr4ad_decode_workspace_bytes(const gr4ad_decoder *dec, int32_t B, int32_t S, const int32_t *beam);

@@ -993,9 +993,12 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
 // Requests up to which the tiles run side by side: 128 at d = 512, 64 at d = 1024.  Their cost grows with the requests (each tile reads the
 // request's queries again: 1.7 us a request at d = 1024 and 64 queries, 0.27 us at d = 512 and 24), the one-pass kernel's only
 // from 256 requests on (111 us and 53 us there).
-static bool context_split(int B, int d) { return (int64_t)B * d <= 65536; }
+#define CONTEXT_SPLIT_ROWS 65536
+static bool context_split(int B, int d) { return (int64_t)B * d <= CONTEXT_SPLIT_ROWS; }
+// (more requests than that need none of it; they are told the same size as the most that do, so that a larger batch's scratch serves a smaller one)
 size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S, int d) {
-    if (!context_attention_covers(dtype, RQ, d) || !context_split(B, d)) return 0;
+    if (!context_attention_covers(dtype, RQ, d)) return 0;
+    if (!context_split(B, d)) B = CONTEXT_SPLIT_ROWS / d;
     return (size_t)B * ((S + 31) / 32) * (RQ > 32 ? 2 : 1) * (1024 + 32) * sizeof(float);
 }
 

@@ -28,3 +28,19 @@ def test_few_requests_equal_the_same_requests_in_a_large_batch(d, H, T, S, lens)
     torch.cuda.synchronize()
     assert torch.equal(few_sid, sid[:n]) and torch.equal(few_lp, lp[:n])
     dec.close()
+
+
+@pytest.mark.parametrize("d,H", [(512, 8), (1024, 16)])
+def test_workspace_of_a_larger_batch_serves_a_smaller_one(d, H):
+    """Across the batch size from which the lazy layers need no scratch of their own."""
+    most = 65536 // d
+    w = synth.Workload("split", "bf16", most + 2, 64, d, 2, 1, H, 256, 3, [64] * 3, [2] * 3)
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    sizes = [dec.workspace_bytes(B, w.S, w.beam) for B in range(most - 2, most + 3)]
+    assert sizes == sorted(sizes)
+    ctx = torch.randn(most, w.S, d, generator=torch.Generator(device="cuda").manual_seed(d), device="cuda").bfloat16()
+    sid, lp = dec.decode_batch(ctx, None, w.beam, workspace=torch.empty(sizes[3], dtype=torch.uint8, device="cuda"))
+    want = dec.decode_batch(ctx, None, w.beam)
+    torch.cuda.synchronize()
+    assert torch.equal(sid, want[0]) and torch.equal(lp, want[1])
+    dec.close()
