@@ -748,7 +748,8 @@ static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ct
 // ---------------------------------------------------------------------------
 // The same for few requests: the tiles of a request side by side.  One workgroup per request leaves most of the chip idle below some
 // hundred requests and walks its tiles one after the other, 2.9 us each (8 requests of 1024 rows: 93 us).  Here context_scores
-// computes the scores of every tile at once, one workgroup per (request, tile), and context_sums gives every request D / 128 (one
+// computes the scores of every tile at once, with one workgroup per compute unit dealt to the requests (it keeps its fragments of the
+// queries over its tiles, and contexts far shorter than S leave few idle workgroups), and context_sums gives every request D / 128 (one
 // query tile: D / 256) workgroups, one per slice of the columns of z: they repeat the cheap part, the running maxima over the tile
 // maxima and the exponentials, and walk the tiles only for their product.  Every sum keeps the order of the one-pass kernel (partial
 // scores of the same slices of D, the lazily refreshed maximum tile by tile, the normaliser per half wavefront, z over the rows), so
@@ -756,64 +757,73 @@ static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ct
 // ---------------------------------------------------------------------------
 #define CTX_CHUNK 8  // tiles whose probabilities are formed together
 #define CTX_STAGE (32 * 1024)
+#define CTX_SCORE_GROUPS 256  // workgroups of context_scores; more than the most requests
 
 // sc: [B][ntiles][QT][4][64 lanes][4] raw scores as a wavefront holds them; mxs: [B][ntiles][QT][32] scaled maximum of each tile's valid rows
 template <int D, int QT>
 __global__ __launch_bounds__(512) void context_scores(const bf16 *__restrict__ qp, const bf16 *__restrict__ x, const int32_t *__restrict__ ctx_len,
-                                                      float *__restrict__ sc, float *__restrict__ mxs, int RQ, int rq_stride, int S, float scale_log2e) {
+                                                      float *__restrict__ sc, float *__restrict__ mxs, int RQ, int rq_stride, int S, int ntiles, float scale_log2e) {
     constexpr int KSPLIT = 8 / QT, KSL = D / KSPLIT, KSTEPS = KSL / 16;
-    __shared__ __attribute__((aligned(16))) char part[QT * (KSPLIT - 1) * 4096];
+    constexpr int PART = QT * (KSPLIT - 1) * 4096;
+    __shared__ __attribute__((aligned(16))) char parts[2 * PART];  // (two tiles: one barrier each)
     const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const int tile = blockIdx.x, ntiles = gridDim.x, b = blockIdx.y;
+    const int b = blockIdx.y;
     const int r32 = lane % 32, g = lane / 32, kq = wave % KSPLIT, qh = wave / KSPLIT;
     int len = ctx_len ? ctx_len[b] : S;
     len = len < 1 ? 1 : (len > S ? S : len);
-    if (tile * 32 >= len) return;
-    const int row = tile * 32 + r32 < len ? tile * 32 + r32 : len - 1, qrow = qh * 32 + r32 < RQ ? qh * 32 + r32 : RQ - 1;
-    const bf16 *xr = x + ((int64_t)b * S + row) * D + kq * KSL + 8 * g;
+    if ((int)blockIdx.x * 32 >= len) return;
+    const int qrow = qh * 32 + r32 < RQ ? qh * 32 + r32 : RQ - 1;
     const bf16 *qr = qp + ((int64_t)b * rq_stride + qrow) * D + kq * KSL + 8 * g;
-    bf16x8 xf[KSTEPS], qf[KSTEPS];
+    bf16x8 qf[KSTEPS];
 #pragma unroll
-    for (int st = 0; st < KSTEPS; st++) { xf[st] = *(const bf16x8 *)(xr + 16 * st); qf[st] = *(const bf16x8 *)(qr + 16 * st); }
-    __builtin_amdgcn_sched_barrier(0);  // (every load on its way before the first product: one latency)
-    floatx16 s;
+    for (int st = 0; st < KSTEPS; st++) qf[st] = *(const bf16x8 *)(qr + 16 * st);
+    char *part = parts;
+    for (int tile = blockIdx.x; tile * 32 < len; tile += gridDim.x, part = part == parts ? parts + PART : parts) {
+        const int row = tile * 32 + r32 < len ? tile * 32 + r32 : len - 1;
+        const bf16 *xr = x + ((int64_t)b * S + row) * D + kq * KSL + 8 * g;
+        bf16x8 xf[KSTEPS];
 #pragma unroll
-    for (int v = 0; v < 16; v++) s[v] = 0.0f;
+        for (int st = 0; st < KSTEPS; st++) xf[st] = *(const bf16x8 *)(xr + 16 * st);
+        __builtin_amdgcn_sched_barrier(0);  // (every load on its way before the first product: one latency)
+        floatx16 s;
 #pragma unroll
-    for (int st = 0; st < KSTEPS; st++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[st], qf[st], s, 0, 0, 0);
-    if (kq > 0) {
+        for (int v = 0; v < 16; v++) s[v] = 0.0f;
+#pragma unroll
+        for (int st = 0; st < KSTEPS; st++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[st], qf[st], s, 0, 0, 0);
+        if (kq > 0) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                floatx4 pk;
+#pragma unroll
+                for (int e = 0; e < 4; e++) pk[e] = s[4 * i + e];
+                *(floatx4 *)(part + (qh * (KSPLIT - 1) + kq - 1) * 4096 + (i * 64 + lane) * 16) = pk;
+            }
+        }
+        __syncthreads();
+        if (kq > 0) continue;
+#pragma unroll
+        for (int k = 0; k < KSPLIT - 1; k++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const floatx4 pk = *(const floatx4 *)(part + (qh * (KSPLIT - 1) + k) * 4096 + (i * 64 + lane) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; e++) s[4 * i + e] += pk[e];
+            }
+        const int64_t unit = ((int64_t)b * ntiles + tile) * QT + qh;
+        float mx = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             floatx4 pk;
 #pragma unroll
-            for (int e = 0; e < 4; e++) pk[e] = s[4 * i + e];
-            *(floatx4 *)(part + (qh * (KSPLIT - 1) + kq - 1) * 4096 + (i * 64 + lane) * 16) = pk;
+            for (int e = 0; e < 4; e++) {
+                pk[e] = s[4 * i + e];
+                if (tile * 32 + 8 * i + 4 * g + e < len) mx = fmaxf(mx, pk[e]);
+            }
+            *(floatx4 *)(sc + unit * 1024 + (i * 64 + lane) * 4) = pk;
         }
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;
+        if (g == 0) mxs[unit * 32 + r32] = mx;
     }
-    __syncthreads();
-    if (kq > 0) return;
-#pragma unroll
-    for (int k = 0; k < KSPLIT - 1; k++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const floatx4 pk = *(const floatx4 *)(part + (qh * (KSPLIT - 1) + k) * 4096 + (i * 64 + lane) * 16);
-#pragma unroll
-            for (int e = 0; e < 4; e++) s[4 * i + e] += pk[e];
-        }
-    const int64_t unit = ((int64_t)b * ntiles + tile) * QT + qh;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        floatx4 pk;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            pk[e] = s[4 * i + e];
-            if (tile * 32 + 8 * i + 4 * g + e < len) mx = fmaxf(mx, pk[e]);
-        }
-        *(floatx4 *)(sc + unit * 1024 + (i * 64 + lane) * 4) = pk;
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;
-    if (g == 0) mxs[unit * 32 + r32] = mx;
 }
 
 template <int D, int QT>
@@ -990,16 +1000,16 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
     }
 }
 
-// Requests up to which the tiles run side by side: 128 at d = 512, 64 at d = 1024.  Their cost grows with the requests (each tile reads the
-// request's queries again: 1.7 us a request at d = 1024 and 64 queries, 0.27 us at d = 512 and 24), the one-pass kernel's only
-// from 256 requests on (111 us and 53 us there).
-#define CONTEXT_SPLIT_ROWS 65536
-static bool context_split(int B, int d) { return (int64_t)B * d <= CONTEXT_SPLIT_ROWS; }
+// Requests up to which the tiles run side by side.  The line lies where the workgroups of context_sums outnumber the compute units (one fits a
+// unit, D * QT / 256 to a request); at d = 1024 and two query tiles a little beyond.  Decodes with six lazy layers, one-pass kernel and side by
+// side, 1024 context rows: d = 512, 24 queries, 128 requests 1382 and 1225 us; 40 queries, 64 requests 1340 and 1236, 80 requests 1495 and 1521;
+// d = 1024, 64 queries, 48 requests 1802 and 1689, 64 requests of 256 rows 1142 and 1150.
+static int context_split_most(int RQ, int d) { return RQ <= 32 ? 65536 / d : (d == 512 ? 64 : 48); }
 // (more requests than that need none of it; they are told the same size as the most that do, so that a larger batch's scratch serves a smaller one)
 size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S, int d) {
     if (!context_attention_covers(dtype, RQ, d)) return 0;
-    if (!context_split(B, d)) B = CONTEXT_SPLIT_ROWS / d;
-    return (size_t)B * ((S + 31) / 32) * (RQ > 32 ? 2 : 1) * (1024 + 32) * sizeof(float);
+    const int most = context_split_most(RQ, d);
+    return (size_t)(B < most ? B : most) * ((S + 31) / 32) * (RQ > 32 ? 2 : 1) * (1024 + 32) * sizeof(float);
 }
 
 template <int D, int QT>
@@ -1016,7 +1026,9 @@ static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ct
     const int nt = (S + 31) / 32;
     float *mxs = ws + (size_t)B * nt * QT * 1024;
     ProfScope ps(KC_CONTEXT_ATTN, st, 4.0 * B * (double)RQ * S * D, (2.0 * B * (double)RQ * D + B * (double)S * D) * sizeof(bf16));
-    hipLaunchKernelGGL((context_scores<D, QT>), dim3(nt, B), dim3(512), 0, st, qp, x, ctx_len, ws, mxs, RQ, rq_stride, S, scale * 1.4426950408889634f);
+    const int per_request = nt * B <= CTX_SCORE_GROUPS ? nt : CTX_SCORE_GROUPS / B;
+    hipLaunchKernelGGL((context_scores<D, QT>), dim3(per_request, B), dim3(512), 0, st, qp, x, ctx_len, ws, mxs, RQ, rq_stride, S, nt,
+                       scale * 1.4426950408889634f);
     GR4AD_LAUNCH_CHECK();
     hipLaunchKernelGGL(sums, dim3(D * QT / 256, B), dim3(512), LDS_BYTES, st, x, ctx_len, (const float *)ws, (const float *)mxs, z, RQ, rq_stride, S, nt,
                        scale * 1.4426950408889634f);
@@ -1035,7 +1047,7 @@ int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, c
         bf16 *zz = (bf16 *)z + (int64_t)q0 * d;
         const int nq = RQ - q0 < 64 ? RQ - q0 : 64;
         int s;
-        if (ws && context_split(B, d)) {
+        if (ws && B <= context_split_most(RQ, d)) {
             float *w = (float *)ws;
             if (d == 1024) s = nq > 32 ? launch_context_split<1024, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st)
                                        : launch_context_split<1024, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st);

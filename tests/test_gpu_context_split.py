@@ -15,6 +15,9 @@ pytestmark = pytest.mark.gpu
     (512, 8, 7, 64, [64, 1, 40]),                             # two query tiles, one stage
     (1024, 16, 4, 290, [290, 289, 3, 128]),                   # 64 queries
     (1024, 16, 5, 96, [96, 65]),                              # 80 queries: two launches
+    (512, 8, 3, 100, list(range(1, 101)) + [100] * 28),       # as many requests as run side by side: several tiles to a workgroup
+    (512, 8, 7, 300, [300 - 7 * i for i in range(40)] + [300] * 24),
+    (1024, 16, 4, 290, [290 - 6 * i for i in range(48)]),
 ])
 def test_few_requests_equal_the_same_requests_in_a_large_batch(d, H, T, S, lens):
     n, big = len(lens), 65536 // d + 1
@@ -30,10 +33,9 @@ def test_few_requests_equal_the_same_requests_in_a_large_batch(d, H, T, S, lens)
     dec.close()
 
 
-@pytest.mark.parametrize("d,H", [(512, 8), (1024, 16)])
-def test_workspace_of_a_larger_batch_serves_a_smaller_one(d, H):
+@pytest.mark.parametrize("d,H,most", [(512, 8, 128), (1024, 16, 48)])
+def test_workspace_of_a_larger_batch_serves_a_smaller_one(d, H, most):
     """Across the batch size from which the lazy layers need no scratch of their own."""
-    most = 65536 // d
     w = synth.Workload("split", "bf16", most + 2, 64, d, 2, 1, H, 256, 3, [64] * 3, [2] * 3)
     dec = binding.decoder_for(w, synth.make_weights(w))
     sizes = [dec.workspace_bytes(B, w.S, w.beam) for B in range(most - 2, most + 3)]
