@@ -1047,8 +1047,8 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
     __shared__ int sel_digit, sel_krem, sel_cnt, out_cnt;
     const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
     const int64_t b = blockIdx.x;
-    const unsigned long long *src = cand + b * req_stride;  // the request's candidates: the first req_count[b] keys of its segment
-    const int64_t ncand = req_count[b * count_pitch];
+    const unsigned long long *src = cand + b * req_stride;  // the request's candidates: the first keys of its segment, all of them without a count
+    const int64_t ncand = req_count ? req_count[b * count_pitch] : req_stride;
     int kp = 1;
     while (kp < k) kp <<= 1;
 
@@ -1236,11 +1236,6 @@ static int launch_rows(const RowsLaunch &a, int64_t rows, int mode) {
 // Half-precision logits are taken by the wavefront kernel only: 16-byte pieces of 8 values.
 bool select_takes_f16(int V) { return V >= 8 && V <= 8192 && V % 8 == 0; }
 
-__global__ __launch_bounds__(256) void fill_count_kernel(int *__restrict__ req_count, int count_pitch, int B, int v) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b < B) req_count[(int64_t)b * count_pitch] = v;
-}
-
 // Workspace: candidates [B][n*m] keys, the request counts, the scores behind the bounds [B][2R], the count of listed rows (one int in 256
 // bytes) and the list {row, slot} [B*n].  The size callers are told, r() rounding up to 256 bytes, is
 // r(8 B n m) + r(8 B m) + r(8 B) + r(4 B) + 256 + r(8 B n): the parts never need more (counts: at most 4 m bytes per request; scores: 8, or at
@@ -1312,13 +1307,9 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
                 hipLaunchKernelGGL(select_rows<64>, dim3((unsigned)rows), dim3(256), stage_bytes, st, logits, cum, n, V, m, cand);
         }
         GR4AD_LAUNCH_CHECK();
-        if (!bounded) {  // every row wrote its m: the request's candidates are the n*m keys of its rows
-            hipLaunchKernelGGL(fill_count_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, req_count, p.count_pitch, B, n * m);
-            GR4AD_LAUNCH_CHECK();
-        }
     }
     ProfScope ps(KC_SELECT_REQUEST, st, 0.0, (bounded ? (double)B * k : (double)rows * m) * 8 + (double)B * k * 12);  // (same convention)
-    hipLaunchKernelGGL(select_request, dim3((unsigned)B), dim3(SELB_THREADS), 0, st, (const unsigned long long *)ws, (int64_t)n * m, req_count, p.count_pitch, V, k,
+    hipLaunchKernelGGL(select_request, dim3((unsigned)B), dim3(SELB_THREADS), 0, st, (const unsigned long long *)ws, (int64_t)n * m, bounded ? req_count : nullptr, p.count_pitch, V, k,
                        parent, tok, score, sid_old, sid_new, anc_old, anc_new, n, T, level);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
