@@ -78,7 +78,7 @@ struct RowShared {
     uint32_t u[2][4][2];
     int wave_tot[4];
     int scan_base, out_gt, out_eq, sel_bin, sel_krem, sel_cnt, list_n;
-    int hist[ROW_BINS];
+    int hist[ROW_BINS + 64];  // (past the bins: one place per lane for what is not counted)
     unsigned long long list[ROW_LIST];
 };
 
@@ -385,7 +385,8 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
     const int b0 = ROW_BINS - 1 - 4 * tid;  // thread t owns bins 1023-4t .. 1020-4t
     float inv_w;
     int h[4], incl, excl;
-    auto bin_of = [&](float v) { return (int)fminf((v - lo) * inv_w, (float)(ROW_BINS - 1)); };  // of a logit from lo on
+    // (-1 a bin or more below lo; bin 0 reaches a bin below lo, which is of no harm to ranks at or above lo)
+    auto bin_of = [&](float v) { return (int)__builtin_amdgcn_fmed3f((v - lo) * inv_w, -1.0f, (float)(ROW_BINS - 1)); };
     auto find = [&](int rank, int &above, int &cnt) {  // the bin of a rank in (excl, incl], how many values lie above it and in it
         int at = 0;
         above = excl;
@@ -398,8 +399,10 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
     for (int pass = 0;; pass++) {
         inv_w = mx > lo && mx - lo < INFINITY ? (float)ROW_BINS / (mx - lo) : 0.0f;
 #pragma unroll
-        for (int j = 0; j < ITEMS; j++)
-            if (x[j] >= lo) atomicAdd(&sh.hist[bin_of(x[j])], 1);
+        for (int j = 0; j < ITEMS; j++) {
+            const int bin = bin_of(x[j]);
+            atomicAdd(&sh.hist[bin >= 0 ? bin : ROW_BINS + tid % 64], 1);
+        }
         if (tid == 0) sh.sel_bin = -1;
         __syncthreads();
         // inclusive scan from the top bin down
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
         float from = INFINITY;
 #pragma unroll
         for (int j = 0; j < ITEMS; j++)
-            if (x[j] >= lo && bin_of(x[j]) >= T) from = fminf(from, x[j]);
+            if (bin_of(x[j]) >= T) from = fminf(from, x[j]);
         from = -block_max_256(-from, sh, 1);
         if (from == lo) break;
         lo = from;
@@ -451,7 +454,7 @@ __global__ __launch_bounds__(256) void row_bounds(const LT *__restrict__ logits,
     float *list = (float *)sh.list;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++)
-        if (x[j] >= lo && bin_of(x[j]) == T) list[atomicAdd(&sh.list_n, 1)] = x[j];
+        if (bin_of(x[j]) == T) list[atomicAdd(&sh.list_n, 1)] = x[j];
     __syncthreads();
     for (int i = tid; i < cnt; i += 256) {
         const float v = list[i];
