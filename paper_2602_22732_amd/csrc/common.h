@@ -232,8 +232,9 @@ struct ProfScope {
     int idx_;
     hipStream_t st_;
 };
-bool prof_on();
-void prof_scale_work(double f);  // factor on the work of the launches that follow (rows that turned out not to be there)
+// The work of this thread's launches that follow is counted on `rows` rows, of which there are count_dev[0] (on the device; NULL: all).
+// Copied behind the work on the stream, without waiting for it; nothing is done while timing is off or the stream is captured.
+void prof_rows(const int32_t *count_dev, int64_t rows, hipStream_t st);
 
 #define GR4AD_LAUNCH_CHECK()                                   \
     do {                                                       \

@@ -682,7 +682,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         g.table = (const float *)f;
         return gemm_f8_on_persistent_kernel(aq, d, dec->layers[K].wo_s8, d, rows, d, d, g);
     };
-    prof_scale_work(1.0);  // (a call that failed inside a level may have left its factor)
+    prof_rows(nullptr, 0, st);  // (a call that failed inside a level may have left its count)
     LevelMaps maps;
     memset(&maps, 0, sizeof(maps));
     bool any_map = false;
@@ -716,14 +716,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             maps.map[t] = dr.map;
             any_map = true;
             distinct = dr.total;
-            hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-            if (prof_on()) HIP_TRY(dec, hipStreamIsCapturing(st, &capturing));
-            if (prof_on() && capturing == hipStreamCaptureStatusNone) {  // the timing attributes work to launches: let it know how many rows there are
-                int32_t u = 0;
-                HIP_TRY(dec, hipMemcpyAsync(&u, dr.total, sizeof(u), hipMemcpyDeviceToHost, st));
-                HIP_TRY(dec, hipStreamSynchronize(st));
-                prof_scale_work((double)u / (double)rows);
-            }
+            prof_rows(dr.total, rows, st);
         }
         if (dec->vanilla) {
             // vanilla decoder (section 3.2): h^(0)_t = s_{t-1} + p_t
@@ -758,7 +751,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             if (f8) OP_TRY(dec, gemm8(rows, lw.wqkv_s8, lw.s_wqkv_s, 3 * d, d, plain_epilogue(qkv_lvl(t, a), 3 * d)), "self-attention qkv");
             else OP_TRY(dec, gemm(xn, rows, lw.wqkv_s, 3 * d, d, reads_norm(plain_epilogue(qkv_lvl(t, a), 3 * d))), "self-attention qkv");
             distinct = nullptr;  // from here on: every beam
-            prof_scale_work(1.0);
+            prof_rows(nullptr, 0, st);
             OP_TRY(dec, launch_self_attention_step(dt, qkv_lvl(t, a), prev, (const int32_t *)(ws + p.anc[cur]), o, rows, t, T, d, H, st, mapped ? &maps : nullptr),
                    "self-attention");
             GemmEpilogue out_s = resid_epi(h, d);

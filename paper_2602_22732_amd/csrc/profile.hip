@@ -6,12 +6,18 @@
 #include "common.h"
 
 namespace {
-struct Record { hipEvent_t start, stop; int cls; double flops, bytes; };
+struct Record { hipEvent_t start, stop; int cls; double flops, bytes; int slot; int64_t rows; };  // slot: row count of the launch (-1: as counted)
 bool g_on = false;
-double g_scale = 1.0;                // factor on the algorithmic work of the launches
 std::vector<Record> g_records;       // events in flight since the last read
 std::vector<Record> g_pool;          // recycled event pairs
 const size_t kMaxRecords = 1 << 16;
+// Row counts that only the device knows: copied here on the stream, read with the events.  Pinned, allocated at the first such count, kept.
+const int kMaxSlots = 1 << 14;
+int32_t *g_slots = nullptr;
+int g_slots_used = 0;
+// the slot in force and the rows the launches are counted with (a thread's own: decodes of several threads do not touch one another's)
+thread_local int t_slot = -1;
+thread_local int64_t t_rows = 0;
 const char *kNames[KC_COUNT] = {"gemm_bf16_tile", "gemm_simple", "cross_attn_flash_bf16",
                                 "cross_attn_simple", "self_attn_step", "trunk_self_attn", "rmsnorm", "fuse_gate", "select_rows",
                                 "select_request", "gather_rows", "broadcast_rows", "v_transpose", "gemm_bf16_ring", "masked_softmax_rows",
@@ -32,8 +38,10 @@ ProfScope::ProfScope(int cls, hipStream_t st, double flops, double bytes) : idx_
         }
     }
     r.cls = cls;
-    r.flops = flops * g_scale;
-    r.bytes = bytes * g_scale;
+    r.flops = flops;
+    r.bytes = bytes;
+    r.slot = t_slot;
+    r.rows = t_rows;
     (void)hipEventRecord(r.start, st);
     g_records.push_back(r);
     idx_ = (int)g_records.size() - 1;
@@ -43,8 +51,18 @@ ProfScope::~ProfScope() {
     if (idx_ >= 0) (void)hipEventRecord(g_records[idx_].stop, st_);
 }
 
-bool prof_on() { return g_on; }
-void prof_scale_work(double f) { g_scale = f; }
+void prof_rows(const int32_t *count_dev, int64_t rows, hipStream_t st) {
+    t_slot = -1;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (!count_dev || !g_on || g_slots_used >= kMaxSlots || hipStreamIsCapturing(st, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return;
+    if (!g_slots && hipHostMalloc((void **)&g_slots, kMaxSlots * sizeof(int32_t)) != hipSuccess) {
+        g_slots = nullptr;
+        return;
+    }
+    if (hipMemcpyAsync(g_slots + g_slots_used, count_dev, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess) return;
+    t_slot = g_slots_used++;
+    t_rows = rows;
+}
 
 extern "C" {
 
@@ -65,13 +83,15 @@ int gr4ad_profile_read(double *ms, double *flops, double *bytes, int64_t *launch
         float t = 0;
         if (hipEventElapsedTime(&t, r.start, r.stop) != hipSuccess) return GR4AD_EHIP;
         ms[r.cls] += t;
-        flops[r.cls] += r.flops;
-        bytes[r.cls] += r.bytes;
+        const double f = r.slot < 0 ? 1.0 : (double)g_slots[r.slot] / (double)r.rows;
+        flops[r.cls] += r.flops * f;
+        bytes[r.cls] += r.bytes * f;
         launches[r.cls] += 1;
     }
     if (reset) {
         for (const Record &r : g_records) g_pool.push_back(r);
         g_records.clear();
+        g_slots_used = 0;
     }
     return GR4AD_OK;
 }

@@ -77,3 +77,35 @@ def test_captured_replays_match_eager_calls():
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     dec.close()
+
+
+def test_profiled_decode_counts_distinct_rows_without_waiting():
+    """The timing counts the work of the rows that are there, and a profiled call only enqueues work like any other."""
+    B, n, S, d, L, K, T = 130, 64, 70, 512, 4, 1, 4
+    w = synth.Workload("distinct", "bf16", B, S, d, L, K, 8, 1024, T, [64, 5, 70, 300], [n] * T, zipf_bias=True, fp8=True)
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    ctx = torch.randn(B, S, d, generator=torch.Generator(device="cuda").manual_seed(2), device="cuda").bfloat16()
+    tr = dec.enable_trace(B, w.beam)
+    dec.decode_batch(ctx, None, w.beam)
+    torch.cuda.synchronize()
+    binding.profile_read(reset=True)
+    binding.profile_enable(True)
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    for _ in range(200):  # some tenths of a second of work in front
+        a @ a
+    busy = torch.cuda.Event()
+    busy.record()
+    dec.decode_batch(ctx, None, w.beam)
+    waited = busy.query()
+    prof = binding.profile_read(reset=True)
+    binding.profile_enable(False)
+    assert not waited
+    want = 0.0
+    for t in range(T):
+        rows = B * (n if t else 1)
+        first = rows
+        if t >= 2:  # a request's beams share their previous tokens
+            first = sum(len(torch.unique(tr["tok"][t - 1][b])) for b in range(B))
+        want += 4.0 * S * d * (first + (L - K - 1) * rows)
+    assert abs(prof["cross_attn_flash_bf16"]["flops"] / want - 1) < 1e-9
+    dec.close()
