@@ -1,7 +1,9 @@
 """Levels whose token-only part runs on their distinct (request, previous token) rows.
 
 FP8 products compute the same at every row count, so the same requests decoded in a batch below the size from which levels share rows
-(8192) must come out bit for bit; bf16 decodes are held to the oracle."""
+(8192) must come out bit for bit; bf16 decodes are held to the oracle and, bit for bit, to decodes that compute every row."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -36,7 +38,42 @@ def test_fp8_decode_equals_the_same_requests_in_a_small_batch(B, beam, V, Ve, va
     dec.close()
 
 
-@pytest.mark.parametrize("V,Ve,vanilla", [([64, 6, 200, 96], 0, False), ([512, 512, 512], 0, False), ([64, 40, 64], 32, False), ([64, 7, 256], 0, True)])
+def profiled(dec, *args, **kw):
+    binding.profile_read(reset=True)
+    binding.profile_enable(True)
+    out = dec.decode_batch(*args, **kw)
+    prof = binding.profile_read(reset=True)
+    binding.profile_enable(False)
+    return out, "distinct_rows" in prof
+
+
+@pytest.mark.parametrize("d,V,Ve,vanilla", [(256, [64, 6, 256, 300], 0, False), (512, [300, 300, 300], 0, False), (256, [64, 40, 264], 256, False),
+                                            (256, [64, 7, 256], 0, True)])
+def test_bf16_decode_equals_one_that_computes_every_row(d, V, Ve, vanilla):
+    """(Sharing needs classifiers of 256 columns.)  Levels share rows only where the FFN is wide enough to lend its hidden rows; a narrower one is the same function as a wide one whose further hidden
+    units are zero, so the two models give the same bits, one with and one without shared rows."""
+    T, F = len(V), d
+    w = synth.Workload("distinct", "bf16", 131, 40, d, 3, 0 if vanilla else 1, d // 64, F, T, V, [64] * T, len_min=3, zipf_bias=True, Ve=Ve, vanilla=vanilla)
+    W = synth.make_weights(w)
+    lens = synth.make_lengths(w, seed=3)
+    ctx, cl = torch.from_numpy(synth.make_context(w, lens)).to("cuda", torch.bfloat16), torch.from_numpy(lens).int().cuda()
+    dec = binding.decoder_for(w, W)
+    every, found = profiled(dec, ctx, cl, w.beam, value=bool(Ve))
+    assert not found
+    dec.close()
+    wide = dataclasses.replace(w, F=2 * F)
+    pad = dict(W, layers=[dict(lw, w1=np.pad(lw["w1"], ((0, F), (0, 0))), w2=np.pad(lw["w2"], ((0, 0), (0, F)))) for lw in W["layers"]])
+    dec = binding.decoder_for(wide, pad)
+    shared, found = profiled(dec, ctx, cl, w.beam, value=bool(Ve))
+    assert found
+    torch.cuda.synchronize()
+    for a, b in zip(shared, every):
+        assert torch.equal(a, b)
+    dec.close()
+
+
+@pytest.mark.parametrize("V,Ve,vanilla", [([64, 6, 200, 96], 0, False), ([64, 6, 256, 300], 0, False), ([512, 512, 512], 0, False), ([64, 40, 64], 32, False),
+                                          ([64, 40, 264], 256, False), ([64, 7, 256], 0, True)])
 def test_bf16_decode_matches_oracle(V, Ve, vanilla):
     T = len(V)
     w = synth.Workload("distinct", "bf16", 131, 20, 256, 2, 0 if vanilla else 1, 4, 512, T, V, [64] * T, len_min=3, zipf_bias=True, Ve=Ve, vanilla=vanilla)
