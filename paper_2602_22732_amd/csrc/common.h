@@ -115,7 +115,7 @@ struct GemmEpilogue {
 int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                 const GemmEpilogue &epi, hipStream_t st);
 // true if this product is one of the large class, which folds the RMSNorm and writes half-precision logits
-bool gemm_on_persistent_kernel(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
+bool gemm_large_class(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                                const GemmEpilogue &epi);
 
 // FP8 (OCP E4M3) operands: C = (a_scale[row] * w_scale) * Aq Wq^T followed by the same epilogues; lda, ldw in elements (bytes);
@@ -216,7 +216,7 @@ int launch_trunk_self_attention(gr4ad_dtype dtype, const void *qkv, void *out, i
 size_t select_workspace_bytes(int B, int n, int V, int k);
 // sid_old [B,n,T] / sid_new [B,k,T] may be NULL (no path bookkeeping); anc_old / anc_new likewise: batch-wide row index of
 // each survivor's ancestor at levels 0..level (anc_new[.., level] = b*n + parent); level = 0-based t
-// logits_f16 != 0: logits is a half-precision array (what the classifier's persistent GEMM leaves for large levels); needs select_takes_f16(V)
+// logits_f16 != 0: logits is a half-precision array (what a classifier of the large class leaves for large levels); needs select_takes_f16(V)
 int launch_select(const void *logits, int logits_f16, const float *cum, int B, int n, int V, int k, void *ws, size_t ws_bytes, int32_t *parent,
                   int32_t *tok, float *score, const int32_t *sid_old, int32_t *sid_new, const int32_t *anc_old, int32_t *anc_new, int T,
                   int level, hipStream_t st);

@@ -88,7 +88,7 @@ bool beams_ok(const gr4ad_decoder *dec, const int32_t *beam) {
 GemmEpilogue plain_epilogue(void *C, int64_t ldc);
 
 // Level t (0-based) with `rows` beam rows: does the classifier leave its logits in half precision for the selection?  It does
-// where the persistent GEMM runs the classifier (it alone has that epilogue) and the wavefront selection kernel takes the
+// where the classifier is a product of the large class (whose kernels have that epilogue) and the wavefront selection kernel takes the
 // codebook size: the logits then make their round trip through HBM in 2 instead of 4 bytes.  The log-sum-exp, the scores and
 // the selection stay float32; the rounding of a logit (at most 2^-11 of its magnitude) is far below what bf16 operands leave
 // in it.  float32 storage, small levels and the value step (whose output IS the distribution) keep float32 logits.
@@ -98,7 +98,7 @@ bool level_logits_f16(const gr4ad_decoder *dec, int64_t rows, int t) {
     g.out_f32 = 1;
     g.out_f16 = 1;
     if (dec->fp8) return gemm_f8_on_persistent_kernel(dec->ln_out, dec->d, dec->cls8[t], dec->d, rows, dec->V[t], dec->d, g);
-    return gemm_on_persistent_kernel(dec->dtype, dec->ln_out, dec->d, dec->cls[t], dec->d, rows, dec->V[t], dec->d, g);
+    return gemm_large_class(dec->dtype, dec->ln_out, dec->d, dec->cls[t], dec->d, rows, dec->V[t], dec->d, g);
 }
 
 Plan make_plan(const gr4ad_decoder *dec, int64_t B, int64_t S, const int32_t *beam) {
@@ -503,14 +503,14 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     auto silu_epi = [&](void *x, int64_t ld) { GemmEpilogue g = plain_epilogue(x, ld); g.act = ACT_SILU; return g; };
 
     // RMSNorm folded into the projections around it.  Every norm sits between a projection that writes the residual
-    // stream x (residual update or Fuse) and one that reads norm(x).  On launches that run on the persistent kernel the
+    // stream x (residual update or Fuse) and one that reads norm(x).  On products of the large class the
     // writer also stores gain * x (storage dtype, into xn) and per-row partial sums of x^2, and the reader scales its
     // product rows by 1/rms(x) - (gain * x / rms) W^T = (1/rms) (gain * x) W^T - so the norm kernel and its pass over
     // the stream disappear.  Elsewhere (small launches, float32, widths the kernel does not cover) the reader forms its operand itself
     // (GemmEpilogue::pre_x).
     const int nparts = d / 64;
     float *ss = (float *)(ws + p.ss), *rinv = ss + (size_t)p.rows_max * nparts;  // partial sums of x^2; 1/rms per row
-    bool fold = false;             // set per phase: this row count and these widths run on the persistent kernel
+    bool fold = false;             // set per phase: products of this row count and these widths are of the large class
     bool scaled = false;           // xn holds gain * x without the 1/rms factor; its reader must apply row_ss
     const void *emitted = nullptr; // gain the last writer of x folded in (xn and ss are current for exactly that norm)
     auto fold_ok = [&](int64_t rows, int n_cls) -> bool {
@@ -520,8 +520,8 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         g.norm_gain = dec->ln_out; g.norm_out = xn; g.norm_ld = d; g.norm_ss = ss;
         GemmEpilogue r = plain_epilogue(q, d);      // representative reader
         r.row_inv = rinv;
-        return gemm_on_persistent_kernel(dt, o, d, dec->layers[0].wo_x, d, rows, d, d, g) &&
-               gemm_on_persistent_kernel(dt, xn, d, dec->layers[0].wq_x, d, rows, d, d, r);
+        return gemm_large_class(dt, o, d, dec->layers[0].wo_x, d, rows, d, d, g) &&
+               gemm_large_class(dt, xn, d, dec->layers[0].wq_x, d, rows, d, d, r);
     };
     auto emit_norm = [&](GemmEpilogue g, const void *next_gain) {  // writer side: x is followed by RMSNorm with next_gain
         emitted = nullptr;

@@ -1504,7 +1504,7 @@ static bool mfma_ok(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W
     return dtype == GR4AD_BF16 && kind >= 0 && K % 64 == 0 && lda % 8 == 0 && ldw % 8 == 0 && lda < (1 << 23) && ldw < (1 << 23) && ((uintptr_t)A % 16) == 0 && ((uintptr_t)W % 16) == 0;
 }
 
-bool gemm_on_persistent_kernel(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
+bool gemm_large_class(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                                const GemmEpilogue &epi) {
     const int kind = epilogue_kind(epi);
     if (M <= 0 || N <= 0 || K <= 0 || !mfma_ok(dtype, A, lda, W, ldw, K, kind)) return false;
@@ -1516,8 +1516,8 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
                 const GemmEpilogue &epi, hipStream_t st) {
     if (M <= 0 || N <= 0 || K <= 0) return GR4AD_EINVAL;
     const int kind = epilogue_kind(epi);
-    // only the persistent kernel folds the RMSNorm or writes half-precision logits: never drop such a request silently
-    if ((epi.norm_out || epi.row_inv || epi.out_f16) && !gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) return GR4AD_EUNSUPPORTED;
+    // only products of the large class fold the RMSNorm or write half-precision logits: never drop such a request silently
+    if ((epi.norm_out || epi.row_inv || epi.out_f16) && !gemm_large_class(dtype, A, lda, W, ldw, M, N, K, epi)) return GR4AD_EUNSUPPORTED;
     if (epi.pre_x) {
         if (lda != K || !epi.pre_gain) return GR4AD_EINVAL;
         if (dtype == GR4AD_F32 && !f32_big_tiles(M, N) && f32_mfma_ok(epi.pre_x, lda, W, ldw, K) && ((uintptr_t)epi.pre_gain % 16) == 0)
@@ -1530,7 +1530,7 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
     }
     if (mfma_ok(dtype, A, lda, W, ldw, K, kind)) {
         const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
-        if (gemm_on_persistent_kernel(dtype, A, lda, W, ldw, M, N, K, epi)) {
+        if (gemm_large_class(dtype, A, lda, W, ldw, M, N, K, epi)) {
             const int run = pick_kernel(M, N, K, 1, false, tile_staged_ok(kind, N, epi), true);
             return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, kind, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, kind, epi, st);
         }

@@ -1278,8 +1278,8 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
     int *req_count = (int *)((char *)ws + p.counts), *todo_count = (int *)((char *)ws + p.todo_count);
     const bool wave_path = V <= 8192 && V % 4 == 0 && ((uintptr_t)logits % 16) == 0;
     // Request-level bound (several rows per request, a cut smaller than the row): see row_bounds.  One row per request - the first level of
-    // every decode - is its own cut and done: a bound would only read the row twice.  64 requests of one row of 8192, k = 256: 36 us so and
-    // 53 bounded for halves, 31.5 and 29.5 for float32; 1024 of 4096, k = 128: 38 and 51, 41 and 40.5.
+    // every decode - is its own cut and done: a bound would only read the row twice.  64 requests of one row of 8192, k = 256: 41 us so and
+    // 54 bounded for halves, 31.5 and 30.5 for float32.
     const bool bounded = wave_path && n > 1 && k <= V;
     {
         // algorithmic bytes: every logit once; the candidates written depend on the data (between k per request and m per row):
