@@ -9,8 +9,9 @@
 //  * gemm_simple<T>      64x64 tile, plain FMA, any shape; fallback.
 //  * gemm_f32_mfma<T>    float32 operands on the matrix cores.
 //  * gemm_bf16_tile<..>  bf16 operands, fp32 accumulation on the matrix cores with
-//                        v_mfma_f32_32x32x16_bf16; 64x64 and 128x128 tiles for the
-//                        small and middle shapes, operands streamed into LDS.
+//                        v_mfma_f32_32x32x16_bf16; 32x32 to 256x128 tiles for the
+//                        small and middle shapes, operands streamed into LDS by
+//                        wavefronts of their own.
 //  * gemm_bf16_ring<..>  the kernel of the large shapes: persistent, 256x256 tiles,
 //                        operands stream global -> LDS without passing registers.
 #include <string.h>
@@ -965,38 +966,38 @@ static int epilogue_kind(const GemmEpilogue &e) {
 // MFMA kernel of the small and middle shapes: one output tile per workgroup, ring of ST k-tiles in LDS
 // ---------------------------------------------------------------------------
 // The persistent kernel needs about one 256x256 tile per compute unit; a decode of a few requests has products of 1 to a few
-// thousand rows, whose time is the latency of one tile.  So the tiles are small (32x32 to 128x128, one wave tile of WT x WT per
-// wavefront) to spread over the chip, and the operands of the next ST - 1 k-tiles (64 values of k) are always in flight, straight
-// from global memory into LDS (up to K = 64 * ST the whole operand slab is requested at once): one memory latency per tile instead
-// of one per k-tile.  Same LDS geometry as the persistent kernel: 128-byte rows, chunk c of row r at position c ^ ((r >> 1) & 7).
-// One barrier per k-tile, in its middle: the fragments of k-steps 2 and 3 have been read by then, so the slot is free for k-tile
-// kt + ST, and the first fragments of the next k-tile are read under the MFMAs of steps 2 and 3.  A product of one C element is the
-// same sequence of v_mfma_f32_32x32x16 over k as in the persistent kernel: the two give the same bits.
-// STAGED (WT = 64, N and C aligned): operands swapped, C leaves through LDS in 16-byte pieces of whole rows, with everything the
+// thousand rows, whose time is the latency of one tile.  So the tiles are small (32x32 to 256x128) to spread over the chip, and the work of a
+// workgroup is divided: wavefronts of their own (NL loaders) stream the operands from global memory into an LDS ring of ST k-tiles (64 values of
+// k) and the others multiply.  A wavefront issues a 1 KB load every 25 to 35 cycles while its data comes from beyond the L1, so a wavefront that
+// multiplied and loaded spent more cycles issuing the eight loads of its k-tile (264) than on its four MFMAs (144), and none of its MFMAs ran before
+// the first ST k-tiles were requested: M = 32, N = K = 512 took 4.0 us with the loads between the MFMAs of 32x64 tiles, now 3.3 (an empty kernel: 2.35);
+// N = K = 1024 5.3, now 4.0; N = 1024, K = 4096 17.1, now 8.5 to 10.8; on 128x128 tiles M = 4096, N = K = 1024 13.5, now 12.2.
+// Same LDS geometry as the persistent kernel: 128-byte rows, chunk c of row r at position c ^ ((r >> 1) & 7).  One barrier per k-tile: the loaders
+// pass it when the k-tile has landed, the others when the one before (32x32 blocks: the one before that) has left LDS.  A product of one C
+// element is the same sequence of v_mfma_f32_32x32x16 over k as in the persistent kernel: the two give the same bits.
+// STAGED (WN = 64, N and C aligned): operands swapped, C leaves through LDS in 16-byte pieces of whole rows, with everything the
 // persistent kernel's epilogue offers.  Otherwise a lane stores the 16 rows of its column directly (64 or 128 bytes per half
 // wavefront and register), any N and pitch; EPI_VT swaps the operands so that these are 32 consecutive tokens of a column.
-// The addends of a wave tile in the read-back layout of the staged epilogue: piece it of pass p is row p*32 + it*4 + lane/16, columns
+// The addends of 32 rows in the read-back layout of the staged epilogue: piece it is row it*4 + lane/16, columns
 // (lane%16)*4 .. +3 (zero outside C).  Requested before the operands, they arrive under the main loop; requested in the epilogue
 // each pass waits for them (8192 x 512 x 512: 14.2 us, now 11).
-template <int KIND, int TM>
-__device__ __forceinline__ void staged_addends(floatx4 (&adds)[TM][8], int64_t wrow0, int wcol0, int64_t M, int N, const GemmEpilogue &epi, int lane) {
+template <int KIND>
+__device__ __forceinline__ void staged_addends(floatx4 (&adds)[8], int64_t row0, int wcol0, int64_t M, int N, const GemmEpilogue &epi, int lane) {
     if (KIND != EPI_F32_RESID && KIND != EPI_F32_TABLE) return;
     const int ecol = wcol0 + (lane % 16) * 4;
 #pragma unroll
-    for (int pass = 0; pass < TM; pass++)
-#pragma unroll
-        for (int it = 0; it < 8; it++) {
-            const int64_t row = wrow0 + pass * 32 + it * 4 + lane / 16;
-            adds[pass][it] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (row < M && ecol < N) {
-                if (KIND == EPI_F32_RESID) adds[pass][it] = *(const floatx4 *)(epi.resid + row * epi.ldr + ecol);
-                else adds[pass][it] = *(const floatx4 *)(epi.table + (epi.tok ? (int64_t)epi.tok[row] : 0) * N + ecol);
-            }
+    for (int it = 0; it < 8; it++) {
+        const int64_t row = row0 + it * 4 + lane / 16;
+        adds[it] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (row < M && ecol < N) {
+            if (KIND == EPI_F32_RESID) adds[it] = *(const floatx4 *)(epi.resid + row * epi.ldr + ecol);
+            else adds[it] = *(const floatx4 *)(epi.table + (epi.tok ? (int64_t)epi.tok[row] : 0) * N + ecol);
         }
+    }
 }
 
-template <int KIND, int TM>
-__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], const floatx4 (&adds)[TM][8], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
+template <int KIND, int TM, bool LATE>
+__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], floatx4 (&adds)[TM][8], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
                                                 const GemmEpilogue &epi, int lane) {
     const int frow = lane % 32, hf = lane / 32;
     if (epi.row_inv) {  // folded RMSNorm, reader side: a lane owns row frow of each 32-row block
@@ -1054,6 +1055,7 @@ __device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], const fl
         }
 #pragma unroll
         for (int pass = 0; pass < TM; pass++) {
+            if (LATE) staged_addends<KIND>(adds[pass], wrow0 + pass * 32, wcol0, M, N, epi, lane);
 #pragma unroll
             for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -1102,18 +1104,43 @@ __device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], const fl
     }
 }
 
+template <typename T> __device__ __forceinline__ void step_ptr(T *&p, int64_t by) {
+    p += by;
+    asm volatile("" : "+v"(p));  // (keeps the compiler from forming every address anew: a 64-bit multiply-add is three quarter-rate instructions)
+}
+
 // One wave tile of 32 x 32 accumulators at (row0, col0), operands in natural order (a lane owns column lane % 32 and, per register v,
-// row 8 * (v / 4) + 4 * (lane / 32) + v % 4); EPI_VT: swapped (a lane owns row lane % 32 and 16 columns).
+// row 8 * (v / 4) + 4 * (lane / 32) + v % 4); EPI_VT: swapped (a lane owns row lane % 32 and 16 columns).  The addresses run: formed one
+// by one they cost 0.3 us of a small product each way.
+template <typename T> __device__ __forceinline__ void next_row(T *&p, int v, int64_t ld) { step_ptr(p, v % 4 == 3 ? 5 * ld : ld); }  // register v to v + 1
 // What the epilogue adds to the 16 elements of a lane; rows and columns past the edge read inside the arrays and are dropped.
 template <int KIND>
 __device__ __forceinline__ void direct_addends(float (&add)[16], int64_t row0, int col0, int64_t M, int N, const GemmEpilogue &epi, int lane) {
     if (KIND != EPI_F32_RESID && KIND != EPI_F32_TABLE) return;
     const int hf = lane / 32, c = col0 + lane % 32, col = c < N ? c : N - 1;
+    if (row0 >= M) row0 = M - 1;  // (a block wholly past the edge)
+    const int last = M - 1 - row0 < 31 ? (int)(M - 1 - row0) : 31;  // last row of the block inside C, 0 .. 31
+    if (KIND == EPI_F32_RESID) {
+        const float *p = epi.resid + (row0 + 4 * hf) * epi.ldr + col, *end = epi.resid + (row0 + last) * epi.ldr + col;
 #pragma unroll
-    for (int v = 0; v < 16; v++) {
-        const int64_t r = row0 + 4 * hf + 8 * (v / 4) + (v % 4), row = r < M ? r : M - 1;
-        if (KIND == EPI_F32_RESID) add[v] = epi.resid[row * epi.ldr + col];
-        else add[v] = epi.table[(epi.tok ? (int64_t)epi.tok[row] : 0) * N + col];
+        for (int v = 0; v < 16; v++) {
+            add[v] = *(last == 31 || p < end ? p : end);
+            next_row(p, v, epi.ldr);
+        }
+    } else {
+        uint32_t sel[16];
+        if (epi.tok) {
+#pragma unroll
+            for (int v = 0; v < 16; v++) {
+                const int r = 8 * (v / 4) + v % 4 + 4 * hf;
+                sel[v] = (uint32_t)(epi.tok + row0)[r < last ? r : last];
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; v++) sel[v] = 0;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) add[v] = (epi.table + col)[(uint64_t)sel[v] * (uint32_t)N];
     }
 }
 
@@ -1126,52 +1153,66 @@ __device__ __forceinline__ void direct_epilogue(const floatx16 &acc, const float
         // request's first tokens also clear the padding columns S .. ldc - 1
         const int64_t row = row0 + frow;
         if (row >= M) return;
-        const int64_t b = row / epi.vt_S;
-        const int s = (int)(row - b * epi.vt_S);
+        const uint32_t b = (uint32_t)row / (uint32_t)epi.vt_S;  // (fewer than 2^31 rows)
+        const int s = (int)((uint32_t)row - b * (uint32_t)epi.vt_S);
         int len = epi.ctx_len ? epi.ctx_len[b] : epi.vt_S;
         len = len < 1 ? 1 : (len > epi.vt_S ? epi.vt_S : len);
         const int pad = (int)epi.ldc - epi.vt_S;
+        bf16 *o = (bf16 *)epi.C + ((int64_t)b * N + col0 + 4 * hf) * epi.ldc + s;
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-            const int col = col0 + 8 * (v / 4) + 4 * hf + v % 4;
-            if (col < N) {
-                bf16 *o = (bf16 *)epi.C + (b * N + col) * epi.ldc;
-                o[s] = s < len ? (bf16)acc[v] : (bf16)0.0f;
-                if (s < pad) o[epi.vt_S + s] = (bf16)0.0f;
+            if (col0 + 4 * hf + 8 * (v / 4) + v % 4 < N) {
+                *o = s < len ? (bf16)acc[v] : (bf16)0.0f;
+                if (s < pad) o[epi.vt_S] = (bf16)0.0f;
             }
+            next_row(o, v, epi.ldc);
         }
         return;
     }
     const int col = col0 + frow;
     if (col >= N) return;
     const float bias = (KIND == EPI_F32 && epi.bias) ? epi.bias[col] : 0.0f;
-#pragma unroll
-    for (int v = 0; v < 16; v++) {
-        const int64_t row = row0 + 4 * hf + 8 * (v / 4) + (v % 4);
-        if (row >= M) continue;
+    constexpr int E = kind_f32(KIND) ? 4 : 2;
+    char *p = (char *)epi.C + ((row0 + 4 * hf) * epi.ldc + col) * E;
+    auto store = [&](int v) {
         const float x = acc[v];
-        if (KIND == EPI_STORE) ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)x;
-        else if (KIND == EPI_SILU) ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)fast_silu(x);
-        else if (KIND == EPI_SILU_DIV) ((bf16 *)epi.C)[row * epi.ldc + col] = (bf16)(x / (1.0f + __expf(-x)));
-        else if (KIND == EPI_F32) ((float *)epi.C)[row * epi.ldc + col] = x + bias;
-        else ((float *)epi.C)[row * epi.ldc + col] = x + add[v];
+        if (KIND == EPI_STORE) *(bf16 *)p = (bf16)x;
+        else if (KIND == EPI_SILU) *(bf16 *)p = (bf16)fast_silu(x);
+        else if (KIND == EPI_SILU_DIV) *(bf16 *)p = (bf16)(x / (1.0f + __expf(-x)));
+        else if (KIND == EPI_F32) *(float *)p = x + bias;
+        else *(float *)p = x + add[v];
+    };
+    const int rows = M - row0 < 32 ? (int)(M - row0) : 32;
+    if (rows == 32) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            store(v);
+            next_row(p, v, epi.ldc * E);
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            if (4 * hf + 8 * (v / 4) + v % 4 < rows) store(v);
+            next_row(p, v, epi.ldc * E);
+        }
     }
 }
 
-template <int BM, int BN, int WT, int ST, int KIND, bool STAGED, bool BATCHED>
-__global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(const bf16 *__restrict__ A, int64_t lda, const bf16 *__restrict__ W,
-                                                                             int64_t ldw, int64_t M, int N, int K, int tiles_m, int tiles_n,
-                                                                             GemmEpilogue epi, int64_t batch_a, int64_t batch_w, int64_t batch_c) {
-    constexpr int WAVES_N = BN / WT, NW = (BM / WT) * WAVES_N, T = WT / 32;
-    constexpr int LPW = (BM + BN) / 8 / NW;           // loads of a wavefront per k-tile (1 KB each: 8 rows)
+template <int BM, int BN, int WM, int WN, int NL, int ST, int KIND, bool STAGED, bool BATCHED>
+__global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_tile(const bf16 *__restrict__ A, int64_t lda, const bf16 *__restrict__ W,
+                                                                                    int64_t ldw, int64_t M, int N, int K, int tiles_m, int tiles_n,
+                                                                                    GemmEpilogue epi, int64_t batch_a, int64_t batch_w, int64_t batch_c) {
+    constexpr int WAVES_N = BN / WN, NC = (BM / WM) * WAVES_N, TM = WM / 32, TN = WN / 32;
+    constexpr int LPW = (BM + BN) / 8 / NL;           // loads of a loader per k-tile (1 KB each: 8 rows)
     constexpr int STAGE = (BM + BN) * 128;            // bytes of a k-tile
     constexpr bool SWAP = STAGED || KIND == EPI_VT;   // W fragment first
-    static_assert((BM + BN) / 8 % NW == 0 && (ST - 1) * LPW <= 63 && ST >= 2 && ST <= 4, "load counts");
-    static_assert(!STAGED || WT == 64, "the staged epilogue takes 64 x 64 wave tiles");
+    constexpr bool ONE = TM * TN == 1;                // one 32x32 block per wavefront: a whole k-tile of fragments ahead
+    constexpr int LAG = ONE ? 2 : 1;                  // past barrier j the slots of k-tiles up to j - LAG are free
+    static_assert((BM + BN) / 8 % NL == 0 && (ST - 1) * LPW <= 63 && ST > LAG, "load counts");
+    static_assert(!STAGED || WN == 64, "the staged epilogue takes wave tiles of 64 columns");
     extern __shared__ bf16x8 smem[];
-    const int tid = threadIdx.x, lane = tid % 64;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     // blockIdx.y: batch index; the operands and the output of batch i start batch_a/w/c elements further on
     if (BATCHED) {
         A += (int64_t)blockIdx.y * batch_a;
@@ -1206,129 +1247,194 @@ __global__ __launch_bounds__((BM / WT) * (BN / WT) * 64) void gemm_bf16_tile(con
         }
     }
     const int KT = K / 64;
-
-    // ---- loads: piece p = i * NW + wave fills rows 8p .. 8p+7 of the k-tile's BM rows of A and BN rows of W, lane -> row lane/8,
-    // position lane%8 (rows past the matrix edge re-read its last row) ----
-    // A lane's byte offset in its operand block stays, the two block addresses move on: no vector arithmetic per k-tile.
-    const char *base_a = (const char *)(A + m0 * lda), *base_w = (const char *)(W + (int64_t)n0 * ldw);
-    uint32_t off[LPW];
-#pragma unroll
-    for (int i = 0; i < LPW; i++) {
-        const int p = i * NW + wave, r = p * 8 + lane / 8, chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
-        if (p < BM / 8) off[i] = (uint32_t)(m0 + r < M ? r : M - 1 - m0) * ((uint32_t)lda * 2) + chunk * 16;
-        else off[i] = (uint32_t)(n0 + r - BM < N ? r - BM : N - 1 - n0) * ((uint32_t)ldw * 2) + chunk * 16;
-    }
-    auto issue = [&](uint32_t at) {  // k-tiles are requested in ascending order; at: byte offset of the slot
-#pragma unroll
-        for (int i = 0; i < LPW; i++)
-            ring_dma16(((i * NW + wave) < BM / 8 ? base_a : base_w) + off[i], (bf16x8 *)((char *)smem + at + (i * NW + wave) * 1024));
-        base_a += 128;
-        base_w += 128;
+    auto bar = [&]() {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     };
-    // wait until at most n of this wavefront's k-tiles are in flight
-    auto wait_tiles = [&](auto n) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n.value * LPW) : "memory"); };
+    if (wave >= NC) {
+        // ---- loader: piece p = i * NL + me fills rows 8p .. 8p+7 of the k-tile's BM rows of A and BN rows of W, lane -> row lane/8,
+        // position lane%8 (rows past the matrix edge re-read its last row) ----
+        // A lane's byte offset in its operand block stays, the two block addresses move on: no vector arithmetic per k-tile.
+        const int me = wave - NC;
+        const char *base_a = (const char *)(A + m0 * lda), *base_w = (const char *)(W + (int64_t)n0 * ldw);
+        uint32_t off[LPW];
+#pragma unroll
+        for (int i = 0; i < LPW; i++) {
+            const int p = i * NL + me, r = p * 8 + lane / 8, chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
+            if (p < BM / 8) off[i] = (uint32_t)(m0 + r < M ? r : M - 1 - m0) * ((uint32_t)lda * 2) + chunk * 16;
+            else off[i] = (uint32_t)(n0 + r - BM < N ? r - BM : N - 1 - n0) * ((uint32_t)ldw * 2) + chunk * 16;
+        }
+        auto issue = [&](uint32_t at) {  // k-tiles are requested in ascending order; at: byte offset of the slot
+#pragma unroll
+            for (int i = 0; i < LPW; i++)
+                ring_dma16(((i * NL + me) < BM / 8 ? base_a : base_w) + off[i], (bf16x8 *)((char *)smem + at + (i * NL + me) * 1024));
+            base_a += 128;
+            base_w += 128;
+        };
+        auto landed = [&](auto n) {  // this loader's share of all but the newest n k-tiles is there
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n.value * LPW) : "memory");
+            bar();
+        };
+        auto rest = [&](auto self, auto n) {  // the last n + 1 k-tiles
+            if constexpr (n.value >= 0) {
+                if (KT > n.value) landed(n);
+                self(self, std::integral_constant<int, n.value - 1>());
+            }
+        };
+        const int first = KT < ST ? KT : ST;
+        for (int t = 0; t < first; t++) issue((uint32_t)(t * STAGE));
+        if (KT >= ST) {
+            landed(std::integral_constant<int, ST - 1>());
+            if constexpr (LAG == 2) landed(std::integral_constant<int, ST - 2>());
+            uint32_t at = 0;
+            for (int t = ST; t < KT; t++) {  // past the barrier of k-tile t - ST + LAG the slot of k-tile t - ST is free
+                landed(std::integral_constant<int, ST - 1 - LAG>());
+                issue(at);
+                at = at + STAGE == (uint32_t)(ST * STAGE) ? 0u : at + (uint32_t)STAGE;
+            }
+            rest(rest, std::integral_constant<int, ST - 1 - LAG>());
+        } else {
+            rest(rest, std::integral_constant<int, ST - 2>());
+        }
+        return;
+    }
 
     // ---- fragments: lane reads row frow of a 32-row block, chunk 2s + hf of k-step s, i.e. position (hf ^ fx) ^ 2s ----
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int64_t wrow0 = m0 + wm * WM;
+    const int wcol0 = n0 + wn * WN;
+    float add[16];
+    floatx4 adds[TM][8];
+    constexpr bool LATE = BM > 128;  // (three wavefronts per SIMD: no registers to hold them under the main loop)
+    // (on their way before the operands)
+    if constexpr (STAGED && !LATE) {
+#pragma unroll
+        for (int i = 0; i < TM; i++) staged_addends<KIND>(adds[i], wrow0 + i * 32, wcol0, M, N, epi, lane);
+    } else if (ONE) direct_addends<KIND>(add, wrow0, wcol0, M, N, epi, lane);
     const int frow = lane % 32, hf = lane / 32, fx = (frow >> 1) & 7;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
-    const uint32_t a_lane = lds0 + (uint32_t)((wm * WT + frow) * 8 + (hf ^ fx)) * 16;
-    const uint32_t w_lane = lds0 + (uint32_t)((BM + wn * WT + frow) * 8 + (hf ^ fx)) * 16;
-    bf16x8 af[4][T], wf[4][T];
-    auto read = [&](uint32_t at, int s) {
-        const uint32_t pa = (a_lane ^ (uint32_t)(s << 5)) + at, pw = (w_lane ^ (uint32_t)(s << 5)) + at;
-        asm volatile("ds_read_b128 %0, %1" : "=v"(af[s][0]) : "v"(pa));
-        if (T > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(af[s][T - 1]) : "v"(pa));
-        asm volatile("ds_read_b128 %0, %1" : "=v"(wf[s][0]) : "v"(pw));
-        if (T > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(wf[s][T - 1]) : "v"(pw));
-    };
-    auto wait_frags = [&](int s, int steps) {  // fragments of step s are there, those of `steps` later steps may still be on the way
-#define WF_(n) \
-    if constexpr (T == 2) asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(af[s][0]), "+v"(af[s][T - 1]), "+v"(wf[s][0]), "+v"(wf[s][T - 1]) : "n"((n) * 2 * T)); \
-    else asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(af[s][0]), "+v"(wf[s][0]) : "n"((n) * 2 * T))
-        if (steps == 0) { WF_(0); } else if (steps == 2) { WF_(2); } else { WF_(3); }
-#undef WF_
-    };
-    floatx16 acc[T][T];
+    const uint32_t a_lane = lds0 + (uint32_t)((wm * WM + frow) * 8 + (hf ^ fx)) * 16;
+    const uint32_t w_lane = lds0 + (uint32_t)((BM + wn * WN + frow) * 8 + (hf ^ fx)) * 16;
+    floatx16 acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < T; i++)
+    for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int j = 0; j < T; j++)
+        for (int j = 0; j < TN; j++)
 #pragma unroll
             for (int v = 0; v < 16; v++) acc[i][j][v] = 0.0f;
-    auto mma1 = [&](int s, int i, int j) {
-        acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0)
-                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s][i], wf[s][j], acc[i][j], 0, 0, 0);
-    };
-    auto mma = [&](int s) {
-#pragma unroll
-        for (int i = 0; i < T; i++)
-#pragma unroll
-            for (int j = 0; j < T; j++) mma1(s, i, j);
-    };
-
-#define SB __builtin_amdgcn_sched_barrier(0)
-    float add[16];
-    floatx4 adds[T][8];
-    // (on their way before the operands)
-    if constexpr (STAGED) staged_addends<KIND, T>(adds, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
-    else if (T == 1) direct_addends<KIND>(add, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
-    const int first = KT < ST ? KT : ST;
-    for (int t = 0; t < first; t++) issue((uint32_t)(t * STAGE));
-    if (KT < ST) wait_tiles(std::integral_constant<int, 0>());
-    else wait_tiles(std::integral_constant<int, ST - 1>());
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    read(0, 0);
-    read(0, 1);
     uint32_t at = 0;
-    // One k-tile.  ahead: k-tiles that may be in flight beyond the next one (-1: this is the last); refill: k-tile kt + ST goes into its slot.
-    // Everything the loop would branch on is known at compile time: in a product that is one latency chain the scalar
-    // branches of a wait by count cost as much as the MFMAs (0.16 us per k-tile without any memory traffic, now 0.13).
-    auto step = [&](auto ahead, auto refill) {
-        SB; read(at, 2); read(at, 3);
-        wait_frags(0, 3); SB; mma(0); SB;
-        wait_frags(1, 2); SB; mma(1); SB;
-        wait_frags(2, 0); wait_frags(3, 0); SB;
-        if constexpr (ahead.value >= 0) {
-            wait_tiles(ahead);             // this wavefront's share of the next k-tile has landed
-            __builtin_amdgcn_s_barrier();  // everybody's has, and everybody has read this one
-            asm volatile("" ::: "memory");
-            const uint32_t next = at + STAGE == (uint32_t)(ST * STAGE) ? 0u : at + (uint32_t)STAGE;
-            if constexpr (refill.value) issue(at);
-            SB; read(next, 0); read(next, 1); SB;
-            at = next;
+    auto advance = [&]() { at = at + STAGE == (uint32_t)(ST * STAGE) ? 0u : at + (uint32_t)STAGE; };
+#define SB __builtin_amdgcn_sched_barrier(0)
+    if constexpr (ONE) {
+        // The k-tile is one chain of four MFMAs (144 cycles), shorter than an LDS read takes: the fragments of a k-tile are read under the
+        // MFMAs of the one before the last.
+        bf16x8 af[2][4], wf[2][4];
+        auto read = [&](auto p) {  // the next k-tile's fragments into set p
+            bar();
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                asm volatile("ds_read_b128 %0, %1" : "=v"(af[p.value][s]) : "v"((a_lane ^ (uint32_t)(s << 5)) + at));
+                asm volatile("ds_read_b128 %0, %1" : "=v"(wf[p.value][s]) : "v"((w_lane ^ (uint32_t)(s << 5)) + at));
+            }
+            advance();
+        };
+        auto mma = [&](auto p, auto behind) {  // behind: reads issued after set p's
+            bf16x8(&a)[4] = af[p.value], (&w)[4] = wf[p.value];
+            SB;
+            asm volatile("s_waitcnt lgkmcnt(%8)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : "n"(behind.value));
+            SB;
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+                acc[0][0] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s], a[s], acc[0][0], 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], w[s], acc[0][0], 0, 0, 0);
+            SB;
+        };
+        constexpr std::integral_constant<int, 0> c0{};
+        constexpr std::integral_constant<int, 1> c1{};
+        constexpr std::integral_constant<int, 8> c8{};
+        read(c0);
+        int kt = 1;
+        for (; kt + 1 < KT; kt += 2) {
+            read(c1);
+            mma(c0, c8);
+            read(c0);
+            mma(c1, c8);
         }
-        mma(2); mma(3);
-    };
-    for (int kt = ST; kt < KT; kt++) step(std::integral_constant<int, ST - 2>(), std::true_type());
-    if constexpr (ST >= 4)
-        if (KT >= 4) step(std::integral_constant<int, 2>(), std::false_type());
-    if constexpr (ST >= 3)
-        if (KT >= 3) step(std::integral_constant<int, 1>(), std::false_type());
-    if (KT >= 2) step(std::integral_constant<int, 0>(), std::false_type());
-    step(std::integral_constant<int, -1>(), std::false_type());
+        if (kt < KT) {
+            read(c1);
+            mma(c0, c8);
+            mma(c1, c0);
+        } else {
+            mma(c0, c0);
+        }
+    } else {
+        // One barrier per k-tile, in its middle: the fragments of k-steps 2 and 3 have been read by then, so the slot is free, and the
+        // first fragments of the next k-tile are read under the MFMAs of steps 2 and 3.
+        bf16x8 af[4][TM], wf[4][TN];
+        constexpr int R = TM + TN;  // reads of a k-step
+        auto read = [&](int s) {
+            const uint32_t pa = (a_lane ^ (uint32_t)(s << 5)) + at, pw = (w_lane ^ (uint32_t)(s << 5)) + at;
+            asm volatile("ds_read_b128 %0, %1" : "=v"(af[s][0]) : "v"(pa));
+            if constexpr (TM > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(af[s][TM > 1 ? 1 : 0]) : "v"(pa));
+            if constexpr (TM > 2) asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(af[s][TM > 2 ? 2 : 0]) : "v"(pa));
+            if constexpr (TM > 2) asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(af[s][TM > 2 ? 3 : 0]) : "v"(pa));
+            asm volatile("ds_read_b128 %0, %1" : "=v"(wf[s][0]) : "v"(pw));
+            if constexpr (TN > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(wf[s][TN - 1]) : "v"(pw));
+        };
+        auto wait = [&](int s, auto n) {  // the fragments of step s are there, the newest n reads may still be on the way
+            static_assert((TM == 2 || TM == 4) && TN == 2, "wave tiles");
+            bf16x8(&fa)[TM] = af[s], (&fw)[TN] = wf[s];
+            if constexpr (TM == 2) asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(fa[0]), "+v"(fa[1]), "+v"(fw[0]), "+v"(fw[1]) : "n"(n.value));
+            else asm volatile("s_waitcnt lgkmcnt(%6)" : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[TM - 2]), "+v"(fa[TM - 1]), "+v"(fw[0]), "+v"(fw[1]) : "n"(n.value));
+        };
+        auto mma = [&](int s) {
+#pragma unroll
+            for (int i = 0; i < TM; i++)
+#pragma unroll
+                for (int j = 0; j < TN; j++)
+                    acc[i][j] = SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s][j], af[s][i], acc[i][j], 0, 0, 0)
+                                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[s][i], wf[s][j], acc[i][j], 0, 0, 0);
+        };
+        constexpr std::integral_constant<int, 0> c0{};
+        constexpr std::integral_constant<int, 2 * R> c2{};
+        constexpr std::integral_constant<int, (3 * R < 16 ? 3 * R : 15)> c3{};
+        bar();
+        read(0);
+        read(1);
+        for (int kt = 0; kt < KT; kt++) {
+            SB; read(2); read(3);
+            wait(0, c3); SB; mma(0); SB;
+            wait(1, c2); SB; mma(1); SB;
+            wait(2, c0); wait(3, c0); SB;
+            if (kt + 1 < KT) {
+                bar();
+                advance();
+                SB; read(0); read(1); SB;
+            }
+            mma(2); mma(3);
+        }
+    }
 #undef SB
     if constexpr (STAGED) {
-        __builtin_amdgcn_s_barrier();  // every wavefront has read its last fragments: LDS becomes the staging area
-        asm volatile("" ::: "memory");
-        staged_epilogue<KIND, T>(acc, adds, (char *)smem + wave * 8192, m0 + wm * WT, n0 + wn * WT, M, N, epi, lane);
+        bar();  // every wavefront has read its last fragments: LDS becomes the staging area
+        staged_epilogue<KIND, TM, LATE>(acc, adds, (char *)smem + wave * 8192, wrow0, wcol0, M, N, epi, lane);
     } else {
 #pragma unroll
-        for (int i = 0; i < T; i++)
+        for (int i = 0; i < TM; i++)
 #pragma unroll
-            for (int j = 0; j < T; j++) {
-                if (T > 1) direct_addends<KIND>(add, m0 + wm * WT + i * 32, n0 + wn * WT + j * 32, M, N, epi, lane);
-                direct_epilogue<KIND>(acc[i][j], add, m0 + wm * WT + i * 32, n0 + wn * WT + j * 32, M, N, epi, lane);
+            for (int j = 0; j < TN; j++) {
+                if (!ONE) direct_addends<KIND>(add, wrow0 + i * 32, wcol0 + j * 32, M, N, epi, lane);
+                direct_epilogue<KIND>(acc[i][j], add, wrow0 + i * 32, wcol0 + j * 32, M, N, epi, lane);
             }
     }
 }
 
-template <int BM, int BN, int WT, int ST, int KIND, bool STAGED, bool BATCHED = false>
+template <int BM, int BN, int WM, int WN, int NL, int ST, int KIND, bool STAGED, bool BATCHED = false>
 static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi,
                             hipStream_t st, int batch = 1, int64_t batch_a = 0, int64_t batch_w = 0, int64_t batch_c = 0) {
-    constexpr int NT = (BM / WT) * (BN / WT) * 64;
+    constexpr int NT = ((BM / WM) * (BN / WN) + NL) * 64;
     constexpr size_t smem = (size_t)ST * (BM + BN) * 128;
-    auto kern = gemm_bf16_tile<BM, BN, WT, ST, KIND, STAGED, BATCHED>;
+    auto kern = gemm_bf16_tile<BM, BN, WM, WN, NL, ST, KIND, STAGED, BATCHED>;
     static bool attr_done = false;  // one attribute call per instantiation is enough (value never changes)
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return GR4AD_EHIP;
@@ -1346,61 +1452,74 @@ static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t l
     return GR4AD_OK;
 }
 
-template <int BM, int BN, int WT, int ST, bool STAGED>
+template <int BM, int BN, int WM, int WN, int NL, int ST, bool STAGED>
 static int launch_tile_cfg(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
                            hipStream_t st, int batch, int64_t ba, int64_t bw, int64_t bc) {
-#define KIND_(k) case k: return launch_tile_kind<BM, BN, WT, ST, k, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
+#define KIND_(k) case k: return launch_tile_kind<BM, BN, WM, WN, NL, ST, k, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
     if (batch > 1) {
-        if (kind == EPI_STORE) return launch_tile_kind<BM, BN, WT, ST, EPI_STORE, STAGED, true>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
-        if (kind == EPI_F32) return launch_tile_kind<BM, BN, WT, ST, EPI_F32, STAGED, true>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+        if (kind == EPI_STORE) return launch_tile_kind<BM, BN, WM, WN, NL, ST, EPI_STORE, STAGED, true>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
+        if (kind == EPI_F32) return launch_tile_kind<BM, BN, WM, WN, NL, ST, EPI_F32, STAGED, true>(A, lda, W, ldw, M, N, K, epi, st, batch, ba, bw, bc);
         return GR4AD_EUNSUPPORTED;
     }
     switch (kind) {
         KIND_(EPI_STORE) KIND_(EPI_SILU_DIV) KIND_(EPI_F32) KIND_(EPI_F32_RESID) KIND_(EPI_F32_TABLE)
-        case EPI_SILU: if constexpr (STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_SILU, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
+        case EPI_SILU: if constexpr (STAGED) return launch_tile_kind<BM, BN, WM, WN, NL, ST, EPI_SILU, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
             return GR4AD_EUNSUPPORTED;
-        case EPI_VT: if constexpr (!STAGED) return launch_tile_kind<BM, BN, WT, ST, EPI_VT, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
+        case EPI_VT: if constexpr (!STAGED) return launch_tile_kind<BM, BN, WM, WN, NL, ST, EPI_VT, STAGED>(A, lda, W, ldw, M, N, K, epi, st);
             return GR4AD_EUNSUPPORTED;
     }
 #undef KIND_
     return GR4AD_EUNSUPPORTED;
 }
 
-// Which kernel runs a product, by an estimate of its time in microseconds (all give the same bits).  Measured on MI355X, 1 <= M <= 16384,
-// 512 <= N <= 8192, 512 <= K <= 4096, per k-tile of 64: a 64x64 tile takes 0.19 us alone on a compute unit (the latency of its
-// LDS reads, MFMA chain and barrier) and as much each when several share one; 128x128 tiles 0.50 us alone, 0.585 us each in
-// pairs; a wave of 256x256 tiles between 1.15 us (few of them) and 1.9 us (every unit busy: the clock falls); plus a fixed part for
-// epilogue and first loads.  Before (128x128 tiles below 8192 rows, register-staged), M = 512, K = 1024: N = 1024 17 us, now 6.2;
-// N = 4096 20 us, now 9.5.
-enum { RUN_TILE64 = 0, RUN_TILE128, RUN_RING };
-static int pick_kernel(int64_t M, int N, int K, int batch, bool tile64, bool tile128, bool ring) {
+// Which kernel runs a product, by an estimate of its time in microseconds (all give the same bits).  Tiles of 32x32, 32x64 and 64x64 while
+// each fits a compute unit of its own (at these sizes the time is the k-loop of one tile; the smallest tiles have the shortest); beyond that the
+// least of the estimates, measured on MI355X for 1 <= M <= 8192, 512 <= N <= 4096, 512 <= K <= 4096 (kt: k-tiles of 64, n: tiles per compute unit):
+// 64x64 0.18 us per k-tile and tile, 128x128 0.53, 256x128 1.08, a wave of 256x256 tiles on the persistent kernel between 1.15 (few of them) and 1.9 (every
+// unit busy: the clock falls), plus what a tile costs beside its k-loop, which is more where the epilogue reads addends.
+// Where the lines lie (us, this kernel against the next best): 1024 x 512 x 512 32x64 4.2, 32x32 4.4; 256 x 3072 x 1024 64x64 6.0, 128x128 9.7; 2048 x 1024 x 4096
+// 64x64 25, 128x128 30; 4096 x 1024 x 1024 128x128 12, 64x64 15; 8192 x 1024 x 1024 with a residual 256x128 27, 128x128 31, 256x256 32; 4096 x 3072 x 1024
+// 256x256 26, 128x128 32.
+enum { RUN_TILE32 = 0, RUN_TILE32X64, RUN_TILE64, RUN_TILE64_PAIRED, RUN_TILE128, RUN_TILE256X128, RUN_RING };
+static int pick_kernel(int64_t M, int N, int K, int kind, int batch, bool tile64, bool tile128, bool tile256, bool ring) {
     const float kt = (float)(K / 64);
-    auto rounds = [&](int tile) { return (float)ceil_div64(ceil_div64(M, tile) * ceil_div64(N, tile) * batch, 256); };
-    const float r64 = rounds(64), r128 = rounds(128);
-    const float t64 = r64 * (0.4f + 0.19f * kt);
-    const float t128 = r128 * 1.1f + kt * (r128 > 1.0f ? 0.585f * r128 : 0.5f);
-    const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256) * batch, full = tiles / 256;
-    const float rest = (float)(tiles % 256) / 256.0f;
-    const float tr = (float)(full + (rest > 0.0f)) * 1.3f + kt * (1.9f * (float)full + (rest > 0.0f ? 1.15f + 0.72f * rest * rest : 0.0f));
-    if (ring && (!tile128 || tr <= t128) && (!tile64 || tr <= t64)) return RUN_RING;
-    return tile128 && (!tile64 || t128 < t64) ? RUN_TILE128 : RUN_TILE64;
+    auto tiles = [&](int bm, int bn) { return ceil_div64(M, bm) * ceil_div64(N, bn) * batch; };
+    if (tile64) {
+        if (tiles(32, 32) <= 256) return RUN_TILE32;
+        if (tiles(32, 64) <= 256) return RUN_TILE32X64;
+        if (tiles(64, 64) <= 256) return K > 512 ? RUN_TILE64 : RUN_TILE64_PAIRED;
+    }
+    const float adds = kind == EPI_F32_RESID || kind == EPI_F32_TABLE ? 1.0f : 0.0f;
+    auto rounds = [&](int bm, int bn) { return (float)ceil_div64(tiles(bm, bn), 256); };
+    float best = 1e30f;
+    int run = RUN_TILE128;
+    auto offer = [&](bool ok, int what, float t) {
+        if (ok && t < best) { best = t; run = what; }
+    };
+    offer(tile64, RUN_TILE64_PAIRED, 2.5f + rounds(64, 64) * (0.3f + 0.4f * adds + 0.18f * kt));
+    offer(tile128, RUN_TILE128, 2.0f + rounds(128, 128) * (1.2f + 3.5f * adds + 0.53f * kt));
+    offer(tile256 && adds, RUN_TILE256X128, 2.5f + rounds(256, 128) * (6.7f + 1.08f * kt));
+    const int64_t t256 = tiles(256, 256), full = t256 / 256;
+    const float rest = (float)(t256 % 256) / 256.0f;
+    offer(ring, RUN_RING, (float)(full + (rest > 0.0f)) * 1.3f + adds * (14.0f * (float)full + (rest > 0.0f ? 4.0f + 9.0f * rest : 0.0f)) +
+                          kt * (1.9f * (float)full + (rest > 0.0f ? 1.15f + 0.72f * rest * rest : 0.0f)));
+    return run;
 }
 
 static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
                        hipStream_t st, int batch = 1, int64_t ba = 0, int64_t bw = 0, int64_t bc = 0) {
-    if (run == RUN_TILE64) {
-        // at most one 32x64 tile per compute unit: the smaller tiles (0.18 us per k-tile); at most one 64x64 tile: four k-tiles in LDS; else
-        // three, so that three workgroups fit a unit
-        const int64_t cols = ceil_div64(N, 64) * batch;
-        if (ceil_div64(M, 32) * cols <= 256) return launch_tile_cfg<32, 64, 32, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-        if (ceil_div64(M, 64) * cols <= 256) return launch_tile_cfg<64, 64, 32, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-        return launch_tile_cfg<64, 64, 32, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    switch (run) {
+        // one workgroup per compute unit: eight k-tiles in LDS; 64x64 tiles in pairs (or of few k-tiles, which wait for fewer requests first): four
+        case RUN_TILE32: return launch_tile_cfg<32, 32, 32, 32, 2, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        case RUN_TILE32X64: return launch_tile_cfg<32, 64, 32, 32, 2, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        case RUN_TILE64: return launch_tile_cfg<64, 64, 32, 32, 4, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        case RUN_TILE64_PAIRED: return launch_tile_cfg<64, 64, 32, 32, 4, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        case RUN_TILE256X128:
+            if (kind == EPI_F32_RESID) return launch_tile_kind<256, 128, 64, 64, 4, 3, EPI_F32_RESID, true>(A, lda, W, ldw, M, N, K, epi, st);
+            return launch_tile_kind<256, 128, 64, 64, 4, 3, EPI_F32_TABLE, true>(A, lda, W, ldw, M, N, K, epi, st);
     }
-    if (kind == EPI_VT || !tile_staged_ok(kind, N, epi)) return launch_tile_cfg<128, 128, 64, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-    // one tile per compute unit: three k-tiles in flight; more: two workgroups share a unit (64 KB of LDS each)
-    if (ceil_div64(M, 128) * ceil_div64(N, 128) * batch <= 256)
-        return launch_tile_cfg<128, 128, 64, 3, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-    return launch_tile_cfg<128, 128, 64, 2, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    if (kind == EPI_VT || !tile_staged_ok(kind, N, epi)) return launch_tile_cfg<128, 128, 64, 64, 4, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    return launch_tile_cfg<128, 128, 64, 64, 4, 3, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
 }
 
 // Batched product on the tile kernels: for i < batch, C_i[M,N] = A_i[M,K] * W_i[N,K]^T with A_i = A + i*batch_a elements etc.
@@ -1421,7 +1540,7 @@ int launch_gemm_batched(const void *A, int64_t lda, int64_t batch_a, const void 
     e.len_bounds = batch_len ? len_bounds : 0;
     const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
     const int kind = out_f32 ? EPI_F32 : EPI_STORE;
-    return launch_tile(pick_kernel(M, N, K, batch, true, true, false), a, lda, w, ldw, M, N, K, kind, e, st, batch, batch_a, batch_w, batch_c);
+    return launch_tile(pick_kernel(M, N, K, kind, batch, true, true, false, false), a, lda, w, ldw, M, N, K, kind, e, st, batch, batch_a, batch_w, batch_c);
 }
 
 // Transposed-per-request product for the context values: out[(b*N + n) * ld_out + s] = sum_k A[b*S + s][k] * W[n][k] for
@@ -1446,7 +1565,7 @@ int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64
     e.vt_S = S;
     e.skip_len = ctx_len;  // key tiles beyond ceil(len / 64) * 64 are never read by the attention kernel
     e.skip_S = S;
-    const int run = pick_kernel(M, N, K, 1, true, true, ring_vt_ok(M, N, K, S, lda, ldw));
+    const int run = pick_kernel(M, N, K, EPI_VT, 1, true, true, false, ring_vt_ok(M, N, K, S, lda, ldw));
     if (run == RUN_RING) return launch_ring((const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
     return launch_tile(run, (const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
 }
@@ -1531,11 +1650,12 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
     if (mfma_ok(dtype, A, lda, W, ldw, K, kind)) {
         const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
         if (gemm_large_class(dtype, A, lda, W, ldw, M, N, K, epi)) {
-            const int run = pick_kernel(M, N, K, 1, false, tile_staged_ok(kind, N, epi), true);
+            const bool staged = tile_staged_ok(kind, N, epi);
+            const int run = pick_kernel(M, N, K, kind, 1, false, staged, staged, true);
             return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, kind, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, kind, epi, st);
         }
         const int k = kind == EPI_SILU ? EPI_SILU_DIV : kind;
-        const int run = pick_kernel(M, N, K, 1, true, true, N >= 256 && ring_ok(k, N, K, lda, ldw, epi));
+        const int run = pick_kernel(M, N, K, k, 1, true, true, tile_staged_ok(k, N, epi), N >= 256 && ring_ok(k, N, K, lda, ldw, epi));
         return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, k, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, k, epi, st);
     }
     if (dtype == GR4AD_F32 && f32_mfma_ok(A, lda, W, ldw, K))

@@ -61,3 +61,19 @@ def test_f32_requests_do_not_depend_on_their_batch(d, H):
         one = dec.decode_batch(ctx[b:b + 1].contiguous(), cl[b:b + 1].contiguous(), w.beam)
         assert torch.equal(one[0][0], sid[b]) and torch.equal(one[1][0], lp[b])
     dec.close()
+
+
+@pytest.mark.parametrize("N,K", [
+    (512, 64), (520, 448), (512, 512), (1032, 576),  # one k-tile; one less than, as many as and one more than the deepest ring; ragged columns
+    (3072, 1088), (264, 4096),
+])
+def test_bf16_rows_do_not_depend_on_the_row_count(N, K):
+    """Below 8192 rows every kernel that runs a product adds in one order: rows alone, on each of the tiles, and among many give the same bits."""
+    g = torch.Generator().manual_seed(N + K)
+    a, w = torch.randn(8000, K, generator=g).bfloat16().cuda(), (torch.randn(N, K, generator=g) / K**0.5).bfloat16().cuda()
+    many, many32 = binding.op_linear(a, w), binding.op_linear(a, w, out_f32=True)
+    for first, rows in ((0, 1), (37, 33), (100, 97), (1000, 300), (2000, 700), (3001, 1500), (4000, 4000)):
+        some = a[first:first + rows].contiguous()
+        assert torch.equal(binding.op_linear(some, w), many[first:first + rows])
+        assert torch.equal(binding.op_linear(some, w, out_f32=True), many32[first:first + rows])
+    np.testing.assert_allclose(many32[:64].double().cpu().numpy(), (a[:64].double() @ w.double().t()).cpu().numpy(), atol=2e-5, rtol=1e-5)
