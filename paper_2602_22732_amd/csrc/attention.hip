@@ -143,10 +143,10 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const bf16 *__restrict
 // first product with index bits 2 and 3 swapped, which makes the 8 keys a lane holds for
 // one MFMA k-step consecutive (one 16-byte chunk of a V^T row).
 template <int DH, int QT, int NW, int SUBS>
-__global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void cross_attn_flash_bf16(const bf16 *__restrict__ q, int64_t ldq, const bf16 *__restrict__ kv,
-                                                                 const bf16 *__restrict__ vt, const int32_t *__restrict__ ctx_len,
-                                                                 bf16 *__restrict__ out, int64_t ldo, int n, int S, int Spad, int d,
-                                                                 int H, float scale_log2e, int beam_blocks, int64_t total_blocks,
+__global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void cross_attn_flash_bf16(const bf16 *__restrict__ q, int64_t ldq, const bf16 *__restrict__ kv, int64_t ldk,
+                                                                 const bf16 *__restrict__ vt, int64_t vt_req, const int32_t *__restrict__ ctx_len,
+                                                                 bf16 *__restrict__ out, int64_t ldo, int n, int S, int Spad, int H,
+                                                                 float scale_log2e, int beam_blocks, int64_t total_blocks,
                                                                  const int32_t *__restrict__ q_first, const int32_t *__restrict__ q_count) {
     constexpr int KCH = DH / 8;                   // 16-byte chunks per K row
     constexpr int K_CHUNKS = 64 * KCH, V_CHUNKS = DH * 8;
@@ -203,8 +203,8 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
     // The macro-tiles are requested in ascending order, so each of a wavefront's NL loads keeps a running per-lane source
     // address that advances by a fixed step per macro-tile; only a tile that reaches past row S-1 of the keys (the last one,
     // when S is not a multiple of 64) computes clamped addresses.
-    const bf16 *kbase = kv + (int64_t)b * S * 2 * d + h * DH;
-    const bf16 *vbase = vt + ((int64_t)b * d + h * DH) * Spad;
+    const bf16 *kbase = kv + (int64_t)b * S * ldk + h * DH;
+    const bf16 *vbase = vt + (int64_t)b * vt_req + (int64_t)h * DH * Spad;
     constexpr int KI = K_CHUNKS / 64, VI = V_CHUNKS / 64, PER_TILE = KI + VI, NL = (SUBS * PER_TILE + NW - 1) / NW;
     const bf16 *lsrc[NL];
 #pragma unroll
@@ -214,14 +214,14 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
         if (w < KI) {
             const int id = w * 64 + lane, r = id / KCH, pslot = id % KCH;
             const int c = pslot ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1));
-            lsrc[i] = kbase + (int64_t)(sub * 64 + r) * 2 * d + c * 8;
+            lsrc[i] = kbase + (int64_t)(sub * 64 + r) * ldk + c * 8;
         } else {
             const int id = (w - KI) * 64 + lane, r = id / 8, pslot = id % 8;
             const int c = pslot ^ ((r >> 1) & 7);
             lsrc[i] = vbase + (int64_t)r * Spad + sub * 64 + c * 8;
         }
     }
-    const int64_t kstep = (int64_t)SUBS * 64 * 2 * d, vstep = SUBS * 64;  // elements per macro-tile
+    const int64_t kstep = (int64_t)SUBS * 64 * ldk, vstep = SUBS * 64;  // elements per macro-tile
     auto issue_macro = [&](int macro, int buf) {  // macro = 0, 1, 2, ... in this order
 #pragma unroll
         for (int i = 0; i < NL; i++) {
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
                     const int c = pslot ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1));
                     int key = tile * 64 + r;
                     if (key > S - 1) key = S - 1;
-                    src = kbase + (int64_t)key * 2 * d + c * 8;
+                    src = kbase + (int64_t)key * ldk + c * 8;
                 }
                 __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
                                                  (void __attribute__((address_space(3))) *)dst, 16, 0, 0);
@@ -1066,7 +1066,7 @@ int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, c
 }
 
 template <int DH, int QT, int NW, int SUBS>
-static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, const bf16 *vt, const int32_t *ctx_len, bf16 *out, int64_t ldo, int B,
+static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, int64_t ldk, const bf16 *vt, int64_t vt_req, const int32_t *ctx_len, bf16 *out, int64_t ldo, int B,
                         int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
     auto kern = cross_attn_flash_bf16<DH, QT, NW, SUBS>;
     constexpr int LDS_BYTES = 2 * SUBS * (64 * (DH / 8) + DH * 8) * 16;
@@ -1083,18 +1083,18 @@ static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, const bf16 *
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
     // flops on the padded length S; bytes: queries and outputs once, keys and values once per request (beam-shared)
     ProfScope ps(KC_XATTN_FLASH, st, 4.0 * B * (double)n * S * d, (2.0 * B * n * d + 2.0 * B * (double)S * d) * sizeof(bf16));
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS_BYTES, st, q, ldq, kv, vt, ctx_len, out, ldo, n, S, (S + 63) / 64 * 64, d, H, scale_log2e,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS_BYTES, st, q, ldq, kv, ldk, vt, vt_req, ctx_len, out, ldo, n, S, (S + 63) / 64 * 64, H, scale_log2e,
                        beam_blocks, total_blocks, dr ? dr->first : nullptr, dr ? dr->count : nullptr);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
 
-int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, const void *vt, const int32_t *ctx_len, void *out,
-                           int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
+int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, int64_t ldk, const void *vt, int64_t vt_req, const int32_t *ctx_len,
+                           void *out, int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
     if (B <= 0 || n <= 0 || S <= 0 || d <= 0 || H <= 0 || d % H) return GR4AD_EINVAL;
     const int dh = d / H;
     if (dh > 128) return GR4AD_EUNSUPPORTED;
-    if (vt && cross_attention_workspace_bytes(dtype, B, S, d, H) && ldq % 8 == 0 && ldo % 4 == 0 && ((uintptr_t)q % 16) == 0 &&
+    if (vt && cross_attention_workspace_bytes(dtype, B, S, d, H) && ldq % 8 == 0 && ldk % 8 == 0 && ldo % 4 == 0 && ((uintptr_t)q % 16) == 0 &&
         ((uintptr_t)out % 8) == 0) {
         const bf16 *qq = (const bf16 *)q, *kk = (const bf16 *)kv, *vv = (const bf16 *)vt;
         bf16 *oo = (bf16 *)out;
@@ -1104,13 +1104,13 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
             // SIMD: the kernel waits on LDS, barrier and dependent-MFMA latencies, and occupancy is what hides them.  Blocks
             // of 8 wavefronts (256 beams) share each staged tile among twice as many beams and are 3-7 % faster than blocks
             // of 4; they are used where they waste no more beam slots.
-            if (n <= 128) return launch_flash<64, 1, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            if ((n + 255) / 256 * 256 == (n + 127) / 128 * 128) return launch_flash<64, 1, 8, 1>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            return launch_flash<64, 1, 4, 1>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if (n <= 128) return launch_flash<64, 1, 4, 2>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if ((n + 255) / 256 * 256 == (n + 127) / 128 * 128) return launch_flash<64, 1, 8, 1>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            return launch_flash<64, 1, 4, 1>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
         } else {
-            if (n <= 128) return launch_flash<32, 1, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            if (n <= 256) return launch_flash<32, 2, 4, 2>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            return launch_flash<32, 2, 8, 4>(qq, ldq, kk, vv, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if (n <= 128) return launch_flash<32, 1, 4, 2>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if (n <= 256) return launch_flash<32, 2, 4, 2>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            return launch_flash<32, 2, 8, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
         }
     }
     if (dr) return GR4AD_EUNSUPPORTED;

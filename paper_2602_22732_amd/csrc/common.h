@@ -90,7 +90,7 @@ struct GemmEpilogue {
                          // IEEE half precision, C is a half array (row stride ldc elements): the classifier's logits for the selection
     int act;             // ACT_*
     const int32_t *ctx_len;  // launch_gemm_vt only: valid rows per request (NULL = all)
-    int vt_S;                // launch_gemm_vt only: rows per request
+    int vt_S, vt_rows;       // launch_gemm_vt only (set by it): rows of C per request, a multiple of 64, and those of A
     int len_bounds;            // launch_gemm_batched only, 1: batch_len bounds the columns of C that are needed, 2: it bounds K
     const int32_t *batch_len;  // launch_gemm_batched only: valid length per batch (NULL = none)
     // RMSNorm folded into the projections around it (large products only; launch_gemm fails if it cannot honour them):
@@ -180,10 +180,11 @@ int launch_distinct_rows(const int32_t *tok, int B, int n, const DistinctRows &d
 
 // ---- attention ---------------------------------------------------------------
 // beam-shared cross-attention; q/out row stride ldq/ldo elements, rows (b*n+i)
-// vt: per-(request, head) transposed values built by launch_cross_attention_prepare (NULL: plain kernel on kv alone)
+// vt: per-(request, head) transposed values built by launch_cross_attention_prepare or launch_gemm_vt (NULL: plain kernel on kv alone, [B, S, 2d]),
+// vt_req elements from one request to the next; with vt, kv holds keys only, rows of ldk elements
 // dr: the rows of request b are the dr->count[b] (<= n) rows from dr->first[b] on (matrix-core kernel only)
-int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, const void *vt, const int32_t *ctx_len, void *out,
-                           int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr = nullptr);
+int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, int64_t ldk, const void *vt, int64_t vt_req, const int32_t *ctx_len,
+                           void *out, int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr = nullptr);
 // bytes of the transposed-value buffer the MFMA kernel needs for kv [B,S,2d] (0: the shape runs on the plain kernel)
 size_t cross_attention_workspace_bytes(gr4ad_dtype dtype, int B, int S, int d, int H);
 int launch_cross_attention_prepare(gr4ad_dtype dtype, const void *kv, const int32_t *ctx_len, void *vt, int B, int S, int d, int H,

@@ -14,7 +14,7 @@
 namespace {
 
 struct LayerPacked {
-    void *ln_x, *wq_x, *wkv_x, *wo_x;   // wkv_x [2d,d]: rows of W_k then W_v (context projection)
+    void *ln_x, *wq_x, *wkv_x, *wo_x;   // wkv_x [2d,d]: rows of W_k then W_v (context projection; NULL where wk_ctx / wv_ctx hold them)
     void *ln_s, *wqkv_s, *wo_s;         // wqkv_s [3d,d]
     void *ln_f, *w1, *w2;
     void *wkT_x;  // lazy layers in absorbed form only: [H][d][dh], the key projection transposed per head
@@ -43,6 +43,9 @@ struct gr4ad_decoder {
     void *E[GR4AD_MAX_LEVELS];    // vanilla only: per-level embedding table of the previous token (one BOS row at level 1)
     void *cls[GR4AD_MAX_LEVELS];
     float *cls_bias[GR4AD_MAX_LEVELS];
+    bool flash;                   // the matrix-core attention kernel runs: keys and transposed values of the context in buffers of their own
+    void *wk_ctx[2], *wv_ctx[2];  // flash only: key and value projections of the context, stacked over the lazy layers (0; absorbed form: none) and the
+                                  // autoregressive ones (1)
     std::vector<LayerPacked> layers;
     std::vector<void *> allocs;
     int32_t *tr_parent[GR4AD_MAX_LEVELS], *tr_tok[GR4AD_MAX_LEVELS];
@@ -67,6 +70,11 @@ int fail(gr4ad_decoder *dec, int code, const char *fmt, ...) {
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Context rows of a batch (requests padded to 64 rows) up to which the projections of all lazy layers' keys and values are two products instead of two per layer.  Below it the products
+// are a few tiles per compute unit and mostly latency (64 requests of 256 rows, d = 256, two layers: 39 us as four products, 25 as two); above it they fill the
+// chip one by one, and one layer's buffers serve all.
+constexpr int64_t LAZY_TOGETHER_ROWS = 32768;
 
 // Everything decode_batch carves out of the caller's workspace.
 struct Plan {
@@ -126,12 +134,18 @@ Plan make_plan(const gr4ad_decoder *dec, int64_t B, int64_t S, const int32_t *be
     p.rows_max = B * (nmax > Tp ? nmax : Tp);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
-    p.kv_ar = take((size_t)dec->A * B * S * 2 * d * e);
+    // flash: keys [B*S, A*d] and values [B, A*d, Spad] of all autoregressive layers; else keys and values [B*S, 2d] per layer
+    p.kv_ar = take((size_t)dec->A * B * S * (dec->flash ? 1 : 2) * d * e);
     const bool lazy_kv = dec->K > 0 && !dec->absorbed;
-    p.kv_lazy = take(lazy_kv ? (size_t)B * S * 2 * d * e : 0);
     p.vt_bytes = cross_attention_workspace_bytes(dec->dtype, (int)B, (int)S, dec->d, dec->H);
+    // lazy layers: one layer's at a time, or all layers' of few context rows (a longer or larger batch's size serves a shorter or smaller one)
+    auto lazy_rows = [&](int64_t rows) {
+        const int64_t together = dec->K * (rows < LAZY_TOGETHER_ROWS ? rows : LAZY_TOGETHER_ROWS);
+        return (size_t)(rows > together ? rows : together);
+    };
+    p.kv_lazy = take(!lazy_kv ? 0 : dec->flash ? lazy_rows(B * S) * d * e : (size_t)B * S * 2 * d * e);
     p.vt_ar = take((size_t)dec->A * p.vt_bytes);
-    p.vt_lazy = take(lazy_kv ? p.vt_bytes : 0);
+    p.vt_lazy = take(lazy_kv && dec->flash ? lazy_rows(B * ((S + 63) / 64 * 64)) * d * e : 0);
     if (dec->absorbed) {  // bf16 only
         const int64_t Spad = (S + 63) / 64 * 64, RQ = Tp * dec->H;
         const bool two_pass = !context_attention_covers(dec->dtype, (int)RQ, dec->d);  // (else one kernel, no transposed copy, scores or probabilities in HBM)
@@ -307,8 +321,19 @@ int init_impl(gr4ad_decoder *dec, const gr4ad_model_desc *ds, const gr4ad_weight
         LayerPacked &p = dec->layers[l];
         if ((s = dev_clone(dec, &p.ln_x, x->ln_x, d * e))) return s;
         if ((s = dev_clone(dec, &p.wq_x, x->wq_x, d * d * e))) return s;
-        const void *kv[2] = {x->wk_x, x->wv_x};
-        if ((s = dev_stack(dec, &p.wkv_x, kv, 2, d * d * e))) return s;
+        p.wkv_x = nullptr;
+        if (dec->flash && !(dec->absorbed && l < dec->K)) {
+            const int g = l < dec->K ? 0 : 1, first = g ? dec->K : 0, count = g ? dec->A : dec->K;
+            if (l == first) {
+                if ((s = dev_alloc(dec, &dec->wk_ctx[g], count * d * d * e))) return s;
+                if ((s = dev_alloc(dec, &dec->wv_ctx[g], count * d * d * e))) return s;
+            }
+            HIP_TRY(dec, hipMemcpy((char *)dec->wk_ctx[g] + (l - first) * d * d * e, x->wk_x, d * d * e, hipMemcpyDeviceToDevice));
+            HIP_TRY(dec, hipMemcpy((char *)dec->wv_ctx[g] + (l - first) * d * d * e, x->wv_x, d * d * e, hipMemcpyDeviceToDevice));
+        } else {
+            const void *kv[2] = {x->wk_x, x->wv_x};
+            if ((s = dev_stack(dec, &p.wkv_x, kv, 2, d * d * e))) return s;
+        }
         if ((s = dev_clone(dec, &p.wo_x, x->wo_x, d * d * e))) return s;
         if ((s = dev_clone(dec, &p.ln_s, x->ln_s, d * e))) return s;
         const void *qkv[3] = {x->wq_s, x->wk_s, x->wv_s};
@@ -421,6 +446,7 @@ int gr4ad_decode_init(const gr4ad_model_desc *ds, const gr4ad_weights *w, gr4ad_
         const int dh = dec->d / dec->H;
         dec->absorbed = dec->K > 0 && dec->dtype == GR4AD_BF16 && dh % 64 == 0;
     }
+    dec->flash = cross_attention_workspace_bytes(dec->dtype, 1, 1, dec->d, dec->H) > 0;
     for (int t = 0; t < dec->T; t++) { dec->V[t] = ds->codebook[t]; dec->max_beam[t] = ds->max_beam[t]; }
     if (dec->Ve > 0) dec->V[dec->T] = dec->Ve;
     s = init_impl(dec, ds, w);
@@ -486,7 +512,15 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     char *ws = (char *)workspace;
     void *h = ws + p.h, *xn = ws + p.xn, *q = ws + p.q, *o = ws + p.o, *qkv = ws + p.qkv, *f = ws + p.f, *trunk = ws + p.trunk;
     float *logits = (float *)(ws + p.logits);
-    auto kv_ar = [&](int a) { return (void *)(ws + p.kv_ar + (size_t)a * B * S * 2 * d * e); };
+    const int64_t Spad = (S + 63) / 64 * 64;
+    // context keys (and values) of one layer: of the `G` layers whose keys share a buffer, number i
+    struct ContextKV { const void *k, *vt; int64_t ldk, vt_req; };
+    auto context_of = [&](size_t kv, size_t vt, int i, int G) {
+        ContextKV c;
+        if (dec->flash) c = {ws + kv + (size_t)i * d * e, ws + vt + (size_t)i * d * Spad * e, (int64_t)G * d, (int64_t)G * d * Spad};
+        else c = {ws + kv + (size_t)i * B * S * 2 * d * e, nullptr, 2 * d, 0};
+        return c;
+    };
     auto qkv_lvl = [&](int t, int a) { return (void *)(ws + p.qkv_lvl[t] + (size_t)(t == dec->Tp - 1 ? 0 : a) * p.qkv_lvl_layer_bytes[t]); };
 
     // The token-only part of a level (see the level loop) runs on its distinct rows: while `distinct` is set, the row counts below
@@ -569,13 +603,13 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     };
 
     // cross-attention + its residual; x is the residual stream [rows,d]; next_gain: gain of the norm that follows
-    auto cross_block = [&](const LayerPacked &lw, void *x, int64_t rows, int n, const void *kvbuf, const void *vtbuf, const DistinctRows *dr = nullptr) -> int {
+    auto cross_block = [&](const LayerPacked &lw, void *x, int64_t rows, int n, const ContextKV &c, const DistinctRows *dr = nullptr) -> int {
         int s;
         if ((s = norm(x, lw.ln_x, rows))) return s;
         if (f8) s = gemm8(rows, lw.wq_x8, lw.s_wq_x, d, d, plain_epilogue(q, d));
         else s = gemm(xn, rows, lw.wq_x, d, d, reads_norm(plain_epilogue(q, d)));
         if (s) return s;
-        if ((s = launch_cross_attention(dt, q, d, kvbuf, vtbuf, ctx_len, o, d, B, n, S, d, H, st, dr))) return s;
+        if ((s = launch_cross_attention(dt, q, d, c.k, c.ldk, c.vt, c.vt_req, ctx_len, o, d, B, n, S, d, H, st, dr))) return s;
         if (f8) {
             if ((s = quant_act(o, rows, d))) return s;
             return gemm8(rows, lw.wo_x8, lw.s_wo_x, d, d, resid_epi(x, d));
@@ -595,27 +629,27 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     };
 
     // ---- step 0: context keys/values of the autoregressive layers, once per request ----
-    auto vt_ar = [&](int a) { return p.vt_bytes ? (void *)(ws + p.vt_ar + (size_t)a * p.vt_bytes) : (void *)nullptr; };
-    void *vt_lazy = p.vt_bytes ? (void *)(ws + p.vt_lazy) : (void *)nullptr;
-    // Where the attention kernel reads the values from its transposed copy, the value projection writes that copy
-    // directly (transposed per request, zero beyond the length) and only the key half of the K/V buffer is filled.
-    auto context_kv = [&](const LayerPacked &lw, void *kvbuf, void *vtbuf) -> int {
-        const void *wv = (const char *)lw.wkv_x + (size_t)d * d * e;
-        const int64_t Spad = (S + 63) / 64 * 64;
-        if (vtbuf && gemm_vt_supported(dt, ctx, d, wv, d, (int64_t)B * S, d, d, S, vtbuf, Spad)) {
-            // (keys and values of rows past a request's length are never read: whole tiles of them are not computed)
-            GemmEpilogue ke = plain_epilogue(kvbuf, 2 * d);
-            ke.skip_len = ctx_len;
-            ke.skip_S = S;
-            int s = gemm(ctx, (int64_t)B * S, lw.wkv_x, d, d, ke);
-            if (s) return s;
-            return launch_gemm_vt(ctx, d, wv, d, (int64_t)B * S, d, d, S, ctx_len, vtbuf, Spad, st);
-        }
-        int s = gemm(ctx, (int64_t)B * S, lw.wkv_x, 2 * d, d, plain_epilogue(kvbuf, 2 * d));
+    // The matrix-core attention kernel reads the values from a transposed copy (per request, zero beyond the length), which their projection writes
+    // directly; keys and values of several layers are one product each, their weights stacked (32 requests of 512 rows, d = 512, six layers: 240 us as
+    // twelve products, now 118 as two).
+    auto context_products = [&](const void *wk, const void *wv, int G, size_t kv, size_t vt) -> int {
+        GemmEpilogue ke = plain_epilogue(ws + kv, (int64_t)G * d);
+        ke.skip_len = ctx_len;  // (keys and values of rows past a request's length are never read: whole tiles of them are not computed)
+        ke.skip_S = S;
+        const int s = gemm(ctx, (int64_t)B * S, wk, G * d, d, ke);
         if (s) return s;
-        return launch_cross_attention_prepare(dt, kvbuf, ctx_len, vtbuf, B, S, d, H, st);
+        return launch_gemm_vt(ctx, d, wv, d, (int64_t)B * S, G * d, d, S, ctx_len, ws + vt, Spad, st);
     };
-    for (int a = 0; a < A; a++) OP_TRY(dec, context_kv(dec->layers[K + a], kv_ar(a), vt_ar(a)), "context K/V projection");
+    auto context_kv = [&](const LayerPacked &lw, const ContextKV &c) {  // plain attention kernel: keys and values side by side
+        return gemm(ctx, (int64_t)B * S, lw.wkv_x, 2 * d, d, plain_epilogue((void *)c.k, 2 * d));
+    };
+    if (dec->flash) {
+        OP_TRY(dec, context_products(dec->wk_ctx[1], dec->wv_ctx[1], A, p.kv_ar, p.vt_ar), "context K/V projection");
+    } else {
+        for (int a = 0; a < A; a++) OP_TRY(dec, context_kv(dec->layers[K + a], context_of(p.kv_ar, 0, a, A)), "context K/V projection");
+    }
+    const bool lazy_together = dec->flash && !dec->absorbed && K > 0 && B * Spad <= LAZY_TOGETHER_ROWS;
+    if (lazy_together) OP_TRY(dec, context_products(dec->wk_ctx[0], dec->wv_ctx[0], K, p.kv_lazy, p.vt_lazy), "lazy context K/V projection");
 
     // Lazy layers, cross-attention in absorbed form.  With k_s = W_k x_s and v_s = W_v x_s (per head h: rows h*dh.. of W_k, W_v),
     //   q_h . k_{s,h} = (W_{k,h}^T q_h) . x_s        and        sum_s p_s v_{s,h} = W_{v,h} (sum_s p_s x_s),
@@ -625,7 +659,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     // fall on q' = W_{k,h}^T q_h and z = sum_s p_s x_s instead of on k_s and v_s.
     auto absorbed_cross_block = [&](const LayerPacked &lw, bool first) -> int {
         const int64_t rows = (int64_t)B * Tq, RQ = (int64_t)Tq * H;
-        const int dh = d / H, Spad = (S + 63) / 64 * 64;
+        const int dh = d / H;
         char *xt = ws + p.xt, *qp = ws + p.qp, *zb = ws + p.zb, *pb = ws + p.pb;
         float *sc = (float *)(ws + p.sc);
         const char *wv = (const char *)lw.wkv_x + (size_t)d * d * e;
@@ -656,13 +690,14 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
     fold = K > 0 && fold_ok((int64_t)B * Tq, 0);
     for (int l = 0; l < K; l++) {
         const LayerPacked &lw = dec->layers[l];
-        void *kvl = ws + p.kv_lazy;
         const int64_t rows = (int64_t)B * Tq;
         if (dec->absorbed) {
             OP_TRY(dec, absorbed_cross_block(lw, l == 0), "lazy cross-attention (absorbed form)");
         } else {
-            OP_TRY(dec, context_kv(lw, kvl, vt_lazy), "lazy context K/V projection");
-            OP_TRY(dec, cross_block(lw, trunk, rows, Tq, kvl, vt_lazy), "lazy cross-attention");
+            const size_t w = (size_t)l * d * d * e;
+            if (!dec->flash) OP_TRY(dec, context_kv(lw, context_of(p.kv_lazy, 0, 0, 1)), "lazy context K/V projection");
+            else if (!lazy_together) OP_TRY(dec, context_products((char *)dec->wk_ctx[0] + w, (char *)dec->wv_ctx[0] + w, 1, p.kv_lazy, p.vt_lazy), "lazy context K/V projection");
+            OP_TRY(dec, cross_block(lw, trunk, rows, Tq, lazy_together ? context_of(p.kv_lazy, p.vt_lazy, l, K) : context_of(p.kv_lazy, p.vt_lazy, 0, 1)), "lazy cross-attention");
         }
         OP_TRY(dec, norm(trunk, lw.ln_s, rows), "lazy norm");
         OP_TRY(dec, gemm(xn, rows, lw.wqkv_s, 3 * d, d, reads_norm(plain_epilogue(qkv, 3 * d))), "lazy qkv");
@@ -741,7 +776,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             const LayerPacked &lw = dec->layers[K + a];
             const bool mapped = a == 0 && any_map;
             void *x = a == 0 ? x1 : h;
-            OP_TRY(dec, cross_block(lw, x, rows, n, kv_ar(a), vt_ar(a), distinct ? &dr : nullptr), "cross-attention");
+            OP_TRY(dec, cross_block(lw, x, rows, n, context_of(p.kv_ar, p.vt_ar, a, A), distinct ? &dr : nullptr), "cross-attention");
             OP_TRY(dec, norm(x, lw.ln_s, rows), "self-attention norm");
             LevelBuffers prev;
             for (int u = 0; u < GR4AD_MAX_LEVELS; u++) {
@@ -859,7 +894,7 @@ int gr4ad_op_cross_attention(gr4ad_dtype dtype, const void *q, const void *kv, c
     if (need && (!workspace || workspace_bytes < need)) return GR4AD_EWORKSPACE;
     int s = launch_cross_attention_prepare(dtype, kv, ctx_len, workspace, B, S, d, H, (hipStream_t)hip_stream);
     if (s) return s;
-    return launch_cross_attention(dtype, q, d, kv, need ? workspace : nullptr, ctx_len, out, d, B, n, S, d, H, (hipStream_t)hip_stream);
+    return launch_cross_attention(dtype, q, d, kv, 2 * d, need ? workspace : nullptr, (int64_t)d * ((S + 63) / 64 * 64), ctx_len, out, d, B, n, S, d, H, (hipStream_t)hip_stream);
 }
 
 int gr4ad_op_context_attention(gr4ad_dtype dtype, const void *q, const void *x, const int32_t *ctx_len, void *out, int32_t B, int32_t RQ,

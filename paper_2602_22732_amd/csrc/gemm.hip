@@ -354,10 +354,19 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
     const char *baseA, *baseW, *baseAn, *baseWn;
     int maxa, maxw, maxan, maxwn;
     auto tile_sources = [&](int64_t tm0, int tn0, const char *&bA, const char *&bW, int &mA, int &mW) {
-        bA = (const char *)A + tm0 * lda2;
         bW = (const char *)W + (int64_t)tn0 * ldw2;
-        mA = (int)(M - 1 - tm0 < 255 ? M - 1 - tm0 : 255);
         mW = N - 1 - tn0 < 255 ? N - 1 - tn0 : 255;
+        if (KIND == EPI_VT) {
+            // the rows count every request's vt_rows tokens up to vt_S, a multiple of 64: a wavefront's 32 rows lie in one request, those past its
+            // last token (and past the last request) re-read it
+            const uint32_t row = (uint32_t)tm0 + wave * 32, v = row < (uint32_t)M ? row : (uint32_t)M - 1;
+            const uint32_t b = v / (uint32_t)epi.vt_S, s = v - b * (uint32_t)epi.vt_S, last = (uint32_t)epi.vt_rows - 1, at = s < last ? s : last;
+            bA = (const char *)A + ((int64_t)b * epi.vt_rows + at - wave * 32) * lda2;
+            mA = wave * 32 + (int)(last - at < 31 ? last - at : 31);
+            return;
+        }
+        bA = (const char *)A + tm0 * lda2;
+        mA = (int)(M - 1 - tm0 < 255 ? M - 1 - tm0 : 255);
     };
     tile_sources(m0, n0, baseA, baseW, maxa, maxw);
     // Without a next tile the loads that would fetch its first k-tiles re-read the current tile's instead (valid memory, into
@@ -615,8 +624,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                         for (int v = 0; v < 16; v++) acc[i][j][v] *= rinv[i];
             }
             if (KIND == EPI_VT) {
-                // C^T per request: out[(b*N + n) * ldc + s] = C[b*S + s][n] for s < len_b, 0 beyond (values of the context, transposed
-                // per head for the attention kernel's second product).  S is a multiple of 64, so the 64 rows of a pass share one request.
+                // C^T per request: out[(b*N + n) * ldc + s] = C[b*vt_S + s][n] for s < len_b, 0 beyond (values of the context, transposed
+                // per head for the attention kernel's second product).  vt_S is a multiple of 64, so the 64 rows of a pass share one request.
                 // Two passes of 64 rows: staged as 64 columns x 64 rows (128-byte lines of 8 chunks, chunk c of line r at c ^ (r & 7)).
 #pragma unroll
                 for (int pass = 0; pass < 2; pass++) {
@@ -637,10 +646,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     const int64_t t0 = wrow0 + pass * 64;  // first of the 64 rows (tokens) of this pass
                     if (t0 < M) {
-                        const int64_t b = t0 / epi.vt_S;
-                        const int s0 = (int)(t0 - b * epi.vt_S);
-                        int len = epi.ctx_len ? epi.ctx_len[b] : epi.vt_S;
-                        len = len < 1 ? 1 : (len > epi.vt_S ? epi.vt_S : len);
+                        const uint32_t b = (uint32_t)t0 / (uint32_t)epi.vt_S;
+                        const int s0 = (int)((uint32_t)t0 - b * (uint32_t)epi.vt_S);
+                        int len = epi.ctx_len ? epi.ctx_len[b] : epi.vt_rows;
+                        len = len < 1 ? 1 : (len > epi.vt_rows ? epi.vt_rows : len);
 #pragma unroll 4
                         for (int it = 0; it < 8; it++) {
                             const int r = it * 8 + lane / 8, c = lane % 8;
@@ -648,7 +657,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                             const int col = wcol0 + r, s = s0 + c * 8;
 #pragma unroll
                             for (int e = 0; e < 8; e++) if (s + e >= len) x[e] = (bf16)0.0f;
-                            if (col < N) __builtin_nontemporal_store(x, (bf16x8 *)((bf16 *)epi.C + (b * N + col) * epi.ldc + s));
+                            if (col < N) __builtin_nontemporal_store(x, (bf16x8 *)((bf16 *)epi.C + ((int64_t)b * N + col) * epi.ldc + s));
                         }
                     }
                     if (pass == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1149,22 +1158,17 @@ __device__ __forceinline__ void direct_epilogue(const floatx16 &acc, const float
                                                 const GemmEpilogue &epi, int lane) {
     const int frow = lane % 32, hf = lane / 32;
     if (KIND == EPI_VT) {
-        // out[(b*N + n) * ldc + s] for token s of request b: zero from the request's length on; where S is no multiple of 64, the
-        // request's first tokens also clear the padding columns S .. ldc - 1
+        // out[(b*N + n) * ldc + s] for token s of request b: zero from the request's length on
         const int64_t row = row0 + frow;
         if (row >= M) return;
         const uint32_t b = (uint32_t)row / (uint32_t)epi.vt_S;  // (fewer than 2^31 rows)
         const int s = (int)((uint32_t)row - b * (uint32_t)epi.vt_S);
-        int len = epi.ctx_len ? epi.ctx_len[b] : epi.vt_S;
-        len = len < 1 ? 1 : (len > epi.vt_S ? epi.vt_S : len);
-        const int pad = (int)epi.ldc - epi.vt_S;
+        int len = epi.ctx_len ? epi.ctx_len[b] : epi.vt_rows;
+        len = len < 1 ? 1 : (len > epi.vt_rows ? epi.vt_rows : len);
         bf16 *o = (bf16 *)epi.C + ((int64_t)b * N + col0 + 4 * hf) * epi.ldc + s;
 #pragma unroll
         for (int v = 0; v < 16; v++) {
-            if (col0 + 4 * hf + 8 * (v / 4) + v % 4 < N) {
-                *o = s < len ? (bf16)acc[v] : (bf16)0.0f;
-                if (s < pad) o[epi.vt_S] = (bf16)0.0f;
-            }
+            if (col0 + 4 * hf + 8 * (v / 4) + v % 4 < N) *o = s < len ? (bf16)acc[v] : (bf16)0.0f;
             next_row(o, v, epi.ldc);
         }
         return;
@@ -1256,12 +1260,19 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
         // position lane%8 (rows past the matrix edge re-read its last row) ----
         // A lane's byte offset in its operand block stays, the two block addresses move on: no vector arithmetic per k-tile.
         const int me = wave - NC;
-        const char *base_a = (const char *)(A + m0 * lda), *base_w = (const char *)(W + (int64_t)n0 * ldw);
+        auto source = [&](int64_t row) -> int64_t {  // row of A behind row `row` of C
+            const int64_t r = row < M ? row : M - 1;
+            if (KIND != EPI_VT) return r;
+            const uint32_t b = (uint32_t)r / (uint32_t)epi.vt_S, t = (uint32_t)r - b * (uint32_t)epi.vt_S;  // (see the persistent kernel)
+            return (int64_t)b * epi.vt_rows + (t < (uint32_t)epi.vt_rows ? t : (uint32_t)epi.vt_rows - 1);
+        };
+        const int64_t first_row = source(m0);
+        const char *base_a = (const char *)(A + first_row * lda), *base_w = (const char *)(W + (int64_t)n0 * ldw);
         uint32_t off[LPW];
 #pragma unroll
         for (int i = 0; i < LPW; i++) {
             const int p = i * NL + me, r = p * 8 + lane / 8, chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
-            if (p < BM / 8) off[i] = (uint32_t)(m0 + r < M ? r : M - 1 - m0) * ((uint32_t)lda * 2) + chunk * 16;
+            if (p < BM / 8) off[i] = (uint32_t)(source(m0 + r) - first_row) * ((uint32_t)lda * 2) + chunk * 16;
             else off[i] = (uint32_t)(n0 + r - BM < N ? r - BM : N - 1 - n0) * ((uint32_t)ldw * 2) + chunk * 16;
         }
         auto issue = [&](uint32_t at) {  // k-tiles are requested in ascending order; at: byte offset of the slot
@@ -1496,8 +1507,9 @@ static int pick_kernel(int64_t M, int N, int K, int kind, int batch, bool tile64
     auto offer = [&](bool ok, int what, float t) {
         if (ok && t < best) { best = t; run = what; }
     };
-    offer(tile64, RUN_TILE64_PAIRED, 2.5f + rounds(64, 64) * (0.3f + 0.4f * adds + 0.18f * kt));
-    offer(tile128, RUN_TILE128, 2.0f + rounds(128, 128) * (1.2f + 3.5f * adds + 0.53f * kt));
+    const float scatter = kind == EPI_VT ? 1.0f : 0.0f;  // (the tile kernels store the transposed values one by one)
+    offer(tile64, RUN_TILE64_PAIRED, 2.5f + rounds(64, 64) * (0.3f + 0.4f * adds + 1.0f * scatter + 0.18f * kt));
+    offer(tile128, RUN_TILE128, 2.0f + rounds(128, 128) * (1.2f + 3.5f * adds + 5.0f * scatter + 0.53f * kt));
     offer(tile256 && adds, RUN_TILE256X128, 2.5f + rounds(256, 128) * (6.7f + 1.08f * kt));
     const int64_t t256 = tiles(256, 256), full = t256 / 256;
     const float rest = (float)(t256 % 256) / 256.0f;
@@ -1544,15 +1556,13 @@ int launch_gemm_batched(const void *A, int64_t lda, int64_t batch_a, const void 
 }
 
 // Transposed-per-request product for the context values: out[(b*N + n) * ld_out + s] = sum_k A[b*S + s][k] * W[n][k] for
-// s < len_b, 0 for len_b <= s < ld_out (ld_out = S rounded up to 64).  false = shape not covered (caller takes another route).
-static bool ring_vt_ok(int64_t M, int N, int K, int S, int64_t lda, int64_t ldw) {
-    return K >= 192 && S % 64 == 0 && M >= 256 && N >= 256 && lda < (1 << 22) && ldw < (1 << 22);
-}
+// s < len_b, 0 for len_b <= s < ld_out (ld_out = S rounded up to 64).  The kernels see requests of ld_out rows, so that no 64 rows straddle two
+// requests and the transposed lines are written in whole aligned pieces at every S (32 requests of 500 rows, N = K = 1024: 64 us on 128x128 tiles
+// that scattered single values, now 30 as a third of 3072 columns).  false = shape not covered.
 bool gemm_vt_supported(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K, int S,
                        const void *out, int64_t ld_out) {
-    if (dtype != GR4AD_BF16 || K % 64 || M % S || lda % 8 || ldw % 8 || ((uintptr_t)A % 16) || ((uintptr_t)W % 16) || ((uintptr_t)out % 16)) return false;
-    // (the padding columns of a request are cleared by the lanes of its first tokens, see direct_epilogue)
-    return ld_out == (S + 63) / 64 * 64 && ld_out - S <= S && M <= 0x7fffff00LL;
+    if (dtype != GR4AD_BF16 || K % 64 || S < 1 || M % S || lda % 8 || ldw % 8 || ((uintptr_t)A % 16) || ((uintptr_t)W % 16) || ((uintptr_t)out % 16)) return false;
+    return ld_out == (S + 63) / 64 * 64 && M / S * ld_out <= 0x7fffff00LL;
 }
 int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K, int S, const int32_t *ctx_len, void *out,
                    int64_t ld_out, hipStream_t st) {
@@ -1562,12 +1572,15 @@ int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64
     e.C = out;
     e.ldc = ld_out;
     e.ctx_len = ctx_len;
-    e.vt_S = S;
+    e.vt_S = (int)ld_out;
+    e.vt_rows = S;
     e.skip_len = ctx_len;  // key tiles beyond ceil(len / 64) * 64 are never read by the attention kernel
-    e.skip_S = S;
-    const int run = pick_kernel(M, N, K, EPI_VT, 1, true, true, false, ring_vt_ok(M, N, K, S, lda, ldw));
-    if (run == RUN_RING) return launch_ring((const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
-    return launch_tile(run, (const bf16 *)A, lda, (const bf16 *)W, ldw, M, N, K, EPI_VT, e, st);
+    e.skip_S = (int)ld_out;
+    const int64_t rows = M / S * ld_out;
+    const bool ring = K >= 192 && rows >= 256 && N >= 256 && lda < (1 << 22) && ldw < (1 << 22);
+    const int run = pick_kernel(rows, N, K, EPI_VT, 1, true, true, false, ring);
+    if (run == RUN_RING) return launch_ring((const bf16 *)A, lda, (const bf16 *)W, ldw, rows, N, K, EPI_VT, e, st);
+    return launch_tile(run, (const bf16 *)A, lda, (const bf16 *)W, ldw, rows, N, K, EPI_VT, e, st);
 }
 
 // ---------------------------------------------------------------------------
