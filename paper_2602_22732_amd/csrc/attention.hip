@@ -20,6 +20,8 @@
 //  * trunk_self_attn<T>     causal self-attention over the T trunk positions.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 // ---------------------------------------------------------------------------
@@ -130,11 +132,15 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const bf16 *__restrict
     }
 }
 
-// One workgroup: NW wavefronts x QT tiles of 32 beams of one (request, head).  The context streams through LDS
-// in macro-tiles of SUBS x 64 keys (K [64 x DH] and V^T [DH x 64] per 64 keys), two macro-tiles double-buffered,
-// filled by direct global->LDS loads (no staging registers) one whole macro-tile ahead; every beam of the block
-// reuses them.  The workgroup meets at a barrier once per macro-tile only: in between, the two wavefronts that
-// share a SIMD drift apart, so one's softmax (vector instructions, the larger part) overlaps the other's MFMAs.
+// One workgroup: NW wavefronts of 32 beams each of one (request, head).  The context streams through LDS in tiles of 64 keys (K [64 x DH] and
+// V^T [DH x 64]), filled by direct global->LDS loads (no staging registers); every beam of the block reuses them.
+// LD = 0: the wavefronts load what they use, two tiles double-buffered, one barrier per tile: in between, the wavefronts that share a SIMD drift
+// apart, so one's softmax (vector instructions, the larger part) overlaps the other's MFMAs.  For launches that fill the chip many times.
+// LD > 0: LD wavefronts of their own load, three tiles in LDS.  With few blocks per compute unit a wavefront's own chain is what counts, and its share
+// of a tile's loads (address arithmetic, 25 to 35 cycles to issue each) is a fifth to a third of it: 1 request of 512 keys, d = 512, 1 / 128 / 256 beams 12.1 / 13.1 /
+// 13.7 -> 8.3 / 9.2 / 9.3 us; 32 requests, 128 beams 16.2 -> 11.8; 8 requests of 1024 keys, d = 1024, 256 beams 24.9 -> 16.9; 128 such, 128 beams 129 -> 109; head
+// width 32, 64 requests of 256 keys, 64 beams 9.0 -> 7.4, of 512 keys, 512 beams 74 -> 67 (before: pairs of tiles double-buffered; head width 32 with up to 64 beams
+// to a wavefront).
 // Both products are computed transposed,
 //   S^T = K Q^T  (keys x beams)   and   O^T = V^T P^T  (head dims x beams),
 // so that each lane owns one beam: its running max / sum are lane-local, P^T leaves the
@@ -142,8 +148,8 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const bf16 *__restrict
 // only cross-lane step is one exchange between the two half-waves.  Key rows enter the
 // first product with index bits 2 and 3 swapped, which makes the 8 keys a lane holds for
 // one MFMA k-step consecutive (one 16-byte chunk of a V^T row).
-template <int DH, int QT, int NW, int SUBS>
-__global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void cross_attn_flash_bf16(const bf16 *__restrict__ q, int64_t ldq, const bf16 *__restrict__ kv, int64_t ldk,
+template <int DH, int NW, int LD>
+__global__ __launch_bounds__((NW + LD) * 64, 4) void cross_attn_flash_bf16(const bf16 *__restrict__ q, int64_t ldq, const bf16 *__restrict__ kv, int64_t ldk,
                                                                  const bf16 *__restrict__ vt, int64_t vt_req, const int32_t *__restrict__ ctx_len,
                                                                  bf16 *__restrict__ out, int64_t ldo, int n, int S, int Spad, int H,
                                                                  float scale_log2e, int beam_blocks, int64_t total_blocks,
@@ -151,9 +157,14 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
     constexpr int KCH = DH / 8;                   // 16-byte chunks per K row
     constexpr int K_CHUNKS = 64 * KCH, V_CHUNKS = DH * 8;
     constexpr int STAGE = K_CHUNKS + V_CHUNKS;    // one 64-key tile
-    constexpr int MACRO = SUBS * STAGE;
+    constexpr int BUFS = LD ? 3 : 2;              // tiles in LDS
     constexpr int KSTEPS = DH / 16, MT = DH / 32;
-    extern __shared__ bf16x8 smem[];              // 2 * MACRO chunks
+    // A tile is K_CHUNKS/64 wave loads of K rows and V_CHUNKS/64 of V^T rows, dealt in turn to the NLW wavefronts that load.  A wave load fills 64
+    // consecutive 16-byte slots; slot p of row r holds chunk p ^ swizzle(r), applied on the global side.  Keys past the context end re-read its last
+    // row (masked later); V^T is zero beyond the length.
+    constexpr int KI = K_CHUNKS / 64, NLW = LD ? LD : NW, NL = STAGE / 64 / NLW;
+    static_assert(STAGE / 64 % NLW == 0, "every loading wavefront issues the same number of loads");
+    extern __shared__ bf16x8 smem[];              // BUFS * STAGE chunks
     const int tid = threadIdx.x, lane = tid % 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     // Workgroup ids are dealt to the 8 XCDs in turn, each with an L2 of its own.  The beam blocks of one (request, head) read the
@@ -177,113 +188,139 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
     int len = ctx_len ? ctx_len[b] : S;
     len = len < 1 ? 1 : (len > S ? S : len);
     const int ntiles = (len + 63) / 64;
-    const int nmacro = (ntiles + SUBS - 1) / SUBS;
-    const int q0 = (beam_block * NW + wave) * (QT * 32);
+    const int q0 = (beam_block * NW + wave) * 32;
     int64_t req_row = (int64_t)b * n;
     if (q_count) {  // rows packed over the requests
         req_row = q_first[b];
         n = q_count[b];
-        if (beam_block * (NW * QT * 32) >= n) return;
+        if (beam_block * (NW * 32) >= n) return;
+    }
+    auto meet = [&]() {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    const bf16 *kbase = kv + (int64_t)b * S * ldk + h * DH;
+    const bf16 *vbase = vt + (int64_t)b * vt_req + (int64_t)h * DH * Spad;
+    auto k_source = [&](int tile, int w) {  // what this lane loads of a tile with load w < KI
+        const int id = w * 64 + lane, r = id / KCH, key = tile * 64 + r;
+        return kbase + (int64_t)(key < S ? key : S - 1) * ldk + ((id % KCH) ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1))) * 8;
+    };
+    auto v_source = [&](int tile, int w) {  // w >= KI
+        const int id = (w - KI) * 64 + lane, r = id / 8;
+        return vbase + (int64_t)r * Spad + tile * 64 + ((id % 8) ^ ((r >> 1) & 7)) * 8;
+    };
+    auto load = [&](const bf16 *src, int buf, int w) {
+        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
+                                         (void __attribute__((address_space(3))) *)(smem + buf * STAGE + w * 64), 16, 0, 0);
+    };
+    if constexpr (LD > 0) {
+        if (wave >= NW) {
+            const int me = wave - NW;
+            auto issue = [&](int tile, int buf) {
+#pragma unroll
+                for (int i = 0; i < NL; i++) {
+                    const int w = i * LD + me;  // wave-uniform
+                    load(w < KI ? k_source(tile, w) : v_source(tile, w), buf, w);
+                }
+            };
+            auto landed = [&](auto k) {  // this loader's share of all but the newest k tiles is there
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(k.value * NL) : "memory");
+                meet();
+            };
+            auto rest = [&](auto self, auto k) {  // the last k + 1 tiles
+                if constexpr (k.value >= 0) {
+                    if (ntiles > k.value) landed(k);
+                    self(self, std::integral_constant<int, k.value - 1>());
+                }
+            };
+            for (int t = 0; t < BUFS && t < ntiles; t++) issue(t, t);
+            if (ntiles >= BUFS) {
+                landed(std::integral_constant<int, BUFS - 1>());
+                int buf = 0;
+                for (int t = BUFS; t < ntiles; t++) {  // past the barrier of tile t - BUFS + 1 tile t - BUFS has been read
+                    landed(std::integral_constant<int, BUFS - 2>());
+                    issue(t, buf);
+                    buf = buf + 1 == BUFS ? 0 : buf + 1;
+                }
+            }
+            rest(rest, std::integral_constant<int, BUFS - 2>());
+            return;
+        }
+    }
+    // LD = 0: tiles are requested in ascending order, so each of a wavefront's NL loads keeps a running per-lane source address that advances by a
+    // fixed step per tile; only a tile that reaches past row S-1 of the keys (the last one, when S is not a multiple of 64) computes clamped
+    // addresses.
+    const bf16 *lsrc[NL];
+    auto issue = [&](int tile, int buf) {  // tile = 0, 1, 2, ... in this order
+#pragma unroll
+        for (int i = 0; i < NL; i++) {
+            const int w = i * NW + wave;
+            const bf16 *src = lsrc[i];
+            lsrc[i] += w < KI ? 64 * ldk : 64;
+            if (w < KI && tile * 64 + 63 > S - 1) src = k_source(tile, w);
+            load(src, buf, w);
+        }
+    };
+    if constexpr (LD == 0) {
+#pragma unroll
+        for (int i = 0; i < NL; i++) {
+            const int w = i * NW + wave;
+            if (w < KI) {
+                const int id = w * 64 + lane, r = id / KCH;
+                lsrc[i] = kbase + (int64_t)r * ldk + ((id % KCH) ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1))) * 8;
+            } else {
+                lsrc[i] = v_source(0, w);
+            }
+        }
     }
 
     // query fragments stay in registers for the whole kernel
-    bf16x8 qf[QT][KSTEPS];
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        int row = q0 + qt * 32 + frow;
+    bf16x8 qf[KSTEPS];
+    {
+        int row = q0 + frow;
         if (row > n - 1) row = n - 1;  // rows past the end are computed and dropped
         const bf16 *qr = q + (req_row + row) * ldq + h * DH;
 #pragma unroll
-        for (int s = 0; s < KSTEPS; s++) qf[qt][s] = *(const bf16x8 *)(qr + 16 * s + 8 * hf);
+        for (int s = 0; s < KSTEPS; s++) qf[s] = *(const bf16x8 *)(qr + 16 * s + 8 * hf);
     }
-
-    // loads of one macro-tile: per 64-key tile, K_CHUNKS/64 wave loads of K rows and V_CHUNKS/64 of V^T rows, dealt round-robin
-    // to the wavefronts.  A wave load fills 64 consecutive 16-byte slots; slot p of row r holds chunk p ^ swizzle(r), applied on
-    // the global side.  Keys past the context end re-read its last row (masked later); V^T is zero beyond the length.
-    // The macro-tiles are requested in ascending order, so each of a wavefront's NL loads keeps a running per-lane source
-    // address that advances by a fixed step per macro-tile; only a tile that reaches past row S-1 of the keys (the last one,
-    // when S is not a multiple of 64) computes clamped addresses.
-    const bf16 *kbase = kv + (int64_t)b * S * ldk + h * DH;
-    const bf16 *vbase = vt + (int64_t)b * vt_req + (int64_t)h * DH * Spad;
-    constexpr int KI = K_CHUNKS / 64, VI = V_CHUNKS / 64, PER_TILE = KI + VI, NL = (SUBS * PER_TILE + NW - 1) / NW;
-    const bf16 *lsrc[NL];
+    float m_run = -INFINITY, l_run = 0.0f;
+    floatx16 o[MT];
 #pragma unroll
-    for (int i = 0; i < NL; i++) {
-        const int idx = i * NW + wave;  // wave-uniform
-        const int sub = idx / PER_TILE, w = idx % PER_TILE;
-        if (w < KI) {
-            const int id = w * 64 + lane, r = id / KCH, pslot = id % KCH;
-            const int c = pslot ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1));
-            lsrc[i] = kbase + (int64_t)(sub * 64 + r) * ldk + c * 8;
-        } else {
-            const int id = (w - KI) * 64 + lane, r = id / 8, pslot = id % 8;
-            const int c = pslot ^ ((r >> 1) & 7);
-            lsrc[i] = vbase + (int64_t)r * Spad + sub * 64 + c * 8;
-        }
-    }
-    const int64_t kstep = (int64_t)SUBS * 64 * ldk, vstep = SUBS * 64;  // elements per macro-tile
-    auto issue_macro = [&](int macro, int buf) {  // macro = 0, 1, 2, ... in this order
+    for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-        for (int i = 0; i < NL; i++) {
-            const int idx = i * NW + wave;
-            const int sub = idx / PER_TILE, w = idx % PER_TILE;
-            const int tile = macro * SUBS + sub;
-            const bf16 *src = lsrc[i];
-            lsrc[i] += w < KI ? kstep : vstep;
-            if (idx < SUBS * PER_TILE && tile < ntiles) {
-                bf16x8 *dst = smem + buf * MACRO + sub * STAGE + (w < KI ? w * 64 : K_CHUNKS + (w - KI) * 64);
-                if (w < KI && tile * 64 + 63 > S - 1) {
-                    const int id = w * 64 + lane, r = id / KCH, pslot = id % KCH;
-                    const int c = pslot ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1));
-                    int key = tile * 64 + r;
-                    if (key > S - 1) key = S - 1;
-                    src = kbase + (int64_t)key * ldk + c * 8;
-                }
-                __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
-                                                 (void __attribute__((address_space(3))) *)dst, 16, 0, 0);
-            }
-        }
-    };
-
-    float m_run[QT], l_run[QT];
-    floatx16 o[QT][MT];
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        m_run[qt] = -INFINITY;
-        l_run[qt] = 0.0f;
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int v = 0; v < 16; v++) o[qt][mt][v] = 0.0f;
-    }
+        for (int v = 0; v < 16; v++) o[mt][v] = 0.0f;
     // key row read by this lane in the first product: bits 2 and 3 of the row index swapped
     const int krow = (frow & 0x13) | ((frow & 4) << 1) | ((frow & 8) >> 1);
 
-    issue_macro(0, 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    if (nmacro > 1) issue_macro(1, 1);
+    if constexpr (LD == 0) {
+        issue(0, 0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        meet();
+        if (ntiles > 1) issue(1, 1);
+    }
+    int buf = 0;  // the tile's
     for (int tile = 0; tile < ntiles; tile++) {
-        const int macro = tile / SUBS, sub_tile = tile % SUBS;
-        if (sub_tile == 0 && macro > 0) {
-            // the previous macro-tile is read out and this wave's share of the current one has landed: meet, then refill the free buffer
+        if constexpr (LD > 0) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the tile before is read out; once everybody meets, this one has landed
+            meet();
+            if (tile > 0) buf = buf + 1 == BUFS ? 0 : buf + 1;
+        } else if (tile > 0) {
+            // the previous tile is read out and this wave's share of the current one has landed: meet, then refill the free buffer
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            if (macro + 1 < nmacro) issue_macro(macro + 1, (macro + 1) & 1);
+            meet();
+            if (tile + 1 < ntiles) issue(tile + 1, buf);
+            buf ^= 1;
         }
-        if (q0 >= n) continue;  // a wavefront without beams only helps to load
-        const bf16x8 *sk = smem + (macro & 1) * MACRO + sub_tile * STAGE, *sv = sk + K_CHUNKS;
+        if (q0 >= n) continue;  // a wavefront without beams
+        const bf16x8 *sk = smem + buf * STAGE, *sv = sk + K_CHUNKS;
         // first product: the two 32-key halves are independent accumulation chains, issued in turn; the key fragments of
         // k-step st+1 are read while step st multiplies
-        floatx16 s[QT][2];
+        floatx16 s[2];
 #pragma unroll
         for (int sub = 0; sub < 2; sub++)
 #pragma unroll
-            for (int qt = 0; qt < QT; qt++)
-#pragma unroll
-                for (int v = 0; v < 16; v++) s[qt][sub][v] = 0.0f;
+            for (int v = 0; v < 16; v++) s[sub][v] = 0.0f;
         auto key_frag = [&](int sub, int st) {
             const int r = sub * 32 + krow;
             return sk[r * KCH + ((2 * st + hf) ^ ((KCH == 8 ? (r >> 1) : (r >> 2)) & (KCH - 1)))];
@@ -298,85 +335,73 @@ __global__ __launch_bounds__(NW * 64, (QT == 1 && SUBS == 1) ? 16 / NW : 1) void
                 kf[(st + 1) & 1][1] = key_frag(1, st + 1);
             }
 #pragma unroll
-            for (int sub = 0; sub < 2; sub++)
-#pragma unroll
-                for (int qt = 0; qt < QT; qt++)
-                    s[qt][sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st & 1][sub], qf[qt][st], s[qt][sub], 0, 0, 0);
+            for (int sub = 0; sub < 2; sub++) s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st & 1][sub], qf[st], s[sub], 0, 0, 0);
         }
-        // this lane holds, for beam frow of each tile qt, keys tile*64 + 32*sub + 16*(v/8) + 8*hf + v%8.
+        // this lane holds, for beam frow, keys tile*64 + 32*sub + 16*(v/8) + 8*hf + v%8.
         // The softmax is the instruction-bound part of the kernel (about three vector instructions per MFMA flop-cycle),
         // so it is kept lean: scores stay raw and the scale enters through one fused multiply-add per element; only a
         // partial last tile is masked; and the running maximum is refreshed lazily -- as long as no score exceeds the
         // maximum in use by more than 2^8 the old one stays, p <= 256 is harmless in fp32 sums and bf16 operands, and
         // the rescaling of O (one multiply per score element) is skipped.
         const int key0 = tile * 64 + 8 * hf;
-        const bool partial = tile * 64 + 64 > len;
-        bf16x8 pf[QT][4];
-#pragma unroll
-        for (int qt = 0; qt < QT; qt++) {
-            if (partial) {
-#pragma unroll
-                for (int sub = 0; sub < 2; sub++)
-#pragma unroll
-                    for (int v = 0; v < 16; v++)
-                        if (key0 + 32 * sub + 16 * (v / 8) + (v % 8) >= len) s[qt][sub][v] = -INFINITY;
-            }
-            float mx = -INFINITY;
+        bf16x8 pf[4];
+        if (tile * 64 + 64 > len) {
 #pragma unroll
             for (int sub = 0; sub < 2; sub++)
 #pragma unroll
-                for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[qt][sub][v]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;  // finite: every tile holds at least one valid key
-            if (__builtin_amdgcn_ballot_w64(mx > m_run[qt] + 8.0f) != 0) {  // some beam of the wave outgrew its maximum
-                const float mnew = mx > m_run[qt] + 8.0f ? mx : m_run[qt];
-                const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - mnew);  // m_run = -inf on the first tile gives 0
-                m_run[qt] = mnew;
-                l_run[qt] *= alpha;
-#pragma unroll
-                for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-                    for (int v = 0; v < 16; v++) o[qt][mt][v] *= alpha;
-            }
-            const float neg_m = -m_run[qt];
-            float lsum = 0.0f;
-#pragma unroll
-            for (int sub = 0; sub < 2; sub++)
-#pragma unroll
-                for (int v = 0; v < 16; v++) {
-                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][sub][v], scale_log2e, neg_m));
-                    lsum += pv;
-                    pf[qt][2 * sub + v / 8][v % 8] = (bf16)pv;  // k-step 2*sub + v/8 of the second product
-                }
-            l_run[qt] += lsum;  // per half-wave partial sum, joined at the end
+                for (int v = 0; v < 16; v++)
+                    if (key0 + 32 * sub + 16 * (v / 8) + (v % 8) >= len) s[sub][v] = -INFINITY;
         }
-        // second product; V^T fragments are shared by the QT beam tiles
+        float mx = -INFINITY;
+#pragma unroll
+        for (int sub = 0; sub < 2; sub++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[sub][v]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;  // finite: every tile holds at least one valid key
+        if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.0f) != 0) {  // some beam of the wave outgrew its maximum
+            const float mnew = mx > m_run + 8.0f ? mx : m_run;
+            const float alpha = __builtin_amdgcn_exp2f(m_run - mnew);  // m_run = -inf on the first tile gives 0
+            m_run = mnew;
+            l_run *= alpha;
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) o[mt][v] *= alpha;
+        }
+        const float neg_m = -m_run;
+        float lsum = 0.0f;
+#pragma unroll
+        for (int sub = 0; sub < 2; sub++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) {
+                const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[sub][v], scale_log2e, neg_m));
+                lsum += pv;
+                pf[2 * sub + v / 8][v % 8] = (bf16)pv;  // k-step 2*sub + v/8 of the second product
+            }
+        l_run += lsum;  // per half-wave partial sum, joined at the end
 #pragma unroll
         for (int ks = 0; ks < 4; ks++)
 #pragma unroll
             for (int mt = 0; mt < MT; mt++) {
                 const int r = mt * 32 + frow;
                 const bf16x8 vf = sv[r * 8 + ((2 * ks + hf) ^ ((r >> 1) & 7))];
-#pragma unroll
-                for (int qt = 0; qt < QT; qt++) o[qt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[qt][ks], o[qt][mt], 0, 0, 0);
+                o[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks], o[mt], 0, 0, 0);
             }
     }
+    const float l = l_run + __shfl_xor(l_run, 32, 64);
+    const float inv = 1.0f / l;
+    const int row = q0 + frow;
+    if (row < n) {
+        bf16 *orow = out + (req_row + row) * ldo + h * DH;
 #pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-        const float l = l_run[qt] + __shfl_xor(l_run[qt], 32, 64);
-        const float inv = 1.0f / l;
-        const int row = q0 + qt * 32 + frow;
-        if (row < n) {
-            bf16 *orow = out + (req_row + row) * ldo + h * DH;
+        for (int mt = 0; mt < MT; mt++)
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++)
+            for (int g = 0; g < 4; g++) {
+                bf16x4 pk;
 #pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    bf16x4 pk;
-#pragma unroll
-                    for (int j = 0; j < 4; j++) pk[j] = (bf16)(o[qt][mt][4 * g + j] * inv);
-                    *(bf16x4 *)(orow + mt * 32 + 8 * g + 4 * hf) = pk;
-                }
-        }
+                for (int j = 0; j < 4; j++) pk[j] = (bf16)(o[mt][4 * g + j] * inv);
+                *(bf16x4 *)(orow + mt * 32 + 8 * g + 4 * hf) = pk;
+            }
     }
 }
 
@@ -1065,17 +1090,17 @@ int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, c
     return GR4AD_OK;
 }
 
-template <int DH, int QT, int NW, int SUBS>
+template <int DH, int NW, int LD>
 static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, int64_t ldk, const bf16 *vt, int64_t vt_req, const int32_t *ctx_len, bf16 *out, int64_t ldo, int B,
                         int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
-    auto kern = cross_attn_flash_bf16<DH, QT, NW, SUBS>;
-    constexpr int LDS_BYTES = 2 * SUBS * (64 * (DH / 8) + DH * 8) * 16;
+    auto kern = cross_attn_flash_bf16<DH, NW, LD>;
+    constexpr int LDS_BYTES = (LD ? 3 : 2) * (64 * (DH / 8) + DH * 8) * 16;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
-    const int per_block = NW * QT * 32;
+    const int per_block = NW * 32;
     const int beam_blocks = (n + per_block - 1) / per_block;
     const int64_t total_blocks = (int64_t)beam_blocks * H * B;
     const int64_t grid = (total_blocks + 7) / 8 * 8;
@@ -1083,7 +1108,7 @@ static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, int64_t ldk,
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
     // flops on the padded length S; bytes: queries and outputs once, keys and values once per request (beam-shared)
     ProfScope ps(KC_XATTN_FLASH, st, 4.0 * B * (double)n * S * d, (2.0 * B * n * d + 2.0 * B * (double)S * d) * sizeof(bf16));
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS_BYTES, st, q, ldq, kv, ldk, vt, vt_req, ctx_len, out, ldo, n, S, (S + 63) / 64 * 64, H, scale_log2e,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((NW + LD) * 64), LDS_BYTES, st, q, ldq, kv, ldk, vt, vt_req, ctx_len, out, ldo, n, S, (S + 63) / 64 * 64, H, scale_log2e,
                        beam_blocks, total_blocks, dr ? dr->first : nullptr, dr ? dr->count : nullptr);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
@@ -1098,20 +1123,17 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
         ((uintptr_t)out % 8) == 0) {
         const bf16 *qq = (const bf16 *)q, *kk = (const bf16 *)kv, *vv = (const bf16 *)vt;
         bf16 *oo = (bf16 *)out;
-        if (dh == 64) {
-            // Measured at 256, 512 and 1024 beams per request: 32 beams per wavefront with single 64-key tiles, four wavefronts
-            // per SIMD, beat two-tile staging (-25 %) and 64 beams per wavefront (-10 %), which both halve the wavefronts per
-            // SIMD: the kernel waits on LDS, barrier and dependent-MFMA latencies, and occupancy is what hides them.  Blocks
-            // of 8 wavefronts (256 beams) share each staged tile among twice as many beams and are 3-7 % faster than blocks
-            // of 4; they are used where they waste no more beam slots.
-            if (n <= 128) return launch_flash<64, 1, 4, 2>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            if ((n + 255) / 256 * 256 == (n + 127) / 128 * 128) return launch_flash<64, 1, 8, 1>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            return launch_flash<64, 1, 4, 1>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-        } else {
-            if (n <= 128) return launch_flash<32, 1, 4, 2>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            if (n <= 256) return launch_flash<32, 2, 4, 2>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            return launch_flash<32, 2, 8, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-        }
+        if (dh == 32) return launch_flash<32, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+        // Where the lines lie, in us, 8 wavefronts that load for themselves / 4 that do / 4 with 4 loaders (blocks of 256 / 128 / 128 beams; one card, others differ by
+        // up to 8 %): 1 request of 512 keys, d = 512, 256 beams 13.8 / 10.6 / 9.5; 32 of them 18.4 / 18.7 / 17.5 (512 blocks of 128 beams); 45 of 389 keys, 512 beams 37.1 / 33.9 /
+        // 35.7 (1440); 128 of 512 keys, 256 beams 55.1 / 53.9 / 59.3 (2048); 128 of 1024 keys, d = 1024, 256 beams 170 / 174 / 180 and 64 with 512 157 / 164 / 171 (4096).  Many
+        // blocks: occupancy hides LDS, barrier and dependent-MFMA latencies, and a staged tile serves twice as many beams.  At most 128 beams: 128
+        // requests of 1024 keys, d = 1024, 64 beams 97 / 97 / 95, 128 beams 117 / 113 / 113.  (Distinct rows: n is a bound, most blocks find less.)
+        const int64_t blocks = (int64_t)((n + 127) / 128) * H * B;
+        if (n <= 128 || blocks <= 512) return launch_flash<64, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+        if (blocks <= 2048 || (n + 255) / 256 * 256 != (n + 127) / 128 * 128)
+            return launch_flash<64, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+        return launch_flash<64, 8, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
     }
     if (dr) return GR4AD_EUNSUPPORTED;
     const int64_t rows = (int64_t)B * n;

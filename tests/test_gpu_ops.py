@@ -288,3 +288,28 @@ def test_gather_rows_is_an_exact_copy(dtype):
     ref = torch.stack([src[b][parent[b].long()] for b in range(B)])
     assert torch.equal(dst[:, :, :3], ref[:, :, :3])
     assert (dst[:, :, 3] == 0).all()
+
+
+@pytest.mark.parametrize("S,d,H,n", [
+    (1, 64, 1, 4096), (64, 64, 2, 300), (129, 512, 8, 2100), (200, 512, 8, 4096),  # one tile, as many and more tiles than LDS holds; every number of blocks
+    (193, 256, 8, 300), (577, 128, 2, 5),
+])
+def test_cross_attention_of_a_beam_does_not_depend_on_the_others(S, d, H, n):
+    """The number of beams picks the wavefronts of a block and who loads; a beam's output is the same bits with any of them."""
+    B = 9
+    g = torch.Generator().manual_seed(S + n)
+    q, kv = (torch.randn(B, n, d, generator=g) * 2).bfloat16().cuda(), torch.randn(B, S, 2 * d, generator=g).bfloat16().cuda()
+    lens = torch.randint(1, S + 1, (B,), generator=g).int().cuda()
+    lens[0] = S
+    full = binding.op_cross_attention(q, kv, lens, H)
+    for first, m in ((0, 1), (0, min(n, 128)), (n // 2, min(33, n - n // 2)), (0, min(n, 700)), (0, n - 1)):
+        some = binding.op_cross_attention(q[:, first:first + m].contiguous(), kv, lens, H)
+        assert torch.equal(some, full[:, first:first + m])
+    b = 0
+    qd, kd, vd = q[b, :64].double().cpu(), kv[b, :, :d].double().cpu(), kv[b, :, d:].double().cpu()
+    dh = d // H
+    for h in range(H):
+        c = slice(h * dh, (h + 1) * dh)
+        p = torch.softmax(qd[:, c] @ kd[:, c].t() / dh**0.5, dim=1)
+        # (probabilities and outputs are rounded to bf16: 2^-8 of the largest value averaged, with room for the sum's own rounding)
+        assert (full[b, :64, c].double().cpu() - p @ vd[:, c]).abs().max() <= 2.0**-7 * vd[:, c].abs().max()
