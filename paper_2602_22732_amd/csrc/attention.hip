@@ -27,11 +27,14 @@
 // ---------------------------------------------------------------------------
 // simple cross-attention: wave per (row, head)
 // ---------------------------------------------------------------------------
-template <typename T>
+// A wavefront's time is a few memory latencies, so a tile's keys and values (64 keys, all loads at once while a head is at most 64 wide) are requested
+// together, before the scores are formed: 12 to 64 workgroups of 64 keys, head width 32, 9.5 to 10.4 us with the values requested 16 keys at a time
+// after the softmax, now 8.5 to 9.1.
+template <typename T, bool WIDE>  // WIDE: heads of more than 64 columns
 __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q, int64_t ldq, const T *__restrict__ kv,
                                                          const int32_t *__restrict__ ctx_len, T *__restrict__ out, int64_t ldo,
                                                          int64_t rows, int n, int S, int d, int H) {
-    __shared__ float sq[4][128];
+    __shared__ __attribute__((aligned(16))) float sq[4][128];
     __shared__ float sp[4][64];
     const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
     const int64_t wid = (int64_t)blockIdx.x * 4 + wv;
@@ -45,26 +48,44 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
     const float scale = 1.0f / sqrtf((float)dh);
     for (int c = lane; c < dh; c += 64) sq[wv][c] = to_f(q[row * ldq + h * dh + c]) * scale;
     const T *kbase = kv + b * (int64_t)S * 2 * d + h * dh;  // key j at kbase + j*2d, value at + d
-    const bool vec = ((uintptr_t)kbase % 16) == 0 && (2 * d) % (16 / (int)sizeof(T)) == 0 && dh % (16 / (int)sizeof(T)) == 0;
+    constexpr int E = 16 / sizeof(T), U = 32 / E;           // values of a 16-byte load; loads of 32 columns
+    const bool vec = ((uintptr_t)kbase % 16) == 0 && (2 * d) % E == 0 && dh % E == 0;
     float m = -INFINITY, l = 0.0f, acc[2] = {0.0f, 0.0f};
+    constexpr int G = WIDE ? 16 : 64;  // keys whose values are in flight
     for (int j0 = 0; j0 < len; j0 += 64) {
-        const int j = j0 + lane;
-        float s = -INFINITY;
-        if (j < len) {
-            const T *kr = kbase + (int64_t)j * 2 * d;
-            s = 0.0f;
-            if (vec) {  // 16 bytes per load, same order of additions
-                constexpr int E = 16 / sizeof(T);
-#pragma unroll 4
-                for (int c = 0; c < dh; c += E) {
-                    const uint4 raw = *(const uint4 *)(kr + c);
+        const int j = j0 + lane, cnt = (len - j0) < 64 ? (len - j0) : 64;
+        float v0[G], v1[WIDE ? G : 1];
+        auto load_values = [&](int j1) {  // (keys past the tile's last re-read it and count as zero: 0 * v is no zero where v is infinite)
 #pragma unroll
-                    for (int e = 0; e < E; e++) s = fmaf(sq[wv][c + e], to_f(((const T *)&raw)[e]), s);
-                }
-            } else {
-                for (int c = 0; c < dh; c++) s = fmaf(sq[wv][c], to_f(kr[c]), s);
+            for (int u = 0; u < G; u++) {
+                const T *vr = kbase + (int64_t)(j0 + (j1 + u < cnt ? j1 + u : cnt - 1)) * 2 * d + d;
+                v0[u] = lane < dh ? to_f(vr[lane]) : 0.0f;
+                if constexpr (WIDE) v1[u] = lane + 64 < dh ? to_f(vr[lane + 64]) : 0.0f;
             }
+        };
+        const T *kr = kbase + (int64_t)(j < len ? j : len - 1) * 2 * d;
+        float s = 0.0f;
+        if (vec) {  // 16 bytes per load, same order of additions
+            uint4 raw[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) raw[u] = *(const uint4 *)(kr + (u * E < dh ? u * E : 0));
+            if constexpr (!WIDE) load_values(0);
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int e = 0; e < E; e++)
+                    if (u * E < dh) s = fmaf(sq[wv][u * E + e], to_f(((const T *)&raw[u])[e]), s);
+#pragma unroll 4
+            for (int c = 32; c < dh; c += E) {
+                const uint4 more = *(const uint4 *)(kr + c);
+#pragma unroll
+                for (int e = 0; e < E; e++) s = fmaf(sq[wv][c + e], to_f(((const T *)&more)[e]), s);
+            }
+        } else {
+            if constexpr (!WIDE) load_values(0);
+            for (int c = 0; c < dh; c++) s = fmaf(sq[wv][c], to_f(kr[c]), s);
         }
+        if (j >= len) s = -INFINITY;
         const float mnew = fmaxf(m, wave_max(s));
         const float p = (j < len) ? __expf(s - mnew) : 0.0f;
         const float alpha = __expf(m - mnew);  // m = -inf on the first tile gives 0
@@ -73,26 +94,21 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
         sp[wv][lane] = p;
         acc[0] *= alpha;
         acc[1] *= alpha;
-        const int cnt = (len - j0) < 64 ? (len - j0) : 64;
-        // values: loads of 16 keys in flight (keys past the tile's last re-read it and count as zero: 0 * v is no zero where v is infinite)
-        for (int j1 = 0; j1 < cnt; j1 += 16) {
-            float v0[16], v1[16];
+        for (int j1 = 0; j1 < cnt; j1 += G) {
+            if constexpr (WIDE) load_values(j1);
+            if (j1 + G > cnt) {
 #pragma unroll
-            for (int u = 0; u < 16; u++) {
-                const T *vr = kbase + (int64_t)(j0 + (j1 + u < cnt ? j1 + u : cnt - 1)) * 2 * d + d;
-                v0[u] = lane < dh ? to_f(vr[lane]) : 0.0f;
-                v1[u] = lane + 64 < dh ? to_f(vr[lane + 64]) : 0.0f;
-            }
-            if (j1 + 16 > cnt) {
-#pragma unroll
-                for (int u = 0; u < 16; u++)
-                    if (j1 + u >= cnt) v0[u] = v1[u] = 0.0f;
+                for (int u = 0; u < G; u++)
+                    if (j1 + u >= cnt) {
+                        v0[u] = 0.0f;
+                        if constexpr (WIDE) v1[u] = 0.0f;
+                    }
             }
 #pragma unroll
-            for (int u = 0; u < 16; u++) {
+            for (int u = 0; u < G; u++) {
                 const float pj = j1 + u < cnt ? sp[wv][j1 + u] : 0.0f;
                 acc[0] = fmaf(pj, v0[u], acc[0]);
-                acc[1] = fmaf(pj, v1[u], acc[1]);
+                if constexpr (WIDE) acc[1] = fmaf(pj, v1[u], acc[1]);
             }
         }
     }
@@ -357,7 +373,7 @@ __global__ __launch_bounds__((NW + LD) * 64, 4) void cross_attn_flash_bf16(const
         for (int sub = 0; sub < 2; sub++)
 #pragma unroll
             for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[sub][v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;  // finite: every tile holds at least one valid key
+        mx = halves_max(mx) * scale_log2e;  // finite: every tile holds at least one valid key
         if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.0f) != 0) {  // some beam of the wave outgrew its maximum
             const float mnew = mx > m_run + 8.0f ? mx : m_run;
             const float alpha = __builtin_amdgcn_exp2f(m_run - mnew);  // m_run = -inf on the first tile gives 0
@@ -388,7 +404,7 @@ __global__ __launch_bounds__((NW + LD) * 64, 4) void cross_attn_flash_bf16(const
                 o[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks], o[mt], 0, 0, 0);
             }
     }
-    const float l = l_run + __shfl_xor(l_run, 32, 64);
+    const float l = halves_sum(l_run);
     const float inv = 1.0f / l;
     const int row = q0 + frow;
     if (row < n) {
@@ -632,7 +648,7 @@ __global__ __launch_bounds__(512) void context_attn_flash_bf16(const bf16 *__res
             float mx = -INFINITY;
 #pragma unroll
             for (int v = 0; v < 16; v++) mx = fmaxf(mx, sacc[v]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;  // finite: every tile holds at least one valid row
+            mx = halves_max(mx) * scale_log2e;  // finite: every tile holds at least one valid row
             float alpha = 1.0f;
             if (mx > m_run + 8.0f) {
                 alpha = __builtin_amdgcn_exp2f(m_run - mx);  // m_run = -inf on the first tile gives 0
@@ -725,7 +741,7 @@ __global__ __launch_bounds__(512) void context_attn_flash_bf16(const bf16 *__res
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a one-tile request never waited for its second buffer: no load may outlive the workgroup's LDS)
     // 1 / sum of every query through LDS (the last barrier of the loop is behind every read of the factors)
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);  // (all lanes: the exchange needs both half-waves)
+    const float l_tot = halves_sum(l_run);  // (all lanes: the exchange needs both half-waves)
     if (kq == 0 && g == 0) *(float *)(ctx_lds + ABUF + (qh * 32 + r32) * 4) = 1.0f / l_tot;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -846,7 +862,7 @@ __global__ __launch_bounds__(512) void context_scores(const bf16 *__restrict__ q
             }
             *(floatx4 *)(sc + unit * 1024 + (i * 64 + lane) * 4) = pk;
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * scale_log2e;
+        mx = halves_max(mx) * scale_log2e;
         if (g == 0) mxs[unit * 32 + r32] = mx;
     }
 }
@@ -1007,7 +1023,7 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
             }
         }
     }
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = halves_sum(l_run);
     float *inv_l = (float *)(ctx_lds + IB);
     if (wave < QT && g == 0) inv_l[wave * 32 + r32] = 1.0f / l_tot;
     __syncthreads();
@@ -1140,10 +1156,11 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
     const int64_t grid = ceil_div64(rows * H, 4);
     if (grid > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
     ProfScope ps(KC_XATTN_SIMPLE, st, 4.0 * B * (double)n * S * d, (2.0 * B * n * d + 2.0 * B * (double)S * d) * (dtype == GR4AD_BF16 ? 2 : 4));
-    if (dtype == GR4AD_BF16)
-        hipLaunchKernelGGL(cross_attn_simple<bf16>, dim3((unsigned)grid), dim3(256), 0, st, (const bf16 *)q, ldq, (const bf16 *)kv, ctx_len, (bf16 *)out, ldo, rows, n, S, d, H);
-    else
-        hipLaunchKernelGGL(cross_attn_simple<float>, dim3((unsigned)grid), dim3(256), 0, st, (const float *)q, ldq, (const float *)kv, ctx_len, (float *)out, ldo, rows, n, S, d, H);
+#define SIMPLE_(T, WIDE) hipLaunchKernelGGL((cross_attn_simple<T, WIDE>), dim3((unsigned)grid), dim3(256), 0, st, (const T *)q, ldq, (const T *)kv, ctx_len, (T *)out, ldo, rows, n, S, d, H)
+    if (dtype == GR4AD_BF16) { if (dh > 64) SIMPLE_(bf16, true); else SIMPLE_(bf16, false); }
+    else if (dh > 64) SIMPLE_(float, true);
+    else SIMPLE_(float, false);
+#undef SIMPLE_
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
@@ -1231,7 +1248,11 @@ __global__ __launch_bounds__(256) void self_attn_step(const T *__restrict__ qkv,
             float part = 0.0f;
 #pragma unroll
             for (int i = 0; i < 8; i++) part = fmaf(qv[i], kk[i], part);
-            for (int o = 1; o < lph; o <<= 1) part += __shfl_xor(part, o, 64);
+            // over the head's lph lanes: lane ^ 1, 2, 4, 8 (the mirrors of 8 and of 16 lanes, whose quads and halves agree by then)
+            if (lph > 1) part += lane_xor1(part);
+            if (lph > 2) part += lane_xor2(part);
+            if (lph > 4) part += dpp_move<0x141, 0xF>(part, part);
+            if (lph > 8) part += dpp_move<0x140, 0xF>(part, part);
             s[p] = part * scale;
             mx = fmaxf(mx, s[p]);
         }

@@ -23,25 +23,51 @@ template <typename T> __device__ __forceinline__ T from_f(float x);
 template <> __device__ __forceinline__ float from_f<float>(float x) { return x; }
 template <> __device__ __forceinline__ bf16 from_f<bf16>(float x) { return (bf16)x; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// The same reductions through data-parallel-primitive operands instead of LDS permutes (a few cycles per step instead of an
-// LDS round trip); every lane must be active.  Rotations by 8, 4, 2, 1 inside each row of 16 lanes leave the row's result in
-// all of its lanes; two row broadcasts (lane 15 into the next row for rows 1 and 3, lane 31 into rows 2 and 3) leave the
-// wavefront's result in lane 63, which is read back as a scalar.  The summation tree differs from wave_sum's: kernels that
-// must agree to the bit use the same one.
+// Exchanges between lanes without LDS permutes (a few cycles instead of an LDS round trip); every lane must be active.
 template <int CTRL, int ROW_MASK> __device__ __forceinline__ float dpp_move(float old, float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
 }
+__device__ __forceinline__ float lane_xor1(float v) { return dpp_move<0xB1, 0xF>(v, v); }  // quad_perm
+__device__ __forceinline__ float lane_xor2(float v) { return dpp_move<0x4E, 0xF>(v, v); }
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uintx2 both_halves(float v) {  // the values of lanes lane % 32 and lane % 32 + 32
+    return __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+}
+__device__ __forceinline__ float halves_sum(float v) {
+    const uintx2 p = both_halves(v);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float halves_max(float v) {
+    const uintx2 p = both_halves(v);
+    return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+// Sum and maximum over the wavefront, in every lane: the butterfly over lane ^ 32, 16, 8, 4, 2, 1 (after the step before, a rotation by o inside a row of
+// 16 lanes reaches what lane ^ o holds).
+__device__ __forceinline__ float wave_sum(float v) {
+    v = halves_sum(v);
+    const uintx2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    v += dpp_move<0x128, 0xF>(0.0f, v);  // row_ror:8
+    v += dpp_move<0x124, 0xF>(0.0f, v);  // row_ror:4
+    v += dpp_move<0x122, 0xF>(0.0f, v);  // row_ror:2
+    v += dpp_move<0x121, 0xF>(0.0f, v);  // row_ror:1
+    return v;
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = halves_max(v);
+    const uintx2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    v = fmaxf(v, dpp_move<0x128, 0xF>(v, v));
+    v = fmaxf(v, dpp_move<0x124, 0xF>(v, v));
+    v = fmaxf(v, dpp_move<0x122, 0xF>(v, v));
+    v = fmaxf(v, dpp_move<0x121, 0xF>(v, v));
+    return v;
+}
+
+// The same reductions with the result in a scalar.  Rotations by 8, 4, 2, 1 inside each row of 16 lanes leave the row's result in
+// all of its lanes; two row broadcasts (lane 15 into the next row for rows 1 and 3, lane 31 into rows 2 and 3) leave the
+// wavefront's result in lane 63, which is read back.  The summation tree differs from wave_sum's: kernels that
+// must agree to the bit use the same one.
 __device__ __forceinline__ float wave_sum_dpp(float v) {
     v += dpp_move<0x128, 0xF>(0.0f, v);  // row_ror:8
     v += dpp_move<0x124, 0xF>(0.0f, v);  // row_ror:4

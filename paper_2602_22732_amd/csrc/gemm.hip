@@ -31,15 +31,20 @@ __device__ __forceinline__ float to_f(fp8e4m3 x) {
 // ---------------------------------------------------------------------------
 // epilogue of one element (plain kernel)
 // ---------------------------------------------------------------------------
+struct Addends { float bias, table, resid; };  // what the epilogue adds to an element
+__device__ __forceinline__ Addends epilogue_addends(const GemmEpilogue &e, int64_t row, int col, int N) {
+    Addends a = {0.0f, 0.0f, 0.0f};
+    if (e.bias) a.bias = e.bias[col];
+    if (e.table) a.table = e.table[(e.tok ? (int64_t)e.tok[row] : 0) * N + col];
+    if (e.resid) a.resid = e.resid[row * e.ldr + col];
+    return a;
+}
 template <typename T>
-__device__ __forceinline__ void epilogue_store(const GemmEpilogue &e, int64_t row, int col, int N, float v) {
-    if (e.bias) v += e.bias[col];
-    if (e.table) {
-        int64_t tr = e.tok ? (int64_t)e.tok[row] : 0;
-        v += e.table[tr * N + col];
-    }
+__device__ __forceinline__ void epilogue_store(const GemmEpilogue &e, int64_t row, int col, float v, const Addends &a) {
+    if (e.bias) v += a.bias;
+    if (e.table) v += a.table;
     if (e.act == ACT_SILU) v = v / (1.0f + __expf(-v));
-    if (e.resid) v += e.resid[row * e.ldr + col];
+    if (e.resid) v += a.resid;
     if (e.out_f32)
         ((float *)e.C)[row * e.ldc + col] = v;
     else
@@ -90,7 +95,7 @@ __global__ __launch_bounds__(256) void gemm_simple(const T *__restrict__ A, int6
             if (row < M && col < N) {
                 float v = acc[i][j];
                 if (epi.a_scale) v *= epi.a_scale[row] * epi.w_scale;
-                epilogue_store<TO>(epi, row, col, N, v);
+                epilogue_store<TO>(epi, row, col, v, epilogue_addends(epi, row, col, N));
             }
         }
 }
@@ -126,8 +131,62 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
         w[g] = W + (int64_t)(wr < N ? wr : N - 1) * ldw + k4;
     }
     __shared__ float rinv[16];
+    const int nb = (K + KB - 1) / KB, per = (nb + 3) / 4;  // blocks of KB values of k; blocks in a quarter
+    floatx4 av[UN][G], wv[UN][G];
+    auto load = [&](int b, int b1) {
+#pragma unroll
+        for (int u = 0; u < UN; u++) {
+            const int k = (b + u) * KB + k4;
+#pragma unroll
+            for (int g = 0; g < G; g++) {
+                av[u][g] = wv[u][g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (b + u < b1 && k < K) {
+                    av[u][g] = *(const floatx4 *)(a[g] + (int64_t)(b + u) * KB);
+                    wv[u][g] = *(const floatx4 *)(w[g] + (int64_t)(b + u) * KB);
+                }
+            }
+        }
+    };
+    auto scale = [&](int b, int b1) {  // A = RMSNorm(pre_x)
+#pragma unroll
+        for (int u = 0; u < UN; u++) {
+            const int k = (b + u) * KB + k4;
+            if (b + u < b1 && k < K) av[u][0] = *(const floatx4 *)((const float *)epi.pre_gain + k) * av[u][0] * rinv[lane % 16];
+        }
+    };
+    auto multiply = [&](floatx4 (&acc)[G][G]) {
+#pragma unroll
+        for (int u = 0; u < UN; u++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+                for (int i = 0; i < G; i++)
+#pragma unroll
+                    for (int j = 0; j < G; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], wv[u][j][e], acc[i][j], 0, 0, 0);
+    };
+    auto quarter = [&](int s, floatx4 (&acc)[G][G], bool loaded) {  // loaded: the first blocks are there (scaled)
+        const int b0 = s * per, b1 = b0 + per < nb ? b0 + per : nb;
+#pragma unroll
+        for (int i = 0; i < G; i++)
+#pragma unroll
+            for (int j = 0; j < G; j++) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int b = b0; b < b1; b += UN) {
+            if (!loaded || b > b0) {
+                load(b, b1);
+                if constexpr (T == 16)
+                    if (epi.pre_x) scale(b, b1);
+            }
+            multiply(acc);
+        }
+    };
+    Addends add = {0.0f, 0.0f, 0.0f};
     if constexpr (T == 16) {
-        if (epi.pre_x) {  // A = RMSNorm(pre_x): 1/rms of the tile's rows, four per wavefront (the loads below take the gain), as rmsnorm_kernel has it
+        // Every memory latency of the tile at once: the first operand blocks and what the epilogue adds are requested before the rows are summed up.
+        const int64_t row = m0 + threadIdx.x / 16;
+        const int col = n0 + threadIdx.x % 16, b0 = wave * per;
+        load(b0, b0 + per < nb ? b0 + per : nb);
+        if (row < M && col < N) add = epilogue_addends(epi, row, col, N);
+        if (epi.pre_x) {  // 1/rms of the tile's rows, four per wavefront, as rmsnorm_kernel has it
             float ss[4] = {};
             for (int k = lane * 4; k < K; k += 256)
 #pragma unroll
@@ -142,45 +201,13 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
                 if (lane == 0) rinv[wave + 4 * q] = 1.0f / sqrtf(ss[q] / (float)K + epi.pre_eps);
             }
             __syncthreads();
+            scale(b0, b0 + per < nb ? b0 + per : nb);
         }
     }
-    const int nb = (K + KB - 1) / KB, per = (nb + 3) / 4;  // blocks of KB values of k; blocks in a quarter
-    auto quarter = [&](int s, floatx4 (&acc)[G][G]) {
-        const int b0 = s * per, b1 = b0 + per < nb ? b0 + per : nb;
-#pragma unroll
-        for (int i = 0; i < G; i++)
-#pragma unroll
-            for (int j = 0; j < G; j++) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int b = b0; b < b1; b += UN) {
-            floatx4 av[UN][G], wv[UN][G];
-#pragma unroll
-            for (int u = 0; u < UN; u++) {
-                const int k = (b + u) * KB + k4;
-#pragma unroll
-                for (int g = 0; g < G; g++) {
-                    av[u][g] = wv[u][g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-                    if (b + u < b1 && k < K) {
-                        av[u][g] = *(const floatx4 *)(a[g] + (int64_t)(b + u) * KB);
-                        wv[u][g] = *(const floatx4 *)(w[g] + (int64_t)(b + u) * KB);
-                        if constexpr (T == 16)
-                            if (epi.pre_x) av[u][g] = *(const floatx4 *)((const float *)epi.pre_gain + k) * av[u][g] * rinv[lane % 16];
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UN; u++)
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-#pragma unroll
-                    for (int i = 0; i < G; i++)
-#pragma unroll
-                        for (int j = 0; j < G; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], wv[u][j][e], acc[i][j], 0, 0, 0);
-        }
-    };
     floatx4 acc[G][G];
     // accumulators: column lane % 16, row 4 * (lane / 16) + v
     if constexpr (T == 16) {
-        quarter(wave, acc);
+        quarter(wave, acc, true);
         __shared__ float part[4][256];
 #pragma unroll
         for (int v = 0; v < 4; v++) part[wave][(4 * (lane / 16) + v) * 16 + lane % 16] = acc[0][0][v];
@@ -188,7 +215,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
         const int t = threadIdx.x;
         const int64_t row = m0 + t / 16;
         const int col = n0 + t % 16;
-        if (row < M && col < N) epilogue_store<float>(epi, row, col, N, (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]));
+        if (row < M && col < N) epilogue_store<float>(epi, row, col, (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]), add);
     } else {
         floatx4 low[G][G], high[G][G];
         auto join = [&](floatx4 (&sum)[G][G]) {
@@ -197,11 +224,11 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
 #pragma unroll
                 for (int j = 0; j < G; j++) sum[i][j] += acc[i][j];
         };
-        quarter(0, low);
-        quarter(1, acc);
+        quarter(0, low, false);
+        quarter(1, acc, false);
         join(low);
-        quarter(2, high);
-        quarter(3, acc);
+        quarter(2, high, false);
+        quarter(3, acc, false);
         join(high);
 #pragma unroll
         for (int i = 0; i < G; i++)
@@ -211,7 +238,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
                 for (int v = 0; v < 4; v++) {
                     const int64_t row = m0 + i * 16 + 4 * (lane / 16) + v;
                     const int col = n0 + j * 16 + lane % 16;
-                    if (row < M && col < N) epilogue_store<float>(epi, row, col, N, low[i][j][v] + high[i][j][v]);
+                    if (row < M && col < N) epilogue_store<float>(epi, row, col, low[i][j][v] + high[i][j][v], epilogue_addends(epi, row, col, N));
                 }
     }
 }
@@ -788,8 +815,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                             if (HAS_ADD) x += adds[it];
                             if (emit) {  // (as below)
                                 float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
-                                sq += __shfl_xor(sq, 1, 64);
-                                sq += __shfl_xor(sq, 2, 64);
+                                sq += lane_xor1(sq);
+                                sq += lane_xor2(sq);
                                 sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x114, 0xf, 0xf, true));
                                 sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x118, 0xf, 0xf, true));
                                 if (lane % 16 == 15) ssp[(int64_t)(it * 4) * (N / 64)] = sq;
@@ -820,8 +847,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring(const bf16 *__restrict__ A
                         if (HAS_ADD) x += adds[it];  // (zero where the lane stores nothing or takes the slow path below)
                         if (emit) {  // sum of squares over the row's 64 columns in this wave: the 16 lanes of a DPP row
                             float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
-                            sq += __shfl_xor(sq, 1, 64);
-                            sq += __shfl_xor(sq, 2, 64);  // every lane: its quad's sum
+                            sq += lane_xor1(sq);
+                            sq += lane_xor2(sq);  // every lane: its quad's sum
                             // row_shr:4 then row_shr:8 (lane i takes lane i-4 / i-8 of its row, 0 if there is none): lane 15 of the
                             // row ends with all four quads
                             sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x114, 0xf, 0xf, true));
@@ -1084,8 +1111,8 @@ __device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], floatx4 
                 if (KIND != EPI_F32) x += adds[pass][it];
                 if (emit) {  // sum of squares over the row's 64 columns of this wavefront: the same tree as in the persistent kernel
                     float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
-                    sq += __shfl_xor(sq, 1, 64);
-                    sq += __shfl_xor(sq, 2, 64);
+                    sq += lane_xor1(sq);
+                    sq += lane_xor2(sq);
                     sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x114, 0xf, 0xf, true));
                     sq += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sq), 0x118, 0xf, 0xf, true));
                     if (lane % 16 == 15 && row < M) epi.norm_ss[row * (N / 64) + (wcol0 >> 6)] = sq;
