@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
     if (rows_dev) rows = rows_dev[0];
     if (row >= rows) return;
     const int nvec = d / N;
-    float v[MAXV][N];
+    float v[MAXV][N], gg[MAXV][N];
     float ss = 0.0f;
 #pragma unroll
     for (int i = 0; i < MAXV; i++) {
@@ -44,6 +44,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
         if (c < nvec) {
 #pragma unroll
             for (int e = 0; e < N; e += 4) load16<float>(x + row * d + (int64_t)c * N + e, &v[i][e]);
+            load16<T>(g + (int64_t)c * N, gg[i]);  // (on its way beside the row: its latency would follow the sum)
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MAXV; i++) {
+        int c = lane + i * 64;
+        if (c < nvec) {
             if constexpr (N == 4) {
                 ss += sum_sq4(v[i][0], v[i][1], v[i][2], v[i][3]);
             } else {
@@ -59,10 +66,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
     for (int i = 0; i < MAXV; i++) {
         int c = lane + i * 64;
         if (c < nvec) {
-            float gg[N];
-            load16<T>(g + (int64_t)c * N, gg);
 #pragma unroll
-            for (int e = 0; e < N; e++) v[i][e] = gg[e] * v[i][e] * inv;
+            for (int e = 0; e < N; e++) v[i][e] = gg[i][e] * v[i][e] * inv;
             store16<T>(y + row * d + (int64_t)c * N, v[i]);
         }
     }
