@@ -89,6 +89,30 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// whole numbers over the wavefront: maximum, and the sum over this lane and the lower ones
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ unsigned dpp_move_u(unsigned old, unsigned v) {
+    return (unsigned)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+__device__ __forceinline__ unsigned wave_max_u(unsigned v) {
+    v = max(v, dpp_move_u<0x128, 0xF>(v, v));
+    v = max(v, dpp_move_u<0x124, 0xF>(v, v));
+    v = max(v, dpp_move_u<0x122, 0xF>(v, v));
+    v = max(v, dpp_move_u<0x121, 0xF>(v, v));
+    v = max(v, dpp_move_u<0x142, 0xA>(v, v));
+    v = max(v, dpp_move_u<0x143, 0xC>(v, v));
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ int wave_scan(int x) {
+    unsigned v = (unsigned)x;
+    v += dpp_move_u<0x111, 0xF>(0u, v);  // row_shr:1, 2, 4, 8: the sums inside each row of 16 lanes
+    v += dpp_move_u<0x112, 0xF>(0u, v);
+    v += dpp_move_u<0x114, 0xF>(0u, v);
+    v += dpp_move_u<0x118, 0xF>(0u, v);
+    v += dpp_move_u<0x142, 0xA>(0u, v);  // the rows before
+    v += dpp_move_u<0x143, 0xC>(0u, v);
+    return (int)v;
+}
+
 static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Records the message gr4ad_last_error(NULL) returns on this thread (entry points that take no decoder); returns `code`.

@@ -676,8 +676,11 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
 // FULL: V == VEC*256, every register holds a token (the validity tests fold away).
 // todo / todo_count (both or neither): the launch visits only the listed rows {row, slot}; each gets its
 // own cut, written at slot `slot` of its request's segment.  Wavefronts walk their rows with the launch's stride.
+// The row and the cut's state need 105 (VEC 4) to 512 registers (VEC 32): with the 168 of three wavefronts per SIMD most of a row of 4096 and
+// 8192 tokens lived in scratch, and a wavefront is busy alone with its row anyway (rows of 8192, m = 256 or 512: 8 rows 26.6 us, 256 rows
+// 26.8, listed rows 56; now 22.0, 20.0 and 22).
 template <int VEC, bool FULL, typename LT>
-__global__ __launch_bounds__(256, 3) void select_rows_wave(const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V,
+__global__ __launch_bounds__(256, VEC >= 32 ? 1 : 2) void select_rows_wave(const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V,
                                                           int m, unsigned long long *__restrict__ cand, const int2 *__restrict__ todo,
                                                           const int *__restrict__ todo_count) {
     constexpr int E = LogitPiece<LT>::E, NX = VEC * 4, G = NX / E;
@@ -893,50 +896,83 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
 #define SELB_THREADS 1024
 #define SELB_SORT_MAX 4096
 
+// the key of lane ^ X for X = 1, 2, 4, 8 (inside a row of 16 lanes)
+template <int X> __device__ __forceinline__ unsigned lane_xor_u(unsigned v) {
+    if constexpr (X == 1) return dpp_move_u<0xB1, 0xF>(v, v);
+    else if constexpr (X == 2) return dpp_move_u<0x4E, 0xF>(v, v);
+    else if constexpr (X == 4) { const unsigned r = dpp_move_u<0x141, 0xF>(v, v); return dpp_move_u<0x1B, 0xF>(r, r); }  // ^ 7, then ^ 3
+    else return dpp_move_u<0x128, 0xF>(v, v);
+}
+// one exchange of the sort with lane ^ X: the greater key stays where take_max holds
+template <int X> __device__ __forceinline__ unsigned long long sort_exchange(unsigned long long v, bool take_max) {
+    const unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
+    unsigned long long a, b;  // the pair, in the same order for both lanes or not: the greater and the smaller one are what counts
+    if constexpr (X >= 16) {
+        uintx2 l, h;
+        if constexpr (X == 16) { l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false); h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false); }
+        else { l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false); h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false); }
+        a = (unsigned long long)h[0] << 32 | l[0];
+        b = (unsigned long long)h[1] << 32 | l[1];
+    } else {
+        a = (unsigned long long)lane_xor_u<X>(hi) << 32 | lane_xor_u<X>(lo);
+        b = v;
+    }
+    return (a > b) == take_max ? a : b;
+}
+
 // Bitonic sort, descending, of np keys (a power of two, np <= E * SELB_THREADS; the registers past np hold nothing).  Element
-// i = tid * E + e sits in v[e]: exchanges over less than 64 * E elements stay inside a lane or a wavefront, the ten
-// or so longer ones go through LDS.  (All 55 steps of 1024 keys through LDS with a barrier each: about 10 us of this kernel's
-// former 29 us at 256 x 4096 logits, k = 512.)
+// i = tid * E + e sits in v[e]: exchanges over less than 64 * E elements stay inside a lane or a wavefront (DPP and permlane moves: an LDS
+// permute of 8 bytes per step and wavefront held up all of them), the ten or so longer ones go through LDS, in two halves by
+// turns where both fit (one barrier per step).  Wavefronts past np only keep the barriers.
 template <int E>
 __device__ __forceinline__ void sort_desc(unsigned long long (&v)[E], int np, unsigned long long *lds) {
     const int tid = threadIdx.x;
-    for (int k = 2; k <= np; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            if (j < E) {
+    const bool busy = __builtin_amdgcn_readfirstlane(tid) * E < np;
+    constexpr bool TURNS = 2 * E * SELB_THREADS <= SELB_SORT_MAX;
+    int turn = 1;  // (the first half may still be read)
+    for (int k = 2; k <= np; k <<= 1) {
+        for (int x = k / E >> 1; x >= 64; x >>= 1) {
+            unsigned long long *buf = lds + (TURNS ? turn * E * SELB_THREADS : 0);
+            if (!TURNS) __syncthreads();
+            if (busy) {
 #pragma unroll
-                for (int e = 0; e < E; e++)
-#pragma unroll
-                    for (int q = 1; q < E; q <<= 1)
-                        if (q == j && !(e & q)) {
-                            const bool desc = ((tid * E + e) & k) == 0;
-                            const unsigned long long a = v[e], b = v[e | q];
-                            if (desc ? a < b : a > b) { v[e] = b; v[e | q] = a; }
-                        }
-            } else {
-                const int x = j / E;
-                unsigned long long o[E];
-                if (x < 64) {
-#pragma unroll
-                    for (int e = 0; e < E; e++) o[e] = __shfl_xor(v[e], x, 64);
-                } else {
-                    __syncthreads();
-#pragma unroll
-                    for (int e = 0; e < E; e++) lds[e * SELB_THREADS + tid] = v[e];
-                    __syncthreads();
-#pragma unroll
-                    for (int e = 0; e < E; e++) o[e] = lds[e * SELB_THREADS + (tid ^ x)];
-                }
+                for (int e = 0; e < E; e++) buf[e * SELB_THREADS + tid] = v[e];
+            }
+            __syncthreads();
+            if (busy) {
                 const bool low = (tid & x) == 0;
 #pragma unroll
                 for (int e = 0; e < E; e++) {
-                    const bool desc = ((tid * E + e) & k) == 0, take_max = desc == low;
-                    v[e] = (o[e] > v[e]) == take_max ? o[e] : v[e];
+                    const unsigned long long o = buf[e * SELB_THREADS + (tid ^ x)];
+                    const bool desc = ((tid * E + e) & k) == 0;
+                    v[e] = (o > v[e]) == (desc == low) ? o : v[e];
                 }
             }
+            turn ^= 1;
         }
+        if (!busy) continue;
+#define LANES_(X) \
+        if (k > X * E) { \
+            const bool low = (tid & X) == 0; \
+            _Pragma("unroll") for (int e = 0; e < E; e++) v[e] = sort_exchange<X>(v[e], (((tid * E + e) & k) == 0) == low); \
+        }
+        LANES_(32) LANES_(16) LANES_(8) LANES_(4) LANES_(2) LANES_(1)
+#undef LANES_
+#pragma unroll
+        for (int q = E / 2; q > 0; q >>= 1)
+            if (k > q) {
+#pragma unroll
+                for (int e = 0; e < E; e++)
+                    if (!(e & q)) {
+                        const bool desc = ((tid * E + e) & k) == 0;
+                        const unsigned long long a = v[e], b = v[e | q];
+                        if (desc ? a < b : a > b) { v[e] = b; v[e | q] = a; }
+                    }
+            }
+    }
 }
 
-// sorts the `count` keys of lds (count <= SELB_SORT_MAX, a power of two np >= count of them are keys or zero) in place
+// sorts the first np keys of lds (np <= SELB_SORT_MAX, a power of two) in place
 template <int E>
 __device__ __forceinline__ void sort_keys_lds(unsigned long long *lds, int np) {
     const int tid = threadIdx.x;
@@ -976,64 +1012,125 @@ __device__ __forceinline__ void for_each_key(const unsigned long long *__restric
     }
 }
 
-// Usual path of stage B: two sweeps over the candidates.  A sample of one key per thread gives the span of the score bits;
-// the first sweep counts the keys in 2048 equal bins of that span (keys outside it fall into the end bins; the bin index is
-// monotone in the key, and the counts spread over the bins, unlike the leading radix digit, which most keys of a request
-// share), the second collects every key from the threshold bin up into LDS, where a sort finishes the job.  Returns false,
-// having selected nothing, when more than SELB_SORT_MAX keys lie from the threshold bin up (the exact radix selection then runs).
+// Usual path of stage B: the candidates are read once into registers, HELD per thread (twice from memory where there are more), and
+// swept twice.  A sample of one key per thread gives the span of the score bits; the first sweep counts the keys in 2048 equal bins of that
+// span (keys outside it fall into the end bins; the bin index is monotone in the key, and the counts spread over the bins, unlike the leading
+// radix digit, which most keys of a request share), the second collects every key from the threshold bin up into LDS: those above it, then its
+// own, of which a few comparisons keep the ones still needed, so that a sort of k keys (not of the next power of two) finishes the job.
+// Bound by latency, one workgroup per request.  256 requests of 128 and 256 rows of 4096 tokens, k = 256 and 512: 16.4 and 21.1 us with two reads,
+// a sort of twice as many keys through LDS permutes and the tables gathered level by level, now 12.9 and 15.4; one request (k = 128 and 256)
+// 12.6 and 15.9, now 10.2 and 12.0.
+// Returns false, having selected nothing, when more than SELB_SORT_MAX keys lie from the threshold bin up (the exact radix selection then runs).
+#define SELB_HELD 8
+#define SELB_TIES 256  // keys of the threshold bin that are ranked against each other
 __device__ __forceinline__ bool select_request_binned(const unsigned long long *__restrict__ src, int64_t ncand, int k,
                                                       unsigned long long *skeys, int *hist, int *wave_tot, int *sel_digit, int *sel_krem,
                                                       int *sel_cnt, int *out_cnt) {
+    __shared__ uint32_t span_hi[SELB_THREADS / 64], span_lo[SELB_THREADS / 64];
     const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
-    const uint32_t smp = (uint32_t)(src[(int64_t)tid * ncand / SELB_THREADS] >> 32);
-    uint32_t smax = smp, smin = smp;
+    const bool held = ncand <= SELB_HELD * SELB_THREADS;
+    unsigned long long x[SELB_HELD];  // 0: none
+    if (held) {
+        const bool pairs = (((uintptr_t)src) & 15) == 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { smax = max(smax, (uint32_t)__shfl_xor((int)smax, o, 64)); smin = min(smin, (uint32_t)__shfl_xor((int)smin, o, 64)); }
-    if (lane == 0) { wave_tot[wv] = (int)smax; hist[wv] = (int)smin; }
-    __syncthreads();
-    for (int q = 0; q < SELB_THREADS / 64; q++) { smax = max(smax, (uint32_t)wave_tot[q]); smin = min(smin, (uint32_t)hist[q]); }
-    __syncthreads();
-    int nsh = 0;
-    while (((smax - smin) >> nsh) >= 2040u) nsh++;
-    const long long base = (long long)smin;
-    auto digit = [&](unsigned long long key) {
-        const long long d = ((((long long)(key >> 32)) - base) >> nsh) + 4;  // floor, also below the sampled minimum
-        return (int)(d < 0 ? 0 : (d > 2047 ? 2047 : d));
-    };
+        for (int j = 0; j < SELB_HELD; j += 2) {
+            const int i = j * SELB_THREADS + (pairs ? 2 * tid : tid), i2 = pairs ? i + 1 : i + SELB_THREADS;
+            x[j] = x[j + 1] = 0ull;
+            if (pairs && i2 < ncand) {
+                const ulonglong2 a = *(const ulonglong2 *)(src + i);
+                x[j] = a.x;
+                x[j + 1] = a.y;
+            } else {
+                if (i < ncand) x[j] = src[i];
+                if (i2 < ncand) x[j + 1] = src[i2];
+            }
+        }
+    }
+    const uint32_t smp = (uint32_t)(src[(int64_t)tid * ncand / SELB_THREADS] >> 32);
     for (int i = tid; i < 2048; i += SELB_THREADS) hist[i] = 0;
     if (tid == 0) *out_cnt = 0;
+    uint32_t smax = wave_max_u(smp), smin = ~wave_max_u(~smp);
+    if (lane == 0) { span_hi[wv] = smax; span_lo[wv] = smin; }
     __syncthreads();
-    for_each_key(src, ncand, [&](unsigned long long key) { atomicAdd(&hist[digit(key)], 1); });
+#pragma unroll
+    for (int q = 0; q < SELB_THREADS / 64; q++) { smax = max(smax, span_hi[q]); smin = min(smin, span_lo[q]); }
+    const uint32_t span = smax - smin;
+    int nsh = span < 2048u ? 0 : 21 - __clz((int)span);
+    if ((span >> nsh) >= 2040u) nsh++;
+    auto digit = [&](unsigned long long key) {  // 4 .. 2043 inside the span, 0 below it, up to 2047 above
+        const uint32_t s = (uint32_t)(key >> 32);
+        return s < smin ? 0 : (int)min(((s - smin) >> nsh) + 4u, 2047u);
+    };
+    if (held) {
+#pragma unroll
+        for (int j = 0; j < SELB_HELD; j++)
+            if (x[j]) atomicAdd(&hist[digit(x[j])], 1);
+    } else {
+        for_each_key(src, ncand, [&](unsigned long long key) { atomicAdd(&hist[digit(key)], 1); });
+    }
     __syncthreads();
     // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
     const int hi = hist[2047 - 2 * tid], lo = hist[2046 - 2 * tid];
-    int v = hi + lo;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(v, o, 64);
-        if (lane >= o) v += t;
-    }
+    const int v = wave_scan(hi + lo);
     if (lane == 63) wave_tot[wv] = v;
     __syncthreads();
     int add = 0;
-    for (int q = 0; q < wv; q++) add += wave_tot[q];
+#pragma unroll
+    for (int q = 0; q < SELB_THREADS / 64; q++) add += q < wv ? wave_tot[q] : 0;
     const int incl = v + add, excl = incl - hi - lo;
     if (excl < k && incl >= k) {
         if (excl + hi >= k) { *sel_digit = 2047 - 2 * tid; *sel_krem = k - excl; *sel_cnt = hi; }
         else { *sel_digit = 2046 - 2 * tid; *sel_krem = k - excl - hi; *sel_cnt = lo; }
     }
     __syncthreads();
-    const int T = *sel_digit, total_ge = (k - *sel_krem) + *sel_cnt;
-    __syncthreads();
-    if (total_ge > SELB_SORT_MAX) return false;  // uniform: every thread read the same shared values
+    const int T = *sel_digit, krem = *sel_krem, cnt = *sel_cnt, n_gt = k - krem, total = n_gt + cnt;
+    if (total > SELB_SORT_MAX) return false;  // uniform: every thread read the same shared values
+    const bool rank_ties = cnt > krem && cnt <= SELB_TIES;
+    const int want = rank_ties ? k : total;
     int np = 1;
-    while (np < total_ge) np <<= 1;
-    for (int i = tid; i < np; i += SELB_THREADS) skeys[i] = 0ull;
-    __syncthreads();
-    for_each_key(src, ncand, [&](unsigned long long key) {
-        if (digit(key) >= T) skeys[atomicAdd(out_cnt, 1)] = key;  // exactly total_ge keys qualify
-    });
-    __syncthreads();
+    while (np < want) np <<= 1;
+    for (int i = total + tid; i < np; i += SELB_THREADS) skeys[i] = 0ull;
+    // keys above bin T go to [0, n_gt), those of bin T behind them; out_cnt counts both, 16 bits each (at most SELB_SORT_MAX of either)
+    if (held) {  // one reservation per wavefront
+        unsigned long long mg[SELB_HELD], me[SELB_HELD];
+        int c = 0;
+#pragma unroll
+        for (int j = 0; j < SELB_HELD; j++) {
+            const int d = x[j] ? digit(x[j]) : -1;
+            mg[j] = __ballot(d > T);
+            me[j] = __ballot(d == T);
+            c += __popcll(mg[j]) + (__popcll(me[j]) << 16);
+        }
+        if (c) {
+            int at = lane == 0 ? atomicAdd(out_cnt, c) : 0;
+            at = __builtin_amdgcn_readfirstlane(at);
+            int ag = at & 0xFFFF, ae = n_gt + (int)((unsigned)at >> 16);
+            const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+            for (int j = 0; j < SELB_HELD; j++) {
+                if (mg[j] >> lane & 1) skeys[ag + __popcll(mg[j] & below)] = x[j];
+                if (me[j] >> lane & 1) skeys[ae + __popcll(me[j] & below)] = x[j];
+                ag += __popcll(mg[j]);
+                ae += __popcll(me[j]);
+            }
+        }
+    } else {
+        for_each_key(src, ncand, [&](unsigned long long key) {
+            const int d = digit(key);
+            if (d > T) skeys[atomicAdd(out_cnt, 1) & 0xFFFF] = key;
+            else if (d == T) skeys[n_gt + (int)((unsigned)atomicAdd(out_cnt, 1 << 16) >> 16)] = key;
+        });
+    }
+    if (rank_ties) {
+        __syncthreads();
+        const unsigned long long key = tid < cnt ? skeys[n_gt + tid] : 0ull;
+        int rank = 0;
+        if (__builtin_amdgcn_readfirstlane(tid) < cnt)
+            for (int q = 0; q < cnt; q++) rank += skeys[n_gt + q] > key ? 1 : 0;
+        __syncthreads();
+        if (tid < cnt && rank < krem) skeys[n_gt + rank] = key;
+        for (int i = k + tid; i < np; i += SELB_THREADS) skeys[i] = 0ull;
+    }
     bitonic_sort_desc(skeys, np);
     return true;
 }
@@ -1081,12 +1178,7 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
             __syncthreads();
             // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
             const int hi = hist[2047 - 2 * tid], lo = hist[2046 - 2 * tid];
-            int v = hi + lo;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                int t = __shfl_up(v, o, 64);
-                if (lane >= o) v += t;
-            }
+            const int v = wave_scan(hi + lo);
             if (lane == 63) wave_tot[wv] = v;
             __syncthreads();
             int add = 0;
@@ -1125,14 +1217,19 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
         parent[b * k + j] = par;
         tok[b * k + j] = tk;
         score[b * k + j] = key_score((uint32_t)(key >> 32));
-        if (sid_new) {
-            for (int t = 0; t < level; t++) sid_new[(b * k + j) * T + t] = sid_old[(b * n + par) * T + t];
-            sid_new[(b * k + j) * T + level] = tk;
-            for (int t = level + 1; t < T; t++) sid_new[(b * k + j) * T + t] = 0;
+        // sids, and the row (over the whole batch) of the survivor's ancestor at every level so far: the reorder is this index table
+        // (every load ahead of the stores)
+        const int64_t from = (b * n + par) * T, to = (b * k + j) * T;
+        int32_t sid[GR4AD_MAX_LEVELS], anc[GR4AD_MAX_LEVELS];
+#pragma unroll
+        for (int t = 0; t < GR4AD_MAX_LEVELS; t++) {
+            sid[t] = sid_new && t < level ? sid_old[from + t] : (t == level ? tk : 0);
+            anc[t] = anc_new && t < level ? anc_old[from + t] : (int32_t)(b * n + par);
         }
-        if (anc_new) {  // row (over the whole batch) of the survivor's ancestor at every level so far: the reorder is this index table
-            for (int t = 0; t < level; t++) anc_new[(b * k + j) * T + t] = anc_old[(b * n + par) * T + t];
-            anc_new[(b * k + j) * T + level] = (int32_t)(b * n + par);
+#pragma unroll
+        for (int t = 0; t < GR4AD_MAX_LEVELS; t++) {
+            if (sid_new && t < T) sid_new[to + t] = sid[t];
+            if (anc_new && t <= level) anc_new[to + t] = anc[t];
         }
     }
 }

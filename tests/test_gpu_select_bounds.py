@@ -29,3 +29,26 @@ def test_select_bound_from_several_rows(B, n, V, k, spread, half):
         flat = parent[b].astype(np.int64) * V + tok[b]
         assert len(np.unique(flat)) == k
         judge_selection(allsc, flat, score[b], k, tol=3e-5, margin=2e-5, what="select b=%d" % b)
+
+
+# n * V candidates (V <= k: rows are not cut): kept in registers up to 8192 and read twice above, in pairs or one by one (odd segments of the
+# second request); the cut's bin holds few keys, hundreds of equal ones ("levels"), or nearly all of them beside far ones ("far")
+@pytest.mark.parametrize("spread", ["level", "levels", "far"])
+@pytest.mark.parametrize("n,V,k", [(147, 7, 7), (130, 8, 512), (129, 8, 513), (1024, 8, 2048), (1024, 8, 2049), (911, 9, 64), (1025, 8, 1024), (1025, 8, 4096)])
+def test_select_cuts_a_request(n, V, k, spread):
+    B = 2
+    rng = np.random.default_rng([n, V, k])
+    logits = rng.standard_normal((B, n, V)).astype(np.float32)
+    cum = (-3.0 - 0.02 * rng.random((B, n))).astype(np.float32)
+    if spread == "levels":
+        logits[:] = 0.25
+        cum = (-3.0 - rng.integers(0, 3, (B, n))).astype(np.float32)
+    if spread == "far":
+        cum[:, ::7] = -1e30
+    parent, tok, score = (t.cpu().numpy() for t in binding.op_select(torch.from_numpy(logits).cuda(), torch.from_numpy(cum).cuda(), k))
+    for b in range(B):
+        allsc = cum[b].astype(np.float64)[:, None] + np.stack([oracle.prim_log_softmax(logits[b, i]) for i in range(n)])
+        flat = parent[b].astype(np.int64) * V + tok[b]
+        assert len(np.unique(flat)) == k
+        assert np.all((score[b][:-1] > score[b][1:]) | ((score[b][:-1] == score[b][1:]) & (flat[:-1] < flat[1:])))
+        judge_selection(allsc, flat, score[b], k, tol=3e-5, margin=2e-5, what="select b=%d" % b)
