@@ -1057,9 +1057,9 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
     const uint32_t span = smax - smin;
     int nsh = span < 2048u ? 0 : 21 - __clz((int)span);
     if ((span >> nsh) >= 2040u) nsh++;
-    auto digit = [&](unsigned long long key) {  // 4 .. 2043 inside the span, 0 below it, up to 2047 above
+    auto digit = [&](unsigned long long key) {  // 4 .. 2043 inside the span, 0 below it, up to 2047 above (the addition cannot wrap)
         const uint32_t s = (uint32_t)(key >> 32);
-        return s < smin ? 0 : (int)min(((s - smin) >> nsh) + 4u, 2047u);
+        return s < smin ? 0 : (int)(min((s - smin) >> nsh, 2043u) + 4u);
     };
     if (held) {
 #pragma unroll

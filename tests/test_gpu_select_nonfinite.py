@@ -71,6 +71,18 @@ def test_select_of_scores_that_are_no_numbers(B, n, V, k, where, kind, half):
         assert np.array_equal(flat[at[2]:], none[:take[3]]) and np.isnan(score[b, at[2]:]).all()
 
 
+@pytest.mark.parametrize("high", [0x7FFFFFFF, 0x7FFFFFFC, 0x7F800000, 0x3F800000])
+def test_select_cut_spans_all_score_keys(high):
+    """Without a bound a request's candidates rank by their score keys, whatever the scores are.  All candidates but one carry the NaN of the lowest
+    key, the other one (not among the cut's samples, every second candidate) a score of a far higher key, up to the highest there is."""
+    n, k, at = 2048, 5, 1027
+    cum = np.full((1, n), 0xFFFFFFFF, np.uint32)
+    cum[0, at] = high
+    parent, tok, score = (t.cpu().numpy() for t in binding.op_select(torch.zeros(1, n, 1, device="cuda"), torch.from_numpy(cum.view(np.int32)).cuda().view(torch.float32), k))
+    assert parent.tolist() == [[at, 0, 1, 2, 3]] and not tok.any()
+    assert score.view(np.uint32)[0].tolist() == [high] + [0xFFFFFFFF] * (k - 1)
+
+
 @pytest.mark.parametrize("dtype,B,d", [("f32", 5, 128), ("bf16", 140, 256)])
 def test_request_of_nan_contexts_leaves_the_others_alone(dtype, B, d):
     w = synth.Workload("poisoned", dtype, B, 24, d, 3, 1, 4, 2 * d, 3, [264, 96, 512], [64, 64, 64])
