@@ -14,6 +14,7 @@ LIB = os.path.join(HERE, "libgr4ad.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 SOURCES = ["gemm.hip", "attention.hip", "elementwise.hip", "select.hip", "profile.hip", "decoder.hip", "serving.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
+         "-falign-loops=64",  # (a loop across a line of instructions more: 64x64 tiles, K = 4096, float32 16.9 us, aligned 14.9)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 

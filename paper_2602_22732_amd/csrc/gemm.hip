@@ -9,12 +9,14 @@
 //  * gemm_simple<T>      64x64 tile, plain FMA, any shape; fallback.
 //  * gemm_f32_mfma<T>    float32 operands on the matrix cores.
 //  * gemm_bf16_tile<..>  bf16 operands, fp32 accumulation on the matrix cores with
-//                        v_mfma_f32_32x32x16_bf16; 32x32 to 256x128 tiles for the
-//                        small and middle shapes, operands streamed into LDS by
-//                        wavefronts of their own.
+//                        v_mfma_f32_32x32x16_bf16; 32x32 to 128x128 tiles for the
+//                        small and middle shapes, operands streamed into LDS,
+//                        by wavefronts of their own where tiles are few.
 //  * gemm_bf16_ring<..>  the kernel of the large shapes: persistent, 256x256 tiles,
 //                        operands stream global -> LDS without passing registers.
 #include <string.h>
+
+#include <algorithm>
 
 #include <type_traits>
 
@@ -1002,12 +1004,16 @@ static int epilogue_kind(const GemmEpilogue &e) {
 // MFMA kernel of the small and middle shapes: one output tile per workgroup, ring of ST k-tiles in LDS
 // ---------------------------------------------------------------------------
 // The persistent kernel needs about one 256x256 tile per compute unit; a decode of a few requests has products of 1 to a few
-// thousand rows, whose time is the latency of one tile.  So the tiles are small (32x32 to 256x128) to spread over the chip, and the work of a
+// thousand rows, whose time is the latency of one tile.  So the tiles are small (32x32 to 128x128) to spread over the chip, and the work of a
 // workgroup is divided: wavefronts of their own (NL loaders) stream the operands from global memory into an LDS ring of ST k-tiles (64 values of
 // k) and the others multiply.  A wavefront issues a 1 KB load every 25 to 35 cycles while its data comes from beyond the L1, so a wavefront that
 // multiplied and loaded spent more cycles issuing the eight loads of its k-tile (264) than on its four MFMAs (144), and none of its MFMAs ran before
 // the first ST k-tiles were requested: M = 32, N = K = 512 took 4.0 us with the loads between the MFMAs of 32x64 tiles, now 3.3 (an empty kernel: 2.35);
 // N = K = 1024 5.3, now 4.0; N = 1024, K = 4096 17.1, now 8.5 to 10.8; on 128x128 tiles M = 4096, N = K = 1024 13.5, now 12.2.
+// NL = 0: every wavefront loads its share of the k-tiles itself, and two (128x128, 64 KB of LDS) or three (64x64) workgroups share a compute unit: one's
+// epilogue runs beside another's k-loop.  For launches of several rounds, where the loaders' one workgroup per unit has nothing beside its epilogue: 8192 x 1024 x 1024 with a
+// residual 36.6 us with loaders, 27.6 without; sixteen batches of 8192 x 1024 x 64 105 and 71; 64x64 tiles 8000 x 1024 x 1024 float32 32.5 and 30.4.  LDS is
+// only asked for the k-tiles that exist (K = 64: one).
 // Same LDS geometry as the persistent kernel: 128-byte rows, chunk c of row r at position c ^ ((r >> 1) & 7).  One barrier per k-tile: the loaders
 // pass it when the k-tile has landed, the others when the one before (32x32 blocks: the one before that) has left LDS.  A product of one C
 // element is the same sequence of v_mfma_f32_32x32x16 over k as in the persistent kernel: the two give the same bits.
@@ -1032,8 +1038,8 @@ __device__ __forceinline__ void staged_addends(floatx4 (&adds)[8], int64_t row0,
     }
 }
 
-template <int KIND, int TM, bool LATE>
-__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], floatx4 (&adds)[TM][8], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
+template <int KIND, int TM>
+__device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], const floatx4 (&adds)[TM][8], char *stage, int64_t wrow0, int wcol0, int64_t M, int N,
                                                 const GemmEpilogue &epi, int lane) {
     const int frow = lane % 32, hf = lane / 32;
     if (epi.row_inv) {  // folded RMSNorm, reader side: a lane owns row frow of each 32-row block
@@ -1091,7 +1097,6 @@ __device__ __forceinline__ void staged_epilogue(floatx16 (&acc)[TM][2], floatx4 
         }
 #pragma unroll
         for (int pass = 0; pass < TM; pass++) {
-            if (LATE) staged_addends<KIND>(adds[pass], wrow0 + pass * 32, wcol0, M, N, epi, lane);
 #pragma unroll
             for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -1234,12 +1239,15 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
                                                                                     int64_t ldw, int64_t M, int N, int K, int tiles_m, int tiles_n,
                                                                                     GemmEpilogue epi, int64_t batch_a, int64_t batch_w, int64_t batch_c) {
     constexpr int WAVES_N = BN / WN, NC = (BM / WM) * WAVES_N, TM = WM / 32, TN = WN / 32;
-    constexpr int LPW = (BM + BN) / 8 / NL;           // loads of a loader per k-tile (1 KB each: 8 rows)
+    constexpr bool OWN = NL == 0;                     // the wavefronts load what they multiply
+    constexpr int NLW = OWN ? NC : NL;                // wavefronts that load
+    constexpr int LPW = (BM + BN) / 8 / NLW;          // loads of each per k-tile (1 KB each: 8 rows)
     constexpr int STAGE = (BM + BN) * 128;            // bytes of a k-tile
     constexpr bool SWAP = STAGED || KIND == EPI_VT;   // W fragment first
-    constexpr bool ONE = TM * TN == 1;                // one 32x32 block per wavefront: a whole k-tile of fragments ahead
+    constexpr bool ONE = TM * TN == 1 && !OWN;        // one 32x32 block per wavefront: a whole k-tile of fragments ahead
     constexpr int LAG = ONE ? 2 : 1;                  // past barrier j the slots of k-tiles up to j - LAG are free
-    static_assert((BM + BN) / 8 % NL == 0 && (ST - 1) * LPW <= 63 && ST > LAG, "load counts");
+    constexpr int LA = BM / 8 / NLW;                  // the first of them fetch rows of A, the others rows of W
+    static_assert(BM / 8 % NLW == 0 && BN / 8 % NLW == 0 && (ST - 1) * LPW <= 63 && ST > LAG && (!OWN || ST <= 3), "load counts");
     static_assert(!STAGED || WN == 64, "the staged epilogue takes wave tiles of 64 columns");
     extern __shared__ bf16x8 smem[];
     const int lane = threadIdx.x % 64;
@@ -1282,11 +1290,13 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    if (wave >= NC) {
-        // ---- loader: piece p = i * NL + me fills rows 8p .. 8p+7 of the k-tile's BM rows of A and BN rows of W, lane -> row lane/8,
-        // position lane%8 (rows past the matrix edge re-read its last row) ----
-        // A lane's byte offset in its operand block stays, the two block addresses move on: no vector arithmetic per k-tile.
-        const int me = wave - NC;
+    // ---- loads: piece p = i * NLW + me fills rows 8p .. 8p+7 of the k-tile's BM rows of A and BN rows of W, lane -> row lane/8,
+    // position lane%8 (rows past the matrix edge re-read its last row) ----
+    // A lane's byte offset in its operand block stays, the two block addresses move on: no vector arithmetic per k-tile.
+    const int me = OWN ? wave : wave - NC;
+    const char *base_a, *base_w;
+    uint32_t off[LPW];
+    auto start = [&]() {
         auto source = [&](int64_t row) -> int64_t {  // row of A behind row `row` of C
             const int64_t r = row < M ? row : M - 1;
             if (KIND != EPI_VT) return r;
@@ -1294,32 +1304,35 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
             return (int64_t)b * epi.vt_rows + (t < (uint32_t)epi.vt_rows ? t : (uint32_t)epi.vt_rows - 1);
         };
         const int64_t first_row = source(m0);
-        const char *base_a = (const char *)(A + first_row * lda), *base_w = (const char *)(W + (int64_t)n0 * ldw);
-        uint32_t off[LPW];
+        base_a = (const char *)(A + first_row * lda);
+        base_w = (const char *)(W + (int64_t)n0 * ldw);
 #pragma unroll
         for (int i = 0; i < LPW; i++) {
-            const int p = i * NL + me, r = p * 8 + lane / 8, chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
-            if (p < BM / 8) off[i] = (uint32_t)(source(m0 + r) - first_row) * ((uint32_t)lda * 2) + chunk * 16;
+            const int p = i * NLW + me, r = p * 8 + lane / 8, chunk = (lane % 8) ^ ((4 * (p & 1)) ^ (lane / 16));
+            if (i < LA) off[i] = (uint32_t)(source(m0 + r) - first_row) * ((uint32_t)lda * 2) + chunk * 16;
             else off[i] = (uint32_t)(n0 + r - BM < N ? r - BM : N - 1 - n0) * ((uint32_t)ldw * 2) + chunk * 16;
         }
-        auto issue = [&](uint32_t at) {  // k-tiles are requested in ascending order; at: byte offset of the slot
+    };
+    auto issue = [&](uint32_t at) {  // k-tiles are requested in ascending order; at: byte offset of the slot
 #pragma unroll
-            for (int i = 0; i < LPW; i++)
-                ring_dma16(((i * NL + me) < BM / 8 ? base_a : base_w) + off[i], (bf16x8 *)((char *)smem + at + (i * NL + me) * 1024));
-            base_a += 128;
-            base_w += 128;
-        };
-        auto landed = [&](auto n) {  // this loader's share of all but the newest n k-tiles is there
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n.value * LPW) : "memory");
-            bar();
-        };
+        for (int i = 0; i < LPW; i++)
+            ring_dma16((i < LA ? base_a : base_w) + off[i], (bf16x8 *)((char *)smem + at + (i * NLW + me) * 1024));
+        base_a += 128;
+        base_w += 128;
+    };
+    auto landed = [&](auto n) {  // this wavefront's share of all but the newest n k-tiles is there; past the barrier everybody's is
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n.value * LPW) : "memory");
+        bar();
+    };
+    const int first = KT < ST ? KT : ST;
+    if (!OWN && wave >= NC) {  // ---- loader ----
+        start();
         auto rest = [&](auto self, auto n) {  // the last n + 1 k-tiles
             if constexpr (n.value >= 0) {
                 if (KT > n.value) landed(n);
                 self(self, std::integral_constant<int, n.value - 1>());
             }
         };
-        const int first = KT < ST ? KT : ST;
         for (int t = 0; t < first; t++) issue((uint32_t)(t * STAGE));
         if (KT >= ST) {
             landed(std::integral_constant<int, ST - 1>());
@@ -1343,12 +1356,15 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
     const int wcol0 = n0 + wn * WN;
     float add[16];
     floatx4 adds[TM][8];
-    constexpr bool LATE = BM > 128;  // (three wavefronts per SIMD: no registers to hold them under the main loop)
     // (on their way before the operands)
-    if constexpr (STAGED && !LATE) {
+    if constexpr (STAGED) {
 #pragma unroll
         for (int i = 0; i < TM; i++) staged_addends<KIND>(adds[i], wrow0 + i * 32, wcol0, M, N, epi, lane);
-    } else if (ONE) direct_addends<KIND>(add, wrow0, wcol0, M, N, epi, lane);
+    } else if (TM * TN == 1) direct_addends<KIND>(add, wrow0, wcol0, M, N, epi, lane);
+    if (OWN) {
+        start();
+        for (int t = 0; t < first; t++) issue((uint32_t)(t * STAGE));
+    }
     const int frow = lane % 32, hf = lane / 32, fx = (frow >> 1) & 7;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     const uint32_t a_lane = lds0 + (uint32_t)((wm * WM + frow) * 8 + (hf ^ fx)) * 16;
@@ -1413,17 +1429,15 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
         auto read = [&](int s) {
             const uint32_t pa = (a_lane ^ (uint32_t)(s << 5)) + at, pw = (w_lane ^ (uint32_t)(s << 5)) + at;
             asm volatile("ds_read_b128 %0, %1" : "=v"(af[s][0]) : "v"(pa));
-            if constexpr (TM > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(af[s][TM > 1 ? 1 : 0]) : "v"(pa));
-            if constexpr (TM > 2) asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(af[s][TM > 2 ? 2 : 0]) : "v"(pa));
-            if constexpr (TM > 2) asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(af[s][TM > 2 ? 3 : 0]) : "v"(pa));
+            if constexpr (TM > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(af[s][TM - 1]) : "v"(pa));
             asm volatile("ds_read_b128 %0, %1" : "=v"(wf[s][0]) : "v"(pw));
             if constexpr (TN > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(wf[s][TN - 1]) : "v"(pw));
         };
         auto wait = [&](int s, auto n) {  // the fragments of step s are there, the newest n reads may still be on the way
-            static_assert((TM == 2 || TM == 4) && TN == 2, "wave tiles");
+            static_assert(TM == TN && TM <= 2, "wave tiles");
             bf16x8(&fa)[TM] = af[s], (&fw)[TN] = wf[s];
-            if constexpr (TM == 2) asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(fa[0]), "+v"(fa[1]), "+v"(fw[0]), "+v"(fw[1]) : "n"(n.value));
-            else asm volatile("s_waitcnt lgkmcnt(%6)" : "+v"(fa[0]), "+v"(fa[1]), "+v"(fa[TM - 2]), "+v"(fa[TM - 1]), "+v"(fw[0]), "+v"(fw[1]) : "n"(n.value));
+            if constexpr (TM == 2) asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(fa[0]), "+v"(fa[TM - 1]), "+v"(fw[0]), "+v"(fw[TN - 1]) : "n"(n.value));
+            else asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(fa[0]), "+v"(fw[0]) : "n"(n.value));
         };
         auto mma = [&](int s) {
 #pragma unroll
@@ -1435,33 +1449,49 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
         };
         constexpr std::integral_constant<int, 0> c0{};
         constexpr std::integral_constant<int, 2 * R> c2{};
-        constexpr std::integral_constant<int, (3 * R < 16 ? 3 * R : 15)> c3{};
-        bar();
-        read(0);
-        read(1);
-        for (int kt = 0; kt < KT; kt++) {
+        constexpr std::integral_constant<int, 3 * R> c3{};
+        // One k-tile.  ahead (OWN): k-tiles that may be in flight beyond the next one (-1: this is the last); refill: k-tile kt + ST goes into its slot.
+        auto step = [&](auto ahead, auto refill) {
             SB; read(2); read(3);
             wait(0, c3); SB; mma(0); SB;
             wait(1, c2); SB; mma(1); SB;
             wait(2, c0); wait(3, c0); SB;
-            if (kt + 1 < KT) {
-                bar();
+            if constexpr (ahead.value >= 0) {
+                if constexpr (OWN) landed(ahead);
+                else bar();
+                if constexpr (refill.value) issue(at);
                 advance();
                 SB; read(0); read(1); SB;
             }
             mma(2); mma(3);
+        };
+        constexpr std::integral_constant<int, -1> last{};
+        if constexpr (OWN) {
+            if (KT < ST) landed(c0);
+            else landed(std::integral_constant<int, ST - 1>());
+        } else bar();
+        read(0);
+        read(1);
+        if constexpr (OWN) {
+            for (int kt = ST; kt < KT; kt++) step(std::integral_constant<int, ST - 2>(), std::true_type());
+            if constexpr (ST >= 3)
+                if (KT >= 3) step(std::integral_constant<int, 1>(), std::false_type());
+            if (KT >= 2) step(c0, std::false_type());
+        } else {
+            for (int kt = 1; kt < KT; kt++) step(c0, std::false_type());
         }
+        step(last, std::false_type());
     }
 #undef SB
     if constexpr (STAGED) {
         bar();  // every wavefront has read its last fragments: LDS becomes the staging area
-        staged_epilogue<KIND, TM, LATE>(acc, adds, (char *)smem + wave * 8192, wrow0, wcol0, M, N, epi, lane);
+        staged_epilogue<KIND, TM>(acc, adds, (char *)smem + wave * 8192, wrow0, wcol0, M, N, epi, lane);
     } else {
 #pragma unroll
         for (int i = 0; i < TM; i++)
 #pragma unroll
             for (int j = 0; j < TN; j++) {
-                if (!ONE) direct_addends<KIND>(add, wrow0 + i * 32, wcol0 + j * 32, M, N, epi, lane);
+                if (TM * TN > 1) direct_addends<KIND>(add, wrow0 + i * 32, wcol0 + j * 32, M, N, epi, lane);
                 direct_epilogue<KIND>(acc[i][j], add, wrow0 + i * 32, wcol0 + j * 32, M, N, epi, lane);
             }
     }
@@ -1471,13 +1501,14 @@ template <int BM, int BN, int WM, int WN, int NL, int ST, int KIND, bool STAGED,
 static int launch_tile_kind(const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi,
                             hipStream_t st, int batch = 1, int64_t batch_a = 0, int64_t batch_w = 0, int64_t batch_c = 0) {
     constexpr int NT = ((BM / WM) * (BN / WN) + NL) * 64;
-    constexpr size_t smem = (size_t)ST * (BM + BN) * 128;
+    constexpr int STAGE = (BM + BN) * 128, STAGING = STAGED ? (BM / WM) * (BN / WN) * 8192 : 0;  // bytes of a k-tile, and of the staged epilogue
     auto kern = gemm_bf16_tile<BM, BN, WM, WN, NL, ST, KIND, STAGED, BATCHED>;
     static bool attr_done = false;  // one attribute call per instantiation is enough (value never changes)
     if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return GR4AD_EHIP;
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, std::max(ST * STAGE, STAGING)) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
+    const int smem = std::max((K / 64 < ST ? K / 64 : ST) * STAGE, STAGING);
     const int64_t tiles_m = ceil_div64(M, BM), tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n;
     if (total > 0x7ffffff0LL || batch < 1 || batch > 65535 || lda >= (1 << 23) || ldw >= (1 << 23)) return GR4AD_EUNSUPPORTED;
     if (epi.skip_len && M > 0x7fffff00LL) return GR4AD_EUNSUPPORTED;
@@ -1510,55 +1541,68 @@ static int launch_tile_cfg(const bf16 *A, int64_t lda, const bf16 *W, int64_t ld
     return GR4AD_EUNSUPPORTED;
 }
 
-// Which kernel runs a product, by an estimate of its time in microseconds (all give the same bits).  Tiles of 32x32, 32x64 and 64x64 while
-// each fits a compute unit of its own (at these sizes the time is the k-loop of one tile; the smallest tiles have the shortest); beyond that the
-// least of the estimates, measured on MI355X for 1 <= M <= 8192, 512 <= N <= 4096, 512 <= K <= 4096 (kt: k-tiles of 64, n: tiles per compute unit):
-// 64x64 0.18 us per k-tile and tile, 128x128 0.53, 256x128 1.08, a wave of 256x256 tiles on the persistent kernel between 1.15 (few of them) and 1.9 (every
-// unit busy: the clock falls), plus what a tile costs beside its k-loop, which is more where the epilogue reads addends.
-// Where the lines lie (us, this kernel against the next best): 1024 x 512 x 512 32x64 4.2, 32x32 4.4; 256 x 3072 x 1024 64x64 6.0, 128x128 9.7; 2048 x 1024 x 4096
-// 64x64 25, 128x128 30; 4096 x 1024 x 1024 128x128 12, 64x64 15; 8192 x 1024 x 1024 with a residual 256x128 27, 128x128 31, 256x256 32; 4096 x 3072 x 1024
-// 256x256 26, 128x128 32.
-enum { RUN_TILE32 = 0, RUN_TILE32X64, RUN_TILE64, RUN_TILE64_PAIRED, RUN_TILE128, RUN_TILE256X128, RUN_RING };
-static int pick_kernel(int64_t M, int N, int K, int kind, int batch, bool tile64, bool tile128, bool tile256, bool ring) {
+// Which kernel runs a product: the least of these estimates of its time in microseconds (all give the same bits).  Fitted to every kernel's time on 5300 products on
+// MI355X: 64 <= M <= 32768, 256 <= N <= 8192, 64 <= K <= 4096, each epilogue, transposed values, and batches of 1 to 256 products of 1 to 12288 rows (rms error of an
+// estimate 4 to 12 %; the kernel it picks takes 0.8 % longer than the best one in the mean, 1.4 times as long at worst).  A tile of the first round costs first[kind] +
+// kt * k_first (kt: k-tiles of 64), every further round of 256 tiles more[kind] + kt * k_more, of which the second costs k_second.
+// Where the lines lie (us, this kernel against the next best): 1024 x 512 x 512 32x64 4.2, 32x32 4.4; 256 x 3072 x 1024 64x64 6.0, 128x128 9.7; 2048 x 512 x 4096
+// 64x64 15, 128x128 19; 4096 x 1024 x 1024 128x128 with loaders 12, 64x64 15; 8192 x 1024 x 1024 with a residual 128x128 in pairs 27.6, 256x256 33, 128x128 with
+// loaders 37; 4096 x 3072 x 1024 256x256 26, 128x128 32; sixteen batches of 8192 x 1024 x 64 128x128 in pairs 71, with loaders 105.
+enum { RUN_TILE32 = 0, RUN_TILE32X64, RUN_TILE64, RUN_TILE64_OWN, RUN_TILE128, RUN_TILE128_OWN, RUN_RING };
+static int pick_kernel(int64_t M, int N, int K, int kind, int batch, bool tile64, bool tile128, bool ring) {
+    struct Cost { int bm, bn; float start, first[6], more[6], k_first, k_second, k_more; };  // (kinds: bf16, SiLU, float32, residual, table, transposed)
+    static const Cost cost[RUN_RING] = {
+        {32, 32, 2.73f, {0.06f, 0.19f, 0.17f, 0.0f, 0.02f, 0.72f}, {0.14f, 0.18f, 0.18f, 0.22f, 0.23f, 0.09f}, 0.11f, 0.06f, 0.11f},
+        {32, 64, 2.83f, {0.09f, 0.29f, 0.21f, 0.0f, 0.09f, 0.77f}, {0.22f, 0.33f, 0.27f, 0.4f, 0.42f, 0.35f}, 0.12f, 0.18f, 0.18f},
+        {64, 64, 2.84f, {0.0f, 0.29f, 0.3f, 0.17f, 0.18f, 0.73f}, {0.7f, 0.78f, 0.74f, 1.1f, 1.06f, 0.68f}, 0.16f, 0.25f, 0.22f},
+        {64, 64, 2.86f, {0.0f, 0.07f, 0.16f, 0.32f, 0.26f, 0.43f}, {0.36f, 0.58f, 0.54f, 1.07f, 1.05f, 0.44f}, 0.19f, 0.15f, 0.17f},
+        {128, 128, 3.51f, {0.0f, 2.01f, 2.85f, 2.21f, 4.75f, 2.46f}, {1.69f, 2.47f, 3.09f, 7.33f, 8.75f, 3.64f}, 0.43f, 0.6f, 0.55f},
+        {128, 128, 3.39f, {0.0f, 2.0f, 2.59f, 2.61f, 4.72f, 2.2f}, {1.28f, 1.95f, 2.45f, 5.46f, 5.85f, 2.03f}, 0.55f, 0.4f, 0.51f},
+    };
+    const int kc = kind == EPI_STORE ? 0 : kind == EPI_SILU || kind == EPI_SILU_DIV ? 1 : kind == EPI_F32 ? 2 : kind == EPI_F32_RESID ? 3 : kind == EPI_F32_TABLE ? 4 : 5;
     const float kt = (float)(K / 64);
-    auto tiles = [&](int bm, int bn) { return ceil_div64(M, bm) * ceil_div64(N, bn) * batch; };
-    if (tile64) {
-        if (tiles(32, 32) <= 256) return RUN_TILE32;
-        if (tiles(32, 64) <= 256) return RUN_TILE32X64;
-        if (tiles(64, 64) <= 256) return K > 512 ? RUN_TILE64 : RUN_TILE64_PAIRED;
-    }
-    const float adds = kind == EPI_F32_RESID || kind == EPI_F32_TABLE ? 1.0f : 0.0f;
-    auto rounds = [&](int bm, int bn) { return (float)ceil_div64(tiles(bm, bn), 256); };
+    // Batches stream operands that no other batch reads, and eight k-tiles of LDS leave one workgroup per compute unit to ask for them (45 batches of 16 x 1024 x 512
+    // 15.4 us on 32x64 tiles, 11.0 on 64x64 in threes)
+    const bool stream = batch > 1 && ceil_div64(M, 64) * ceil_div64(N, 64) * batch > 256;
     float best = 1e30f;
     int run = RUN_TILE128;
-    auto offer = [&](bool ok, int what, float t) {
-        if (ok && t < best) { best = t; run = what; }
-    };
-    const float scatter = kind == EPI_VT ? 1.0f : 0.0f;  // (the tile kernels store the transposed values one by one)
-    offer(tile64, RUN_TILE64_PAIRED, 2.5f + rounds(64, 64) * (0.3f + 0.4f * adds + 1.0f * scatter + 0.18f * kt));
-    offer(tile128, RUN_TILE128, 2.0f + rounds(128, 128) * (1.2f + 3.5f * adds + 5.0f * scatter + 0.53f * kt));
-    offer(tile256 && adds, RUN_TILE256X128, 2.5f + rounds(256, 128) * (6.7f + 1.08f * kt));
-    const int64_t t256 = tiles(256, 256), full = t256 / 256;
-    const float rest = (float)(t256 % 256) / 256.0f;
-    offer(ring, RUN_RING, (float)(full + (rest > 0.0f)) * 1.3f + adds * (14.0f * (float)full + (rest > 0.0f ? 4.0f + 9.0f * rest : 0.0f)) +
-                          kt * (1.9f * (float)full + (rest > 0.0f ? 1.15f + 0.72f * rest * rest : 0.0f)));
+    for (int r = stream ? RUN_TILE64_OWN : RUN_TILE32; r < RUN_RING; r++) {
+        const Cost &c = cost[r];
+        if (!(c.bm < 128 ? tile64 : tile128)) continue;
+        int64_t tiles = ceil_div64(M, c.bm) * ceil_div64(N, c.bn);
+        if (batch > 1) tiles = (tiles + 7) / 8 * 8 * batch;  // (a batch's tiles are dealt to the eight XCDs from the first on)
+        const float more = (float)(ceil_div64(tiles, 256) - 1);
+        const float t = c.start + c.first[kc] + kt * c.k_first + more * c.more[kc] + (more > 0.0f ? kt * (c.k_second + (more - 1.0f) * c.k_more) : 0.0f);
+        if (t < best) { best = t; run = r; }
+    }
+    if (ring) {  // 256x256 tiles: full rounds, and a last one whose clock falls as it fills the chip
+        static const float full[6] = {5.4f, 7.3f, 10.8f, 20.4f, 20.3f, 6.4f}, any[6] = {1.45f, 7.25f, 3.15f, 4.4f, 8.0f, 3.4f},
+                           part[6] = {2.4f, 0.0f, 5.6f, 12.3f, 12.2f, 0.4f};
+        const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256);
+        const float f = (float)(tiles / 256), rest = (float)(tiles % 256) / 256.0f;
+        const float t = 3.3f + f * (full[kc] + 1.49f * kt) + (rest > 0.0f ? any[kc] + 1.05f * kt + rest * (part[kc] + 0.44f * rest * kt) : 0.0f);
+        if (t < best) run = RUN_RING;
+    }
     return run;
 }
 
 static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi,
                        hipStream_t st, int batch = 1, int64_t ba = 0, int64_t bw = 0, int64_t bc = 0) {
+    const bool staged = kind != EPI_VT && tile_staged_ok(kind, N, epi);
     switch (run) {
-        // one workgroup per compute unit: eight k-tiles in LDS; 64x64 tiles in pairs (or of few k-tiles, which wait for fewer requests first): four
+        // with loaders: eight k-tiles in LDS, three of the large tiles; without: three and two, so that three and two workgroups share a compute unit
         case RUN_TILE32: return launch_tile_cfg<32, 32, 32, 32, 2, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
         case RUN_TILE32X64: return launch_tile_cfg<32, 64, 32, 32, 2, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-        case RUN_TILE64: return launch_tile_cfg<64, 64, 32, 32, 4, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-        case RUN_TILE64_PAIRED: return launch_tile_cfg<64, 64, 32, 32, 4, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-        case RUN_TILE256X128:
-            if (kind == EPI_F32_RESID) return launch_tile_kind<256, 128, 64, 64, 4, 3, EPI_F32_RESID, true>(A, lda, W, ldw, M, N, K, epi, st);
-            return launch_tile_kind<256, 128, 64, 64, 4, 3, EPI_F32_TABLE, true>(A, lda, W, ldw, M, N, K, epi, st);
+        case RUN_TILE64:  // (up to eight k-tiles: four, requested sooner: 256 x 3072 x 512 4.4 us, 4.1)
+            if (K <= 512) return launch_tile_cfg<64, 64, 32, 32, 4, 4, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+            return launch_tile_cfg<64, 64, 32, 32, 4, 8, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        case RUN_TILE64_OWN: return launch_tile_cfg<64, 64, 32, 32, 0, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+        case RUN_TILE128_OWN:
+            if (staged) return launch_tile_cfg<128, 128, 64, 64, 0, 2, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+            return launch_tile_cfg<128, 128, 64, 64, 0, 2, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
     }
-    if (kind == EPI_VT || !tile_staged_ok(kind, N, epi)) return launch_tile_cfg<128, 128, 64, 64, 4, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
-    return launch_tile_cfg<128, 128, 64, 64, 4, 3, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    if (staged) return launch_tile_cfg<128, 128, 64, 64, 4, 3, true>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
+    return launch_tile_cfg<128, 128, 64, 64, 4, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
 }
 
 // Batched product on the tile kernels: for i < batch, C_i[M,N] = A_i[M,K] * W_i[N,K]^T with A_i = A + i*batch_a elements etc.
@@ -1579,7 +1623,7 @@ int launch_gemm_batched(const void *A, int64_t lda, int64_t batch_a, const void 
     e.len_bounds = batch_len ? len_bounds : 0;
     const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
     const int kind = out_f32 ? EPI_F32 : EPI_STORE;
-    return launch_tile(pick_kernel(M, N, K, kind, batch, true, true, false, false), a, lda, w, ldw, M, N, K, kind, e, st, batch, batch_a, batch_w, batch_c);
+    return launch_tile(pick_kernel(M, N, K, kind, batch, true, true, false), a, lda, w, ldw, M, N, K, kind, e, st, batch, batch_a, batch_w, batch_c);
 }
 
 // Transposed-per-request product for the context values: out[(b*N + n) * ld_out + s] = sum_k A[b*S + s][k] * W[n][k] for
@@ -1605,7 +1649,7 @@ int launch_gemm_vt(const void *A, int64_t lda, const void *W, int64_t ldw, int64
     e.skip_S = (int)ld_out;
     const int64_t rows = M / S * ld_out;
     const bool ring = K >= 192 && rows >= 256 && N >= 256 && lda < (1 << 22) && ldw < (1 << 22);
-    const int run = pick_kernel(rows, N, K, EPI_VT, 1, true, true, false, ring);
+    const int run = pick_kernel(rows, N, K, EPI_VT, 1, true, true, ring);
     if (run == RUN_RING) return launch_ring((const bf16 *)A, lda, (const bf16 *)W, ldw, rows, N, K, EPI_VT, e, st);
     return launch_tile(run, (const bf16 *)A, lda, (const bf16 *)W, ldw, rows, N, K, EPI_VT, e, st);
 }
@@ -1690,12 +1734,11 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
     if (mfma_ok(dtype, A, lda, W, ldw, K, kind)) {
         const bf16 *a = (const bf16 *)A, *w = (const bf16 *)W;
         if (gemm_large_class(dtype, A, lda, W, ldw, M, N, K, epi)) {
-            const bool staged = tile_staged_ok(kind, N, epi);
-            const int run = pick_kernel(M, N, K, kind, 1, false, staged, staged, true);
+            const int run = pick_kernel(M, N, K, kind, 1, false, tile_staged_ok(kind, N, epi), true);
             return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, kind, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, kind, epi, st);
         }
         const int k = kind == EPI_SILU ? EPI_SILU_DIV : kind;
-        const int run = pick_kernel(M, N, K, k, 1, true, true, tile_staged_ok(k, N, epi), N >= 256 && ring_ok(k, N, K, lda, ldw, epi));
+        const int run = pick_kernel(M, N, K, k, 1, true, true, N >= 256 && ring_ok(k, N, K, lda, ldw, epi));
         return run == RUN_RING ? launch_ring(a, lda, w, ldw, M, N, K, k, epi, st) : launch_tile(run, a, lda, w, ldw, M, N, K, k, epi, st);
     }
     if (dtype == GR4AD_F32 && f32_mfma_ok(A, lda, W, ldw, K))

@@ -14,6 +14,9 @@ pytestmark = pytest.mark.gpu
     (2049, 3072, 192), (4100, 1000, 128),          # 128x128 tiles: paired and with a ragged edge
     (4096, 4096, 192), (4500, 3080, 256),          # few and many 256x256 tiles below 8192 rows
     (8200, 512, 192), (8192, 520, 256),            # the large class on 128x128 and on 256x256 tiles
+    (2017, 1000, 64), (1030, 1500, 128),           # tiles that load for themselves, 64x64: one k-tile, fewer than LDS holds, ragged edges
+    (500, 3001, 448), (4100, 1001, 192),           # as many and more; an odd number of columns
+    (8191, 3080, 64), (4096, 4096, 128), (3000, 3001, 1024),  # 128x128: one k-tile, as many as LDS holds, more; ragged edges, odd columns
 ])
 def test_linear_at_tile_edges(M, N, K):
     g = torch.Generator().manual_seed(M * 7 + N * 3 + K)
@@ -68,7 +71,7 @@ def test_f32_requests_do_not_depend_on_their_batch(d, H):
     (3072, 1088), (264, 4096),
 ])
 def test_bf16_rows_do_not_depend_on_the_row_count(N, K):
-    """Below 8192 rows every kernel that runs a product adds in one order: rows alone, on each of the tiles, and among many give the same bits."""
+    """Below 8192 rows every kernel that runs a product adds in one order: rows alone, on small tiles, and among many, on larger ones, give the same bits."""
     g = torch.Generator().manual_seed(N + K)
     a, w = torch.randn(8000, K, generator=g).bfloat16().cuda(), (torch.randn(N, K, generator=g) / K**0.5).bfloat16().cuda()
     many, many32 = binding.op_linear(a, w), binding.op_linear(a, w, out_f32=True)
@@ -77,3 +80,18 @@ def test_bf16_rows_do_not_depend_on_the_row_count(N, K):
         assert torch.equal(binding.op_linear(some, w), many[first:first + rows])
         assert torch.equal(binding.op_linear(some, w, out_f32=True), many32[first:first + rows])
     np.testing.assert_allclose(many32[:64].double().cpu().numpy(), (a[:64].double() @ w.double().t()).cpu().numpy(), atol=2e-5, rtol=1e-5)
+
+
+@pytest.mark.parametrize("d,H,F", [(256, 8, 1024), (512, 4, 2048)])
+@pytest.mark.parametrize("B,n", [(3, 33), (47, 33), (97, 31), (239, 33)])
+def test_requests_do_not_depend_on_their_batch(d, H, F, B, n):
+    """The products that add a residual or a table row: one request's rows on the smallest tiles, those of a batch (99 to 7887, ragged) on all the others."""
+    w = synth.Workload("tiles", "bf16", B, 40, d, 3, 1, H, F, 3, [512, 300, 264], [n, n, n])
+    dec = binding.decoder_for(w, synth.make_weights(w))
+    ctx = torch.randn(B, 40, d, generator=torch.Generator(device="cuda").manual_seed(B + d), device="cuda").bfloat16()
+    sid, lp = dec.decode_batch(ctx, None, w.beam)
+    for b in (0, B // 2, B - 1):
+        one = dec.decode_batch(ctx[b:b + 1].contiguous(), None, w.beam)
+        assert torch.equal(one[0][0], sid[b]) and torch.equal(one[1][0], lp[b])
+    assert torch.isfinite(lp).all()
+    dec.close()
