@@ -41,12 +41,13 @@ __device__ __forceinline__ Addends epilogue_addends(const GemmEpilogue &e, int64
     if (e.resid) a.resid = e.resid[row * e.ldr + col];
     return a;
 }
+// a: the element's addends where they were requested ahead (NULL: they are read here; both reading and asking again cost a 64x64 float32 tile 0.9 us)
 template <typename T>
-__device__ __forceinline__ void epilogue_store(const GemmEpilogue &e, int64_t row, int col, float v, const Addends &a) {
-    if (e.bias) v += a.bias;
-    if (e.table) v += a.table;
+__device__ __forceinline__ void epilogue_store(const GemmEpilogue &e, int64_t row, int col, int N, float v, const Addends *a = nullptr) {
+    if (e.bias) v += a ? a->bias : e.bias[col];
+    if (e.table) v += a ? a->table : e.table[(e.tok ? (int64_t)e.tok[row] : 0) * N + col];
     if (e.act == ACT_SILU) v = v / (1.0f + __expf(-v));
-    if (e.resid) v += a.resid;
+    if (e.resid) v += a ? a->resid : e.resid[row * e.ldr + col];
     if (e.out_f32)
         ((float *)e.C)[row * e.ldc + col] = v;
     else
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(256) void gemm_simple(const T *__restrict__ A, int6
             if (row < M && col < N) {
                 float v = acc[i][j];
                 if (epi.a_scale) v *= epi.a_scale[row] * epi.w_scale;
-                epilogue_store<TO>(epi, row, col, v, epilogue_addends(epi, row, col, N));
+                epilogue_store<TO>(epi, row, col, N, v);
             }
         }
 }
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(256) void gemm_simple(const T *__restrict__ A, int6
 // accumulators per wavefront, at the rate of one v_mfma_f32_32x32x2_f32) over the same quarters of K, joined in the same way; a wavefront with
 // 32x32 elements walks the quarters in turn.
 // Replaces 64x64 FMA tiles staged through LDS value by value: 27 us on average for the products of a decode of 4 requests at d = 128,
-// now 3 to 4 us.  Needs K % 4 == 0 and 16-byte aligned rows.
+// now 2.8 to 4 us (64 x 128 x 512 with a residual 4.0, 64 x 512 x 128 behind a norm 4.1; 1024 x 1024 x 512 on 64x64 tiles 19.2).  Needs K % 4 == 0 and 16-byte aligned rows.
 template <int T>
 __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A, int64_t lda, const float *__restrict__ W, int64_t ldw, int64_t M,
                                                      int N, int K, GemmEpilogue epi) {
@@ -133,30 +134,31 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
         w[g] = W + (int64_t)(wr < N ? wr : N - 1) * ldw + k4;
     }
     __shared__ float rinv[16];
+    __shared__ __attribute__((aligned(16))) float gain[1024];  // its first 1024 values (a read from memory between the norm and the first MFMA is a latency more)
     const int nb = (K + KB - 1) / KB, per = (nb + 3) / 4;  // blocks of KB values of k; blocks in a quarter
-    floatx4 av[UN][G], wv[UN][G];
-    auto load = [&](int b, int b1) {
+    struct Blocks { floatx4 a[UN][G], w[UN][G]; };
+    auto load = [&](Blocks &x, int b, int b1) {
 #pragma unroll
         for (int u = 0; u < UN; u++) {
             const int k = (b + u) * KB + k4;
 #pragma unroll
             for (int g = 0; g < G; g++) {
-                av[u][g] = wv[u][g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                x.a[u][g] = x.w[u][g] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
                 if (b + u < b1 && k < K) {
-                    av[u][g] = *(const floatx4 *)(a[g] + (int64_t)(b + u) * KB);
-                    wv[u][g] = *(const floatx4 *)(w[g] + (int64_t)(b + u) * KB);
+                    x.a[u][g] = *(const floatx4 *)(a[g] + (int64_t)(b + u) * KB);
+                    x.w[u][g] = *(const floatx4 *)(w[g] + (int64_t)(b + u) * KB);
                 }
             }
         }
     };
-    auto scale = [&](int b, int b1) {  // A = RMSNorm(pre_x)
+    auto scale = [&](Blocks &x, int b, int b1) {  // A = RMSNorm(pre_x)
 #pragma unroll
         for (int u = 0; u < UN; u++) {
             const int k = (b + u) * KB + k4;
-            if (b + u < b1 && k < K) av[u][0] = *(const floatx4 *)((const float *)epi.pre_gain + k) * av[u][0] * rinv[lane % 16];
+            if (b + u < b1 && k < K) x.a[u][0] = *(const floatx4 *)(k < 1024 ? gain + k : (const float *)epi.pre_gain + k) * x.a[u][0] * rinv[lane % 16];
         }
     };
-    auto multiply = [&](floatx4 (&acc)[G][G]) {
+    auto multiply = [&](const Blocks &x, floatx4 (&acc)[G][G]) {
 #pragma unroll
         for (int u = 0; u < UN; u++)
 #pragma unroll
@@ -164,9 +166,9 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
 #pragma unroll
                 for (int i = 0; i < G; i++)
 #pragma unroll
-                    for (int j = 0; j < G; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], wv[u][j][e], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < G; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.a[u][i][e], x.w[u][j][e], acc[i][j], 0, 0, 0);
     };
-    auto quarter = [&](int s, floatx4 (&acc)[G][G], bool loaded) {  // loaded: the first blocks are there (scaled)
+    auto quarter = [&](int s, floatx4 (&acc)[G][G], Blocks &x, bool loaded) {  // loaded: x holds its first blocks
         const int b0 = s * per, b1 = b0 + per < nb ? b0 + per : nb;
 #pragma unroll
         for (int i = 0; i < G; i++)
@@ -174,21 +176,28 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
             for (int j = 0; j < G; j++) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int b = b0; b < b1; b += UN) {
             if (!loaded || b > b0) {
-                load(b, b1);
+                load(x, b, b1);
                 if constexpr (T == 16)
-                    if (epi.pre_x) scale(b, b1);
+                    if (epi.pre_x) scale(x, b, b1);
             }
-            multiply(acc);
+            multiply(x, acc);
         }
     };
-    Addends add = {0.0f, 0.0f, 0.0f};
+    floatx4 acc[G][G];
+    // accumulators: column lane % 16, row 4 * (lane / 16) + v
     if constexpr (T == 16) {
         // Every memory latency of the tile at once: the first operand blocks and what the epilogue adds are requested before the rows are summed up.
         const int64_t row = m0 + threadIdx.x / 16;
         const int col = n0 + threadIdx.x % 16, b0 = wave * per;
-        load(b0, b0 + per < nb ? b0 + per : nb);
+        const int g4 = (int)threadIdx.x * 4;
+        floatx4 first_gain = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (epi.pre_x && g4 < K) first_gain = *(const floatx4 *)((const float *)epi.pre_gain + g4);
+        Blocks x;
+        Addends add = {0.0f, 0.0f, 0.0f};
+        load(x, b0, b0 + per < nb ? b0 + per : nb);
         if (row < M && col < N) add = epilogue_addends(epi, row, col, N);
         if (epi.pre_x) {  // 1/rms of the tile's rows, four per wavefront, as rmsnorm_kernel has it
+            *(floatx4 *)(gain + g4) = first_gain;
             float ss[4] = {};
             for (int k = lane * 4; k < K; k += 256)
 #pragma unroll
@@ -203,21 +212,15 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
                 if (lane == 0) rinv[wave + 4 * q] = 1.0f / sqrtf(ss[q] / (float)K + epi.pre_eps);
             }
             __syncthreads();
-            scale(b0, b0 + per < nb ? b0 + per : nb);
+            scale(x, b0, b0 + per < nb ? b0 + per : nb);
         }
-    }
-    floatx4 acc[G][G];
-    // accumulators: column lane % 16, row 4 * (lane / 16) + v
-    if constexpr (T == 16) {
-        quarter(wave, acc, true);
+        quarter(wave, acc, x, true);
         __shared__ float part[4][256];
 #pragma unroll
         for (int v = 0; v < 4; v++) part[wave][(4 * (lane / 16) + v) * 16 + lane % 16] = acc[0][0][v];
         __syncthreads();
         const int t = threadIdx.x;
-        const int64_t row = m0 + t / 16;
-        const int col = n0 + t % 16;
-        if (row < M && col < N) epilogue_store<float>(epi, row, col, (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]), add);
+        if (row < M && col < N) epilogue_store<float>(epi, row, col, N, (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]), &add);
     } else {
         floatx4 low[G][G], high[G][G];
         auto join = [&](floatx4 (&sum)[G][G]) {
@@ -226,11 +229,15 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
 #pragma unroll
                 for (int j = 0; j < G; j++) sum[i][j] += acc[i][j];
         };
-        quarter(0, low, false);
-        quarter(1, acc, false);
+        auto walk = [&](int s, floatx4 (&sum)[G][G]) {  // (blocks of its own: kept over the quarters they went to scratch, 1024 x 1024 x 512 19.3 us to 30.6)
+            Blocks x;
+            quarter(s, sum, x, false);
+        };
+        walk(0, low);
+        walk(1, acc);
         join(low);
-        quarter(2, high, false);
-        quarter(3, acc, false);
+        walk(2, high);
+        walk(3, acc);
         join(high);
 #pragma unroll
         for (int i = 0; i < G; i++)
@@ -240,7 +247,7 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
                 for (int v = 0; v < 4; v++) {
                     const int64_t row = m0 + i * 16 + 4 * (lane / 16) + v;
                     const int col = n0 + j * 16 + lane % 16;
-                    if (row < M && col < N) epilogue_store<float>(epi, row, col, low[i][j][v] + high[i][j][v], epilogue_addends(epi, row, col, N));
+                    if (row < M && col < N) epilogue_store<float>(epi, row, col, N, low[i][j][v] + high[i][j][v]);
                 }
     }
 }
