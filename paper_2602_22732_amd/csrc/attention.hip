@@ -27,10 +27,10 @@
 // ---------------------------------------------------------------------------
 // simple cross-attention: wave per (row, head)
 // ---------------------------------------------------------------------------
-// A wavefront's time is a few memory latencies, so a tile's keys and values (64 keys, all loads at once while a head is at most 64 wide) are requested
-// together, before the scores are formed: 12 to 64 workgroups of 64 keys, head width 32, 9.5 to 10.4 us with the values requested 16 keys at a time
-// after the softmax, now 8.5 to 9.1.
-template <typename T, bool WIDE>  // WIDE: heads of more than 64 columns
+// AHEAD (heads of at most 64 columns): with few workgroups a wavefront's time is a few memory latencies, so the keys and values of a tile of 64 keys are requested
+// together, before the scores are formed.  Otherwise the values follow the softmax, 16 keys at a time, and keys past the end cost nothing: the rule is at the
+// launch.
+template <typename T, bool AHEAD>
 __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q, int64_t ldq, const T *__restrict__ kv,
                                                          const int32_t *__restrict__ ctx_len, T *__restrict__ out, int64_t ldo,
                                                          int64_t rows, int n, int S, int d, int H) {
@@ -51,38 +51,40 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
     constexpr int E = 16 / sizeof(T), U = 32 / E;           // values of a 16-byte load; loads of 32 columns
     const bool vec = ((uintptr_t)kbase % 16) == 0 && (2 * d) % E == 0 && dh % E == 0;
     float m = -INFINITY, l = 0.0f, acc[2] = {0.0f, 0.0f};
-    constexpr int G = WIDE ? 16 : 64;  // keys whose values are in flight
+    constexpr int G = AHEAD ? 64 : 16;  // keys whose values are in flight
     for (int j0 = 0; j0 < len; j0 += 64) {
         const int j = j0 + lane, cnt = (len - j0) < 64 ? (len - j0) : 64;
-        float v0[G], v1[WIDE ? G : 1];
+        float v0[G], v1[AHEAD ? 1 : G];
         auto load_values = [&](int j1) {  // (keys past the tile's last re-read it and count as zero: 0 * v is no zero where v is infinite)
 #pragma unroll
             for (int u = 0; u < G; u++) {
                 const T *vr = kbase + (int64_t)(j0 + (j1 + u < cnt ? j1 + u : cnt - 1)) * 2 * d + d;
                 v0[u] = lane < dh ? to_f(vr[lane]) : 0.0f;
-                if constexpr (WIDE) v1[u] = lane + 64 < dh ? to_f(vr[lane + 64]) : 0.0f;
+                if constexpr (!AHEAD) v1[u] = lane + 64 < dh ? to_f(vr[lane + 64]) : 0.0f;
             }
         };
         const T *kr = kbase + (int64_t)(j < len ? j : len - 1) * 2 * d;
         float s = 0.0f;
-        if (vec) {  // 16 bytes per load, same order of additions
-            uint4 raw[U];
+        if (AHEAD ? vec : vec && j < len) {  // 16 bytes per load, same order of additions
+            if constexpr (AHEAD) {
+                uint4 raw[U];
 #pragma unroll
-            for (int u = 0; u < U; u++) raw[u] = *(const uint4 *)(kr + (u * E < dh ? u * E : 0));
-            if constexpr (!WIDE) load_values(0);
+                for (int u = 0; u < U; u++) raw[u] = *(const uint4 *)(kr + (u * E < dh ? u * E : 0));
+                load_values(0);
 #pragma unroll
-            for (int u = 0; u < U; u++)
+                for (int u = 0; u < U; u++)
 #pragma unroll
-                for (int e = 0; e < E; e++)
-                    if (u * E < dh) s = fmaf(sq[wv][u * E + e], to_f(((const T *)&raw[u])[e]), s);
+                    for (int e = 0; e < E; e++)
+                        if (u * E < dh) s = fmaf(sq[wv][u * E + e], to_f(((const T *)&raw[u])[e]), s);
+            }
 #pragma unroll 4
-            for (int c = 32; c < dh; c += E) {
+            for (int c = AHEAD ? 32 : 0; c < dh; c += E) {
                 const uint4 more = *(const uint4 *)(kr + c);
 #pragma unroll
                 for (int e = 0; e < E; e++) s = fmaf(sq[wv][c + e], to_f(((const T *)&more)[e]), s);
             }
-        } else {
-            if constexpr (!WIDE) load_values(0);
+        } else if (AHEAD || j < len) {
+            if constexpr (AHEAD) load_values(0);
             for (int c = 0; c < dh; c++) s = fmaf(sq[wv][c], to_f(kr[c]), s);
         }
         if (j >= len) s = -INFINITY;
@@ -95,20 +97,20 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
         acc[0] *= alpha;
         acc[1] *= alpha;
         for (int j1 = 0; j1 < cnt; j1 += G) {
-            if constexpr (WIDE) load_values(j1);
+            if constexpr (!AHEAD) load_values(j1);
             if (j1 + G > cnt) {
 #pragma unroll
                 for (int u = 0; u < G; u++)
                     if (j1 + u >= cnt) {
                         v0[u] = 0.0f;
-                        if constexpr (WIDE) v1[u] = 0.0f;
+                        if constexpr (!AHEAD) v1[u] = 0.0f;
                     }
             }
 #pragma unroll
             for (int u = 0; u < G; u++) {
                 const float pj = j1 + u < cnt ? sp[wv][j1 + u] : 0.0f;
                 acc[0] = fmaf(pj, v0[u], acc[0]);
-                if constexpr (WIDE) acc[1] = fmaf(pj, v1[u], acc[1]);
+                if constexpr (!AHEAD) acc[1] = fmaf(pj, v1[u], acc[1]);
             }
         }
     }
@@ -1139,15 +1141,21 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
         ((uintptr_t)out % 8) == 0) {
         const bf16 *qq = (const bf16 *)q, *kk = (const bf16 *)kv, *vv = (const bf16 *)vt;
         bf16 *oo = (bf16 *)out;
-        if (dh == 32) return launch_flash<32, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
         // Where the lines lie, in us, 8 wavefronts that load for themselves / 4 that do / 4 with 4 loaders (blocks of 256 / 128 / 128 beams; one card, others differ by
         // up to 8 %): 1 request of 512 keys, d = 512, 256 beams 13.8 / 10.6 / 9.5; 32 of them 18.4 / 18.7 / 17.5 (512 blocks of 128 beams); 45 of 389 keys, 512 beams 37.1 / 33.9 /
         // 35.7 (1440); 128 of 512 keys, 256 beams 55.1 / 53.9 / 59.3 (2048); 128 of 1024 keys, d = 1024, 256 beams 170 / 174 / 180 and 64 with 512 157 / 164 / 171 (4096).  Many
         // blocks: occupancy hides LDS, barrier and dependent-MFMA latencies, and a staged tile serves twice as many beams.  At most 128 beams: 128
         // requests of 1024 keys, d = 1024, 64 beams 97 / 97 / 95, 128 beams 117 / 113 / 113.  (Distinct rows: n is a bound, most blocks find less.)
+        // One or two tiles of keys leave the loaders nothing to run ahead on: 32 requests of 64 keys, d = 1024, 256 beams 12.6 / 14.2 / 12.7 (1024 blocks).  Blocks that at most 64 beams fill by
+        // half are better alone, where many share a unit: 128 requests of 100 keys, d = 512, 33 beams (4 without loaders / with) 8.3 / 10.6, 128 beams 18.8 / 16.8.  At head width 32 a tile is half as
+        // much work for the same loads: 128 requests, d = 1024, 64 keys, 64 beams 15.3 / 20.9 and 256 beams 33.5 / 41.6; 1024 keys, 64 beams 114 / 127 and 256 beams 250 / 266.
         const int64_t blocks = (int64_t)((n + 127) / 128) * H * B;
-        if (n <= 128 || blocks <= 512) return launch_flash<64, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-        if (blocks <= 2048 || (n + 255) / 256 * 256 != (n + 127) / 128 * 128)
+        if (dh == 32) {
+            if (blocks <= 768 || (n > 64 && n <= 128 && S > 192)) return launch_flash<32, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            return launch_flash<32, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+        }
+        if (blocks <= 768 || (n <= 128 && (n > 64 || S > 256))) return launch_flash<64, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+        if (n <= 128 || (blocks <= 2048 && S > 128) || (n + 255) / 256 * 256 != (n + 127) / 128 * 128)
             return launch_flash<64, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
         return launch_flash<64, 8, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
     }
@@ -1156,9 +1164,12 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
     const int64_t grid = ceil_div64(rows * H, 4);
     if (grid > 0x7fffffffLL) return GR4AD_EUNSUPPORTED;
     ProfScope ps(KC_XATTN_SIMPLE, st, 4.0 * B * (double)n * S * d, (2.0 * B * n * d + 2.0 * B * (double)S * d) * (dtype == GR4AD_BF16 ? 2 : 4));
-#define SIMPLE_(T, WIDE) hipLaunchKernelGGL((cross_attn_simple<T, WIDE>), dim3((unsigned)grid), dim3(256), 0, st, (const T *)q, ldq, (const T *)kv, ctx_len, (T *)out, ldo, rows, n, S, d, H)
-    if (dtype == GR4AD_BF16) { if (dh > 64) SIMPLE_(bf16, true); else SIMPLE_(bf16, false); }
-    else if (dh > 64) SIMPLE_(float, true);
+    // Ahead where most of the tiles' 64 keys exist and the registers (three wavefronts per SIMD) suffice: head width 32, 64 keys, up to 512 workgroups 9.5 us, 7.5 ahead,
+    // 16384 workgroups 140, 156 ahead; 65 keys, 512 workgroups 12.4, 14.4 ahead; 5 keys, 512 workgroups 6.9, 10.8 ahead.
+    const bool ahead = dh <= 64 && (S <= 64 ? S > 32 : 5 * (int64_t)S > 3 * (((int64_t)S + 63) / 64 * 64)) && grid < 1024;
+#define SIMPLE_(T, AHEAD) hipLaunchKernelGGL((cross_attn_simple<T, AHEAD>), dim3((unsigned)grid), dim3(256), 0, st, (const T *)q, ldq, (const T *)kv, ctx_len, (T *)out, ldo, rows, n, S, d, H)
+    if (dtype == GR4AD_BF16) { if (ahead) SIMPLE_(bf16, true); else SIMPLE_(bf16, false); }
+    else if (ahead) SIMPLE_(float, true);
     else SIMPLE_(float, false);
 #undef SIMPLE_
     GR4AD_LAUNCH_CHECK();

@@ -292,7 +292,7 @@ def test_gather_rows_is_an_exact_copy(dtype):
 
 @pytest.mark.parametrize("S,d,H,n", [
     (1, 64, 1, 4096), (64, 64, 2, 300), (129, 512, 8, 2100), (200, 512, 8, 4096),  # one tile, as many and more tiles than LDS holds; every number of blocks
-    (193, 256, 8, 300), (577, 128, 2, 5),
+    (193, 256, 8, 300), (577, 128, 2, 5), (100, 256, 8, 1500),
 ])
 def test_cross_attention_of_a_beam_does_not_depend_on_the_others(S, d, H, n):
     """The number of beams picks the wavefronts of a block and who loads; a beam's output is the same bits with any of them."""
