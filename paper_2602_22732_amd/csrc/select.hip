@@ -1027,6 +1027,7 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
                                                       unsigned long long *skeys, int *hist, int *wave_tot, int *sel_digit, int *sel_krem,
                                                       int *sel_cnt, int *out_cnt) {
     __shared__ uint32_t span_hi[SELB_THREADS / 64], span_lo[SELB_THREADS / 64];
+    __shared__ int gathered;
     const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
     const bool held = ncand <= SELB_HELD * SELB_THREADS;
     unsigned long long x[SELB_HELD];  // 0: none
@@ -1048,7 +1049,7 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
     }
     const uint32_t smp = (uint32_t)(src[(int64_t)tid * ncand / SELB_THREADS] >> 32);
     for (int i = tid; i < 2048; i += SELB_THREADS) hist[i] = 0;
-    if (tid == 0) *out_cnt = 0;
+    if (tid == 0) *out_cnt = gathered = 0;
     uint32_t smax = wave_max_u(smp), smin = ~wave_max_u(~smp);
     if (lane == 0) { span_hi[wv] = smax; span_lo[wv] = smin; }
     __syncthreads();
@@ -1090,36 +1091,38 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
     int np = 1;
     while (np < want) np <<= 1;
     for (int i = total + tid; i < np; i += SELB_THREADS) skeys[i] = 0ull;
-    // keys above bin T go to [0, n_gt), those of bin T behind them; out_cnt counts both, 16 bits each (at most SELB_SORT_MAX of either)
-    if (held) {  // one reservation per wavefront
-        unsigned long long mg[SELB_HELD], me[SELB_HELD];
-        int c = 0;
+    if (!held) {  // the keys from bin T up, at most SELB_SORT_MAX (a counter for either end in this sweep cost 20 to 60 us of a million keys)
+        for_each_key(src, ncand, [&](unsigned long long key) {
+            if (digit(key) >= T) skeys[atomicAdd(&gathered, 1)] = key;
+        });
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < SELB_HELD; j++) x[j] = j < SELB_SORT_MAX / SELB_THREADS && j * SELB_THREADS + tid < total ? skeys[j * SELB_THREADS + tid] : 0ull;
+        __syncthreads();
+    }
+    // keys above bin T go to [0, n_gt), those of bin T behind them; out_cnt counts both, 16 bits each (at most SELB_SORT_MAX of either); one reservation
+    // per wavefront
+    unsigned long long mg[SELB_HELD], me[SELB_HELD];
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < SELB_HELD; j++) {
+        const int d = x[j] ? digit(x[j]) : -1;
+        mg[j] = __ballot(d > T);
+        me[j] = __ballot(d == T);
+        c += __popcll(mg[j]) + (__popcll(me[j]) << 16);
+    }
+    if (c) {
+        int at = lane == 0 ? atomicAdd(out_cnt, c) : 0;
+        at = __builtin_amdgcn_readfirstlane(at);
+        int ag = at & 0xFFFF, ae = n_gt + (int)((unsigned)at >> 16);
+        const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
         for (int j = 0; j < SELB_HELD; j++) {
-            const int d = x[j] ? digit(x[j]) : -1;
-            mg[j] = __ballot(d > T);
-            me[j] = __ballot(d == T);
-            c += __popcll(mg[j]) + (__popcll(me[j]) << 16);
+            if (mg[j] >> lane & 1) skeys[ag + __popcll(mg[j] & below)] = x[j];
+            if (me[j] >> lane & 1) skeys[ae + __popcll(me[j] & below)] = x[j];
+            ag += __popcll(mg[j]);
+            ae += __popcll(me[j]);
         }
-        if (c) {
-            int at = lane == 0 ? atomicAdd(out_cnt, c) : 0;
-            at = __builtin_amdgcn_readfirstlane(at);
-            int ag = at & 0xFFFF, ae = n_gt + (int)((unsigned)at >> 16);
-            const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-            for (int j = 0; j < SELB_HELD; j++) {
-                if (mg[j] >> lane & 1) skeys[ag + __popcll(mg[j] & below)] = x[j];
-                if (me[j] >> lane & 1) skeys[ae + __popcll(me[j] & below)] = x[j];
-                ag += __popcll(mg[j]);
-                ae += __popcll(me[j]);
-            }
-        }
-    } else {
-        for_each_key(src, ncand, [&](unsigned long long key) {
-            const int d = digit(key);
-            if (d > T) skeys[atomicAdd(out_cnt, 1) & 0xFFFF] = key;
-            else if (d == T) skeys[n_gt + (int)((unsigned)atomicAdd(out_cnt, 1 << 16) >> 16)] = key;
-        });
     }
     if (rank_ties) {
         __syncthreads();
