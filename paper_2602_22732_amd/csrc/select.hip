@@ -502,8 +502,9 @@ __device__ __forceinline__ unsigned long long staged_to_key(unsigned long long s
 // token held in register i of a lane: piece i / E of the lane, element i % E of the piece
 template <int E> __device__ __forceinline__ int wave_tok(int i, int lane) { return ((i / E) * 64 + lane) * E + (i % E); }
 
-// exact fallback on the registers of one wavefront: radix selection on the score keys, two bits per step
-template <int VEC, int E>
+// exact fallback on the registers of one wavefront: radix selection on the score keys, two bits per step (ALONE: a function for each kernel that calls
+// it, or all of them get the registers of the one with the most)
+template <int VEC, int E, bool ALONE>
 __device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], int V, int m, uint32_t flat0, unsigned long long *stage) {
     const int lane = threadIdx.x % 64;
     uint32_t k_and = 0xFFFFFFFFu, k_or = 0u;
@@ -579,7 +580,7 @@ __device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], i
 
 // The row's own top-m cut.  x[i]: the logit of token wave_tok<E>(i, lane), padding -inf; mx, lse: the row's maximum and
 // log-sum-exp; the m best (score, token) pairs go to dst.
-template <int VEC, bool FULL, int E>
+template <int VEC, bool FULL, int E, bool ALONE>
 __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c, float mx, float lse, unsigned long long *__restrict__ dst,
                                                    uint32_t flat0, uint32_t nflat, int V, int m, unsigned long long *list, int lane) {
     constexpr int NX = VEC * 4;
@@ -639,7 +640,7 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
         float sc[NX];  // a copy, so that only this branch keeps the scores in addressable memory
 #pragma unroll
         for (int i = 0; i < NX; i++) sc[i] = x[i];
-        select_row_radix_wave<VEC, E>(sc, V, m, flat0, stage);
+        select_row_radix_wave<VEC, E, ALONE>(sc, V, m, flat0, stage);
     } else {
         // 3. bins above T go straight to the staged output, bin T to the list (over the dead histogram) for exact ranking
         const int n_gt = m - krem;
@@ -677,10 +678,10 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
 // todo / todo_count (both or neither): the launch visits only the listed rows {row, slot}; each gets its
 // own cut, written at slot `slot` of its request's segment.  Wavefronts walk their rows with the launch's stride.
 // The row and the cut's state need 105 (VEC 4) to 512 registers (VEC 32): with the 168 of three wavefronts per SIMD most of a row of 4096 and
-// 8192 tokens lived in scratch, and a wavefront is busy alone with its row anyway (rows of 8192, m = 256 or 512: 8 rows 26.6 us, 256 rows
-// 26.8, listed rows 56; now 22.0, 20.0 and 22).
-template <int VEC, bool FULL, typename LT>
-__global__ __launch_bounds__(256, VEC >= 32 ? 1 : 2) void select_rows_wave(const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V,
+// 8192 tokens lived in scratch.  ALONE: one wavefront per SIMD, the shortest time of a row of 8192 tokens (m = 256: a few listed rows 17.7 us, 21.8 with two wavefronts
+// per SIMD, 22.2 with three).  Otherwise two: what a long list takes (32768 rows all listed 318 us with one, 206 with two, 226 with three).
+template <int VEC, bool FULL, bool ALONE, typename LT>
+__global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V,
                                                           int m, unsigned long long *__restrict__ cand, const int2 *__restrict__ todo,
                                                           const int *__restrict__ todo_count) {
     constexpr int E = LogitPiece<LT>::E, NX = VEC * 4, G = NX / E;
@@ -728,7 +729,7 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 1 : 2) void select_rows_wave(const
             for (int i = lane; i < m; i += 64) dst[i] = (unsigned long long)LAST_KEY << 32 | (0xFFFFFFFFu - (flat0 + (uint32_t)i));
             continue;
         }
-        select_row_own_cut<VEC, FULL, E>(x, c, mx, lse, dst, flat0, nflat, V, m, list, lane);
+        select_row_own_cut<VEC, FULL, E, ALONE>(x, c, mx, lse, dst, flat0, nflat, V, m, list, lane);
     }
 }
 
@@ -1265,9 +1266,9 @@ static int compute_units() {
     return n_cu;
 }
 // mode 0: every row its own cut; mode 1: the listed rows' own cuts
-template <int VEC, bool FULL, typename LT>
-static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int mode) {
-    auto kern = select_rows_wave<VEC, FULL, LT>;
+template <int VEC, bool FULL, bool ALONE, typename LT>
+static int launch_rows_wave_as(const RowsLaunch &a, int64_t rows, int mode) {
+    auto kern = select_rows_wave<VEC, FULL, ALONE, LT>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (512 + GR4AD_MAX_BEAM + 2) * 8) != hipSuccess) return GR4AD_EHIP;
@@ -1283,6 +1284,14 @@ static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int mode) {
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows, a.n, a.V, a.m, a.cand,
                        mode == 1 ? (const int2 *)a.todo : nullptr, mode == 1 ? (const int *)a.todo_count : nullptr);
     return GR4AD_OK;
+}
+// (The length of a list is known on the device only, and it is short as a rule: beside a sweep of more than 4096 rows the four microseconds of a short one do not
+// show, while a long one takes half as long again on wavefronts of their own.)
+template <int VEC, bool FULL, typename LT>
+static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int mode) {
+    if constexpr (VEC >= 32)
+        if (rows <= 4096) return launch_rows_wave_as<VEC, FULL, true, LT>(a, rows, mode);
+    return launch_rows_wave_as<VEC, FULL, false, LT>(a, rows, mode);
 }
 // mode 2: the bounded pass, which lists the rows that need their own cut
 template <int VEC, bool FULL, typename LT>

@@ -31,6 +31,23 @@ def test_select_bound_from_several_rows(B, n, V, k, spread, half):
         judge_selection(allsc, flat, score[b], k, tol=3e-5, margin=2e-5, what="select b=%d" % b)
 
 
+@pytest.mark.parametrize("V", [4104, 8192])
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("B,n", [(2, 2048), (4097, 1), (1025, 4)])  # 4096 rows, whose own cuts run on wavefronts alone on their SIMD, and more, which share
+def test_select_lists_many_wide_rows(B, n, V, half):
+    """Equal scores overflow every row's segment, so that all rows get their own cut: the k lowest tokens of the request's first row."""
+    k = 24
+    logits = torch.full((B, n, V), 0.25, dtype=torch.float16 if half else torch.float32, device="cuda")
+    logits[:, -1, V - 3] = 1.0
+    parent, tok, score = binding.op_select(logits, torch.zeros(B, n, device="cuda"), k)
+    rest = torch.arange(k - 1, dtype=torch.int32, device="cuda")
+    assert (parent[:, 0] == n - 1).all() and (tok[:, 0] == V - 3).all()
+    assert (parent[:, 1:] == 0).all() and (tok[:, 1:] == rest).all()
+    lse_last, lse = (np.log((V - 1) * np.exp(0.25) + np.exp(1.0)), 0.25 + np.log(V))
+    np.testing.assert_allclose(score[:, 0].double().cpu().numpy(), 1.0 - lse_last, atol=2e-5)
+    np.testing.assert_allclose(score[:, 1:].double().cpu().numpy(), 0.25 - (lse_last if n == 1 else lse), atol=2e-5)
+
+
 # n * V candidates (V <= k: rows are not cut): kept in registers up to 8192 and read twice above, in pairs or one by one (odd segments of the
 # second request); the cut's bin holds few keys, hundreds of equal ones ("levels"), or nearly all of them beside far ones ("far")
 @pytest.mark.parametrize("spread", ["level", "levels", "far"])
