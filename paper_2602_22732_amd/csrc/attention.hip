@@ -1184,7 +1184,7 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
 // query attends to 0..pos.  Beams that share an ancestor read the same row.
 // One thread owns 8 consecutive channels of one row (16-byte accesses in bf16); the
 // dh/8 threads of a head are neighbouring lanes and join their partial dot products
-// with xor-shuffles, so every access of a wavefront is one contiguous stretch.
+// with moves between lanes, so every access of a wavefront is one contiguous stretch.
 // The positions are a template parameter, so that no branch stands between the loads: the ancestors' numbers, then all keys and values, then the
 // sums.  With a branch, and so a wait, per position the eight calls of 1024 requests x 512 beams x 4 positions (d 1024) took 4.92 ms; now 3.93,
 // where the last two positions move their bytes (the new rows once, 4.3 GB) at the rate of a large copy.

@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void for_each_key(const unsigned long long *__restric
     }
 }
 
-// Usual path of stage B: the candidates are read once into registers, HELD per thread (twice from memory where there are more), and
+// Usual path of stage B: the candidates are read once into registers, SELB_HELD per thread (twice from memory where there are more), and
 // swept twice.  A sample of one key per thread gives the span of the score bits; the first sweep counts the keys in 2048 equal bins of that
 // span (keys outside it fall into the end bins; the bin index is monotone in the key, and the counts spread over the bins, unlike the leading
 // radix digit, which most keys of a request share), the second collects every key from the threshold bin up into LDS: those above it, then its
