@@ -82,7 +82,7 @@ def test_bf16_rows_do_not_depend_on_the_row_count(N, K):
     np.testing.assert_allclose(many32[:64].double().cpu().numpy(), (a[:64].double() @ w.double().t()).cpu().numpy(), atol=2e-5, rtol=1e-5)
 
 
-@pytest.mark.parametrize("d,H,F", [(256, 8, 1024), (512, 4, 2048)])
+@pytest.mark.parametrize("d,H,F", [(256, 8, 1024), (512, 4, 2048), (1024, 16, 2048)])
 @pytest.mark.parametrize("B,n", [(3, 33), (47, 33), (97, 31), (239, 33)])
 def test_requests_do_not_depend_on_their_batch(d, H, F, B, n):
     """The products that add a residual or a table row: one request's rows on the smallest tiles, those of a batch (99 to 7887, ragged) on all the others."""
