@@ -33,7 +33,7 @@ def test_select_bound_from_several_rows(B, n, V, k, spread, half):
 
 @pytest.mark.parametrize("V", [4104, 8192])
 @pytest.mark.parametrize("half", [False, True])
-@pytest.mark.parametrize("B,n", [(2, 2048), (4097, 1), (1025, 4)])  # 4096 rows, whose own cuts run on wavefronts alone on their SIMD, and more, which share
+@pytest.mark.parametrize("B,n", [(4, 2048), (8193, 1), (2049, 4)])  # 8192 rows, whose own cuts run on wavefronts alone on their SIMD, and more, which share
 def test_select_lists_many_wide_rows(B, n, V, half):
     """Equal scores overflow every row's segment, so that all rows get their own cut: the k lowest tokens of the request's first row."""
     k = 24
