@@ -64,6 +64,17 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// the same where the 32 lanes beyond this half hold zeros or another row (both halves get their own sum)
+__device__ __forceinline__ float half_wave_sum(float v) {
+    const uintx2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    v += dpp_move<0x128, 0xF>(0.0f, v);
+    v += dpp_move<0x124, 0xF>(0.0f, v);
+    v += dpp_move<0x122, 0xF>(0.0f, v);
+    v += dpp_move<0x121, 0xF>(0.0f, v);
+    return v;
+}
+
 // The same reductions with the result in a scalar.  Rotations by 8, 4, 2, 1 inside each row of 16 lanes leave the row's result in
 // all of its lanes; two row broadcasts (lane 15 into the next row for rows 1 and 3, lane 31 into rows 2 and 3) leave the
 // wavefront's result in lane 63, which is read back.  The summation tree differs from wave_sum's: kernels that
@@ -79,6 +90,20 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 }
 // four values' part of a sum of squares (spelled out: kernels that must agree to the bit leave the contraction to nobody)
 __device__ __forceinline__ float sum_sq4(float a, float b, float c, float d) { return fmaf(b, b, a * a) + fmaf(d, d, c * c); }
+// bf16 RMSNorm: a lane's sum of squares over its first eight values and over further ones, and 1/rms of a row from the sum over its lanes (wave_sum) - for the
+// norm kernel and the products that normalise, which agree to the bit
+__device__ __forceinline__ float first_squares(const float *v) {
+    float ss = fmaf(v[0], v[0], v[1] * v[1]);
+#pragma unroll
+    for (int e = 2; e < 8; e++) ss = fmaf(v[e], v[e], ss);
+    return ss;
+}
+__device__ __forceinline__ float more_squares(float ss, const float *v) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) ss = fmaf(v[e], v[e], ss);
+    return ss;
+}
+__device__ __forceinline__ float rms_inv(float ss, int d, float eps) { return 1.0f / sqrtf(ss / (float)d + eps); }
 __device__ __forceinline__ float wave_max_dpp(float v) {
     v = fmaxf(v, dpp_move<0x128, 0xF>(v, v));
     v = fmaxf(v, dpp_move<0x124, 0xF>(v, v));

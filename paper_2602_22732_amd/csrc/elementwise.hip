@@ -54,14 +54,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *__restrict__ 
             if constexpr (N == 4) {
                 ss += sum_sq4(v[i][0], v[i][1], v[i][2], v[i][3]);
             } else {
-#pragma unroll
-                for (int e = 0; e < N; e++) ss += v[i][e] * v[i][e];
+                ss = i == 0 ? first_squares(v[i]) : more_squares(ss, v[i]);
             }
         }
     }
-    // (float32: the sum of gemm_f32_mfma's prologue, so that a row is normalised alike in every batch)
+    // (the sums of gemm_f32_mfma's prologue and of gemm_bf16_panel, so that a row is normalised alike in every batch)
     ss = N == 4 ? wave_sum_dpp(ss) : wave_sum(ss);
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+    const float inv = rms_inv(ss, d, eps);
 #pragma unroll
     for (int i = 0; i < MAXV; i++) {
         int c = lane + i * 64;

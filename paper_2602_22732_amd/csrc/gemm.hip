@@ -12,6 +12,8 @@
 //                        v_mfma_f32_32x32x16_bf16; 32x32 to 128x128 tiles for the
 //                        small and middle shapes, operands streamed into LDS,
 //                        by wavefronts of their own where tiles are few.
+//  * gemm_bf16_panel<..> the small products behind an RMSNorm: the workgroup
+//                        normalises the rows it multiplies.
 //  * gemm_bf16_ring<..>  the kernel of the large shapes: persistent, 256x256 tiles,
 //                        operands stream global -> LDS without passing registers.
 #include <string.h>
@@ -1612,6 +1614,239 @@ static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64
     return launch_tile_cfg<128, 128, 64, 64, 4, 3, false>(A, lda, W, ldw, M, N, K, kind, epi, st, batch, ba, bw, bc);
 }
 
+// ---------------------------------------------------------------------------
+// MFMA kernel of the small products behind an RMSNorm: the rows of A are formed by the workgroup that multiplies them
+// ---------------------------------------------------------------------------
+// Where launches are short a norm of its own is a launch of 1.7 to 4.7 us whose rows the product then waits for again.  Here a workgroup (8 wavefronts) requests
+// its rows of x (float32, all K columns) and every k-tile of W it will multiply at once, normalises the rows while W is on the way, leaves them in LDS as the
+// tile kernel's operand (bf16, rounded as the norm kernel rounds them) and multiplies: BM x BN / 1024 wavefronts, 32x32 each, one chain of MFMAs over K without a barrier.
+// The price is that each column of tiles forms the rows anew, so it is for few tiles: the rule is at panel_shape.  Same order of every sum as rmsnorm_kernel
+// and gemm_bf16_tile: same bits.
+// LDS: BM x K values of A (a k-tile of 64 values: BM rows of 128 bytes), then BN x K of W.
+// V: 16-byte pieces of a row per lane (1: K <= 512, 2: K <= 1024), 0: K <= 256, two rows to a wavefront.
+// J: steps a wavefront takes its rows in (fewer than BM has: rows beyond them are past the last one).
+template <int BM, int BN, int V, int J, int KIND>
+__global__ __launch_bounds__(512, 4) void gemm_bf16_panel(const float *__restrict__ x, const bf16 *__restrict__ gain, const bf16 *__restrict__ W, int64_t ldw, int M, int N,
+                                                          int K, float eps, int tiles_m, int tiles_n, void *C, int64_t ldc, const float *__restrict__ bias) {
+    constexpr int WAVES_N = BN / 32, NC = BM / 32 * WAVES_N, WTILE = BN * 128, PIECES = BN / 8;
+    constexpr int VEC = V == 2 ? 2 : 1, KMAX = V == 0 ? 256 : 512 * V;
+    static_assert(J * (V == 0 ? 16 : 8) <= BM, "rows of the tile");
+    extern __shared__ bf16x8 smem[];
+    const int lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    // (the tile order of gemm_bf16_tile)
+    const uint32_t total = (uint32_t)tiles_m * (uint32_t)tiles_n, per_xcd = (total + 7) / 8;
+    const uint32_t l = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per_xcd || l >= total) return;
+    const uint32_t gsz = 8u * (uint32_t)tiles_n, grp = l / gsz, in = l - grp * gsz;
+    const uint32_t left = (uint32_t)tiles_m - grp * 8, gm = left < 8 ? left : 8;
+    const int m0 = (int)(grp * 8 + in % gm) * BM;
+    const int n0 = (int)(in / gm) * BN;
+    const int KT = K / 64;
+    char *const panel = (char *)smem, *const slots = panel + BM * K * 2;
+
+    // ---- the rows of x and the gains: requested first, they are needed first.  Dealt to the wavefronts in turn, rows past the edge re-read the last one.  No
+    // branch between these loads and those of W, so that the compiler can count them and wait for x alone ----
+    const int nvec = K / 8, pos = V == 0 ? lane % 32 : lane, half = V == 0 ? lane / 32 : 0;
+    auto row_of = [&](int j) { return (j * 8 + wave) * (V == 0 ? 2 : 1) + half; };
+    float v[J][VEC][8];
+    bf16x8 g[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; i++) g[i] = *(const bf16x8 *)(gain + (pos + 64 * i < nvec ? pos + 64 * i : nvec - 1) * 8);
+    const float *xr = x + (int64_t)m0 * K;  // (rows and columns of the block by 32-bit offsets)
+#pragma unroll
+    for (int j = 0; j < J; j++) {
+        const int r = row_of(j), off = (m0 + r < M ? r : M - 1 - m0) * K;
+#pragma unroll
+        for (int i = 0; i < VEC; i++) {
+            const float *p = xr + off + (pos + 64 * i < nvec ? pos + 64 * i : nvec - 1) * 8;
+            *(floatx4 *)&v[j][i][0] = *(const floatx4 *)p;
+            *(floatx4 *)&v[j][i][4] = *(const floatx4 *)(p + 4);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- W: piece p of a k-tile is its rows 8p .. 8p+7 (rows past the edge re-read the last one).  A wavefront has one piece of every k-tile (of every other one);
+    // past the last k-tile it loads its last piece again ----
+    auto source = [&](int pc, int t) {
+        const int r = n0 + pc * 8 + lane / 8;
+        return (const char *)(W + (int64_t)(r < N ? r : N - 1) * ldw) + t * 128 + ((lane % 8) ^ ((4 * (pc & 1)) ^ (lane / 16))) * 16;
+    };
+    {
+        constexpr int EVERY = 8 / PIECES, LOADS = KMAX / 64 / EVERY;  // k-tiles from one of a wavefront's loads to the next; its loads
+        const int t0 = wave / PIECES, last = KT > t0 ? (KT - 1 - t0) / EVERY : 0;  // (one k-tile, and none for this wavefront: it loads what another does)
+        const char *src = source(wave % PIECES, KT > t0 ? t0 : 0);
+        char *dst = slots + (KT > t0 ? wave : wave % PIECES) * 1024;
+#pragma unroll
+        for (int i = 0; i < LOADS; i++) {
+            const int at = i < last ? i : last;
+            ring_dma16(src + at * (EVERY * 128), (bf16x8 *)(dst + at * 8192));
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int wrow0 = m0 + wm * 32, wcol0 = n0 + wn * 32;
+    // ---- RMSNorm: four steps' factors at once, one in each lane of a quad (a division and a root are some fifty instructions) ----
+    float ss[J];
+#pragma unroll
+    for (int j = 0; j < J; j++) {
+        const float one = first_squares(v[j][0]);
+        ss[j] = pos < nvec ? one : 0.0f;
+        if constexpr (VEC == 2) {
+            const float two = more_squares(ss[j], v[j][1]);
+            if (pos + 64 < nvec) ss[j] = two;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < J; j++) ss[j] = V == 0 ? half_wave_sum(ss[j]) : wave_sum(ss[j]);
+    float inv[J];
+#pragma unroll
+    for (int j = 0; j < J; j += 4) {
+        float mine = ss[j];
+        if constexpr (J >= 2) mine = (lane & 1) ? ss[j + 1] : mine;
+        if constexpr (J >= 4) mine = (lane & 2) ? ((lane & 1) ? ss[j + 3] : ss[j + 2]) : mine;
+        const float f = rms_inv(mine, K, eps);
+        inv[j] = dpp_move<0x00, 0xF>(f, f);  // quad_perm: one lane of the quad to all four
+        if constexpr (J >= 2) inv[j + 1] = dpp_move<0x55, 0xF>(f, f);
+        if constexpr (J >= 4) {
+            inv[j + 2] = dpp_move<0xAA, 0xF>(f, f);
+            inv[j + 3] = dpp_move<0xFF, 0xF>(f, f);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < J; j++) {
+        const int r = row_of(j);
+#pragma unroll
+        for (int i = 0; i < VEC; i++) {
+            const int c = pos + 64 * i;
+            bf16x8 y;
+#pragma unroll
+            for (int e = 0; e < 8; e++) y[e] = (bf16)((float)g[i][e] * v[j][i][e] * inv[j]);
+            if (c < nvec) *(bf16x8 *)(panel + (c / 8) * (BM * 128) + r * 128 + ((c % 8) ^ ((r >> 1) & 7)) * 16) = y;
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (wave >= NC) return;
+    // ---- products: fragments as in gemm_bf16_tile, a k-tile ahead ----
+    const int frow = lane % 32, hf = lane / 32, fx = (frow >> 1) & 7;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    const uint32_t a_lane = lds0 + (uint32_t)((wm * 32 + frow) * 8 + (hf ^ fx)) * 16;
+    const uint32_t w_lane = lds0 + (uint32_t)(BM * K * 2) + (uint32_t)((wn * 32 + frow) * 8 + (hf ^ fx)) * 16;
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[v] = 0.0f;
+    struct Fragments { bf16x8 a[4], w[4]; };
+    Fragments f0, f1;
+    auto read = [&](Fragments &f, int t) {
+        const uint32_t pa = a_lane + (uint32_t)(t * BM * 128), pw = w_lane + (uint32_t)(t * WTILE);
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            asm volatile("ds_read_b128 %0, %1" : "=v"(f.a[s]) : "v"(pa ^ (uint32_t)(s << 5)));
+            asm volatile("ds_read_b128 %0, %1" : "=v"(f.w[s]) : "v"(pw ^ (uint32_t)(s << 5)));
+        }
+    };
+    auto mma = [&](Fragments &f, bool behind) {  // behind: the other set's eight reads were issued after this one's
+        __builtin_amdgcn_sched_barrier(0);
+        if (behind) asm volatile("s_waitcnt lgkmcnt(8)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.w[2]), "+v"(f.w[3]));
+        else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.w[2]), "+v"(f.w[3]));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 4; s++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s], f.w[s], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    read(f0, 0);
+    int t = 1;
+    for (; t + 1 < KT; t += 2) {
+        read(f1, t);
+        mma(f0, true);
+        read(f0, t + 1);
+        mma(f1, true);
+    }
+    if (t < KT) {
+        read(f1, t);
+        mma(f0, true);
+        mma(f1, false);
+    } else {
+        mma(f0, false);
+    }
+    GemmEpilogue epi = {};
+    epi.C = C;
+    epi.ldc = ldc;
+    epi.bias = bias;
+    float add[16];
+    direct_epilogue<KIND>(acc, add, wrow0, wcol0, M, N, epi, lane);
+}
+
+template <int BM, int BN, int V, int J, int KIND>
+static int launch_panel_kind(const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi, hipStream_t st) {
+    auto kern = gemm_bf16_panel<BM, BN, V, J, KIND>;
+    constexpr int KMAX = V == 0 ? 256 : 512 * V;
+    auto bytes = [](int k) { return (BM + BN) * k * 2; };
+    static_assert(KMAX * (BM + BN) * 2 <= 160 * 1024, "the workgroup's LDS");
+    static bool attr_done = false;
+    if (!attr_done) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes(KMAX)) != hipSuccess) return GR4AD_EHIP;
+        attr_done = true;
+    }
+    const int64_t tiles_m = ceil_div64(M, BM), tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n;
+    {
+        ProfScope ps(KC_GEMM_TILE, st, 2.0 * (double)M * N * K, gemm_bytes(M, N, K, kind_f32(KIND), false) + 2.0 * M * K);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(ceil_div64(total, 8) * 8)), dim3(512), bytes(K), st, epi.pre_x, (const bf16 *)epi.pre_gain, W,
+                           ldw, (int)M, N, K, epi.pre_eps, (int)tiles_m, (int)tiles_n, epi.C, epi.ldc, epi.bias);
+    }
+    GR4AD_LAUNCH_CHECK();
+    return GR4AD_OK;
+}
+
+template <int BM, int BN, int V, int J>
+static int launch_panel_cfg(const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi, hipStream_t st) {
+    switch (kind) {
+        case EPI_STORE: return launch_panel_kind<BM, BN, V, J, EPI_STORE>(W, ldw, M, N, K, epi, st);
+        case EPI_SILU_DIV: return launch_panel_kind<BM, BN, V, J, EPI_SILU_DIV>(W, ldw, M, N, K, epi, st);
+        case EPI_F32: return launch_panel_kind<BM, BN, V, J, EPI_F32>(W, ldw, M, N, K, epi, st);
+    }
+    return GR4AD_EUNSUPPORTED;
+}
+
+// Where the lines lie (us, norm kernel and product / this kernel, calls in a row on weights in turn): K = 256: 64 x 1024 5.4 / 4.2, 512 x 768 5.5 / 4.0 (32x64 tiles, 4.7 on
+// 32x32), 1024 x 1024 6.3 / 5.5 (64x64 tiles, 6.0 on 32x64), 4096 x 256 6.8 / 4.9, 2048 x 1024 7.6 / 7.5 (512 tiles), 4096 x 768 9.1 / 9.9.  K = 512: 64 x 512 5.7 / 4.7,
+// 256 x 2048 6.6 / 6.0 (32x64 tiles, 7.4 on 32x32), 192 x 4096 6.9 / 9.6 (384 tiles), 512 x 1536 on 64x64 tiles 7.0 / 7.3.  K = 1024: 8 x 1024 6.7 / 5.4, but 32 x 1024 6.7 / 6.9:
+// every column of tiles forms the rows anew, 0.85 us of vector arithmetic and 128 KB of x for 32 of them.  Decodes of one request, d = 512, 619 -> 585 us; of 64, d = 256, 577 -> 548.
+enum { PANEL_NONE = 0, PANEL_32, PANEL_32X64, PANEL_64, PANEL_FEW };  // few: at most 16 rows of 32x32 tiles
+static int panel_shape(int64_t M, int N, int K) {
+    if (K > 1024) return PANEL_NONE;
+    auto tiles = [&](int bm, int bn) { return ceil_div64(M, bm) * ((N + bn - 1) / bn); };
+    if (M <= 16) return tiles(32, 32) <= 256 ? PANEL_FEW : PANEL_NONE;
+    if (K > 512) return PANEL_NONE;
+    if (tiles(32, 32) <= (K <= 256 ? 256 : 192)) return PANEL_32;
+    if (tiles(32, 64) <= 256) return PANEL_32X64;
+    return K <= 256 && tiles(64, 64) <= 384 ? PANEL_64 : PANEL_NONE;
+}
+
+static int launch_panel(int shape, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi, hipStream_t st) {
+#define PANEL_(bm, bn, v, j) return launch_panel_cfg<bm, bn, v, j>(W, ldw, M, N, K, kind, epi, st)
+    if (shape == PANEL_FEW) {
+        if (K <= 256) PANEL_(32, 32, 0, 1);
+        if (M <= 8) {
+            if (K <= 512) PANEL_(32, 32, 1, 1);
+            PANEL_(32, 32, 2, 1);
+        }
+        if (K <= 512) PANEL_(32, 32, 1, 2);
+        PANEL_(32, 32, 2, 2);
+    }
+    if (shape == PANEL_32) {
+        if (K <= 256) PANEL_(32, 32, 0, 2);
+        PANEL_(32, 32, 1, 4);
+    }
+    if (shape == PANEL_32X64) {
+        if (K <= 256) PANEL_(32, 64, 0, 2);
+        PANEL_(32, 64, 1, 4);
+    }
+    PANEL_(64, 64, 0, 4);
+#undef PANEL_
+}
+
 // Batched product on the tile kernels: for i < batch, C_i[M,N] = A_i[M,K] * W_i[N,K]^T with A_i = A + i*batch_a elements etc.
 // bf16 operands; C bf16 or (out_f32) float.  Used by the lazy layers' cross-attention in absorbed form (many small products).
 // batch_len (may be NULL), len_bounds: 1 = batch i only needs columns n < batch_len[i] of C_i (the rest may stay unwritten),
@@ -1732,6 +1967,11 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
         if (lda != K || !epi.pre_gain) return GR4AD_EINVAL;
         if (dtype == GR4AD_F32 && !f32_big_tiles(M, N) && f32_mfma_ok(epi.pre_x, lda, W, ldw, K) && ((uintptr_t)epi.pre_gain % 16) == 0)
             return launch_f32(epi.pre_x, lda, (const float *)W, ldw, M, N, K, epi, st);
+        const int kd = kind == EPI_SILU ? EPI_SILU_DIV : kind;
+        if (M < 8192 && !epi.skip_len && mfma_ok(dtype, A, lda, W, ldw, K, kind) && ((uintptr_t)epi.pre_x % 16) == 0 && ((uintptr_t)epi.pre_gain % 16) == 0) {
+            const int shape = panel_shape(M, N, K);
+            if (shape != PANEL_NONE) return launch_panel(shape, (const bf16 *)W, ldw, M, N, K, kd, epi, st);
+        }
         const int s = launch_rmsnorm(dtype, epi.pre_x, epi.pre_gain, (void *)A, M, K, epi.pre_eps, st, epi.skip_len && !epi.skip_S ? epi.skip_len : nullptr);
         if (s) return s;
         GemmEpilogue plain = epi;
