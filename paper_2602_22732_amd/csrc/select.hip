@@ -494,6 +494,7 @@ __device__ __forceinline__ float first_row_bound(float x0, float bound, float c,
 // turned into sortable keys only for the survivors on the way out.
 #define WROW_BINS 1024
 #define WROW_LIST 512  // threshold-bin candidates ranked exactly; the list reuses the histogram's 4 KB
+#define WROW_FEW 64    // up to here at once (each lane reads the whole list: 230 candidates took 50 us)
 
 __device__ __forceinline__ unsigned long long staged_to_key(unsigned long long st) {
     return ((unsigned long long)score_key(__uint_as_float((uint32_t)(st >> 32))) << 32) | (st & 0xFFFFFFFFull);
@@ -505,7 +506,8 @@ template <int E> __device__ __forceinline__ int wave_tok(int i, int lane) { retu
 // exact fallback on the registers of one wavefront: radix selection on the score keys, two bits per step (ALONE: a function for each kernel that calls
 // it, or all of them get the registers of the one with the most)
 template <int VEC, int E, bool ALONE>
-__device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], int V, int m, uint32_t flat0, unsigned long long *stage) {
+__device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], int V, int m, uint32_t flat0, unsigned long long *stage, bool tied, uint32_t tie,
+                                                   int tie_krem) {
     const int lane = threadIdx.x % 64;
     uint32_t k_and = 0xFFFFFFFFu, k_or = 0u;
 #pragma unroll
@@ -516,7 +518,10 @@ __device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], i
     const uint32_t diff = k_and ^ k_or;
     uint32_t decided = 0xFFFFFFFFu, prefix = k_and;
     int krem = m, active = V;
-    if (diff != 0) {
+    if (tied) {  // the threshold is known: tie_krem of the scores equal to `tie` are taken, all above them
+        prefix = tie;
+        krem = tie_krem;
+    } else if (diff != 0) {
         const int top = 31 - __clz(diff);
         decided = ~((2u << top) - 1u);  // top == 31 gives 0
         prefix = k_and & decided;
@@ -584,6 +589,8 @@ template <int VEC, bool FULL, int E, bool ALONE>
 __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c, float mx, float lse, unsigned long long *__restrict__ dst,
                                                    uint32_t flat0, uint32_t nflat, int V, int m, unsigned long long *list, int lane) {
     constexpr int NX = VEC * 4;
+    // Rows of more than 2048 tokens have no registers left for another histogram (77 x 338 listed rows of 7016 tokens that are all masked 1048 us without, 1535 with)
+    constexpr bool AGAIN = VEC <= 8;
     int *hist = (int *)list;
     unsigned long long *stage = list + 512;
     // scores from here on (padding stays -inf)
@@ -591,7 +598,7 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
 #pragma unroll
     for (int i = 0; i < NX; i++) {
         x[i] = c + (x[i] - lse);
-        mn = fminf(mn, (FULL || wave_tok<E>(i, lane) < V) ? x[i] : INFINITY);
+        mn = fminf(mn, ((FULL || wave_tok<E>(i, lane) < V) && (!AGAIN || x[i] > -INFINITY)) ? x[i] : INFINITY);
     }
     if (m >= V) {  // nothing to cut: every token is a candidate
 #pragma unroll
@@ -601,46 +608,77 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
         }
         return;
     }
-    // 1. histogram of the scores over equal-width bins of [lo, hi]; the bin index is monotone in the score
-    const float lo = -wave_max(-mn), hi = c + (mx - lse);
-    const float inv_w = (hi > lo) ? ((float)WROW_BINS - 0.01f) / (hi - lo) : 0.0f;
-    const float k0 = -lo * inv_w;
+    // 1. histogram of the scores over equal-width bins of [lo, hi] (AGAIN: lo is the least that is not -inf, which a masked token has); the bin index is monotone in the score
+    float lo = -wave_max(-mn), hi = c + (mx - lse);
+    float inv_w = (hi > lo) ? ((float)WROW_BINS - 0.01f) / (hi - lo) : 0.0f;
+    float k0 = -lo * inv_w;
+    int T, krem, cntT;
+    bool tied = false;
+    float tie = 0.0f;
+    for (int zoom = 0;; zoom++) {
 #pragma unroll
-    for (int i = 0; i < 4; i++) ((int4 *)hist)[i * 64 + lane] = make_int4(0, 0, 0, 0);
+        for (int i = 0; i < 4; i++) ((int4 *)hist)[i * 64 + lane] = make_int4(0, 0, 0, 0);
 #pragma unroll
-    for (int i = 0; i < NX; i++) {
-        const uint32_t bi = min((uint32_t)__builtin_fmaf(x[i], inv_w, k0), (uint32_t)(WROW_BINS - 1));  // negative and NaN convert to 0
-        if (FULL || wave_tok<E>(i, lane) < V) atomicAdd(&hist[bi], 1);
-    }
-    // 2. lane l owns bins 1023-16l .. 1008-16l; inclusive scan from the top bin down finds the bin T of the m-th best score
-    int h[16];
-    {
-        const int4 *hp = (const int4 *)(hist + WROW_BINS - 16 - 16 * lane);
-#pragma unroll
-        for (int i = 0; i < 4; i++) { const int4 t = hp[i]; h[4 * i] = t.x; h[4 * i + 1] = t.y; h[4 * i + 2] = t.z; h[4 * i + 3] = t.w; }
-    }
-    int mine = 0;
-#pragma unroll
-    for (int i = 0; i < 16; i++) mine += h[i];
-    int incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
-    int above = incl - mine, selT = 0, selK = 0, selC = 0;
-    const bool owner = above < m && incl >= m;
-    if (owner) {
-#pragma unroll
-        for (int i = 15; i >= 0; i--) {  // h[15] is this lane's top bin
-            if (selC == 0 && above + h[i] >= m) { selT = WROW_BINS - 16 - 16 * lane + i; selK = m - above; selC = h[i]; }
-            if (selC == 0) above += h[i];
+        for (int i = 0; i < NX; i++) {
+            const uint32_t bi = min((uint32_t)__builtin_fmaf(x[i], inv_w, k0), (uint32_t)(WROW_BINS - 1));  // negative and NaN convert to 0
+            if (FULL || wave_tok<E>(i, lane) < V) atomicAdd(&hist[bi], 1);
         }
+        // 2. lane l owns bins 1023-16l .. 1008-16l; inclusive scan from the top bin down finds the bin T of the m-th best score
+        int h[16];
+        {
+            const int4 *hp = (const int4 *)(hist + WROW_BINS - 16 - 16 * lane);
+#pragma unroll
+            for (int i = 0; i < 4; i++) { const int4 t = hp[i]; h[4 * i] = t.x; h[4 * i + 1] = t.y; h[4 * i + 2] = t.z; h[4 * i + 3] = t.w; }
+        }
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < 16; i++) mine += h[i];
+        int incl = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
+        int above = incl - mine, selT = 0, selK = 0, selC = 0;
+        const bool owner = above < m && incl >= m;
+        if (owner) {
+#pragma unroll
+            for (int i = 15; i >= 0; i--) {  // h[15] is this lane's top bin
+                if (selC == 0 && above + h[i] >= m) { selT = WROW_BINS - 16 - 16 * lane + i; selK = m - above; selC = h[i]; }
+                if (selC == 0) above += h[i];
+            }
+        }
+        const int src_lane = __ffsll((long long)__ballot(owner)) - 1;
+        T = __shfl(selT, src_lane, 64);
+        krem = __shfl(selK, src_lane, 64);
+        cntT = __shfl(selC, src_lane, 64);
+        if (!AGAIN || cntT <= WROW_FEW) break;
+        // Crowded (masked tokens, or low finite masks that press the other scores into a few bins): equal scores go by their tokens, others take another
+        // histogram over the span of this bin's alone
+        float lo_t = INFINITY, hi_t = -INFINITY, least = INFINITY;  // least: that is not -inf
+        float inv_w2 = inv_w, k02 = k0;
+        asm volatile("" : "+v"(inv_w2), "+v"(k02));
+#pragma unroll
+        for (int i = 0; i < NX; i++) {
+            const int bi = (int)min((uint32_t)__builtin_fmaf(x[i], inv_w2, k02), (uint32_t)(WROW_BINS - 1));
+            if (bi == T && (FULL || wave_tok<E>(i, lane) < V)) {
+                lo_t = fminf(lo_t, x[i]);
+                hi_t = fmaxf(hi_t, x[i]);
+                least = fminf(least, x[i] > -INFINITY ? x[i] : INFINITY);
+            }
+        }
+        lo_t = -wave_max(-lo_t);
+        hi_t = wave_max(hi_t);
+        least = -wave_max(-least);
+        tied = lo_t == hi_t;
+        tie = hi_t;
+        if (tied || zoom == 3 || !(hi_t >= least)) break;
+        inv_w = hi_t > least ? (float)(WROW_BINS - 3) / (hi_t - least) : 1.0f;
+        k0 = 1.5f - least * inv_w;  // (-inf alone in bin 0)
+        if (!(inv_w < INFINITY)) break;
     }
-    const int src_lane = __ffsll((long long)__ballot(owner)) - 1;
-    const int T = __shfl(selT, src_lane, 64), krem = __shfl(selK, src_lane, 64), cntT = __shfl(selC, src_lane, 64);
-    if (cntT > WROW_LIST) {  // crowded threshold bin (e.g. all logits equal): exact radix selection
+    if (tied || cntT > WROW_LIST) {  // ties, or exact radix selection
         float sc[NX];  // a copy, so that only this branch keeps the scores in addressable memory
 #pragma unroll
         for (int i = 0; i < NX; i++) sc[i] = x[i];
-        select_row_radix_wave<VEC, E, ALONE>(sc, V, m, flat0, stage);
+        select_row_radix_wave<VEC, E, ALONE>(sc, V, m, flat0, stage, tied, score_key(tie), krem);
     } else {
         // 3. bins above T go straight to the staged output, bin T to the list (over the dead histogram) for exact ranking
         const int n_gt = m - krem;
@@ -683,7 +721,7 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
 template <int VEC, bool FULL, bool ALONE, typename LT>
 __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V,
                                                           int m, unsigned long long *__restrict__ cand, const int2 *__restrict__ todo,
-                                                          const int *__restrict__ todo_count) {
+                                                          const int *__restrict__ todo_count, bool numbers_first) {
     constexpr int E = LogitPiece<LT>::E, NX = VEC * 4, G = NX / E;
     extern __shared__ unsigned long long wave_lds[];  // per wavefront: 512 slots of histogram / list, then m slots of staged output
     const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
@@ -723,7 +761,7 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
         const uint32_t nflat = 0xFFFFFFFFu - flat0 - (uint32_t)lane * (uint32_t)E;
         const float c = cum ? cum[vrow] : 0.0f;
         unsigned long long *dst = cand + (dst_at >= 0 ? dst_at : vrow * (int64_t)m);
-        if (todo && (lse != lse || c != c)) {
+        if (numbers_first && (lse != lse || c != c)) {
             // No score of the row is a number (a beam whose tokens are all masked, say).  Its tokens rank below every number, -inf too, so they
             // survive only where the request has fewer than k numbers.  (m <= V)
             for (int i = lane; i < m; i += 64) dst[i] = (unsigned long long)LAST_KEY << 32 | (0xFFFFFFFFu - (flat0 + (uint32_t)i));
@@ -1023,39 +1061,26 @@ __device__ __forceinline__ void for_each_key(const unsigned long long *__restric
 // 12.6 and 15.9, now 10.2 and 12.0.
 // Returns false, having selected nothing, when more than SELB_SORT_MAX keys lie from the threshold bin up (the exact radix selection then runs).
 #define SELB_HELD 8
+#define SELB_SORT_ALL 256  // up to here all keys are sorted
 #define SELB_TIES 256  // keys of the threshold bin that are ranked against each other
-__device__ __forceinline__ bool select_request_binned(const unsigned long long *__restrict__ src, int64_t ncand, int k,
-                                                      unsigned long long *skeys, int *hist, int *wave_tot, int *sel_digit, int *sel_krem,
-                                                      int *sel_cnt, int *out_cnt) {
-    __shared__ uint32_t span_hi[SELB_THREADS / 64], span_lo[SELB_THREADS / 64];
-    __shared__ int gathered;
+struct SelbShared {  // (one request's)
+    unsigned long long skeys[SELB_SORT_MAX];
+    int hist[2048];
+    int wave_tot[16];
+    uint32_t span_hi[SELB_THREADS / 64], span_lo[SELB_THREADS / 64];
+    int sel_digit, sel_krem, sel_cnt, out_cnt, gathered;
+};
+// x: the keys of this thread (0: none), all of them (held) or not yet; each(f): every key that is not held; smp_hi, smp_lo: this thread's part of the sampled span
+template <int H, typename EACH>
+__device__ __forceinline__ bool select_binned(unsigned long long (&x)[H], bool held, EACH each, uint32_t smp_hi, uint32_t smp_lo, int k, SelbShared &sh) {
     const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
-    const bool held = ncand <= SELB_HELD * SELB_THREADS;
-    unsigned long long x[SELB_HELD];  // 0: none
-    if (held) {
-        const bool pairs = (((uintptr_t)src) & 15) == 0;
-#pragma unroll
-        for (int j = 0; j < SELB_HELD; j += 2) {
-            const int i = j * SELB_THREADS + (pairs ? 2 * tid : tid), i2 = pairs ? i + 1 : i + SELB_THREADS;
-            x[j] = x[j + 1] = 0ull;
-            if (pairs && i2 < ncand) {
-                const ulonglong2 a = *(const ulonglong2 *)(src + i);
-                x[j] = a.x;
-                x[j + 1] = a.y;
-            } else {
-                if (i < ncand) x[j] = src[i];
-                if (i2 < ncand) x[j + 1] = src[i2];
-            }
-        }
-    }
-    const uint32_t smp = (uint32_t)(src[(int64_t)tid * ncand / SELB_THREADS] >> 32);
-    for (int i = tid; i < 2048; i += SELB_THREADS) hist[i] = 0;
-    if (tid == 0) *out_cnt = gathered = 0;
-    uint32_t smax = wave_max_u(smp), smin = ~wave_max_u(~smp);
-    if (lane == 0) { span_hi[wv] = smax; span_lo[wv] = smin; }
+    for (int i = tid; i < 2048; i += SELB_THREADS) sh.hist[i] = 0;
+    if (tid == 0) sh.out_cnt = sh.gathered = 0;
+    uint32_t smax = wave_max_u(smp_hi), smin = ~wave_max_u(~smp_lo);
+    if (lane == 0) { sh.span_hi[wv] = smax; sh.span_lo[wv] = smin; }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < SELB_THREADS / 64; q++) { smax = max(smax, span_hi[q]); smin = min(smin, span_lo[q]); }
+    for (int q = 0; q < SELB_THREADS / 64; q++) { smax = max(smax, sh.span_hi[q]); smin = min(smin, sh.span_lo[q]); }
     const uint32_t span = smax - smin;
     int nsh = span < 2048u ? 0 : 21 - __clz((int)span);
     if ((span >> nsh) >= 2040u) nsh++;
@@ -1065,60 +1090,61 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
     };
     if (held) {
 #pragma unroll
-        for (int j = 0; j < SELB_HELD; j++)
-            if (x[j]) atomicAdd(&hist[digit(x[j])], 1);
+        for (int j = 0; j < H; j++)
+            if (x[j]) atomicAdd(&sh.hist[digit(x[j])], 1);
     } else {
-        for_each_key(src, ncand, [&](unsigned long long key) { atomicAdd(&hist[digit(key)], 1); });
+        each([&](unsigned long long key) { atomicAdd(&sh.hist[digit(key)], 1); });
     }
     __syncthreads();
     // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
-    const int hi = hist[2047 - 2 * tid], lo = hist[2046 - 2 * tid];
+    const int hi = sh.hist[2047 - 2 * tid], lo = sh.hist[2046 - 2 * tid];
     const int v = wave_scan(hi + lo);
-    if (lane == 63) wave_tot[wv] = v;
+    if (lane == 63) sh.wave_tot[wv] = v;
     __syncthreads();
     int add = 0;
 #pragma unroll
-    for (int q = 0; q < SELB_THREADS / 64; q++) add += q < wv ? wave_tot[q] : 0;
+    for (int q = 0; q < SELB_THREADS / 64; q++) add += q < wv ? sh.wave_tot[q] : 0;
     const int incl = v + add, excl = incl - hi - lo;
     if (excl < k && incl >= k) {
-        if (excl + hi >= k) { *sel_digit = 2047 - 2 * tid; *sel_krem = k - excl; *sel_cnt = hi; }
-        else { *sel_digit = 2046 - 2 * tid; *sel_krem = k - excl - hi; *sel_cnt = lo; }
+        if (excl + hi >= k) { sh.sel_digit = 2047 - 2 * tid; sh.sel_krem = k - excl; sh.sel_cnt = hi; }
+        else { sh.sel_digit = 2046 - 2 * tid; sh.sel_krem = k - excl - hi; sh.sel_cnt = lo; }
     }
     __syncthreads();
-    const int T = *sel_digit, krem = *sel_krem, cnt = *sel_cnt, n_gt = k - krem, total = n_gt + cnt;
+    const int T = sh.sel_digit, krem = sh.sel_krem, cnt = sh.sel_cnt, n_gt = k - krem, total = n_gt + cnt;
     if (total > SELB_SORT_MAX) return false;  // uniform: every thread read the same shared values
     const bool rank_ties = cnt > krem && cnt <= SELB_TIES;
     const int want = rank_ties ? k : total;
     int np = 1;
     while (np < want) np <<= 1;
+    unsigned long long *skeys = sh.skeys;
     for (int i = total + tid; i < np; i += SELB_THREADS) skeys[i] = 0ull;
     if (!held) {  // the keys from bin T up, at most SELB_SORT_MAX (a counter for either end in this sweep cost 20 to 60 us of a million keys)
-        for_each_key(src, ncand, [&](unsigned long long key) {
-            if (digit(key) >= T) skeys[atomicAdd(&gathered, 1)] = key;
+        each([&](unsigned long long key) {
+            if (digit(key) >= T) skeys[atomicAdd(&sh.gathered, 1)] = key;
         });
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < SELB_HELD; j++) x[j] = j < SELB_SORT_MAX / SELB_THREADS && j * SELB_THREADS + tid < total ? skeys[j * SELB_THREADS + tid] : 0ull;
+        for (int j = 0; j < H; j++) x[j] = j < SELB_SORT_MAX / SELB_THREADS && j * SELB_THREADS + tid < total ? skeys[j * SELB_THREADS + tid] : 0ull;
         __syncthreads();
     }
     // keys above bin T go to [0, n_gt), those of bin T behind them; out_cnt counts both, 16 bits each (at most SELB_SORT_MAX of either); one reservation
     // per wavefront
-    unsigned long long mg[SELB_HELD], me[SELB_HELD];
+    unsigned long long mg[H], me[H];
     int c = 0;
 #pragma unroll
-    for (int j = 0; j < SELB_HELD; j++) {
+    for (int j = 0; j < H; j++) {
         const int d = x[j] ? digit(x[j]) : -1;
         mg[j] = __ballot(d > T);
         me[j] = __ballot(d == T);
         c += __popcll(mg[j]) + (__popcll(me[j]) << 16);
     }
     if (c) {
-        int at = lane == 0 ? atomicAdd(out_cnt, c) : 0;
+        int at = lane == 0 ? atomicAdd(&sh.out_cnt, c) : 0;
         at = __builtin_amdgcn_readfirstlane(at);
         int ag = at & 0xFFFF, ae = n_gt + (int)((unsigned)at >> 16);
         const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
-        for (int j = 0; j < SELB_HELD; j++) {
+        for (int j = 0; j < H; j++) {
             if (mg[j] >> lane & 1) skeys[ag + __popcll(mg[j] & below)] = x[j];
             if (me[j] >> lane & 1) skeys[ae + __popcll(me[j] & below)] = x[j];
             ag += __popcll(mg[j]);
@@ -1139,103 +1165,250 @@ __device__ __forceinline__ bool select_request_binned(const unsigned long long *
     return true;
 }
 
-__global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned long long *__restrict__ cand, int64_t req_stride,
-                                                               const int *__restrict__ req_count, int count_pitch, int V, int k,
-                                                               int32_t *__restrict__ parent, int32_t *__restrict__ tok,
-                                                               float *__restrict__ score, const int32_t *__restrict__ sid_old,
-                                                               int32_t *__restrict__ sid_new, const int32_t *__restrict__ anc_old,
-                                                               int32_t *__restrict__ anc_new, int n, int T, int level) {
-    __shared__ unsigned long long skeys[SELB_SORT_MAX];
-    __shared__ int hist[2048];
-    __shared__ int wave_tot[16];
-    __shared__ int sel_digit, sel_krem, sel_cnt, out_cnt;
+// Exact whatever the keys: radix selection on the unique 64-bit keys, 11-bit digits from the top; stops as soon as the chosen bin holds exactly the number of
+// keys still needed.  each(f): every key.
+template <typename EACH> __device__ __forceinline__ void select_radix(EACH each, int k, int kp, SelbShared &sh) {
     const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+    unsigned long long prefix = 0;  // value of key >> shift
+    int krem = k, shift = 64;
+    const int widths[6] = {11, 11, 11, 11, 11, 9};
+    for (int pass = 0; pass < 6; pass++) {
+        const int w = widths[pass];
+        const int nshift = shift - w;
+        for (int i = tid; i < 2048; i += SELB_THREADS) sh.hist[i] = 0;
+        __syncthreads();
+        each([&](unsigned long long key) {
+            if (pass == 0 || (key >> shift) == prefix) atomicAdd(&sh.hist[(int)((key >> nshift) & ((1u << w) - 1))], 1);
+        });
+        __syncthreads();
+        // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
+        const int hi = sh.hist[2047 - 2 * tid], lo = sh.hist[2046 - 2 * tid];
+        const int v = wave_scan(hi + lo);
+        if (lane == 63) sh.wave_tot[wv] = v;
+        __syncthreads();
+        int add = 0;
+        for (int q = 0; q < wv; q++) add += sh.wave_tot[q];
+        const int incl = v + add, excl = incl - hi - lo;
+        if (excl < krem && incl >= krem) {
+            if (excl + hi >= krem) { sh.sel_digit = 2047 - 2 * tid; sh.sel_krem = krem - excl; sh.sel_cnt = hi; }
+            else { sh.sel_digit = 2046 - 2 * tid; sh.sel_krem = krem - excl - hi; sh.sel_cnt = lo; }
+        }
+        __syncthreads();
+        prefix = (prefix << w) | (unsigned long long)sh.sel_digit;
+        krem = sh.sel_krem;
+        shift = nshift;
+        const int cnt = sh.sel_cnt;
+        __syncthreads();
+        if (cnt == krem || shift == 0) break;  // uniform: all threads read the same shared values
+    }
+    if (tid == 0) sh.out_cnt = 0;
+    for (int i = tid; i < kp; i += SELB_THREADS) sh.skeys[i] = 0ull;
+    __syncthreads();
+    each([&](unsigned long long key) {
+        if ((key >> shift) >= prefix) {
+            int p = atomicAdd(&sh.out_cnt, 1);
+            if (p < kp) sh.skeys[p] = key;
+        }
+    });
+    __syncthreads();
+    bitonic_sort_desc(sh.skeys, kp);
+}
+
+// What a selection returns
+struct Survivors {
+    int32_t *parent, *tok;
+    float *score;
+    const int32_t *sid_old;
+    int32_t *sid_new;
+    const int32_t *anc_old;
+    int32_t *anc_new;
+    int T, level;
+};
+__device__ __forceinline__ void write_survivors(const Survivors &o, const unsigned long long *skeys, int64_t b, int n, int V, int k) {
+    for (int j = threadIdx.x; j < k; j += SELB_THREADS) {
+        const unsigned long long key = skeys[j];
+        const uint32_t flat = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
+        // (a request lists at least k candidates; the clamp keeps what is read through the parent inside the batch whatever the keys hold)
+        const int par = min((int)(flat / (uint32_t)V), n - 1), tk = (int)(flat % (uint32_t)V);
+        o.parent[b * k + j] = par;
+        o.tok[b * k + j] = tk;
+        o.score[b * k + j] = key_score((uint32_t)(key >> 32));
+        // sids, and the row (over the whole batch) of the survivor's ancestor at every level so far: the reorder is this index table
+        // (every load ahead of the stores)
+        const int64_t from = (b * n + par) * o.T, to = (b * k + j) * o.T;
+        int32_t sid[GR4AD_MAX_LEVELS], anc[GR4AD_MAX_LEVELS];
+#pragma unroll
+        for (int t = 0; t < GR4AD_MAX_LEVELS; t++) {
+            sid[t] = o.sid_new && t < o.level ? o.sid_old[from + t] : (t == o.level ? tk : 0);
+            anc[t] = o.anc_new && t < o.level ? o.anc_old[from + t] : (int32_t)(b * n + par);
+        }
+#pragma unroll
+        for (int t = 0; t < GR4AD_MAX_LEVELS; t++) {
+            if (o.sid_new && t < o.T) o.sid_new[to + t] = sid[t];
+            if (o.anc_new && t <= o.level) o.anc_new[to + t] = anc[t];
+        }
+    }
+}
+
+__global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned long long *__restrict__ cand, int64_t req_stride, const int *__restrict__ req_count,
+                                                               int count_pitch, int V, int k, int n, Survivors out) {
+    __shared__ SelbShared sh;
+    const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const unsigned long long *src = cand + b * req_stride;  // the request's candidates: the first keys of its segment, all of them without a count
     const int64_t ncand = req_count ? req_count[b * count_pitch] : req_stride;
     int kp = 1;
     while (kp < k) kp <<= 1;
+    auto each = [&](auto f) { for_each_key(src, ncand, f); };
 
-    // few enough to sort them all (a cut down to about k keys costs two sweeps, about as much as sorting 1024 keys)
-    if (ncand <= SELB_THREADS || ncand <= kp) {
+    // few enough to sort them all (a cut down to k keys costs two sweeps; worth it from 1024 keys on, and from 257 where three quarters of them go)
+    if (ncand <= SELB_SORT_ALL || ncand <= kp || (ncand <= SELB_THREADS && ncand < 4 * k)) {
         int np = 1;
         while (np < ncand) np <<= 1;
-        for (int i = tid; i < (np > kp ? np : kp); i += SELB_THREADS) skeys[i] = i < ncand ? src[i] : 0ull;
+        for (int i = tid; i < (np > kp ? np : kp); i += SELB_THREADS) sh.skeys[i] = i < ncand ? src[i] : 0ull;
         __syncthreads();
-        bitonic_sort_desc(skeys, np);
-    } else if (select_request_binned(src, ncand, k, skeys, hist, wave_tot, &sel_digit, &sel_krem, &sel_cnt, &out_cnt)) {
-        // done: skeys holds the k best in order
+        bitonic_sort_desc(sh.skeys, np);
     } else {
-        // radix select on the unique 64-bit keys, 11-bit digits from the top; stops as
-        // soon as the chosen bin holds exactly the number of keys still needed
-        unsigned long long prefix = 0;  // value of key >> shift
-        int krem = k, shift = 64;
-        const int widths[6] = {11, 11, 11, 11, 11, 9};
-        for (int pass = 0; pass < 6; pass++) {
-            const int w = widths[pass];
-            const int nshift = shift - w;
-            for (int i = tid; i < 2048; i += SELB_THREADS) hist[i] = 0;
-            __syncthreads();
-            for_each_key(src, ncand, [&](unsigned long long key) {
-                if (pass == 0 || (key >> shift) == prefix) atomicAdd(&hist[(int)((key >> nshift) & ((1u << w) - 1))], 1);
-            });
-            __syncthreads();
-            // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
-            const int hi = hist[2047 - 2 * tid], lo = hist[2046 - 2 * tid];
-            const int v = wave_scan(hi + lo);
-            if (lane == 63) wave_tot[wv] = v;
-            __syncthreads();
-            int add = 0;
-            for (int q = 0; q < wv; q++) add += wave_tot[q];
-            const int incl = v + add, excl = incl - hi - lo;
-            if (excl < krem && incl >= krem) {
-                if (excl + hi >= krem) { sel_digit = 2047 - 2 * tid; sel_krem = krem - excl; sel_cnt = hi; }
-                else { sel_digit = 2046 - 2 * tid; sel_krem = krem - excl - hi; sel_cnt = lo; }
+        const bool held = ncand <= SELB_HELD * SELB_THREADS;
+        unsigned long long x[SELB_HELD];  // 0: none
+        if (held) {
+            const bool pairs = (((uintptr_t)src) & 15) == 0;
+#pragma unroll
+            for (int j = 0; j < SELB_HELD; j += 2) {
+                const int i = j * SELB_THREADS + (pairs ? 2 * tid : tid), i2 = pairs ? i + 1 : i + SELB_THREADS;
+                x[j] = x[j + 1] = 0ull;
+                if (pairs && i2 < ncand) {
+                    const ulonglong2 a = *(const ulonglong2 *)(src + i);
+                    x[j] = a.x;
+                    x[j + 1] = a.y;
+                } else {
+                    if (i < ncand) x[j] = src[i];
+                    if (i2 < ncand) x[j + 1] = src[i2];
+                }
             }
-            __syncthreads();
-            prefix = (prefix << w) | (unsigned long long)sel_digit;
-            krem = sel_krem;
-            shift = nshift;
-            const int cnt = sel_cnt;
-            __syncthreads();
-            if (cnt == krem || shift == 0) break;  // uniform: all threads read the same shared values
         }
-        if (tid == 0) out_cnt = 0;
-        for (int i = tid; i < kp; i += SELB_THREADS) skeys[i] = 0ull;
-        __syncthreads();
-        for_each_key(src, ncand, [&](unsigned long long key) {
-            if ((key >> shift) >= prefix) {
-                int p = atomicAdd(&out_cnt, 1);
-                if (p < kp) skeys[p] = key;
-            }
-        });
-        __syncthreads();
-        bitonic_sort_desc(skeys, kp);
+        const uint32_t smp = (uint32_t)(src[(int64_t)tid * ncand / SELB_THREADS] >> 32);
+        if (!select_binned<SELB_HELD>(x, held, each, smp, smp, k, sh)) select_radix(each, k, kp, sh);
     }
+    write_survivors(out, sh.skeys, b, n, V, k);
+}
 
-    for (int j = tid; j < k; j += SELB_THREADS) {
-        const unsigned long long key = skeys[j];
-        const uint32_t flat = 0xFFFFFFFFu - (uint32_t)(key & 0xFFFFFFFFull);
-        // (a request lists at least k candidates; the clamp keeps what is read through the parent inside the batch whatever the keys hold)
-        const int par = min((int)(flat / (uint32_t)V), n - 1), tk = (int)(flat % (uint32_t)V);
-        parent[b * k + j] = par;
-        tok[b * k + j] = tk;
-        score[b * k + j] = key_score((uint32_t)(key >> 32));
-        // sids, and the row (over the whole batch) of the survivor's ancestor at every level so far: the reorder is this index table
-        // (every load ahead of the stores)
-        const int64_t from = (b * n + par) * T, to = (b * k + j) * T;
-        int32_t sid[GR4AD_MAX_LEVELS], anc[GR4AD_MAX_LEVELS];
+// ---------------------------------------------------------------------------
+// A request of one row - the first level of every decode - in one launch
+// ---------------------------------------------------------------------------
+// The row's cut and the request's sort were two launches, the first of a single wavefront (or of 256 threads) per request.  Here 1024 threads hold the row, PER logits each:
+// maximum, exponentials and keys are formed side by side, and only the sum of the exponentials, whose order decides the last bit of every score, is
+// added up as the row kernels add it (ORDER_WAVE: select_rows_wave, a lane walks its pieces; else select_rows, a thread walks every 256th token), from LDS.
+template <int PER, bool ORDER_WAVE, typename LT>
+__global__ __launch_bounds__(SELB_THREADS) void select_single(const LT *__restrict__ logits, const float *__restrict__ cum, int V, int k, Survivors out) {
+    constexpr int E = ORDER_WAVE ? LogitPiece<LT>::E : 1, J = PER / E;  // tokens of a load; loads of a thread
+    __shared__ SelbShared sh;
+    __shared__ float red[SELB_THREADS / 64], lse_s;
+    extern __shared__ __attribute__((aligned(16))) float expo[];  // [V]
+    const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+    const int64_t b = blockIdx.x;
+    const LT *z = logits + b * V;
+    const float c = cum ? cum[b] : 0.0f;
+    float x[PER];
+    auto token = [&](int i) { return ((i / E) * SELB_THREADS + tid) * E + i % E; };
 #pragma unroll
-        for (int t = 0; t < GR4AD_MAX_LEVELS; t++) {
-            sid[t] = sid_new && t < level ? sid_old[from + t] : (t == level ? tk : 0);
-            anc[t] = anc_new && t < level ? anc_old[from + t] : (int32_t)(b * n + par);
-        }
+    for (int j = 0; j < J; j++) {
+        const int at = token(j * E);
+        if constexpr (ORDER_WAVE) {
+            if (at < V) {  // (V is a multiple of a piece)
+                LogitPiece<LT>::unpack(((const uint4 *)z)[at / E], &x[j * E]);
+            } else {
 #pragma unroll
-        for (int t = 0; t < GR4AD_MAX_LEVELS; t++) {
-            if (sid_new && t < T) sid_new[to + t] = sid[t];
-            if (anc_new && t <= level) anc_new[to + t] = anc[t];
+                for (int e = 0; e < E; e++) x[j * E + e] = -INFINITY;
+            }
+        } else {
+            x[j] = at < V ? (float)z[at] : -INFINITY;
         }
     }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < PER; i++) mx = fmaxf(mx, x[i]);
+    mx = wave_max_dpp(mx);
+    if (lane == 0) red[wv] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < SELB_THREADS / 64; q++) mx = fmaxf(mx, red[q]);
+    const float mxl = mx * 1.4426950408889634f;
+#pragma unroll
+    for (int i = 0; i < PER; i++)
+        if (token(i) < V) expo[token(i)] = ORDER_WAVE ? __builtin_amdgcn_exp2f(__builtin_fmaf(x[i], 1.4426950408889634f, -mxl)) : __expf(x[i] - mx);
+    __syncthreads();
+    if constexpr (ORDER_WAVE) {
+        if (wv == 0) {
+            float sum = 0.0f;
+#pragma unroll 4
+            for (int at = lane * E; at < V; at += 64 * E) {
+#pragma unroll
+                for (int e = 0; e < E; e += 4) {
+                    const floatx4 p = *(const floatx4 *)(expo + at + e);
+                    sum += p[0];
+                    sum += p[1];
+                    sum += p[2];
+                    sum += p[3];
+                }
+            }
+            const float lse = mx + __logf(wave_sum_dpp(sum));
+            if (lane == 0) lse_s = lse;
+        }
+    } else {
+        if (wv < 4) {
+            float sum = 0.0f;
+#pragma unroll 8
+            for (int at = tid; at < V; at += 256) sum += expo[at];
+            sum = wave_sum(sum);
+            if (lane == 0) red[wv] = sum;
+        }
+        __syncthreads();
+        if (tid == 0) lse_s = mx + __logf((red[0] + red[1]) + (red[2] + red[3]));
+    }
+    __syncthreads();
+    const float lse = lse_s;
+    unsigned long long key[PER];
+    uint32_t hi = 0u, lo = 0xFFFFFFFFu;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        key[i] = token(i) < V ? pack_candidate(c + (x[i] - lse), (uint32_t)token(i)) : 0ull;
+        if (i == 0 && key[i]) hi = lo = (uint32_t)(key[i] >> 32);
+    }
+    int kp = 1;
+    while (kp < k) kp <<= 1;
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int i = 0; i < PER; i++)
+            if (key[i]) f(key[i]);
+    };
+    if (V <= SELB_SORT_ALL) {
+        int np = 1;
+        while (np < V) np <<= 1;
+        for (int i = V + tid; i < np; i += SELB_THREADS) sh.skeys[i] = 0ull;
+#pragma unroll
+        for (int i = 0; i < PER; i++)
+            if (key[i]) sh.skeys[token(i)] = key[i];
+        __syncthreads();
+        bitonic_sort_desc(sh.skeys, np);
+    } else if (!select_binned<PER>(key, true, each, hi, lo, k, sh)) {
+        select_radix(each, k, kp, sh);
+    }
+    write_survivors(out, sh.skeys, b, 1, V, k);
+}
+
+template <int PER, bool ORDER_WAVE, typename LT>
+static int launch_select_single(const void *logits, const float *cum, int B, int V, int k, const Survivors &out, hipStream_t st) {
+    auto kern = select_single<PER, ORDER_WAVE, LT>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PER * SELB_THREADS * (int)sizeof(float)) != hipSuccess) return GR4AD_EHIP;
+        attr_done = true;
+    }
+    ProfScope ps(KC_SELECT_REQUEST, st, 0.0, (double)B * V * sizeof(LT) + (double)B * k * 12);
+    hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(SELB_THREADS), (size_t)V * sizeof(float), st, (const LT *)logits, cum, V, k, out);
+    GR4AD_LAUNCH_CHECK();
+    return GR4AD_OK;
 }
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1254,6 +1427,7 @@ struct RowsLaunch {
     int count_pitch;
     int2 *todo;
     int *todo_count;
+    bool numbers_first;  // rows whose scores are no numbers rank below all numbers (requests that a bound could serve)
 };
 static int compute_units() {
     static int n_cu = 0;
@@ -1282,7 +1456,7 @@ static int launch_rows_wave_as(const RowsLaunch &a, int64_t rows, int mode) {
         if (grid > (int64_t)n_cu * 4) grid = (int64_t)n_cu * 4;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows, a.n, a.V, a.m, a.cand,
-                       mode == 1 ? (const int2 *)a.todo : nullptr, mode == 1 ? (const int *)a.todo_count : nullptr);
+                       mode == 1 ? (const int2 *)a.todo : nullptr, mode == 1 ? (const int *)a.todo_count : nullptr, a.numbers_first);
     return GR4AD_OK;
 }
 // (The length of a list is known on the device only, and it is short as a rule: beside a sweep of more than 8192 rows the four microseconds of a short one do not
@@ -1372,6 +1546,13 @@ static SelectPlan select_plan(int B, int n, int V, int k) {
 }
 size_t select_workspace_bytes(int B, int n, int V, int k) { return select_plan(B, n, V, k).total; }
 
+// Few short rows are faster cut one by one (one launch of wavefronts that each take a row, then the request's sort over all n * m keys, which it holds up to 8192) than
+// bounded, swept and listed in three launches.  Whole selections in us, bounded / row by row: 4 requests of 16 rows of 256 tokens, k = 16 16.8 / 11.6; 64 of 64 rows of 1024,
+// k = 64 (4096 rows) 21.2 / 16.9, 64 of 128 rows, k = 32 (8192 rows) 21.7 / 21.3; of 2048 tokens 16 of 128 rows, k = 32 (2048 rows) 18.8 / 16.0, 64 of 64 rows, k = 64 24.4 / 23.9.
+// (Requests of fewer than 8 rows stay bounded: test_gpu_select_masked.py pins how many candidates they list.)
+static bool rows_cut_alone(int64_t rows, int n, int V, int m) {
+    return n >= 8 && (int64_t)n * m <= SELB_HELD * SELB_THREADS && V <= 2048 && rows <= (V <= 1024 ? 4096 : 2048);
+}
 int launch_select(const void *logits_any, int logits_f16, const float *cum, int B, int n, int V, int k, void *ws, size_t ws_bytes, int32_t *parent,
                   int32_t *tok, float *score, const int32_t *sid_old, int32_t *sid_new, const int32_t *anc_old, int32_t *anc_new, int T, int level,
                   hipStream_t st) {
@@ -1387,17 +1568,26 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
     unsigned long long *cand = (unsigned long long *)ws;
     int *req_count = (int *)((char *)ws + p.counts), *todo_count = (int *)((char *)ws + p.todo_count);
     const bool wave_path = V <= 8192 && V % 4 == 0 && ((uintptr_t)logits % 16) == 0;
-    // Request-level bound (several rows per request, a cut smaller than the row): see row_bounds.  One row per request - the first level of
-    // every decode - is its own cut and done: a bound would only read the row twice.  64 requests of one row of 8192, k = 256: 41 us so and
-    // 54 bounded for halves, 31.5 and 30.5 for float32.
-    const bool bounded = wave_path && n > 1 && k <= V;
+    const Survivors out = {parent, tok, score, sid_old, sid_new, anc_old, anc_new, T, level};
+    // (in one round of workgroups, of which two share a compute unit up to 8192 tokens; us, two launches / one: 64 requests of 256 tokens, k = 16 10.4 / 7.7; of 4096, k = 128
+    // 15.8 / 9.0; of 8192, k = 256 23.4 / 11.5; of 16384, k = 128 21.1 / 13.8; but 1024 requests of 256 tokens 15.8 / 20.0, of 8192 36.8 / 41.2)
+    if (n == 1 && B <= (wave_path ? 512 : 256)) {
+        if (wave_path && logits_f16) return launch_select_single<8, true, _Float16>(logits_any, cum, B, V, k, out, st);
+        if (wave_path && V <= 4096) return launch_select_single<4, true, float>(logits_any, cum, B, V, k, out, st);
+        if (wave_path) return launch_select_single<8, true, float>(logits_any, cum, B, V, k, out, st);
+        if (V <= 4096) return launch_select_single<4, false, float>(logits_any, cum, B, V, k, out, st);
+        return launch_select_single<16, false, float>(logits_any, cum, B, V, k, out, st);
+    }
+    // Request-level bound (several rows per request, a cut smaller than the row): see row_bounds.  One row per request is its own cut: a bound would only
+    // read the row twice.
+    const bool bounded = wave_path && n > 1 && k <= V && !rows_cut_alone(rows, n, V, m);
     {
         // algorithmic bytes: every logit once; the candidates written depend on the data (between k per request and m per row):
         // the lower bound is counted when the request-level bound is in use
         ProfScope ps(KC_SELECT_ROWS, st, 0.0, (double)rows * V * (logits_f16 ? 2 : 4) + (bounded ? (double)B * k : (double)rows * m) * 8);
         if (wave_path) {
             const RowsLaunch a = {st, logits_any, logits_f16, cum, n, V, m, cand, (float *)((char *)ws + p.scores), p.R, req_count, p.count_pitch,
-                            (int2 *)((char *)ws + p.todo), todo_count};
+                            (int2 *)((char *)ws + p.todo), todo_count, n > 1 && k <= V};
             int s;
             if (bounded) {
                 if ((s = launch_rows(a, B, 3))) return s;
@@ -1422,8 +1612,7 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
         GR4AD_LAUNCH_CHECK();
     }
     ProfScope ps(KC_SELECT_REQUEST, st, 0.0, (bounded ? (double)B * k : (double)rows * m) * 8 + (double)B * k * 12);  // (same convention)
-    hipLaunchKernelGGL(select_request, dim3((unsigned)B), dim3(SELB_THREADS), 0, st, (const unsigned long long *)ws, (int64_t)n * m, bounded ? req_count : nullptr, p.count_pitch, V, k,
-                       parent, tok, score, sid_old, sid_new, anc_old, anc_new, n, T, level);
+    hipLaunchKernelGGL(select_request, dim3((unsigned)B), dim3(SELB_THREADS), 0, st, (const unsigned long long *)ws, (int64_t)n * m, bounded ? req_count : nullptr, p.count_pitch, V, k, n, out);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }

@@ -1,0 +1,47 @@
+"""Selections of one row in one launch, and of few short rows cut one by one: against a float64 reference over masks, ties and edges of the tiles."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_22732_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def logits(kind, B, n, V, g):
+    z = torch.randn(B, n, V, generator=g) * 2
+    if kind == "masked":       # half of the tokens
+        z[:, :, : V // 2] = -float("inf")
+    if kind == "low":          # a finite mask that presses the others together
+        z[:, :, : V // 3] = -1e9
+    if kind == "tied":         # more equal scores than survive
+        z = torch.round(z)
+    return z
+
+
+# one row: one key per thread, 256 keys and one more (sorted, cut), a piece per thread and more, the block kernel's order (V not a multiple of 4, more than 8192
+# tokens), everything survives.  Several: 64 and 65 rows of 1024 keys and of more, all keys of a request sorted and cut, 8192 keys in all and one row more
+@pytest.mark.parametrize("B,n,V,k", [(3, 1, 1, 1), (2, 1, 256, 256), (2, 1, 260, 16), (2, 1, 1024, 700), (2, 1, 4096, 1), (2, 1, 4100, 512), (2, 1, 8192, 4096), (2, 1, 5001, 600), (1, 1, 16384, 4096),
+                                     (512, 1, 264, 3), (513, 1, 264, 3), (4, 16, 256, 16), (2, 65, 1024, 64), (64, 64, 1024, 64), (3, 3, 2048, 1500), (1, 128, 72, 64), (1, 129, 72, 64),
+                                     (2, 4, 8, 8)])
+@pytest.mark.parametrize("kind", ["plain", "masked", "low", "tied"])
+def test_short_selections(B, n, V, k, kind):
+    g = torch.Generator().manual_seed(B + n * 7 + V + k)
+    z, cum = logits(kind, B, n, V, g), -torch.sort(torch.rand(B, n, generator=g) * 6 + 3, dim=1).values
+    par, tok, score = binding.op_select(z.cuda(), cum.cuda(), k)
+    par, tok, score = par.cpu().numpy(), tok.cpu().numpy(), score.cpu().numpy().astype(np.float64)
+    ref = (cum[:, :, None].double() + torch.log_softmax(z.double(), dim=2)).reshape(B, n * V).numpy()
+    for b in range(B):
+        flat = par[b].astype(np.int64) * V + tok[b]
+        assert len(set(flat.tolist())) == k and flat.min() >= 0 and flat.max() < n * V
+        order = np.argsort(-ref[b], kind="stable")
+        kth = ref[b][order[k - 1]]
+        got = ref[b][flat]
+        fin = np.isfinite(got)
+        # float32 scores: a few roundings of numbers below 32 (below 2e9 where a mask of -1e9 survives)
+        tol = 1e-5 if kind != "low" else 1e-5 + 2.0**-22 * np.abs(got[fin]).max(initial=0.0)
+        assert np.array_equal(fin, np.isfinite(score[b])) and np.abs(got[fin] - score[b][fin]).max(initial=0.0) <= tol
+        assert (got >= kth - tol).all() and (np.diff(score[b][fin]) <= 0).all()
+        if kind in ("masked", "tied"):  # equal scores go by the lowest (row, token)
+            eq = np.flatnonzero(score[b][1:] == score[b][:-1])
+            assert (flat[eq + 1] > flat[eq]).all()
