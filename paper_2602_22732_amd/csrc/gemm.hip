@@ -1404,6 +1404,8 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) + NL) * 64) void gemm_bf16_t
         auto mma = [&](auto p, auto behind) {  // behind: reads issued after set p's
             bf16x8(&a)[4] = af[p.value], (&w)[4] = wf[p.value];
             SB;
+            asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(behind.value) : "memory");  // (before the copies that the next line's operands may take)
+            SB;
             asm volatile("s_waitcnt lgkmcnt(%8)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : "n"(behind.value));
             SB;
 #pragma unroll
@@ -1747,6 +1749,9 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_panel(const float *__restric
         }
     };
     auto mma = [&](Fragments &f, bool behind) {  // behind: the other set's eight reads were issued after this one's
+        __builtin_amdgcn_sched_barrier(0);
+        if (behind) asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");  // (before the copies that the next lines' operands may take)
+        else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if (behind) asm volatile("s_waitcnt lgkmcnt(8)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.w[2]), "+v"(f.w[3]));
         else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.w[2]), "+v"(f.w[3]));
