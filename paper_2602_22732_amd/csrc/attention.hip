@@ -792,11 +792,12 @@ static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ct
 // The same for few requests: the tiles of a request side by side.  One workgroup per request leaves most of the chip idle below some
 // hundred requests and walks its tiles one after the other, 2.9 us each (8 requests of 1024 rows: 93 us).  Here context_scores
 // computes the scores of every tile at once, with one workgroup per compute unit dealt to the requests (it keeps its fragments of the
-// queries over its tiles, and contexts far shorter than S leave few idle workgroups), and context_sums gives every request D / 128 (one
-// query tile: D / 256) workgroups, one per slice of the columns of z: they repeat the cheap part, the running maxima over the tile
+// queries over its tiles, and contexts far shorter than S leave few idle workgroups), and context_sums gives every request D / 64 workgroups (D / 128, with one
+// query tile D / 256, where those would outnumber the compute units), one per slice of the columns of z: they repeat the cheap part, the running maxima over the tile
 // maxima and the exponentials, and walk the tiles only for their product.  Every sum keeps the order of the one-pass kernel (partial
 // scores of the same slices of D, the lazily refreshed maximum tile by tile, the normaliser per half wavefront, z over the rows), so
-// the two give the same bits.  8 requests of up to 1024 rows, d = 1024, 64 queries: 93 us before, now 29; one of 512 rows, d = 512: 40, now 15.
+// the two give the same bits.  8 requests of up to 1024 rows, d = 1024, 64 queries: 93 us in one pass, now 26 (slices of 128 columns 29); one of 512 rows, d = 512: 40, now 12
+// (slices of 256 columns, each tile's operands read after the product before: 15).
 // ---------------------------------------------------------------------------
 #define CTX_CHUNK 8  // tiles whose probabilities are formed together
 #define CTX_STAGE (32 * 1024)
@@ -869,12 +870,13 @@ __global__ __launch_bounds__(512) void context_scores(const bf16 *__restrict__ q
     }
 }
 
-template <int D, int QT>
+template <int D, int QT, int COLS>
 __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, const int32_t *__restrict__ ctx_len, const float *__restrict__ sc,
                                                     const float *__restrict__ mxs, bf16 *__restrict__ z, int RQ, int rq_stride, int S, int nt_max,
                                                     float scale_log2e) {
-    constexpr int COLS = 256 / QT, ROWB = COLS * 2, CH = COLS / 8;  // columns of this workgroup, bytes and 16-byte pieces of a staged row
-    constexpr int TS = CTX_STAGE / (32 * ROWB);                     // tiles per stage (4, or 2 with one query tile)
+    constexpr int ROWB = COLS * 2, CH = COLS / 8;                   // bytes and 16-byte pieces of a staged row
+    constexpr int TS = CTX_STAGE / (32 * ROWB);                     // tiles per stage (2, 4 or 8)
+    static_assert(CTX_CHUNK % TS == 0 && QT * (COLS / 32) <= 8, "a chunk is whole stages, a wavefront has 32 queries and 32 columns");
     constexpr int UPW = CTX_CHUNK * QT / 8;                         // (tile, query tile) units of probabilities per wavefront and chunk
     constexpr int PB = 3 * CTX_STAGE, MB = PB + CTX_CHUNK * QT * 2048, AB = MB + CTX_CHUNK * QT * 128, LB = AB + 2 * CTX_CHUNK * QT * 128,
                   IB = LB + CTX_CHUNK * QT * 256;
@@ -888,6 +890,7 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
     const bf16 *xb = x + (int64_t)b * S * D + slice * COLS;
     const float *scb = sc + (int64_t)b * nt_max * QT * 1024, *mxb = mxs + (int64_t)b * nt_max * QT * 32;
 
+    auto swz = [](int r) { return CH >= 16 ? ctx_swz(r) : ((r & 3) << 1) | ((r >> 2) & 1); };
     auto issue_stage = [&](int st) {  // rows st*TS*32 .. of this workgroup's columns (past the length: the last valid row again)
         char *dst = ctx_lds + (st % 3) * CTX_STAGE;
 #pragma unroll
@@ -895,7 +898,7 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
             const int id = (i * 8 + wave) * 64 + lane, r = id / CH, pos = id % CH;
             int row = st * TS * 32 + r;
             if (row > len - 1) row = len - 1;
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(xb + (int64_t)row * D + (pos ^ ctx_swz(r)) * 8),
+            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(xb + (int64_t)row * D + (pos ^ swz(r)) * 8),
                                              (void __attribute__((address_space(3))) *)(dst + (i * 8 + wave) * 1024), 16, 0, 0);
         }
     };
@@ -921,7 +924,7 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
     if (nstages > 1) issue_stage(1);
 
     float m_run = -INFINITY, l_run = 0.0f, areg[CTX_CHUNK];  // (first QT wavefronts: lane = query r32, half g)
-    const int qt = wave / (8 / QT), ct = wave % (8 / QT);    // second product: query tile, 32 columns
+    const int qt = wave / (COLS / 32), ct = wave % (COLS / 32);  // second product: query tile, 32 columns (wavefronts past the last query tile load and wait)
     floatx16 o;
 #pragma unroll
     for (int v = 0; v < 16; v++) o[v] = 0.0f;
@@ -932,7 +935,7 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
 #pragma unroll
     for (int h = 0; h < 2; h++) {
         const int sr = 8 * g + 4 * h + i16 / 4;
-        tr_off[h] = (uint32_t)(sr * ROWB + (i16 & 1) * 8 + ((piece ^ ctx_swz(sr)) * 16));
+        tr_off[h] = (uint32_t)(sr * ROWB + (i16 & 1) * 8 + ((piece ^ swz(sr)) * 16));
     }
     int par = 0;
     for (int c0 = 0; c0 < ntiles; c0 += CTX_CHUNK, par ^= 1) {
@@ -987,8 +990,15 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
         }
         if (c0 + CTX_CHUNK < ntiles) load_chunk(c0 + CTX_CHUNK);
         // ---- z^T += x^T P^T over the chunk's stages ----
-#pragma unroll 1
-        for (int st = c0 / TS; st < (c0 + CTX_CHUNK) / TS && st < nstages; st++) {
+        float alpha[CTX_CHUNK];  // rescale factors of the chunk's tiles
+#pragma unroll
+        for (int t = 0; t < CTX_CHUNK; t++) alpha[t] = qt < QT ? aA[(t * QT + qt) * 32 + r32] : 1.0f;
+        struct Fragments { intx2 w[2][2]; intx4 p[2]; };
+        Fragments f0, f1;
+#pragma unroll
+        for (int s = 0; s < CTX_CHUNK / TS; s++) {
+            const int st = c0 / TS + s;
+            if (st >= nstages) break;
             // this wavefront's share of the stage has landed (the next stage's loads, and younger ones, may be in flight); after the
             // barrier everybody's has, and the stage before it is read out: its buffer takes stage st + 2
             if (st + 1 < nstages) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
@@ -996,30 +1006,57 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             if (st + 2 < nstages) issue_stage(st + 2);
+            if (qt >= QT) continue;
+            // the six reads of a tile are on their way under the products of the one before
+            auto read = [&](Fragments &f, int tt) {
+                const int q = qt * 32 + r32;
+                const uint32_t xa = lds0 + (st % 3) * CTX_STAGE + tt * 32 * ROWB, pa = lds0 + PB + (s * TS + tt) * (QT * 2048) + q * 64;
 #pragma unroll
-            for (int tt = 0; tt < TS; tt++) {
-                const int tile = st * TS + tt, t = tile - c0;
-                if (tile < ntiles) {
-                    const float a = aA[(t * QT + qt) * 32 + r32];
-                    if (__builtin_amdgcn_ballot_w64(a != 1.0f) != 0) {
+                for (int ks = 0; ks < 2; ks++) {
+                    asm volatile("ds_read_b128 %0, %1" : "=v"(f.p[ks]) : "v"(pa + (((2 * ks + g) ^ ((q >> 2) & 3)) * 16)));
 #pragma unroll
-                        for (int v = 0; v < 16; v++) o[v] *= a;
-                    }
-                    intx2 w[2][2];
-                    bf16x8 pf[2];
+                    for (int h = 0; h < 2; h++) asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(f.w[ks][h]) : "v"(xa + ks * 16 * ROWB + tr_off[h]));
+                }
+            };
+            auto multiply = [&](Fragments &f, int tt, bool behind) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (behind) asm volatile("s_waitcnt lgkmcnt(6)" : "+v"(f.w[0][0]), "+v"(f.w[0][1]), "+v"(f.w[1][0]), "+v"(f.w[1][1]), "+v"(f.p[0]), "+v"(f.p[1]));
+                else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.w[0][0]), "+v"(f.w[0][1]), "+v"(f.w[1][0]), "+v"(f.w[1][1]), "+v"(f.p[0]), "+v"(f.p[1]));
+                __builtin_amdgcn_sched_barrier(0);
+                const float a = alpha[s * TS + tt];
+                if (__builtin_amdgcn_ballot_w64(a != 1.0f) != 0) {
 #pragma unroll
-                    for (int ks = 0; ks < 2; ks++) {
-                        const int q = qt * 32 + r32;
-                        pf[ks] = *(const bf16x8 *)(ctx_lds + PB + t * (QT * 2048) + q * 64 + (((2 * ks + g) ^ ((q >> 2) & 3)) * 16));
+                    for (int v = 0; v < 16; v++) o[v] *= a;
+                }
 #pragma unroll
-                        for (int h = 0; h < 2; h++)
-                            asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(w[ks][h]) : "v"(lds0 + (st % 3) * CTX_STAGE + (tt * 32 + ks * 16) * ROWB + tr_off[h]));
-                    }
-                    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w[0][0]), "+v"(w[0][1]), "+v"(w[1][0]), "+v"(w[1][1]));
+                for (int ks = 0; ks < 2; ks++) {
+                    const intx4 both = __builtin_shufflevector(f.w[ks][0], f.w[ks][1], 0, 1, 2, 3);
+                    o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), __builtin_bit_cast(bf16x8, f.p[ks]), o, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // (a read and the wait for it stand in one block: a copy of its registers between the two would be of what they held before)
+            const int left = ntiles - st * TS;  // tiles of this stage and later ones, at least one
+            if (left >= TS) {
+                read(f0, 0);
 #pragma unroll
-                    for (int ks = 0; ks < 2; ks++) {
-                        const intx4 both = __builtin_shufflevector(w[ks][0], w[ks][1], 0, 1, 2, 3);
-                        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, both), pf[ks], o, 0, 0, 0);
+                for (int tt = 0; tt < TS; tt += 2) {
+                    read(f1, tt + 1);
+                    multiply(f0, tt, true);
+                    if (tt + 2 < TS) read(f0, tt + 2);
+                    multiply(f1, tt + 1, tt + 2 < TS);
+                }
+            } else {
+#pragma unroll
+                for (int tt = 0; tt < TS; tt += 2) {
+                    if (tt + 1 < left) {
+                        read(f0, tt);
+                        read(f1, tt + 1);
+                        multiply(f0, tt, true);
+                        multiply(f1, tt + 1, false);
+                    } else if (tt < left) {
+                        read(f0, tt);
+                        multiply(f0, tt, false);
                     }
                 }
             }
@@ -1030,7 +1067,7 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
     if (wave < QT && g == 0) inv_l[wave * 32 + r32] = 1.0f / l_tot;
     __syncthreads();
     const int q = qt * 32 + r32;
-    if (q < RQ) {
+    if (qt < QT && q < RQ) {
         const float inv = inv_l[q];
         bf16 *zr = z + ((int64_t)b * rq_stride + q) * D + slice * COLS + ct * 32 + 4 * g;
 #pragma unroll
@@ -1055,10 +1092,10 @@ size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S
     return (size_t)(B < most ? B : most) * ((S + 31) / 32) * (RQ > 32 ? 2 : 1) * (1024 + 32) * sizeof(float);
 }
 
-template <int D, int QT>
-static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
+template <int D, int QT, int COLS>
+static int launch_context_split_as(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
                                 float *ws, hipStream_t st) {
-    auto sums = context_sums<D, QT>;
+    auto sums = context_sums<D, QT, COLS>;
     constexpr int LDS_BYTES = 3 * CTX_STAGE + CTX_CHUNK * QT * (2048 + 128 + 256 + 256) + QT * 128;
     static_assert(LDS_BYTES <= 160 * 1024, "the workgroup's LDS");
     static bool attr_done = false;
@@ -1073,10 +1110,18 @@ static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ct
     hipLaunchKernelGGL((context_scores<D, QT>), dim3(per_request, B), dim3(512), 0, st, qp, x, ctx_len, ws, mxs, RQ, rq_stride, S, nt,
                        scale * 1.4426950408889634f);
     GR4AD_LAUNCH_CHECK();
-    hipLaunchKernelGGL(sums, dim3(D * QT / 256, B), dim3(512), LDS_BYTES, st, x, ctx_len, (const float *)ws, (const float *)mxs, z, RQ, rq_stride, S, nt,
+    hipLaunchKernelGGL(sums, dim3(D / COLS, B), dim3(512), LDS_BYTES, st, x, ctx_len, (const float *)ws, (const float *)mxs, z, RQ, rq_stride, S, nt,
                        scale * 1.4426950408889634f);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
+}
+
+// Slices of 64 columns of z while their workgroups fit the compute units: a quarter (half) of the context's bytes to each.
+template <int D, int QT>
+static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
+                                float *ws, hipStream_t st) {
+    if (B * (D / 64) <= 256) return launch_context_split_as<D, QT, 64>(qp, x, ctx_len, z, B, RQ, rq_stride, S, scale, ws, st);
+    return launch_context_split_as<D, QT, 256 / QT>(qp, x, ctx_len, z, B, RQ, rq_stride, S, scale, ws, st);
 }
 
 // z [B, RQ, d] = attention of the queries qp [B, RQ, d] over the context rows x [B, S, d] as keys and values (above).
