@@ -33,7 +33,7 @@
 template <typename T, bool AHEAD>
 __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q, int64_t ldq, const T *__restrict__ kv,
                                                          const int32_t *__restrict__ ctx_len, T *__restrict__ out, int64_t ldo,
-                                                         int64_t rows, int n, int S, int d, int H) {
+                                                         int64_t rows, int n, int q_stride, int S, int d, int H) {
     __shared__ __attribute__((aligned(16))) float sq[4][128];
     __shared__ float sp[4][64];
     const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
     int len = ctx_len ? ctx_len[b] : S;
     len = len < 1 ? 1 : (len > S ? S : len);
     const float scale = 1.0f / sqrtf((float)dh);
-    for (int c = lane; c < dh; c += 64) sq[wv][c] = to_f(q[row * ldq + h * dh + c]) * scale;
+    for (int c = lane; c < dh; c += 64) sq[wv][c] = to_f(q[(row - b * (n - q_stride)) * ldq + h * dh + c]) * scale;
     const T *kbase = kv + b * (int64_t)S * 2 * d + h * dh;  // key j at kbase + j*2d, value at + d
     constexpr int E = 16 / sizeof(T), U = 32 / E;           // values of a 16-byte load; loads of 32 columns
     const bool vec = ((uintptr_t)kbase % 16) == 0 && (2 * d) % E == 0 && dh % E == 0;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__((NW + LD) * 64, 4) void cross_attn_flash_bf16(const
                                                                  const bf16 *__restrict__ vt, int64_t vt_req, const int32_t *__restrict__ ctx_len,
                                                                  bf16 *__restrict__ out, int64_t ldo, int n, int S, int Spad, int H,
                                                                  float scale_log2e, int beam_blocks, int64_t total_blocks,
-                                                                 const int32_t *__restrict__ q_first, const int32_t *__restrict__ q_count) {
+                                                                 const int32_t *__restrict__ q_first, const int32_t *__restrict__ q_count, int q_stride) {
     constexpr int KCH = DH / 8;                   // 16-byte chunks per K row
     constexpr int K_CHUNKS = 64 * KCH, V_CHUNKS = DH * 8;
     constexpr int STAGE = K_CHUNKS + V_CHUNKS;    // one 64-key tile
@@ -298,7 +298,7 @@ __global__ __launch_bounds__((NW + LD) * 64, 4) void cross_attn_flash_bf16(const
     {
         int row = q0 + frow;
         if (row > n - 1) row = n - 1;  // rows past the end are computed and dropped
-        const bf16 *qr = q + (req_row + row) * ldq + h * DH;
+        const bf16 *qr = q + ((q_count ? req_row : (int64_t)b * q_stride) + row) * ldq + h * DH;  // (q_stride 0: the same queries for every request)
 #pragma unroll
         for (int s = 0; s < KSTEPS; s++) qf[s] = *(const bf16x8 *)(qr + 16 * s + 8 * hf);
     }
@@ -537,7 +537,7 @@ __device__ __forceinline__ int ctx_swz(int r) { return ((r & 3) << 2) | ((r >> 2
 
 template <int D, int QT>
 __global__ __launch_bounds__(512) void context_attn_flash_bf16(const bf16 *__restrict__ qp, const bf16 *__restrict__ x,
-                                                               const int32_t *__restrict__ ctx_len, bf16 *__restrict__ z, int RQ, int rq_stride,
+                                                               const int32_t *__restrict__ ctx_len, bf16 *__restrict__ z, int RQ, int q_stride, int rq_stride,
                                                                int S, float scale_log2e) {
     constexpr int ROWB = D * 2, CH = D / 8, TILE = 32 * ROWB;  // bytes per row, 16-byte pieces per row, bytes per tile
     constexpr int KSPLIT = 8 / QT, KSL = D / KSPLIT, KSTEPS = KSL / 16;
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(512) void context_attn_flash_bf16(const bf16 *__res
     {
         int qrow = qh * 32 + r32;
         if (qrow > RQ - 1) qrow = RQ - 1;  // queries past the end are computed and dropped
-        const bf16 *qr = qp + ((int64_t)b * rq_stride + qrow) * D + kq * KSL + 8 * g;
+        const bf16 *qr = qp + ((int64_t)b * q_stride + qrow) * D + kq * KSL + 8 * g;
 #pragma unroll
         for (int st = 0; st < KSTEPS; st++) qf[st] = *(const bf16x8 *)(qr + 16 * st);
     }
@@ -771,7 +771,7 @@ __global__ __launch_bounds__(512) void context_attn_flash_bf16(const bf16 *__res
 bool context_attention_covers(gr4ad_dtype dtype, int RQ, int d) { return dtype == GR4AD_BF16 && (d == 512 || d == 1024) && RQ >= 1 && RQ <= 128; }
 
 template <int D, int QT>
-static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
+static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int q_stride, int rq_stride, int S, float scale,
                                 hipStream_t st) {  // RQ <= 32 * QT queries per request, rows rq_stride apart from one request to the next
     auto kern = context_attn_flash_bf16<D, QT>;
     constexpr int LDS_BYTES = 2 * 32 * D * 2 + QT * (8 / QT - 1) * 4096 + QT * 2048 + QT * 128;
@@ -783,7 +783,7 @@ static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ct
     }
     // flops on the padded length S, both products; bytes: the context once, queries and sums once
     ProfScope ps(KC_CONTEXT_ATTN, st, 4.0 * B * (double)RQ * S * D, (2.0 * B * (double)RQ * D + B * (double)S * D) * sizeof(bf16));
-    hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(512), LDS_BYTES, st, qp, x, ctx_len, z, RQ, rq_stride, S, scale * 1.4426950408889634f);
+    hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(512), LDS_BYTES, st, qp, x, ctx_len, z, RQ, q_stride, rq_stride, S, scale * 1.4426950408889634f);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
@@ -806,7 +806,7 @@ static int launch_context_flash(const bf16 *qp, const bf16 *x, const int32_t *ct
 // sc: [B][ntiles][QT][4][64 lanes][4] raw scores as a wavefront holds them; mxs: [B][ntiles][QT][32] scaled maximum of each tile's valid rows
 template <int D, int QT>
 __global__ __launch_bounds__(512) void context_scores(const bf16 *__restrict__ qp, const bf16 *__restrict__ x, const int32_t *__restrict__ ctx_len,
-                                                      float *__restrict__ sc, float *__restrict__ mxs, int RQ, int rq_stride, int S, int ntiles, float scale_log2e) {
+                                                      float *__restrict__ sc, float *__restrict__ mxs, int RQ, int q_stride, int S, int ntiles, float scale_log2e) {
     constexpr int KSPLIT = 8 / QT, KSL = D / KSPLIT, KSTEPS = KSL / 16;
     constexpr int PART = QT * (KSPLIT - 1) * 4096;
     __shared__ __attribute__((aligned(16))) char parts[2 * PART];  // (two tiles: one barrier each)
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(512) void context_scores(const bf16 *__restrict__ q
     len = len < 1 ? 1 : (len > S ? S : len);
     if ((int)blockIdx.x * 32 >= len) return;
     const int qrow = qh * 32 + r32 < RQ ? qh * 32 + r32 : RQ - 1;
-    const bf16 *qr = qp + ((int64_t)b * rq_stride + qrow) * D + kq * KSL + 8 * g;
+    const bf16 *qr = qp + ((int64_t)b * q_stride + qrow) * D + kq * KSL + 8 * g;
     bf16x8 qf[KSTEPS];
 #pragma unroll
     for (int st = 0; st < KSTEPS; st++) qf[st] = *(const bf16x8 *)(qr + 16 * st);
@@ -1093,7 +1093,7 @@ size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S
 }
 
 template <int D, int QT, int COLS>
-static int launch_context_split_as(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
+static int launch_context_split_as(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int q_stride, int rq_stride, int S, float scale,
                                 float *ws, hipStream_t st) {
     auto sums = context_sums<D, QT, COLS>;
     constexpr int LDS_BYTES = 3 * CTX_STAGE + CTX_CHUNK * QT * (2048 + 128 + 256 + 256) + QT * 128;
@@ -1107,7 +1107,7 @@ static int launch_context_split_as(const bf16 *qp, const bf16 *x, const int32_t 
     float *mxs = ws + (size_t)B * nt * QT * 1024;
     ProfScope ps(KC_CONTEXT_ATTN, st, 4.0 * B * (double)RQ * S * D, (2.0 * B * (double)RQ * D + B * (double)S * D) * sizeof(bf16));
     const int per_request = nt * B <= CTX_SCORE_GROUPS ? nt : CTX_SCORE_GROUPS / B;
-    hipLaunchKernelGGL((context_scores<D, QT>), dim3(per_request, B), dim3(512), 0, st, qp, x, ctx_len, ws, mxs, RQ, rq_stride, S, nt,
+    hipLaunchKernelGGL((context_scores<D, QT>), dim3(per_request, B), dim3(512), 0, st, qp, x, ctx_len, ws, mxs, RQ, q_stride, S, nt,
                        scale * 1.4426950408889634f);
     GR4AD_LAUNCH_CHECK();
     hipLaunchKernelGGL(sums, dim3(D / COLS, B), dim3(512), LDS_BYTES, st, x, ctx_len, (const float *)ws, (const float *)mxs, z, RQ, rq_stride, S, nt,
@@ -1118,35 +1118,35 @@ static int launch_context_split_as(const bf16 *qp, const bf16 *x, const int32_t 
 
 // Slices of 64 columns of z while their workgroups fit the compute units: a quarter (half) of the context's bytes to each.
 template <int D, int QT>
-static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int rq_stride, int S, float scale,
+static int launch_context_split(const bf16 *qp, const bf16 *x, const int32_t *ctx_len, bf16 *z, int B, int RQ, int q_stride, int rq_stride, int S, float scale,
                                 float *ws, hipStream_t st) {
-    if (B * (D / 64) <= 256) return launch_context_split_as<D, QT, 64>(qp, x, ctx_len, z, B, RQ, rq_stride, S, scale, ws, st);
-    return launch_context_split_as<D, QT, 256 / QT>(qp, x, ctx_len, z, B, RQ, rq_stride, S, scale, ws, st);
+    if (B * (D / 64) <= 256) return launch_context_split_as<D, QT, 64>(qp, x, ctx_len, z, B, RQ, q_stride, rq_stride, S, scale, ws, st);
+    return launch_context_split_as<D, QT, 256 / QT>(qp, x, ctx_len, z, B, RQ, q_stride, rq_stride, S, scale, ws, st);
 }
 
 // z [B, RQ, d] = attention of the queries qp [B, RQ, d] over the context rows x [B, S, d] as keys and values (above).
 int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, const int32_t *ctx_len, void *z, int B, int RQ, int S, int d,
-                             float scale, void *ws, hipStream_t st) {
+                             float scale, void *ws, hipStream_t st, bool shared_q) {
     if (!context_attention_covers(dtype, RQ, d) || B < 1 || S < 1) return GR4AD_EUNSUPPORTED;
     if (!qp || !x || !z || ((uintptr_t)qp % 16) || ((uintptr_t)x % 16) || ((uintptr_t)z % 8) || ((uintptr_t)ws % 16)) return GR4AD_EINVAL;
     const bf16 *xx = (const bf16 *)x;
     for (int q0 = 0; q0 < RQ; q0 += 64) {  // 64 queries of every request per launch
         const bf16 *q = (const bf16 *)qp + (int64_t)q0 * d;
         bf16 *zz = (bf16 *)z + (int64_t)q0 * d;
-        const int nq = RQ - q0 < 64 ? RQ - q0 : 64;
+        const int nq = RQ - q0 < 64 ? RQ - q0 : 64, qs = shared_q ? 0 : RQ;
         int s;
         if (ws && B <= context_split_most(RQ, d)) {
             float *w = (float *)ws;
-            if (d == 1024) s = nq > 32 ? launch_context_split<1024, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st)
-                                       : launch_context_split<1024, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st);
-            else s = nq > 32 ? launch_context_split<512, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st)
-                             : launch_context_split<512, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, w, st);
+            if (d == 1024) s = nq > 32 ? launch_context_split<1024, 2>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, w, st)
+                                       : launch_context_split<1024, 1>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, w, st);
+            else s = nq > 32 ? launch_context_split<512, 2>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, w, st)
+                             : launch_context_split<512, 1>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, w, st);
         } else if (d == 1024) {
-            s = nq > 32 ? launch_context_flash<1024, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st)
-                        : launch_context_flash<1024, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st);
+            s = nq > 32 ? launch_context_flash<1024, 2>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, st)
+                        : launch_context_flash<1024, 1>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, st);
         } else {
-            s = nq > 32 ? launch_context_flash<512, 2>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st)
-                        : launch_context_flash<512, 1>(q, xx, ctx_len, zz, B, nq, RQ, S, scale, st);
+            s = nq > 32 ? launch_context_flash<512, 2>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, st)
+                        : launch_context_flash<512, 1>(q, xx, ctx_len, zz, B, nq, qs, RQ, S, scale, st);
         }
         if (s) return s;
     }
@@ -1155,7 +1155,7 @@ int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, c
 
 template <int DH, int NW, int LD>
 static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, int64_t ldk, const bf16 *vt, int64_t vt_req, const int32_t *ctx_len, bf16 *out, int64_t ldo, int B,
-                        int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
+                        int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr, int q_stride) {
     auto kern = cross_attn_flash_bf16<DH, NW, LD>;
     constexpr int LDS_BYTES = (LD ? 3 : 2) * (64 * (DH / 8) + DH * 8) * 16;
     static bool attr_done = false;
@@ -1172,16 +1172,16 @@ static int launch_flash(const bf16 *q, int64_t ldq, const bf16 *kv, int64_t ldk,
     // flops on the padded length S; bytes: queries and outputs once, keys and values once per request (beam-shared)
     ProfScope ps(KC_XATTN_FLASH, st, 4.0 * B * (double)n * S * d, (2.0 * B * n * d + 2.0 * B * (double)S * d) * sizeof(bf16));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((NW + LD) * 64), LDS_BYTES, st, q, ldq, kv, ldk, vt, vt_req, ctx_len, out, ldo, n, S, (S + 63) / 64 * 64, H, scale_log2e,
-                       beam_blocks, total_blocks, dr ? dr->first : nullptr, dr ? dr->count : nullptr);
+                       beam_blocks, total_blocks, dr ? dr->first : nullptr, dr ? dr->count : nullptr, q_stride);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
 
 int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, int64_t ldk, const void *vt, int64_t vt_req, const int32_t *ctx_len,
-                           void *out, int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr) {
+                           void *out, int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr, bool shared_q) {
     if (B <= 0 || n <= 0 || S <= 0 || d <= 0 || H <= 0 || d % H) return GR4AD_EINVAL;
-    const int dh = d / H;
-    if (dh > 128) return GR4AD_EUNSUPPORTED;
+    const int dh = d / H, q_stride = shared_q ? 0 : n;
+    if (dh > 128 || (shared_q && dr)) return GR4AD_EUNSUPPORTED;
     if (vt && cross_attention_workspace_bytes(dtype, B, S, d, H) && ldq % 8 == 0 && ldk % 8 == 0 && ldo % 4 == 0 && ((uintptr_t)q % 16) == 0 &&
         ((uintptr_t)out % 8) == 0) {
         const bf16 *qq = (const bf16 *)q, *kk = (const bf16 *)kv, *vv = (const bf16 *)vt;
@@ -1196,13 +1196,13 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
         // much work for the same loads: 128 requests, d = 1024, 64 keys, 64 beams 15.3 / 20.9 and 256 beams 33.5 / 41.6; 1024 keys, 64 beams 114 / 127 and 256 beams 250 / 266.
         const int64_t blocks = (int64_t)((n + 127) / 128) * H * B;
         if (dh == 32) {
-            if (blocks <= 768 || (n > 64 && n <= 128 && S > 192)) return launch_flash<32, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-            return launch_flash<32, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            if (blocks <= 768 || (n > 64 && n <= 128 && S > 192)) return launch_flash<32, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr, q_stride);
+            return launch_flash<32, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr, q_stride);
         }
-        if (blocks <= 768 || (n <= 128 && (n > 64 || S > 256))) return launch_flash<64, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+        if (blocks <= 768 || (n <= 128 && (n > 64 || S > 256))) return launch_flash<64, 4, 4>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr, q_stride);
         if (n <= 128 || (blocks <= 2048 && S > 128) || (n + 255) / 256 * 256 != (n + 127) / 128 * 128)
-            return launch_flash<64, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
-        return launch_flash<64, 8, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr);
+            return launch_flash<64, 4, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr, q_stride);
+        return launch_flash<64, 8, 0>(qq, ldq, kk, ldk, vv, vt_req, ctx_len, oo, ldo, B, n, S, d, H, st, dr, q_stride);
     }
     if (dr) return GR4AD_EUNSUPPORTED;
     const int64_t rows = (int64_t)B * n;
@@ -1212,7 +1212,7 @@ int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const 
     // Ahead where most of the tiles' 64 keys exist and the registers (three wavefronts per SIMD) suffice: head width 32, 64 keys, up to 512 workgroups 9.5 us, 7.5 ahead,
     // 16384 workgroups 140, 156 ahead; 65 keys, 512 workgroups 12.4, 14.4 ahead; 5 keys, 512 workgroups 6.9, 10.8 ahead.
     const bool ahead = dh <= 64 && (S <= 64 ? S > 32 : 5 * (int64_t)S > 3 * (((int64_t)S + 63) / 64 * 64)) && grid < 1024;
-#define SIMPLE_(T, AHEAD) hipLaunchKernelGGL((cross_attn_simple<T, AHEAD>), dim3((unsigned)grid), dim3(256), 0, st, (const T *)q, ldq, (const T *)kv, ctx_len, (T *)out, ldo, rows, n, S, d, H)
+#define SIMPLE_(T, AHEAD) hipLaunchKernelGGL((cross_attn_simple<T, AHEAD>), dim3((unsigned)grid), dim3(256), 0, st, (const T *)q, ldq, (const T *)kv, ctx_len, (T *)out, ldo, rows, n, q_stride, S, d, H)
     if (dtype == GR4AD_BF16) { if (ahead) SIMPLE_(bf16, true); else SIMPLE_(bf16, false); }
     else if (ahead) SIMPLE_(float, true);
     else SIMPLE_(float, false);

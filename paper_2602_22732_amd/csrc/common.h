@@ -257,9 +257,10 @@ int launch_distinct_rows(const int32_t *tok, int B, int n, const DistinctRows &d
 // beam-shared cross-attention; q/out row stride ldq/ldo elements, rows (b*n+i)
 // vt: per-(request, head) transposed values built by launch_cross_attention_prepare or launch_gemm_vt (NULL: plain kernel on kv alone, [B, S, 2d]),
 // vt_req elements from one request to the next; with vt, kv holds keys only, rows of ldk elements
+// shared_q: one set of n query rows serves every request
 // dr: the rows of request b are the dr->count[b] (<= n) rows from dr->first[b] on (matrix-core kernel only)
 int launch_cross_attention(gr4ad_dtype dtype, const void *q, int64_t ldq, const void *kv, int64_t ldk, const void *vt, int64_t vt_req, const int32_t *ctx_len,
-                           void *out, int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr = nullptr);
+                           void *out, int64_t ldo, int B, int n, int S, int d, int H, hipStream_t st, const DistinctRows *dr = nullptr, bool shared_q = false);
 // bytes of the transposed-value buffer the MFMA kernel needs for kv [B,S,2d] (0: the shape runs on the plain kernel)
 size_t cross_attention_workspace_bytes(gr4ad_dtype dtype, int B, int S, int d, int H);
 int launch_cross_attention_prepare(gr4ad_dtype dtype, const void *kv, const int32_t *ctx_len, void *vt, int B, int S, int d, int H,
@@ -273,10 +274,11 @@ int launch_masked_softmax(const float *sc, void *p, const int32_t *ctx_len, int6
 // (qp [B, RQ, d], x [B, S, d], bf16; 64 queries of every request per launch).  GR4AD_EUNSUPPORTED for shapes
 // context_attention_covers() refuses.
 bool context_attention_covers(gr4ad_dtype dtype, int RQ, int d);
+// shared_q: qp is [RQ, d], the same queries for every request
 // ws: scratch of context_attention_workspace_bytes() bytes with which few requests run their tiles side by side, or NULL
 size_t context_attention_workspace_bytes(gr4ad_dtype dtype, int B, int RQ, int S, int d);
 int launch_context_attention(gr4ad_dtype dtype, const void *qp, const void *x, const int32_t *ctx_len, void *z, int B, int RQ, int S, int d,
-                             float scale, void *ws, hipStream_t st);
+                             float scale, void *ws, hipStream_t st, bool shared_q = false);
 // autoregressive self-attention of position `pos` for rows (b*n+i).  qkv [rows,3d] holds q, k, v of the new position;
 // the keys and values of position p < pos are columns d..3d of row anc[row*T + p] of prev.p[p] (the [*,3d] q/k/v buffer
 // that level wrote): the beam reorder is the ancestor table, no rows are moved.

@@ -51,6 +51,11 @@ struct gr4ad_decoder {
     int32_t *tr_parent[GR4AD_MAX_LEVELS], *tr_tok[GR4AD_MAX_LEVELS];
     float *tr_score[GR4AD_MAX_LEVELS];
     bool trace;
+    // The lazy pass starts from the position embeddings alone, so the queries of its first layer are the same for every request and are laid out with the weights:
+    // [Tp*H, d] absorbed ones, else [Tp, d]; pos32: the embeddings as the residual stream has them, [Tp, d]; pos_of[v]: position of every row of a batch (v: with the value step's)
+    void *first_q;
+    float *pos32;
+    int32_t *pos_of[2];
     bool absorbed;  // lazy layers' cross-attention runs in absorbed form (see decode_batch)
     bool fp8;       // FP8 mode: the per-beam-row products take E4M3 operands (see decode_batch)
     void *wf1_8, *cls8[GR4AD_MAX_LEVELS];
@@ -395,6 +400,34 @@ int init_impl(gr4ad_decoder *dec, const gr4ad_model_desc *ds, const gr4ad_weight
         for (int t = 0; t < dec->Tp; t++)
             if ((s = quant(dec->cls[t], (size_t)dec->V[t] * d, &dec->cls8[t], &dec->s_cls[t]))) return s;
     }
+    if (dec->K > 0) {
+        const LayerPacked &p = dec->layers[0];
+        const int64_t Tp = dec->Tp;
+        void *xn, *q;
+        if ((s = dev_alloc(dec, (void **)&dec->pos32, Tp * d * sizeof(float)))) return s;
+        if ((s = dev_alloc(dec, &xn, Tp * d * e))) return s;
+        if ((s = dev_alloc(dec, &q, Tp * d * e))) return s;
+        OP_TRY(dec, launch_broadcast_rows(dec->dtype, dec->pos, dec->pos32, 1, (int)Tp, (int)d, 0), "trunk input");
+        GemmEpilogue g = plain_epilogue(q, d);
+        g.pre_x = dec->pos32;
+        g.pre_gain = p.ln_x;
+        g.pre_eps = dec->eps;
+        OP_TRY(dec, launch_gemm(dec->dtype, xn, d, p.wq_x, d, Tp, (int)d, (int)d, g, 0), "first lazy queries");
+        dec->first_q = q;
+        if (dec->absorbed) {
+            const int dh = (int)d / dec->H;
+            if ((s = dev_alloc(dec, &dec->first_q, Tp * dec->H * d * e))) return s;
+            OP_TRY(dec, launch_gemm_batched(q, d, dh, p.wkT_x, dh, (int64_t)d * dh, dec->first_q, (int64_t)dec->H * d, d, 0, Tp, (int)d, dh, dec->H, nullptr, 0, 0),
+                   "first lazy queries (absorbed form)");
+        }
+        for (int v = 0; v < (dec->Ve > 0 ? 2 : 1); v++) {
+            const int Tq = dec->T + v;
+            std::vector<int32_t> of((size_t)dec->max_batch * Tq);
+            for (size_t i = 0; i < of.size(); i++) of[i] = (int32_t)(i % Tq);
+            if ((s = dev_alloc(dec, (void **)&dec->pos_of[v], of.size() * sizeof(int32_t)))) return s;
+            HIP_TRY(dec, hipMemcpy(dec->pos_of[v], of.data(), of.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        }
+    }
     HIP_TRY(dec, hipDeviceSynchronize());
     return GR4AD_OK;
 }
@@ -602,9 +635,20 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         return g;
     };
 
+    // first lazy layer: its queries are laid out, and its output is added to the position embeddings, which are the residual stream until then
+    auto first_epi = [&]() {
+        GemmEpilogue g = f32_epilogue(trunk, d);
+        g.table = dec->pos32;
+        g.tok = dec->pos_of[Tq - T];
+        return g;
+    };
     // cross-attention + its residual; x is the residual stream [rows,d]; next_gain: gain of the norm that follows
-    auto cross_block = [&](const LayerPacked &lw, void *x, int64_t rows, int n, const ContextKV &c, const DistinctRows *dr = nullptr) -> int {
+    auto cross_block = [&](const LayerPacked &lw, void *x, int64_t rows, int n, const ContextKV &c, const DistinctRows *dr = nullptr, bool first = false) -> int {
         int s;
+        if (first) {
+            if ((s = launch_cross_attention(dt, dec->first_q, d, c.k, c.ldk, c.vt, c.vt_req, ctx_len, o, d, B, n, S, d, H, st, nullptr, true))) return s;
+            return gemm(o, rows, lw.wo_x, d, d, emit_norm(first_epi(), lw.ln_s));
+        }
         if ((s = norm(x, lw.ln_x, rows))) return s;
         if (f8) s = gemm8(rows, lw.wq_x8, lw.s_wq_x, d, d, plain_epilogue(q, d));
         else s = gemm(xn, rows, lw.wq_x, d, d, reads_norm(plain_epilogue(q, d)));
@@ -666,27 +710,31 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         int s;
         const bool one_pass = context_attention_covers(dt, (int)RQ, d);
         if (first && !one_pass && (s = launch_context_transpose(ctx, ctx_len, xt, B, S, d, st))) return s;  // once per decode, shared by all lazy layers
-        if ((s = norm(trunk, lw.ln_x, rows))) return s;
-        if ((s = gemm(xn, rows, lw.wq_x, d, d, reads_norm(plain_epilogue(q, d))))) return s;
-        // q'[row][h][:] = W_{k,h}^T q[row][h*dh : (h+1)*dh]      (batch = head)
-        if ((s = launch_gemm_batched(q, d, dh, lw.wkT_x, dh, (int64_t)d * dh, qp, (int64_t)H * d, d, 0, rows, d, dh, H, nullptr, 0, st))) return s;
+        if (first) {
+            qp = (char *)dec->first_q;
+        } else {
+            if ((s = norm(trunk, lw.ln_x, rows))) return s;
+            if ((s = gemm(xn, rows, lw.wq_x, d, d, reads_norm(plain_epilogue(q, d))))) return s;
+            // q'[row][h][:] = W_{k,h}^T q[row][h*dh : (h+1)*dh]      (batch = head)
+            if ((s = launch_gemm_batched(q, d, dh, lw.wkT_x, dh, (int64_t)d * dh, qp, (int64_t)H * d, d, 0, rows, d, dh, H, nullptr, 0, st))) return s;
+        }
         if (one_pass) {
             // scores, softmax and z in one kernel that reads the request's context rows once (widths and query counts it covers)
-            if ((s = launch_context_attention(dt, qp, ctx, ctx_len, zb, B, (int)RQ, S, d, 1.0f / sqrtf((float)dh), sc, st))) return s;
+            if ((s = launch_context_attention(dt, qp, ctx, ctx_len, zb, B, (int)RQ, S, d, 1.0f / sqrtf((float)dh), sc, st, first))) return s;
         } else {
             // raw scores[b][(t,h)][s] = q'[b][(t,h)] . x[b][s]         (batch = request; columns beyond the length are not needed)
-            if ((s = launch_gemm_batched(qp, d, RQ * d, ctx, d, (int64_t)S * d, sc, Spad, RQ * Spad, 1, RQ, S, d, B, ctx_len, 1, st))) return s;
+            if ((s = launch_gemm_batched(qp, d, first ? 0 : RQ * d, ctx, d, (int64_t)S * d, sc, Spad, RQ * Spad, 1, RQ, S, d, B, ctx_len, 1, st))) return s;
             if ((s = launch_masked_softmax(sc, pb, ctx_len, (int64_t)B * RQ, (int)RQ, S, Spad, 1.0f / sqrtf((float)dh), st))) return s;
             // z[b][(t,h)][:] = sum_s p[b][(t,h)][s] x[b][s][:]         (batch = request; p and x^T are zero beyond the length)
             if ((s = launch_gemm_batched(pb, Spad, RQ * Spad, xt, Spad, (int64_t)d * Spad, zb, d, RQ * d, 0, RQ, d, Spad, B, ctx_len, 2, st))) return s;
         }
         // o[row][h*dh : (h+1)*dh] = W_{v,h} z[row][h][:]           (batch = head)
         if ((s = launch_gemm_batched(zb, (int64_t)H * d, d, wv, d, (int64_t)dh * d, o, d, dh, 0, rows, dh, d, H, nullptr, 0, st))) return s;
-        return gemm(o, rows, lw.wo_x, d, d, emit_norm(resid_epi(trunk, d), lw.ln_s));
+        return gemm(o, rows, lw.wo_x, d, d, emit_norm(first ? first_epi() : resid_epi(trunk, d), lw.ln_s));
     };
 
     // ---- step 1: lazy pass (eq. trunk): all T levels at once, no beam dimension ----
-    if (!dec->vanilla) OP_TRY(dec, launch_broadcast_rows(dt, dec->pos, trunk, B, Tq, d, st), "trunk input");
+    if (!dec->vanilla && K == 0) OP_TRY(dec, launch_broadcast_rows(dt, dec->pos, trunk, B, Tq, d, st), "trunk input");
     fold = K > 0 && fold_ok((int64_t)B * Tq, 0);
     for (int l = 0; l < K; l++) {
         const LayerPacked &lw = dec->layers[l];
@@ -697,7 +745,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             const size_t w = (size_t)l * d * d * e;
             if (!dec->flash) OP_TRY(dec, context_kv(lw, context_of(p.kv_lazy, 0, 0, 1)), "lazy context K/V projection");
             else if (!lazy_together) OP_TRY(dec, context_products((char *)dec->wk_ctx[0] + w, (char *)dec->wv_ctx[0] + w, 1, p.kv_lazy, p.vt_lazy), "lazy context K/V projection");
-            OP_TRY(dec, cross_block(lw, trunk, rows, Tq, lazy_together ? context_of(p.kv_lazy, p.vt_lazy, l, K) : context_of(p.kv_lazy, p.vt_lazy, 0, 1)), "lazy cross-attention");
+            OP_TRY(dec, cross_block(lw, trunk, rows, Tq, lazy_together ? context_of(p.kv_lazy, p.vt_lazy, l, K) : context_of(p.kv_lazy, p.vt_lazy, 0, 1), nullptr, l == 0), "lazy cross-attention");
         }
         OP_TRY(dec, norm(trunk, lw.ln_s, rows), "lazy norm");
         OP_TRY(dec, gemm(xn, rows, lw.wqkv_s, 3 * d, d, reads_norm(plain_epilogue(qkv, 3 * d))), "lazy qkv");
@@ -787,8 +835,12 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             else OP_TRY(dec, gemm(xn, rows, lw.wqkv_s, 3 * d, d, reads_norm(plain_epilogue(qkv_lvl(t, a), 3 * d))), "self-attention qkv");
             distinct = nullptr;  // from here on: every beam
             prof_rows(nullptr, 0, st);
-            OP_TRY(dec, launch_self_attention_step(dt, qkv_lvl(t, a), prev, (const int32_t *)(ws + p.anc[cur]), o, rows, t, T, d, H, st, mapped ? &maps : nullptr),
-                   "self-attention");
+            // The first level has one position: the softmax of its one score is 1, the output its value, which the output projection reads in place
+            // (a launch of 2 to 3 us per layer where they are short).
+            const bool one = t == 0 && !f8;
+            if (!one)
+                OP_TRY(dec, launch_self_attention_step(dt, qkv_lvl(t, a), prev, (const int32_t *)(ws + p.anc[cur]), o, rows, t, T, d, H, st, mapped ? &maps : nullptr),
+                       "self-attention");
             GemmEpilogue out_s = resid_epi(h, d);
             if (x != h) {  // the residual stream of every beam starts from its distinct row's
                 out_s.resid = nullptr;
@@ -799,7 +851,8 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
                 OP_TRY(dec, quant_act(o, rows, d), "self-attention output quantisation");
                 OP_TRY(dec, gemm8(rows, lw.wo_s8, lw.s_wo_s, d, d, out_s), "self-attention output");
             } else {
-                OP_TRY(dec, gemm(o, rows, lw.wo_s, d, d, emit_norm(out_s, lw.ln_f)), "self-attention output");
+                const void *attended = one ? (char *)qkv_lvl(t, a) + 2 * d * e : o;
+                OP_TRY(dec, launch_gemm(dt, attended, one ? 3 * d : d, lw.wo_s, d, rows, d, d, emit_norm(out_s, lw.ln_f), st), "self-attention output");
             }
             OP_TRY(dec, ffn_block(lw, h, rows, a + 1 < A ? dec->layers[K + a + 1].ln_x : dec->ln_out), "FFN");
         }
