@@ -189,6 +189,10 @@ struct GemmEpilogue {
 // A row stride lda, W row stride ldw (elements).  dtype: storage type of A, W (and C unless out_f32).
 int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                 const GemmEpilogue &epi, hipStream_t st);
+// the products whose operand a launch of its own would form (see gemm.hip)
+int launch_gemm_gated(gr4ad_dtype dtype, const float *m, int64_t m_req_stride, const float *G, int64_t table_rows, const int32_t *tok, void *gated, int B, int n, const void *W, int N,
+                      int d, const GemmEpilogue &epi, hipStream_t st);
+int launch_gemm_trunk_attended(gr4ad_dtype dtype, const void *qkv, void *o, int B, int T, int H, const void *W, int N, int d, const GemmEpilogue &epi, hipStream_t st);
 // true if this product is one of the large class, which folds the RMSNorm and writes half-precision logits
 bool gemm_large_class(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, int64_t ldw, int64_t M, int N, int K,
                                const GemmEpilogue &epi);

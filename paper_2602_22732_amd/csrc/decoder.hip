@@ -749,8 +749,7 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         }
         OP_TRY(dec, norm(trunk, lw.ln_s, rows), "lazy norm");
         OP_TRY(dec, gemm(xn, rows, lw.wqkv_s, 3 * d, d, reads_norm(plain_epilogue(qkv, 3 * d))), "lazy qkv");
-        OP_TRY(dec, launch_trunk_self_attention(dt, qkv, o, B, Tq, d, H, st), "lazy self-attention");
-        OP_TRY(dec, gemm(o, rows, lw.wo_s, d, d, emit_norm(resid_epi(trunk, d), lw.ln_f)), "lazy self-attention output");
+        OP_TRY(dec, launch_gemm_trunk_attended(dt, qkv, o, B, Tq, H, lw.wo_s, d, d, emit_norm(resid_epi(trunk, d), lw.ln_f), st), "lazy self-attention");
         OP_TRY(dec, ffn_block(lw, trunk, rows, l + 1 < K ? dec->layers[l + 1].ln_x : nullptr), "lazy FFN");
     }
 
@@ -807,17 +806,21 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
         } else {
             // the gated embedding goes through q when the Fuse projection also writes the first norm's input into xn
             void *gated = fold ? q : xn;
-            OP_TRY(dec, launch_fuse_gate(dt, (const float *)trunk + (size_t)t * d, (int64_t)Tq * d, dec->G[t], t == 0 ? 1 : dec->V[t - 1], tok_in, gated, B, n, d, st,
-                                         distinct, dr.req), "Fuse gate");
+            const float *m = (const float *)trunk + (size_t)t * d;
+            const int64_t table_rows = t == 0 ? 1 : dec->V[t - 1];
             GemmEpilogue g = plain_epilogue(x1, d);
             g.out_f32 = 1;
             g.table = (const float *)dec->P[t];
             g.tok = tok_in;
+            if (f8 || distinct)
+                OP_TRY(dec, launch_fuse_gate(dt, m, (int64_t)Tq * d, dec->G[t], table_rows, tok_in, gated, B, n, d, st, distinct, dr.req), "Fuse gate");
             if (f8) {
                 OP_TRY(dec, quant_act(gated, rows, d), "Fuse operand quantisation");
                 OP_TRY(dec, gemm8(rows, dec->wf1_8, dec->s_wf1, d, d, g), "Fuse projection");
             } else {
-                OP_TRY(dec, gemm(gated, rows, dec->wf1, d, d, emit_norm(g, dec->layers[K].ln_x)), "Fuse projection");
+                g = emit_norm(g, dec->layers[K].ln_x);
+                if (distinct) OP_TRY(dec, gemm(gated, rows, dec->wf1, d, d, g), "Fuse projection");
+                else OP_TRY(dec, launch_gemm_gated(dt, m, (int64_t)Tq * d, (const float *)dec->G[t], table_rows, tok_in, gated, B, n, dec->wf1, d, d, g, st), "Fuse projection");
             }
         }
         for (int a = 0; a < A; a++) {

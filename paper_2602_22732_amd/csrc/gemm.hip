@@ -12,8 +12,8 @@
 //                        v_mfma_f32_32x32x16_bf16; 32x32 to 128x128 tiles for the
 //                        small and middle shapes, operands streamed into LDS,
 //                        by wavefronts of their own where tiles are few.
-//  * gemm_bf16_panel<..> the small products behind an RMSNorm: the workgroup
-//                        normalises the rows it multiplies.
+//  * gemm_bf16_panel<..> the small products behind an RMSNorm, a gate or the trunk's
+//                        self-attention: the workgroup forms the rows it multiplies.
 //  * gemm_bf16_ring<..>  the kernel of the large shapes: persistent, 256x256 tiles,
 //                        operands stream global -> LDS without passing registers.
 #include <string.h>
@@ -1617,7 +1617,7 @@ static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64
 }
 
 // ---------------------------------------------------------------------------
-// MFMA kernel of the small products behind an RMSNorm: the rows of A are formed by the workgroup that multiplies them
+// MFMA kernel of the small products behind an RMSNorm, Fuse's gate or the trunk's self-attention: the rows of A are formed by the workgroup that multiplies them
 // ---------------------------------------------------------------------------
 // Where launches are short a norm of its own is a launch of 1.7 to 4.7 us whose rows the product then waits for again.  Here a workgroup (8 wavefronts) requests
 // its rows of x (float32, all K columns) and every k-tile of W it will multiply at once, normalises the rows while W is on the way, leaves them in LDS as the
@@ -1627,9 +1627,59 @@ static int launch_tile(int run, const bf16 *A, int64_t lda, const bf16 *W, int64
 // LDS: BM x K values of A (a k-tile of 64 values: BM rows of 128 bytes), then BN x K of W.
 // V: 16-byte pieces of a row per lane (1: K <= 512, 2: K <= 1024), 0: K <= 256, two rows to a wavefront.
 // J: steps a wavefront takes its rows in (fewer than BM has: rows beyond them are past the last one).
-template <int BM, int BN, int V, int J, int KIND>
-__global__ __launch_bounds__(512, 4) void gemm_bf16_panel(const float *__restrict__ x, const bf16 *__restrict__ gain, const bf16 *__restrict__ W, int64_t ldw, int M, int N,
-                                                          int K, float eps, int tiles_m, int tiles_n, void *C, int64_t ldc, const float *__restrict__ bias) {
+// SRC: what the rows are: norms; products of a trunk row and a gate table's (Fuse); the trunk's causal self-attention - each as the kernel of its own forms it.
+enum { ROWS_NORM = 0, ROWS_GATED, ROWS_TRUNK };
+struct PanelRows {
+    const float *x;       // ROWS_NORM: rows, gains and epsilon; ROWS_GATED: trunk row of request b at x + b * x_req
+    const bf16 *gain;
+    float eps;
+    int n;                // ROWS_GATED: rows of a request; ROWS_TRUNK: its positions
+    int64_t x_req;
+    const float *table;   // ROWS_GATED: row tok[r] (0 if NULL)
+    const int32_t *tok;
+    const bf16 *qkv;      // ROWS_TRUNK: [rows, 3K]
+    int lanes_per_head;   // K / heads / 8: 2, 4 or 8
+};
+struct PanelOut { void *C; int64_t ldc; const float *bias, *resid, *table; const int32_t *tok; int64_t ldr; };
+// eight channels of one trunk row (as trunk_self_attn, whose lanes hold a channel each: its sums over lane ^ 32, ^ 16, ^ 8 are over lanes ^ 4, ^ 2, ^ 1 here, those over lane ^ 4, ^ 2, ^ 1 over
+// a lane's own values)
+__device__ __forceinline__ float lane_xor4(float v) { return dpp_move<0x1B, 0xF>(0.0f, dpp_move<0x141, 0xF>(0.0f, v)); }  // 7 - lane, then 3 - lane of the quad
+__device__ __forceinline__ bf16x8 trunk_attended(const bf16x8 &q, const bf16x8 (&k)[4], const bf16x8 (&v)[4], int tau, int lph) {
+#pragma clang fp contract(off)
+    const float scale = 1.0f / sqrtf((float)(8 * lph));
+    float s[4], mx = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < 4; p++) {
+        float e[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            e[i] = (float)q[i] * (float)k[p][i];
+            if (lph > 4) e[i] += lane_xor4(e[i]);
+            if (lph > 2) e[i] += lane_xor2(e[i]);
+            e[i] += lane_xor1(e[i]);
+        }
+        const float sum = ((e[0] + e[4]) + (e[2] + e[6])) + ((e[1] + e[5]) + (e[3] + e[7]));
+        s[p] = sum * scale;
+        if (p <= tau) mx = fmaxf(mx, s[p]);
+    }
+    float den = 0.0f;
+#pragma unroll
+    for (int p = 0; p < 4; p++)
+        if (p <= tau) { s[p] = __expf(s[p] - mx); den += s[p]; }
+    const float inv = 1.0f / den;
+    bf16x8 y;
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        float o = 0.0f;
+#pragma unroll
+        for (int p = 0; p < 4; p++)
+            if (p <= tau) o = fmaf(s[p] * inv, (float)v[p][i], o);
+        y[i] = (bf16)o;
+    }
+    return y;
+}
+template <int BM, int BN, int V, int J, int SRC, int KIND>
+__global__ __launch_bounds__(512, 4) void gemm_bf16_panel(PanelRows rows, const bf16 *__restrict__ W, int64_t ldw, int M, int N, int K, int tiles_m, int tiles_n, PanelOut out) {
     constexpr int WAVES_N = BN / 32, NC = BM / 32 * WAVES_N, WTILE = BN * 128, PIECES = BN / 8;
     constexpr int VEC = V == 2 ? 2 : 1, KMAX = V == 0 ? 256 : 512 * V;
     static_assert(J * (V == 0 ? 16 : 8) <= BM, "rows of the tile");
@@ -1647,23 +1697,58 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_panel(const float *__restric
     const int KT = K / 64;
     char *const panel = (char *)smem, *const slots = panel + BM * K * 2;
 
-    // ---- the rows of x and the gains: requested first, they are needed first.  Dealt to the wavefronts in turn, rows past the edge re-read the last one.  No
-    // branch between these loads and those of W, so that the compiler can count them and wait for x alone ----
+    // ---- what the rows are formed from: requested first, it is needed first.  Rows are dealt to the wavefronts in turn, those past the edge re-read the last one.
+    // No branch between these loads and those of W, so that the compiler can count them and wait for the rows alone ----
     const int nvec = K / 8, pos = V == 0 ? lane % 32 : lane, half = V == 0 ? lane / 32 : 0;
     auto row_of = [&](int j) { return (j * 8 + wave) * (V == 0 ? 2 : 1) + half; };
-    float v[J][VEC][8];
-    bf16x8 g[VEC];
+    auto inside = [&](int j) { return m0 + row_of(j) < M ? m0 + row_of(j) : M - 1; };
+    auto piece = [&](int i) { return pos + 64 * i < nvec ? pos + 64 * i : nvec - 1; };
+    auto load8 = [](float *v, const float *p) {
+        *(floatx4 *)v = *(const floatx4 *)p;
+        *(floatx4 *)(v + 4) = *(const floatx4 *)(p + 4);
+    };
+    float v[J][VEC][8], u[J][VEC][8];
+    bf16x8 g[VEC], q[J][VEC], k[J][VEC][4], w[J][VEC][4];
+    int tau[J];
+    if constexpr (SRC == ROWS_NORM) {
 #pragma unroll
-    for (int i = 0; i < VEC; i++) g[i] = *(const bf16x8 *)(gain + (pos + 64 * i < nvec ? pos + 64 * i : nvec - 1) * 8);
-    const float *xr = x + (int64_t)m0 * K;  // (rows and columns of the block by 32-bit offsets)
+        for (int i = 0; i < VEC; i++) g[i] = *(const bf16x8 *)(rows.gain + piece(i) * 8);
+        const float *xr = rows.x + (int64_t)m0 * K;  // (rows and columns of the block by 32-bit offsets)
 #pragma unroll
-    for (int j = 0; j < J; j++) {
-        const int r = row_of(j), off = (m0 + r < M ? r : M - 1 - m0) * K;
+        for (int j = 0; j < J; j++) {
+            const int off = (inside(j) - m0) * K;
 #pragma unroll
-        for (int i = 0; i < VEC; i++) {
-            const float *p = xr + off + (pos + 64 * i < nvec ? pos + 64 * i : nvec - 1) * 8;
-            *(floatx4 *)&v[j][i][0] = *(const floatx4 *)p;
-            *(floatx4 *)&v[j][i][4] = *(const floatx4 *)(p + 4);
+            for (int i = 0; i < VEC; i++) load8(v[j][i], xr + off + piece(i) * 8);
+        }
+    } else if constexpr (SRC == ROWS_GATED) {
+        uint32_t sel[J];
+#pragma unroll
+        for (int j = 0; j < J; j++) sel[j] = rows.tok ? (uint32_t)rows.tok[inside(j)] : 0u;
+#pragma unroll
+        for (int j = 0; j < J; j++) {
+            const float *mr = rows.x + (int64_t)((uint32_t)inside(j) / (uint32_t)rows.n) * rows.x_req, *gr = rows.table + (uint64_t)sel[j] * (uint32_t)K;
+#pragma unroll
+            for (int i = 0; i < VEC; i++) {
+                load8(v[j][i], mr + piece(i) * 8);
+                load8(u[j][i], gr + piece(i) * 8);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < J; j++) {
+            const int r = inside(j);
+            tau[j] = r % rows.n;
+#pragma unroll
+            for (int i = 0; i < VEC; i++) {
+                const bf16 *src = rows.qkv + (int64_t)r * 3 * K + piece(i) * 8;
+                q[j][i] = *(const bf16x8 *)src;
+#pragma unroll
+                for (int p = 0; p < 4; p++) {  // (positions past this row's re-read its own and are not used)
+                    const bf16 *at = src - (int64_t)(p < tau[j] ? tau[j] - p : 0) * 3 * K;
+                    k[j][i][p] = *(const bf16x8 *)(at + K);
+                    w[j][i][p] = *(const bf16x8 *)(at + 2 * K);
+                }
+            }
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -1684,47 +1769,74 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_panel(const float *__restric
             ring_dma16(src + at * (EVERY * 128), (bf16x8 *)(dst + at * 8192));
         }
     }
-    __builtin_amdgcn_sched_barrier(0);
+    GemmEpilogue epi = {};
+    epi.C = out.C;
+    epi.ldc = out.ldc;
+    epi.bias = out.bias;
+    epi.resid = out.resid;
+    epi.ldr = out.ldr;
+    epi.table = out.table;
+    epi.tok = out.tok;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int wrow0 = m0 + wm * 32, wcol0 = n0 + wn * 32;
-    // ---- RMSNorm: four steps' factors at once, one in each lane of a quad (a division and a root are some fifty instructions) ----
-    float ss[J];
+    float add[16];
+    if ((KIND == EPI_F32_RESID || KIND == EPI_F32_TABLE) && wave < NC) direct_addends<KIND>(add, wrow0, wcol0, M, N, epi, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    auto put = [&](int j, int i, const bf16x8 &y) {
+        const int r = row_of(j), c = pos + 64 * i;
+        if (c < nvec) *(bf16x8 *)(panel + (c / 8) * (BM * 128) + r * 128 + ((c % 8) ^ ((r >> 1) & 7)) * 16) = y;
+    };
+    if constexpr (SRC == ROWS_NORM) {
+        // ---- RMSNorm: four steps' factors at once, one in each lane of a quad (a division and a root are some fifty instructions) ----
+        float ss[J], inv[J];
 #pragma unroll
-    for (int j = 0; j < J; j++) {
-        const float one = first_squares(v[j][0]);
-        ss[j] = pos < nvec ? one : 0.0f;
-        if constexpr (VEC == 2) {
-            const float two = more_squares(ss[j], v[j][1]);
-            if (pos + 64 < nvec) ss[j] = two;
+        for (int j = 0; j < J; j++) {
+            const float one = first_squares(v[j][0]);
+            ss[j] = pos < nvec ? one : 0.0f;
+            if constexpr (VEC == 2) {
+                const float two = more_squares(ss[j], v[j][1]);
+                if (pos + 64 < nvec) ss[j] = two;
+            }
         }
-    }
 #pragma unroll
-    for (int j = 0; j < J; j++) ss[j] = V == 0 ? half_wave_sum(ss[j]) : wave_sum(ss[j]);
-    float inv[J];
+        for (int j = 0; j < J; j++) ss[j] = V == 0 ? half_wave_sum(ss[j]) : wave_sum(ss[j]);
 #pragma unroll
-    for (int j = 0; j < J; j += 4) {
-        float mine = ss[j];
-        if constexpr (J >= 2) mine = (lane & 1) ? ss[j + 1] : mine;
-        if constexpr (J >= 4) mine = (lane & 2) ? ((lane & 1) ? ss[j + 3] : ss[j + 2]) : mine;
-        const float f = rms_inv(mine, K, eps);
-        inv[j] = dpp_move<0x00, 0xF>(f, f);  // quad_perm: one lane of the quad to all four
-        if constexpr (J >= 2) inv[j + 1] = dpp_move<0x55, 0xF>(f, f);
-        if constexpr (J >= 4) {
-            inv[j + 2] = dpp_move<0xAA, 0xF>(f, f);
-            inv[j + 3] = dpp_move<0xFF, 0xF>(f, f);
+        for (int j = 0; j < J; j += 4) {
+            float mine = ss[j];
+            if constexpr (J >= 2) mine = (lane & 1) ? ss[j + 1] : mine;
+            if constexpr (J >= 4) mine = (lane & 2) ? ((lane & 1) ? ss[j + 3] : ss[j + 2]) : mine;
+            const float f = rms_inv(mine, K, rows.eps);
+            inv[j] = dpp_move<0x00, 0xF>(f, f);  // quad_perm: one lane of the quad to all four
+            if constexpr (J >= 2) inv[j + 1] = dpp_move<0x55, 0xF>(f, f);
+            if constexpr (J >= 4) {
+                inv[j + 2] = dpp_move<0xAA, 0xF>(f, f);
+                inv[j + 3] = dpp_move<0xFF, 0xF>(f, f);
+            }
         }
-    }
 #pragma unroll
-    for (int j = 0; j < J; j++) {
-        const int r = row_of(j);
+        for (int j = 0; j < J; j++)
 #pragma unroll
-        for (int i = 0; i < VEC; i++) {
-            const int c = pos + 64 * i;
-            bf16x8 y;
+            for (int i = 0; i < VEC; i++) {
+                bf16x8 y;
 #pragma unroll
-            for (int e = 0; e < 8; e++) y[e] = (bf16)((float)g[i][e] * v[j][i][e] * inv[j]);
-            if (c < nvec) *(bf16x8 *)(panel + (c / 8) * (BM * 128) + r * 128 + ((c % 8) ^ ((r >> 1) & 7)) * 16) = y;
-        }
+                for (int e = 0; e < 8; e++) y[e] = (bf16)((float)g[i][e] * v[j][i][e] * inv[j]);
+                put(j, i, y);
+            }
+    } else if constexpr (SRC == ROWS_GATED) {
+#pragma unroll
+        for (int j = 0; j < J; j++)
+#pragma unroll
+            for (int i = 0; i < VEC; i++) {
+                bf16x8 y;
+#pragma unroll
+                for (int e = 0; e < 8; e++) y[e] = (bf16)(v[j][i][e] * u[j][i][e]);
+                put(j, i, y);
+            }
+    } else {
+#pragma unroll
+        for (int j = 0; j < J; j++)
+#pragma unroll
+            for (int i = 0; i < VEC; i++) put(j, i, trunk_attended(q[j][i], k[j][i], w[j][i], tau[j], rows.lanes_per_head));
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -1775,17 +1887,12 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_panel(const float *__restric
     } else {
         mma(f0, false);
     }
-    GemmEpilogue epi = {};
-    epi.C = C;
-    epi.ldc = ldc;
-    epi.bias = bias;
-    float add[16];
     direct_epilogue<KIND>(acc, add, wrow0, wcol0, M, N, epi, lane);
 }
 
-template <int BM, int BN, int V, int J, int KIND>
-static int launch_panel_kind(const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi, hipStream_t st) {
-    auto kern = gemm_bf16_panel<BM, BN, V, J, KIND>;
+template <int BM, int BN, int V, int J, int SRC, int KIND>
+static int launch_panel_kind(const PanelRows &rows, const bf16 *W, int64_t ldw, int64_t M, int N, int K, const GemmEpilogue &epi, hipStream_t st) {
+    auto kern = gemm_bf16_panel<BM, BN, V, J, SRC, KIND>;
     constexpr int KMAX = V == 0 ? 256 : 512 * V;
     auto bytes = [](int k) { return (BM + BN) * k * 2; };
     static_assert(KMAX * (BM + BN) * 2 <= 160 * 1024, "the workgroup's LDS");
@@ -1795,29 +1902,32 @@ static int launch_panel_kind(const bf16 *W, int64_t ldw, int64_t M, int N, int K
         attr_done = true;
     }
     const int64_t tiles_m = ceil_div64(M, BM), tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n;
+    const PanelOut out = {epi.C, epi.ldc, epi.bias, epi.resid, epi.table, epi.tok, epi.ldr};
     {
-        ProfScope ps(KC_GEMM_TILE, st, 2.0 * (double)M * N * K, gemm_bytes(M, N, K, kind_f32(KIND), false) + 2.0 * M * K);
-        hipLaunchKernelGGL(kern, dim3((unsigned)(ceil_div64(total, 8) * 8)), dim3(512), bytes(K), st, epi.pre_x, (const bf16 *)epi.pre_gain, W,
-                           ldw, (int)M, N, K, epi.pre_eps, (int)tiles_m, (int)tiles_n, epi.C, epi.ldc, epi.bias);
+        ProfScope ps(KC_GEMM_TILE, st, 2.0 * (double)M * N * K, gemm_bytes(M, N, K, kind_f32(KIND), KIND == EPI_F32_RESID) + 2.0 * M * K);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(ceil_div64(total, 8) * 8)), dim3(512), bytes(K), st, rows, W, ldw, (int)M, N, K, (int)tiles_m, (int)tiles_n, out);
     }
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
 }
 
 template <int BM, int BN, int V, int J>
-static int launch_panel_cfg(const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi, hipStream_t st) {
-    switch (kind) {
-        case EPI_STORE: return launch_panel_kind<BM, BN, V, J, EPI_STORE>(W, ldw, M, N, K, epi, st);
-        case EPI_SILU_DIV: return launch_panel_kind<BM, BN, V, J, EPI_SILU_DIV>(W, ldw, M, N, K, epi, st);
-        case EPI_F32: return launch_panel_kind<BM, BN, V, J, EPI_F32>(W, ldw, M, N, K, epi, st);
-    }
+static int launch_panel_cfg(int src, const PanelRows &rows, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi, hipStream_t st) {
+#define KIND_(s, k) if (src == s && kind == k) return launch_panel_kind<BM, BN, V, J, s, k>(rows, W, ldw, M, N, K, epi, st)
+    KIND_(ROWS_NORM, EPI_STORE);
+    KIND_(ROWS_NORM, EPI_SILU_DIV);
+    KIND_(ROWS_NORM, EPI_F32);
+    KIND_(ROWS_GATED, EPI_F32_TABLE);
+    if constexpr (J <= 2) KIND_(ROWS_TRUNK, EPI_F32_RESID);
+#undef KIND_
     return GR4AD_EUNSUPPORTED;
 }
 
 // Where the lines lie (us, norm kernel and product / this kernel, calls in a row on weights in turn): K = 256: 64 x 1024 5.4 / 4.2, 512 x 768 5.5 / 4.0 (32x64 tiles, 4.7 on
 // 32x32), 1024 x 1024 6.3 / 5.5 (64x64 tiles, 6.0 on 32x64), 4096 x 256 6.8 / 4.9, 2048 x 1024 7.6 / 7.5 (512 tiles), 4096 x 768 9.1 / 9.9.  K = 512: 64 x 512 5.7 / 4.7,
 // 256 x 2048 6.6 / 6.0 (32x64 tiles, 7.4 on 32x32), 192 x 4096 6.9 / 9.6 (384 tiles), 512 x 1536 on 64x64 tiles 7.0 / 7.3.  K = 1024: 8 x 1024 6.7 / 5.4, but 32 x 1024 6.7 / 6.9:
-// every column of tiles forms the rows anew, 0.85 us of vector arithmetic and 128 KB of x for 32 of them.  Decodes of one request, d = 512, 619 -> 585 us; of 64, d = 256, 577 -> 548.
+// every column of tiles forms the rows anew, 0.85 us of vector arithmetic and 128 KB of x for 32 of them.  Decodes of one request, d = 512, 619 -> 585 us; of 64, d = 256, 577 -> 548; gates and
+// the trunk's attention as well 551 -> 544 and 524 -> 515.
 enum { PANEL_NONE = 0, PANEL_32, PANEL_32X64, PANEL_64, PANEL_FEW };  // few: at most 16 rows of 32x32 tiles
 static int panel_shape(int64_t M, int N, int K) {
     if (K > 1024) return PANEL_NONE;
@@ -1829,8 +1939,8 @@ static int panel_shape(int64_t M, int N, int K) {
     return K <= 256 && tiles(64, 64) <= 384 ? PANEL_64 : PANEL_NONE;
 }
 
-static int launch_panel(int shape, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi, hipStream_t st) {
-#define PANEL_(bm, bn, v, j) return launch_panel_cfg<bm, bn, v, j>(W, ldw, M, N, K, kind, epi, st)
+static int launch_panel(int shape, int src, const PanelRows &rows, const bf16 *W, int64_t ldw, int64_t M, int N, int K, int kind, const GemmEpilogue &epi, hipStream_t st) {
+#define PANEL_(bm, bn, v, j) return launch_panel_cfg<bm, bn, v, j>(src, rows, W, ldw, M, N, K, kind, epi, st)
     if (shape == PANEL_FEW) {
         if (K <= 256) PANEL_(32, 32, 0, 1);
         if (M <= 8) {
@@ -1975,7 +2085,11 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
         const int kd = kind == EPI_SILU ? EPI_SILU_DIV : kind;
         if (M < 8192 && !epi.skip_len && mfma_ok(dtype, A, lda, W, ldw, K, kind) && ((uintptr_t)epi.pre_x % 16) == 0 && ((uintptr_t)epi.pre_gain % 16) == 0) {
             const int shape = panel_shape(M, N, K);
-            if (shape != PANEL_NONE) return launch_panel(shape, (const bf16 *)W, ldw, M, N, K, kd, epi, st);
+            PanelRows rows = {};
+            rows.x = epi.pre_x;
+            rows.gain = (const bf16 *)epi.pre_gain;
+            rows.eps = epi.pre_eps;
+            if (shape != PANEL_NONE) return launch_panel(shape, ROWS_NORM, rows, (const bf16 *)W, ldw, M, N, K, kd, epi, st);
         }
         const int s = launch_rmsnorm(dtype, epi.pre_x, epi.pre_gain, (void *)A, M, K, epi.pre_eps, st, epi.skip_len && !epi.skip_S ? epi.skip_len : nullptr);
         if (s) return s;
@@ -2004,4 +2118,44 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
         hipLaunchKernelGGL(gemm_simple<float>, grid, dim3(256), 0, st, (const float *)A, lda, (const float *)W, ldw, M, N, K, epi);
     GR4AD_LAUNCH_CHECK();
     return GR4AD_OK;
+}
+
+// A = the gated rows of Fuse (launch_fuse_gate), formed by the product where it has few tiles, else by a launch of their own into `gated`
+int launch_gemm_gated(gr4ad_dtype dtype, const float *m, int64_t m_req_stride, const float *G, int64_t table_rows, const int32_t *tok, void *gated, int B, int n, const void *W, int N,
+                      int d, const GemmEpilogue &epi, hipStream_t st) {
+    const int64_t M = (int64_t)B * n;
+    const int kind = epilogue_kind(epi);
+    if (M < 8192 && kind == EPI_F32_TABLE && !epi.skip_len && !epi.norm_out && mfma_ok(dtype, gated, d, W, d, d, kind) && ((uintptr_t)m % 16) == 0 && m_req_stride % 4 == 0 && ((uintptr_t)G % 16) == 0) {
+        const int shape = panel_shape(M, N, d);
+        if (shape != PANEL_NONE) {
+            PanelRows rows = {};
+            rows.x = m;
+            rows.x_req = m_req_stride;
+            rows.table = G;
+            rows.tok = tok;
+            rows.n = n;
+            return launch_panel(shape, ROWS_GATED, rows, (const bf16 *)W, d, M, N, d, kind, epi, st);
+        }
+    }
+    const int s = launch_fuse_gate(dtype, m, m_req_stride, G, table_rows, tok, gated, B, n, d, st);
+    return s ? s : launch_gemm(dtype, gated, d, W, d, M, N, d, epi, st);
+}
+
+// A = the trunk's self-attention over qkv [B*T, 3d] (launch_trunk_self_attention), formed by the product where it has few rows, else by a launch of its own into `o`
+int launch_gemm_trunk_attended(gr4ad_dtype dtype, const void *qkv, void *o, int B, int T, int H, const void *W, int N, int d, const GemmEpilogue &epi, hipStream_t st) {
+    const int64_t M = (int64_t)B * T;
+    const int kind = epilogue_kind(epi), dh = d / H;
+    // (up to four positions and head widths 16, 32 and 64; a wavefront holds nine pieces of a row in registers, so two rows of at most 512 columns or one of 1024)
+    if (M < 8192 && kind == EPI_F32_RESID && T <= 4 && (dh == 16 || dh == 32 || dh == 64) && !epi.norm_out && mfma_ok(dtype, o, d, W, d, d, kind) && ((uintptr_t)qkv % 16) == 0) {
+        const int shape = panel_shape(M, N, d);
+        if ((shape == PANEL_FEW && (M <= 8 || d <= 512)) || (d <= 256 && (shape == PANEL_32 || shape == PANEL_32X64))) {
+            PanelRows rows = {};
+            rows.qkv = (const bf16 *)qkv;
+            rows.n = T;
+            rows.lanes_per_head = dh / 8;
+            return launch_panel(shape, ROWS_TRUNK, rows, (const bf16 *)W, d, M, N, d, kind, epi, st);
+        }
+    }
+    const int s = launch_trunk_self_attention(dtype, qkv, o, B, T, d, H, st);
+    return s ? s : launch_gemm(dtype, o, d, W, d, M, N, d, epi, st);
 }

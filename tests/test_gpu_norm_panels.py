@@ -1,4 +1,5 @@
-"""Products that normalise their own rows (at most 1024 columns, few tiles): the same bits as the norm kernel and the product of its own that many rows take."""
+"""Products that form their own rows - norms, gated rows, the trunk's self-attention - (at most 1024 columns, few tiles): the same bits as the kernels of their own that many
+rows take."""
 import pytest
 import torch
 
@@ -9,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 # d: one k-tile, less than the 256 columns that two rows share a wavefront for, as many, more, as many as 512, more (where 16 rows are the most), as many as 1024.
 # n: the rows of one wavefront step, one more, two steps, one more, a second tile of 32 rows
-@pytest.mark.parametrize("d,H", [(64, 1), (192, 3), (256, 8), (320, 5), (512, 8), (576, 9), (1024, 16)])
+@pytest.mark.parametrize("d,H", [(64, 1), (128, 8), (192, 3), (256, 8), (320, 5), (512, 8), (576, 9), (1024, 16)])
 @pytest.mark.parametrize("n", [8, 9, 16, 17, 33])
 def test_requests_do_not_depend_on_their_batch(d, H, n):
     B = 1200 // n  # (enough rows that the first FFN product, 2048 columns, runs behind the norm kernel)
