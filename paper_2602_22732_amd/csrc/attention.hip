@@ -46,7 +46,10 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
     int len = ctx_len ? ctx_len[b] : S;
     len = len < 1 ? 1 : (len > S ? S : len);
     const float scale = 1.0f / sqrtf((float)dh);
-    for (int c = lane; c < dh; c += 64) sq[wv][c] = to_f(q[(row - b * (n - q_stride)) * ldq + h * dh + c]) * scale;
+    const T *qr = q + (row - b * (n - q_stride)) * ldq + h * dh;
+    const float q0 = AHEAD && lane < dh ? to_f(qr[lane]) : 0.0f;  // (put down once the first tile's loads are on their way)
+    if (!AHEAD)
+        for (int c = lane; c < dh; c += 64) sq[wv][c] = to_f(qr[c]) * scale;
     const T *kbase = kv + b * (int64_t)S * 2 * d + h * dh;  // key j at kbase + j*2d, value at + d
     constexpr int E = 16 / sizeof(T), U = 32 / E;           // values of a 16-byte load; loads of 32 columns
     const bool vec = ((uintptr_t)kbase % 16) == 0 && (2 * d) % E == 0 && dh % E == 0;
@@ -71,6 +74,8 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
 #pragma unroll
                 for (int u = 0; u < U; u++) raw[u] = *(const uint4 *)(kr + (u * E < dh ? u * E : 0));
                 load_values(0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (j0 == 0) sq[wv][lane] = q0 * scale;
 #pragma unroll
                 for (int u = 0; u < U; u++)
 #pragma unroll
@@ -84,7 +89,10 @@ __global__ __launch_bounds__(256) void cross_attn_simple(const T *__restrict__ q
                 for (int e = 0; e < E; e++) s = fmaf(sq[wv][c + e], to_f(((const T *)&more)[e]), s);
             }
         } else if (AHEAD || j < len) {
-            if constexpr (AHEAD) load_values(0);
+            if constexpr (AHEAD) {
+                load_values(0);
+                if (j0 == 0) sq[wv][lane] = q0 * scale;
+            }
             for (int c = 0; c < dh; c++) s = fmaf(sq[wv][c], to_f(kr[c]), s);
         }
         if (j >= len) s = -INFINITY;

@@ -209,10 +209,10 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma(const float *__restrict__ A
                     ss[q] += sum_sq4(v[0], v[1], v[2], v[3]);
                 }
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                ss[q] = wave_sum_dpp(ss[q]);
-                if (lane == 0) rinv[wave + 4 * q] = 1.0f / sqrtf(ss[q] / (float)K + epi.pre_eps);
-            }
+            for (int q = 0; q < 4; q++) ss[q] = wave_sum_dpp(ss[q]);
+            const float mine = (lane & 2) ? ((lane & 1) ? ss[3] : ss[2]) : (lane & 1) ? ss[1] : ss[0];  // (one root and two divisions for the four rows)
+            const float inv = rms_inv(mine, K, epi.pre_eps);
+            if (lane < 4) rinv[wave + 4 * lane] = inv;
             __syncthreads();
             scale(x, b0, b0 + per < nb ? b0 + per : nb);
         }
