@@ -772,10 +772,13 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
 }
 
 // The bounded pass.  A row stays in registers as it was read (raw[g]: tokens (g*64 + lane)*E .. +E-1; pieces past V hold -inf): maximum,
-// log-sum-exp and the sweep for candidates at or above the request's bound read it in place.  Wavefronts walk the rows with the launch's
+// log-sum-exp and the sweep for candidates at or above the request's bound read it in place.  Bound by the memory's latency: a wavefront's row is loaded at once
+// and worked on when it is there, so what keeps the memory busy is the other wavefronts of the SIMD.  (A half-precision row used to be requested while the one before it was
+// worked on, in as many registers again: 95 instead of 71 for rows of 4096 tokens, 168 instead of 109 for 8192, five and three wavefronts instead of seven and
+// four, and the last row of each wavefront was requested twice.  65536 rows of 4096 tokens 157 us, 140 without; 32768 of 8192 150 and 127; 262144 of 8192 912 and 856; a million
+// 3.51 and 3.34 ms, whole selections.)  Wavefronts walk the rows with the launch's
 // stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
-// candidates, were 15 % slower); half-precision rows are half the registers, so a wavefront asks for its next row before it works
-// on the current one and the memory latency hides behind the arithmetic.  A row with more than m candidates at the bound reserves m slots and is
+// candidates, were 15 % slower).  A row with more than m candidates at the bound reserves m slots and is
 // put on the list for select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
 template <int VEC, bool FULL, typename LT>
 __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void select_rows_sweep(
@@ -785,7 +788,7 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
     constexpr int NX = VEC * 4, E = LogitPiece<LT>::E, G = NX / E;
     extern __shared__ unsigned long long wave_lds[];  // per wavefront: m slots of staged output
     // The row index is made a scalar of the wavefront (rows < 2^31, checked by the host): its cumulative score and bound then
-    // come through scalar loads, which do not queue behind the vector loads of the next row.
+    // come through scalar loads, which do not queue behind the vector loads of a row.
     const int lane = threadIdx.x % 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     const uint32_t nwaves = gridDim.x * 4u;
     uint32_t row = blockIdx.x * 4u + (uint32_t)wv;
@@ -800,8 +803,8 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
                                : make_uint4(0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u);
         }
     };
-    // per row: request, beam, cumulative score and this lane's slot of the request's bound, fetched one row ahead like the logits
-    // (the slot by a vector load, so before them: loads return in order)
+    // per row: request, beam, cumulative score and this lane's slot of the request's bound, fetched one row ahead
+    // (the slot by a vector load, so before the row's: loads return in order)
     auto row_scalars = [&](uint32_t r, uint32_t &req, uint32_t &beam, float &c, float &rbv) {
         req = r / (uint32_t)n;
         beam = r % (uint32_t)n;
@@ -822,13 +825,9 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         const uint64_t next = (uint64_t)row + nwaves;
         const bool more = next < (uint64_t)rows;
         const uint32_t ahead = more ? (uint32_t)next : row;
-        uint4 nxt[HALF ? G : 1];
-        // (half precision: unconditional - the last row is asked for twice: a branch here would make the compiler wait for these loads at the
-        // first use of the current row, as if they had been skipped)
         uint32_t req_n, beam_n;
         float c_n, rbv_n;
         row_scalars(ahead, req_n, beam_n, c_n, rbv_n);
-        if constexpr (HALF) request_row(ahead, nxt);
         __builtin_amdgcn_sched_barrier(0);  // the loads go out here, not where the instruction scheduler finds the registers cheapest
 
         typename std::conditional<HALF, halfx2, float>::type pmax[G];  // per piece: the maximum (half precision: of its even and of its odd tokens)
@@ -919,12 +918,7 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         }
         if (!more) break;
         row = (uint32_t)next;
-        if constexpr (HALF) {
-#pragma unroll
-            for (int g = 0; g < G; g++) raw[g] = nxt[g];
-        } else {
-            request_row(row, raw);
-        }
+        request_row(row, raw);
         req = req_n; beam = beam_n; c = c_n; rbv = rbv_n;
     }
 }
@@ -1480,9 +1474,9 @@ static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
     const int n_cu = compute_units();
     if (!n_cu) return GR4AD_EHIP;
     const size_t lds = 4 * (size_t)a.m * sizeof(unsigned long long);
-    // Up to eight rows per wavefront, but 64 wavefronts per compute unit come first.  Measured at a million rows of 8192 halves: 3.6 ms,
-    // 4.3 ms with 128 rows per wavefront, 3.8 ms with one; at 16384 rows of 4096: 35 us with one row per wavefront, 44 with four.
-    int64_t rows_per = rows / ((int64_t)n_cu * 64);
+    // Half precision: one row per wavefront (whole selections, one and two rows: 65536 rows of 4096 tokens 140 us and 142, 32768 of 8192 127 and 135, 262144 of 8192 856
+    // and 847, four rows 873).  Float32: up to eight, but 64 wavefronts per compute unit come first.
+    int64_t rows_per = sizeof(LT) == 2 ? 1 : rows / ((int64_t)n_cu * 64);
     rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
     const int64_t grid = ceil_div64(ceil_div64(rows, rows_per), 4);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows,
