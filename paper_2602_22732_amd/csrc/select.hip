@@ -649,7 +649,9 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
         T = __shfl(selT, src_lane, 64);
         krem = __shfl(selK, src_lane, 64);
         cntT = __shfl(selC, src_lane, 64);
-        if (!AGAIN || cntT <= WROW_FEW) break;
+        // (hi not below +inf: some score may be NaN - a NaN logit or log-sum-exp, a cumulative score of +inf over masked tokens - which the minima and maxima
+        // below pass over, so equal extremes would not mean equal scores.  With hi below +inf all scores are numbers or -inf.)
+        if (!AGAIN || cntT <= WROW_FEW || !(hi < INFINITY)) break;
         // Crowded (masked tokens, or low finite masks that press the other scores into a few bins): equal scores go by their tokens, others take another
         // histogram over the span of this bin's alone
         float lo_t = INFINITY, hi_t = -INFINITY, least = INFINITY;  // least: that is not -inf

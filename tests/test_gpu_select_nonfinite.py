@@ -99,3 +99,37 @@ def test_request_of_nan_contexts_leaves_the_others_alone(dtype, B, d):
     assert (sid >= 0).all() and (sid < V).all()
     assert len(torch.unique(sid[2].cpu(), dim=0)) == w.beam[-1]
     dec.close()
+
+
+# live: tokens that are not masked, fewer and more than k.  Rows that get their own cut because the bound lists them (3 rows per request) and without a bound (9 rows; one row in
+# many requests)
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("V,live", [(72, 5), (72, 66), (256, 10), (256, 200), (1024, 12), (1024, 700), (2048, 20), (2048, 1024)])
+@pytest.mark.parametrize("B,n,k", [(4, 3, 16), (5, 9, 32), (520, 1, 16)])
+def test_select_of_infinite_cumulative_score_over_masked_tokens(B, n, k, V, live, half):
+    """Every second request has a row whose cumulative score is +inf: its live tokens score +inf, its masked ones NaN.  The requests between them come out as they do
+    beside numbers (rows share workgroups and their LDS)."""
+    rng = np.random.default_rng([B, n, V, k, live, half])
+    logits = rng.standard_normal((B, n, V)).astype(np.float16 if half else np.float32)
+    logits.reshape(B * n, V)[np.arange(B * n)[:, None], np.argsort(rng.random((B * n, V)), axis=1)[:, live:]] = -np.inf
+    cum = -6.0 * rng.random((B, n)).astype(np.float32)
+    z = torch.from_numpy(logits).cuda()
+    plain = [t.cpu().numpy() for t in binding.op_select(z, torch.from_numpy(cum).cuda(), k)]
+    cum[::2, n // 2] = np.inf
+    print("B n V k live", B, n, V, k, live, "half", half, flush=True)
+    got = [t.cpu().numpy() for t in binding.op_select(z, torch.from_numpy(cum).cuda(), k)]
+    for g, p in zip(got, plain):
+        assert np.array_equal(g[1::2], p[1::2])
+    for b in range(0, B, 2):
+        flat, score = got[0][b].astype(np.int64) * V + got[1][b], got[2][b]
+        assert len(np.unique(flat)) == k and flat.min() >= 0 and flat.max() < n * V
+        with np.errstate(invalid="ignore"):
+            want = cum[b].astype(np.float64)[:, None] + np.stack([oracle.prim_log_softmax(z) for z in logits[b].astype(np.float32)])
+        want = want.ravel()
+        parts = [np.flatnonzero(w) for w in (want == np.inf, np.isfinite(want), want == -np.inf, np.isnan(want))]  # (in the order of their ranks)
+        at = np.cumsum([0] + [len(p) for p in parts]).clip(max=k)
+        for part, lo, hi in zip(parts, at[:-1], at[1:]):
+            if part is parts[1] and hi > lo:
+                judge_selection(np.where(np.isfinite(want), want, -1e30).reshape(n, V), flat[lo:hi], score[lo:hi], hi - lo, tol=3e-5, margin=2e-5, what="request %d" % b)
+            else:  # equal scores go by their tokens
+                assert np.array_equal(flat[lo:hi], part[:hi - lo]) and np.array_equal(score[lo:hi], want[part[:hi - lo]].astype(np.float32), equal_nan=True)
