@@ -672,9 +672,10 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
         tied = lo_t == hi_t;
         tie = hi_t;
         if (tied || zoom == 3 || !(hi_t >= least)) break;
-        inv_w = hi_t > least ? (float)(WROW_BINS - 3) / (hi_t - least) : 1.0f;
+        const float finer = hi_t > least ? (float)(WROW_BINS - 3) / (hi_t - least) : 1.0f;
+        if (!(finer < INFINITY)) break;  // (T, krem and cntT stand for the bins of inv_w and k0)
+        inv_w = finer;
         k0 = 1.5f - least * inv_w;  // (-inf alone in bin 0)
-        if (!(inv_w < INFINITY)) break;
     }
     if (tied || cntT > WROW_LIST) {  // ties, or exact radix selection
         float sc[NX];  // a copy, so that only this branch keeps the scores in addressable memory
