@@ -99,6 +99,16 @@ __device__ __forceinline__ float block_sum_256(float v, RowShared &sh, int slot)
 // score of NaN or +inf.  NaN passes no comparison, so such a row takes no part in the bounded pass; see select_rows_wave.
 __device__ __forceinline__ bool row_is_numbers(float c, float lse) { return fabsf(lse) < INFINITY && c < INFINITY; }
 
+// The sum whose NaN is a's where both are NaN.  Candidates rank by the bits of their scores, a NaN above or below all numbers by its sign, and a row's cumulative score and its
+// log-softmax may be NaN of either sign: kernels that promise each other the same bits cannot leave the order to the compiler.
+__device__ __forceinline__ float sum_a_first(float a, float b) {
+    float r;
+    asm("v_add_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+// Score of a token in the wavefront kernels: NaN of the log-softmax first for rows of up to 2048 tokens, of the cumulative score for longer ones
+template <bool SHORT> __device__ __forceinline__ float wave_score(float c, float log_p) { return SHORT ? sum_a_first(log_p, c) : sum_a_first(c, log_p); }
+
 __device__ __forceinline__ unsigned long long pack_candidate(float score, uint32_t flat) {
     return ((unsigned long long)score_key(score) << 32) | (0xFFFFFFFFu - flat);
 }
@@ -233,7 +243,7 @@ __global__ __launch_bounds__(256) void select_rows(const float *__restrict__ log
     for (int j = 0; j < ITEMS; j++) sum += __expf(x[j] - mx);  // exp(-inf) = 0 for the padding
     const float lse = mx + __logf(block_sum_256(sum, sh, 2));
 #pragma unroll
-    for (int j = 0; j < ITEMS; j++) x[j] = c + (x[j] - lse);  // scores from here on (padding stays -inf)
+    for (int j = 0; j < ITEMS; j++) x[j] = sum_a_first(c, x[j] - lse);  // scores from here on (padding stays -inf)
 
     unsigned long long *dst = cand + row * (int64_t)m;
     const uint32_t flat0 = (uint32_t)((row % n) * (int64_t)V);
@@ -597,7 +607,7 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
     float mn = INFINITY;
 #pragma unroll
     for (int i = 0; i < NX; i++) {
-        x[i] = c + (x[i] - lse);
+        x[i] = wave_score<AGAIN>(c, x[i] - lse);
         mn = fminf(mn, ((FULL || wave_tok<E>(i, lane) < V) && (!AGAIN || x[i] > -INFINITY)) ? x[i] : INFINITY);
     }
     if (m >= V) {  // nothing to cut: every token is a candidate
@@ -1369,7 +1379,8 @@ __global__ __launch_bounds__(SELB_THREADS) void select_single(const LT *__restri
     uint32_t hi = 0u, lo = 0xFFFFFFFFu;
 #pragma unroll
     for (int i = 0; i < PER; i++) {
-        key[i] = token(i) < V ? pack_candidate(c + (x[i] - lse), (uint32_t)token(i)) : 0ull;
+        const float log_p = x[i] - lse, first = sum_a_first(c, log_p);
+        key[i] = token(i) < V ? pack_candidate(ORDER_WAVE && V <= 2048 ? wave_score<true>(c, log_p) : first, (uint32_t)token(i)) : 0ull;
         if (i == 0 && key[i]) hi = lo = (uint32_t)(key[i] >> 32);
     }
     int kp = 1;

@@ -45,3 +45,22 @@ def test_short_selections(B, n, V, k, kind):
         if kind in ("masked", "tied"):  # equal scores go by the lowest (row, token)
             eq = np.flatnonzero(score[b][1:] == score[b][:-1])
             assert (flat[eq + 1] > flat[eq]).all()
+
+
+# up to 512 (rows of a multiple of 4 tokens, at most 8192) or 256 requests of one row run in one launch, more in two.  nan: a cumulative score and some logits, NaN of either sign
+@pytest.mark.parametrize("V,k,most,half", [(V, k, 512, half) for V, k in ((72, 16), (264, 264), (1032, 300), (2048, 64), (2056, 64), (8192, 700)) for half in (False, True)]
+                         + [(301, 16, 256, False), (1030, 600, 256, False), (16384, 200, 256, False)])
+@pytest.mark.parametrize("kind", ["plain", "masked", "tied", "nan"])
+def test_one_launch_selects_what_two_do(V, k, most, kind, half):
+    g = torch.Generator().manual_seed(V + k)
+    z, cum = logits(kind, 4, 1, V, g), -torch.rand(4, 1, generator=g)
+    if kind == "nan":  # (one sign to a row)
+        z[0, 0, V // 2] = float("nan")
+        z[1, 0, 3] = z[1, 0, V - 2] = -float("nan")
+        z[3, 0, 5] = -float("nan")
+        cum[:3, 0] = torch.tensor([float("nan"), -float("nan"), float("nan")])
+    z, cum = z.cuda().to(torch.float16 if half else torch.float32), cum.cuda()
+    one = binding.op_select(z, cum, k)
+    two = binding.op_select(z.repeat(most // 4 + 1, 1, 1), cum.repeat(most // 4 + 1, 1), k)
+    for a, b in zip(one, two):
+        assert torch.equal(a.view(torch.int32), b[-4:].view(torch.int32))
