@@ -789,11 +789,11 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
 // and worked on when it is there, so what keeps the memory busy is the other wavefronts of the SIMD.  (A half-precision row used to be requested while the one before it was
 // worked on, in as many registers again: 95 instead of 71 for rows of 4096 tokens, 168 instead of 109 for 8192, five and three wavefronts instead of seven and
 // four, and the last row of each wavefront was requested twice.  65536 rows of 4096 tokens 157 us, 140 without; 32768 of 8192 150 and 127; 262144 of 8192 912 and 856; a million
-// 3.51 and 3.34 ms, whole selections.)  Wavefronts walk the rows with the launch's
+// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows of fewer than 2048 tokens: see launch_rows_sweep_kind.)  Wavefronts walk the rows with the launch's
 // stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
 // candidates, were 15 % slower).  A row with more than m candidates at the bound reserves m slots and is
 // put on the list for select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
-template <int VEC, bool FULL, typename LT>
+template <int VEC, bool FULL, bool AHEAD, typename LT>
 __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void select_rows_sweep(
     const LT *__restrict__ logits, const float *__restrict__ cum, int64_t rows, int n, int V, int m, unsigned long long *__restrict__ cand,
     const float *__restrict__ rb, int R, int *__restrict__ req_count, int count_pitch, int2 *__restrict__ todo, int *__restrict__ todo_count) {
@@ -838,9 +838,13 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         const uint64_t next = (uint64_t)row + nwaves;
         const bool more = next < (uint64_t)rows;
         const uint32_t ahead = more ? (uint32_t)next : row;
+        uint4 nxt[AHEAD ? G : 1];
         uint32_t req_n, beam_n;
         float c_n, rbv_n;
         row_scalars(ahead, req_n, beam_n, c_n, rbv_n);
+        // (unconditional - the last row is asked for twice: a branch here would make the compiler wait for these loads at the first use of the current
+        // row, as if they had been skipped)
+        if constexpr (AHEAD) request_row(ahead, nxt);
         __builtin_amdgcn_sched_barrier(0);  // the loads go out here, not where the instruction scheduler finds the registers cheapest
 
         typename std::conditional<HALF, halfx2, float>::type pmax[G];  // per piece: the maximum (half precision: of its even and of its odd tokens)
@@ -931,7 +935,12 @@ __global__ __launch_bounds__(256, VEC >= 32 ? 2 : (VEC >= 16 ? 3 : 4)) void sele
         }
         if (!more) break;
         row = (uint32_t)next;
-        request_row(row, raw);
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int g = 0; g < G; g++) raw[g] = nxt[g];
+        } else {
+            request_row(row, raw);
+        }
         req = req_n; beam = beam_n; c = c_n; rbv = rbv_n;
     }
 }
@@ -1477,25 +1486,38 @@ static int launch_rows_wave_kind(const RowsLaunch &a, int64_t rows, int mode) {
     return launch_rows_wave_as<VEC, FULL, false, LT>(a, rows, mode);
 }
 // mode 2: the bounded pass, which lists the rows that need their own cut
-template <int VEC, bool FULL, typename LT>
-static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
-    auto kern = select_rows_sweep<VEC, FULL, LT>;
+template <int VEC, bool FULL, bool AHEAD, typename LT>
+static int launch_rows_sweep_as(const RowsLaunch &a, int64_t rows, int64_t rows_per) {
+    auto kern = select_rows_sweep<VEC, FULL, AHEAD, LT>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * GR4AD_MAX_BEAM * 8) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
-    const int n_cu = compute_units();
-    if (!n_cu) return GR4AD_EHIP;
     const size_t lds = 4 * (size_t)a.m * sizeof(unsigned long long);
-    // Half precision: one row per wavefront (whole selections, one and two rows: 65536 rows of 4096 tokens 140 us and 142, 32768 of 8192 127 and 135, 262144 of 8192 856
-    // and 847, four rows 873).  Float32: up to eight, but 64 wavefronts per compute unit come first.
-    int64_t rows_per = sizeof(LT) == 2 ? 1 : rows / ((int64_t)n_cu * 64);
-    rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
     const int64_t grid = ceil_div64(ceil_div64(rows, rows_per), 4);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, a.st, (const LT *)a.logits, a.cum, rows,
                        a.n, a.V, a.m, a.cand, (const float *)a.rb, a.R, a.req_count, a.count_pitch, a.todo, a.todo_count);
     return GR4AD_OK;
+}
+// Float32: up to eight rows per wavefront, but 64 wavefronts per compute unit come first.  Half precision: one row per wavefront (whole selections, one and two rows: 65536 rows of
+// 4096 tokens 140 us and 142, 32768 of 8192 127 and 135, 262144 of 8192 856 and 847, four rows 873), except that many rows of fewer than 2048 tokens are walked so too, each requested
+// while the one before it is worked on: they are the shorter wait, and what a wavefront costs to start and to end counts.  One row / several with a row ahead, in us: 262144 rows of
+// 264 tokens 202.6 / 190.2, of 520 221.4 / 205.0, of 1024 222.9 / 216.5, of 1536 308.1 / 298.6, of 2040 344.7 / 326.0, but of 2048 264 / 272; 128000 rows of 264 106.5 / 97.5, of
+// 1024 117.4 / 108.0, of 1536 157.7 / 144.8; 131072 of 1024 116.8 / 118.3, of 2040 178.8 / 177.9; 81920 of 1024 83.9 / 85.3, of 1536 106.9 / 109.5; 32768 of 264 41.0 / 40.3.  (Where
+// no cache holds the logits: 262144 rows of 520 225.3 / 207.0, 128000 of 1024 119.8 / 110.8.)
+template <int VEC, bool FULL, typename LT>
+static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
+    const int n_cu = compute_units();
+    if (!n_cu) return GR4AD_EHIP;
+    int64_t rows_per = rows / ((int64_t)n_cu * 64);
+    rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
+    if constexpr (sizeof(LT) == 2) {
+        if constexpr (VEC == 4 || (VEC == 8 && !FULL))
+            if (rows_per >= (VEC == 4 && !FULL ? 2 : 6)) return launch_rows_sweep_as<VEC, FULL, true, LT>(a, rows, rows_per);
+        rows_per = 1;
+    }
+    return launch_rows_sweep_as<VEC, FULL, false, LT>(a, rows, rows_per);
 }
 // the request bounds: R rows of every request
 template <int ITEMS>

@@ -64,3 +64,19 @@ def test_one_launch_selects_what_two_do(V, k, most, kind, half):
     two = binding.op_select(z.repeat(most // 4 + 1, 1, 1), cum.repeat(most // 4 + 1, 1), k)
     for a, b in zip(one, two):
         assert torch.equal(a.view(torch.int32), b[-4:].view(torch.int32))
+
+
+# half-precision rows walked several to a wavefront, the next one requested ahead (fewer than 1024 tokens from 32768 rows on, fewer than 2048 from 98304): rows that do not fill the last workgroup,
+# two, six and eight to a wavefront, pieces that no or half of the lanes have
+@pytest.mark.parametrize("B,n,V,k", [(331, 101, 264, 150), (1300, 102, 72, 64), (760, 130, 1024, 200), (1027, 129, 1032, 140), (1025, 129, 2040, 130)])
+def test_many_short_rows_as_few(B, n, V, k):
+    g = torch.Generator(device="cuda").manual_seed(V)
+    z = torch.randn(B, n, V, generator=g, device="cuda", dtype=torch.float16)
+    z[:, 1::2, : V // 2] = -float("inf")
+    z[1::3, n - 1] = float("nan")
+    cum = -torch.sort(torch.rand(B, n, generator=g, device="cuda") * 6 + 3, dim=1).values
+    many = binding.op_select(z, cum, k)
+    for lo in (0, B // 2, B - 8):
+        few = binding.op_select(z[lo:lo + 8], cum[lo:lo + 8], k)
+        for a, b in zip(few, many):
+            assert torch.equal(a.view(torch.int32), b[lo:lo + 8].view(torch.int32))
