@@ -1028,6 +1028,9 @@ __global__ __launch_bounds__(512) void context_sums(const bf16 *__restrict__ x, 
             };
             auto multiply = [&](Fragments &f, int tt, bool behind) {
                 __builtin_amdgcn_sched_barrier(0);
+                if (behind) asm volatile("s_waitcnt lgkmcnt(6)" ::: "memory");  // (before the copies that the next lines' operands may take)
+                else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
                 if (behind) asm volatile("s_waitcnt lgkmcnt(6)" : "+v"(f.w[0][0]), "+v"(f.w[0][1]), "+v"(f.w[1][0]), "+v"(f.w[1][1]), "+v"(f.p[0]), "+v"(f.p[1]));
                 else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.w[0][0]), "+v"(f.w[0][1]), "+v"(f.w[1][0]), "+v"(f.w[1][1]), "+v"(f.p[0]), "+v"(f.p[1]));
                 __builtin_amdgcn_sched_barrier(0);
