@@ -2083,7 +2083,8 @@ int launch_gemm(gr4ad_dtype dtype, const void *A, int64_t lda, const void *W, in
         if (dtype == GR4AD_F32 && !f32_big_tiles(M, N) && f32_mfma_ok(epi.pre_x, lda, W, ldw, K) && ((uintptr_t)epi.pre_gain % 16) == 0)
             return launch_f32(epi.pre_x, lda, (const float *)W, ldw, M, N, K, epi, st);
         const int kd = kind == EPI_SILU ? EPI_SILU_DIV : kind;
-        if (M < 8192 && !epi.skip_len && mfma_ok(dtype, A, lda, W, ldw, K, kind) && ((uintptr_t)epi.pre_x % 16) == 0 && ((uintptr_t)epi.pre_gain % 16) == 0) {
+        if (M < 8192 && !epi.skip_len && (kd == EPI_STORE || kd == EPI_SILU_DIV || kd == EPI_F32) && mfma_ok(dtype, A, lda, W, ldw, K, kind) && ((uintptr_t)epi.pre_x % 16) == 0 &&
+            ((uintptr_t)epi.pre_gain % 16) == 0) {  // (the epilogues that launch_panel_cfg has behind a norm)
             const int shape = panel_shape(M, N, K);
             PanelRows rows = {};
             rows.x = epi.pre_x;
