@@ -1918,7 +1918,7 @@ static int launch_panel_cfg(int src, const PanelRows &rows, const bf16 *W, int64
     KIND_(ROWS_NORM, EPI_SILU_DIV);
     KIND_(ROWS_NORM, EPI_F32);
     KIND_(ROWS_GATED, EPI_F32_TABLE);
-    if constexpr (J <= 2) KIND_(ROWS_TRUNK, EPI_F32_RESID);
+    if constexpr (J * (V == 2 ? 2 : 1) <= 2) KIND_(ROWS_TRUNK, EPI_F32_RESID);  // (two pieces of a row to a lane: see launch_gemm_trunk_attended)
 #undef KIND_
     return GR4AD_EUNSUPPORTED;
 }
