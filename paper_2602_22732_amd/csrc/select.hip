@@ -789,7 +789,8 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
 // and worked on when it is there, so what keeps the memory busy is the other wavefronts of the SIMD.  (A half-precision row used to be requested while the one before it was
 // worked on, in as many registers again: 95 instead of 71 for rows of 4096 tokens, 168 instead of 109 for 8192, five and three wavefronts instead of seven and
 // four, and the last row of each wavefront was requested twice.  65536 rows of 4096 tokens 157 us, 140 without; 32768 of 8192 150 and 127; 262144 of 8192 912 and 856; a million
-// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows of fewer than 2048 tokens: see launch_rows_sweep_kind.)  Wavefronts walk the rows with the launch's
+// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows of fewer than 2048 tokens: see launch_rows_sweep_kind.  Those are selections one after the other; one alone behind 600 MB
+// of writes elsewhere, a row ahead and without: 64 x 256 rows of 4096 76.9 us and 80.4, of 8192 132.4 and 134.6, 256 x 256 of 4096 208.9 and 198.1, 64 x 512 of 8192 197.3 and 187.9.)  Wavefronts walk the rows with the launch's
 // stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
 // candidates, were 15 % slower).  A row with more than m candidates at the bound reserves m slots and is
 // put on the list for select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
@@ -1579,7 +1580,8 @@ size_t select_workspace_bytes(int B, int n, int V, int k) { return select_plan(B
 // Few short rows are faster cut one by one (one launch of wavefronts that each take a row, then the request's sort over all n * m keys, which it holds up to 8192) than
 // bounded, swept and listed in three launches.  Whole selections in us, bounded / row by row: 4 requests of 16 rows of 256 tokens, k = 16 16.8 / 11.6; 64 of 64 rows of 1024,
 // k = 64 (4096 rows) 21.2 / 16.9, 64 of 128 rows, k = 32 (8192 rows) 21.7 / 21.3; of 2048 tokens 16 of 128 rows, k = 32 (2048 rows) 18.8 / 16.0, 64 of 64 rows, k = 64 24.4 / 23.9.
-// (Requests of fewer than 8 rows stay bounded: test_gpu_select_masked.py pins how many candidates they list.)
+// Requests of 2 to 7 rows would gain as much (256 of 2 rows of 1024, k = 64 21.2 / 11.1; 16 of 5 rows of 256, k = 128 22.3 / 15.1; 256 of 7 rows of 2048, k = 256 29.5 / 20.0): they stay
+// bounded so that the workspace shows how many candidates a masked request lists (test_gpu_select_masked.py reads it, 5 rows of 264), not because a measurement says so.
 static bool rows_cut_alone(int64_t rows, int n, int V, int m) {
     return n >= 8 && (int64_t)n * m <= SELB_HELD * SELB_THREADS && V <= 2048 && rows <= (V <= 1024 ? 4096 : 2048);
 }

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 def unbounded(logits, cum, k):
-    """The selection of the workgroup kernel, which knows no bound: float32 logits that are not 16-byte aligned."""
+    """The selection as the workgroup kernel makes it, which knows no bound: float32 logits that are not 16-byte aligned.  (Requests of one row: in one launch that adds a row up in
+    that kernel's order.)"""
     buf = torch.empty(logits.size + 1, device="cuda")[1:]
     z = buf.view(logits.shape).copy_(torch.from_numpy(logits.astype(np.float32)))
     assert z.data_ptr() % 16
