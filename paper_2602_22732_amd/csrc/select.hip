@@ -789,8 +789,9 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
 // and worked on when it is there, so what keeps the memory busy is the other wavefronts of the SIMD.  (A half-precision row used to be requested while the one before it was
 // worked on, in as many registers again: 95 instead of 71 for rows of 4096 tokens, 168 instead of 109 for 8192, five and three wavefronts instead of seven and
 // four, and the last row of each wavefront was requested twice.  65536 rows of 4096 tokens 157 us, 140 without; 32768 of 8192 150 and 127; 262144 of 8192 912 and 856; a million
-// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows of fewer than 2048 tokens: see launch_rows_sweep_kind.  Those are selections one after the other; one alone behind 600 MB
-// of writes elsewhere, a row ahead and without: 64 x 256 rows of 4096 76.9 us and 80.4, of 8192 132.4 and 134.6, 256 x 256 of 4096 208.9 and 198.1, 64 x 512 of 8192 197.3 and 187.9.)  Wavefronts walk the rows with the launch's
+// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows of fewer than 2048 tokens: see launch_rows_sweep_kind.  Those are selections one after the other.  One waited for, a row ahead and
+// without, on logits that no cache holds: 64 x 256 rows of 4096 62.1 us and 61.6, of 8192 96.3 and 90.5; right behind 600 MB of writes elsewhere, whose lines the caches still have to give back:
+// 78.9 and 82.2, 132.7 and 136.0, 128 x 256 of 4096 136.1 and 132.4.)  Wavefronts walk the rows with the launch's
 // stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
 // candidates, were 15 % slower).  A row with more than m candidates at the bound reserves m slots and is
 // put on the list for select_rows_wave, which gives it its own cut; this kernel carries none of that code or its registers.
