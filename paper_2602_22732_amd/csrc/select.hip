@@ -789,7 +789,7 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
 // and worked on when it is there, so what keeps the memory busy is the other wavefronts of the SIMD.  (A half-precision row used to be requested while the one before it was
 // worked on, in as many registers again: 95 instead of 71 for rows of 4096 tokens, 168 instead of 109 for 8192, five and three wavefronts instead of seven and
 // four, and the last row of each wavefront was requested twice.  65536 rows of 4096 tokens 157 us, 140 without; 32768 of 8192 150 and 127; 262144 of 8192 912 and 856; a million
-// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows of fewer than 2048 tokens: see launch_rows_sweep_kind.  Those are selections one after the other.  One waited for, a row ahead and
+// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows that do not fill their registers: see rows_walked.  Those are selections one after the other.  One waited for, a row ahead and
 // without, on logits that no cache holds: 64 x 256 rows of 4096 62.1 us and 61.6, of 8192 96.3 and 90.5; right behind 600 MB of writes elsewhere, whose lines the caches still have to give back:
 // 78.9 and 82.2, 132.7 and 136.0, 128 x 256 of 4096 136.1 and 132.4.)  Wavefronts walk the rows with the launch's
 // stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
@@ -1502,12 +1502,20 @@ static int launch_rows_sweep_as(const RowsLaunch &a, int64_t rows, int64_t rows_
                        a.n, a.V, a.m, a.cand, (const float *)a.rb, a.R, a.req_count, a.count_pitch, a.todo, a.todo_count);
     return GR4AD_OK;
 }
-// Float32: up to eight rows per wavefront, but 64 wavefronts per compute unit come first.  Half precision: one row per wavefront (whole selections, one and two rows: 65536 rows of
-// 4096 tokens 140 us and 142, 32768 of 8192 127 and 135, 262144 of 8192 856 and 847, four rows 873), except that many rows of fewer than 2048 tokens are walked so too, each requested
-// while the one before it is worked on: they are the shorter wait, and what a wavefront costs to start and to end counts.  One row / several with a row ahead, in us: 262144 rows of
-// 264 tokens 202.6 / 190.2, of 520 221.4 / 205.0, of 1024 222.9 / 216.5, of 1536 308.1 / 298.6, of 2040 344.7 / 326.0, but of 2048 264 / 272; 128000 rows of 264 106.5 / 97.5, of
-// 1024 117.4 / 108.0, of 1536 157.7 / 144.8; 131072 of 1024 116.8 / 118.3, of 2040 178.8 / 177.9; 81920 of 1024 83.9 / 85.3, of 1536 106.9 / 109.5; 32768 of 264 41.0 / 40.3.  (Where
-// no cache holds the logits: 262144 rows of 520 225.3 / 207.0, 128000 of 1024 119.8 / 110.8.)
+// Float32: up to eight rows per wavefront, but 64 wavefronts per compute unit come first.  Half precision: one row per wavefront, or as many as float32 with the next one requested while one
+// is worked on.  Whole selections, time of one row over that of several (rows_per: how many), the popular tokens of a decode and normal logits, 256, 512 and 847 rows per request:
+//   2048, 4096 and 8192 tokens   0.83 to 1.03, k = 1 to 512 (65536 rows of 4096 tokens, k = 512 128 us and 150; 262144 of 8192, k = 32 761 and 800): never
+//   1024 tokens                  rows_per 2 0.97 to 1.04, 3 0.96 to 1.10, 4 0.95 to 1.09, 7 and 8 0.95 to 1.20 (128000 rows, k = 128 93 us and 88)
+//   up to 1016 and up to 2040    rows_per 2 0.97 to 1.17, 3 to 5 0.97 to 1.17, 6 to 8 0.97 to 1.32 (128000 rows of 776, k = 32 88 us and 79; 160000 of 1584, k = 128 187 and 145)
+//   2056 to 4088                 rows_per 2 and 3 0.90 to 1.20, 4 to 8 0.94 to 1.23 (k = 512 on popular tokens 0.94 to 1.05; 65536 rows of 3096, k = 8 114 us and 100, k = 512 139 and 145)
+//   4104 to 8184                 rows_per 2 to 5 0.75 to 1.04, 7 and 8 0.95 to 1.22 for k <= 32, 0.84 to 1.22 above (160000 rows of 8000, k = 8 565 us and 495, k = 512 765 and 772)
+// (rows of so many tokens that every lane has all its pieces gain from the registers alone: see the kernel; what the others pay for each row they have a wavefront to themselves for is
+// not known).
+template <int VEC, bool FULL> static bool rows_walked(int64_t rows_per, int m) {
+    if (FULL) return VEC == 4 && rows_per >= 3;
+    if (VEC <= 8) return rows_per >= 2;
+    return VEC == 16 ? rows_per >= 4 && m <= 256 : rows_per >= 7 && m <= 64;
+}
 template <int VEC, bool FULL, typename LT>
 static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
     const int n_cu = compute_units();
@@ -1515,8 +1523,8 @@ static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
     int64_t rows_per = rows / ((int64_t)n_cu * 64);
     rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
     if constexpr (sizeof(LT) == 2) {
-        if constexpr (VEC == 4 || (VEC == 8 && !FULL))
-            if (rows_per >= (VEC == 4 && !FULL ? 2 : 6)) return launch_rows_sweep_as<VEC, FULL, true, LT>(a, rows, rows_per);
+        if constexpr (VEC == 4 || !FULL)
+            if (rows_walked<VEC, FULL>(rows_per, a.m)) return launch_rows_sweep_as<VEC, FULL, true, LT>(a, rows, rows_per);
         rows_per = 1;
     }
     return launch_rows_sweep_as<VEC, FULL, false, LT>(a, rows, rows_per);
