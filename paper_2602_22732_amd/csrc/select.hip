@@ -789,7 +789,7 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
 // and worked on when it is there, so what keeps the memory busy is the other wavefronts of the SIMD.  (A half-precision row used to be requested while the one before it was
 // worked on, in as many registers again: 95 instead of 71 for rows of 4096 tokens, 168 instead of 109 for 8192, five and three wavefronts instead of seven and
 // four, and the last row of each wavefront was requested twice.  65536 rows of 4096 tokens 157 us, 140 without; 32768 of 8192 150 and 127; 262144 of 8192 912 and 856; a million
-// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for many rows that do not fill their registers: see rows_walked.  Those are selections one after the other.  One waited for, a row ahead and
+// 3.51 and 3.34 ms, whole selections.  AHEAD keeps that for other rows and candidates than these: see rows_walked.  Those are selections one after the other.  One waited for, a row ahead and
 // without, on logits that no cache holds: 64 x 256 rows of 4096 62.1 us and 61.6, of 8192 96.3 and 90.5; right behind 600 MB of writes elsewhere, whose lines the caches still have to give back:
 // 78.9 and 82.2, 132.7 and 136.0, 128 x 256 of 4096 136.1 and 132.4.)  Wavefronts walk the rows with the launch's
 // stride (neighbouring rows in flight together; consecutive rows per wavefront, with one reservation for several rows'
@@ -1510,10 +1510,14 @@ static int launch_rows_sweep_as(const RowsLaunch &a, int64_t rows, int64_t rows_
 //   2056 to 4088                 rows_per 2 and 3 0.90 to 1.20, 4 to 8 0.94 to 1.23 (k = 512 on popular tokens 0.94 to 1.05; 65536 rows of 3096, k = 8 114 us and 100, k = 512 139 and 145)
 //   4104 to 8184                 rows_per 2 to 5 0.75 to 1.04, 7 and 8 0.95 to 1.22 for k <= 32, 0.84 to 1.22 above (160000 rows of 8000, k = 8 565 us and 495, k = 512 765 and 772)
 // (rows of so many tokens that every lane has all its pieces gain from the registers alone: see the kernel; what the others pay for each row they have a wavefront to themselves for is
-// not known).
+// not known).  And where the LDS of m staged candidates to a wavefront leaves no more wavefronts than the registers of a row ahead do, some five to a SIMD up to 4096 tokens and three above: k = 1024
+// 1.00 to 1.33 up to 4088 tokens, 0.95 to 1.04 for 4096, where k = 1400 gives 0.99 to 1.11; k = 2048 1.02 to 1.57, and above 4096 tokens 0.99 to 1.54, where k = 1400 gives 0.88 to 1.17
+// (160000 rows of 4096, k = 4096 1061 us and 829; 128000 of 8000, k = 2048 981 and 637).
 template <int VEC, bool FULL> static bool rows_walked(int64_t rows_per, int m) {
+    if (rows_per < 2) return false;
+    if (160 * 1024 / (4 * 8 * m) <= (VEC > 16 ? 2 : VEC == 16 && FULL ? 4 : 5)) return true;
     if (FULL) return VEC == 4 && rows_per >= 3;
-    if (VEC <= 8) return rows_per >= 2;
+    if (VEC <= 8) return true;
     return VEC == 16 ? rows_per >= 4 && m <= 256 : rows_per >= 7 && m <= 64;
 }
 template <int VEC, bool FULL, typename LT>
@@ -1523,8 +1527,7 @@ static int launch_rows_sweep_kind(const RowsLaunch &a, int64_t rows) {
     int64_t rows_per = rows / ((int64_t)n_cu * 64);
     rows_per = rows_per < 1 ? 1 : (rows_per > 8 ? 8 : rows_per);
     if constexpr (sizeof(LT) == 2) {
-        if constexpr (VEC == 4 || !FULL)
-            if (rows_walked<VEC, FULL>(rows_per, a.m)) return launch_rows_sweep_as<VEC, FULL, true, LT>(a, rows, rows_per);
+        if (rows_walked<VEC, FULL>(rows_per, a.m)) return launch_rows_sweep_as<VEC, FULL, true, LT>(a, rows, rows_per);
         rows_per = 1;
     }
     return launch_rows_sweep_as<VEC, FULL, false, LT>(a, rows, rows_per);

@@ -71,8 +71,9 @@ def test_one_launch_selects_what_two_do(V, k, most, kind, half):
 
 
 # half-precision rows walked several to a wavefront, the next one requested ahead, as one row to a wavefront: rows that do not fill the last workgroup, two to eight to a wavefront, pieces that
-# no or some of the lanes have, every lane (1024)
-@pytest.mark.parametrize("B,n,V,k", [(331, 101, 264, 150), (1300, 102, 72, 64), (520, 101, 1024, 200), (331, 101, 1032, 140), (1025, 129, 2040, 130), (651, 101, 2056, 256), (400, 170, 4088, 9), (901, 130, 4104, 64)])
+# no or some of the lanes have, every lane (1024; 2048, 4096 and 8192 with as many candidates as leave few wavefronts)
+@pytest.mark.parametrize("B,n,V,k", [(331, 101, 264, 150), (1300, 102, 72, 64), (520, 101, 1024, 200), (331, 101, 1032, 140), (1025, 129, 2040, 130), (651, 101, 2056, 256), (400, 170, 4088, 9), (901, 130, 4104, 64), (325, 101, 2048, 1030), (331, 101, 4096, 1300), (331, 101, 8192, 2049),
+                                     (331, 101, 4104, 2049)])
 def test_many_short_rows_as_few(B, n, V, k):
     g = torch.Generator(device="cuda").manual_seed(V)
     z = torch.randn(B, n, V, generator=g, device="cuda", dtype=torch.float16)
