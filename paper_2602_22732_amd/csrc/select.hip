@@ -504,7 +504,14 @@ __device__ __forceinline__ float first_row_bound(float x0, float bound, float c,
 // turned into sortable keys only for the survivors on the way out.
 #define WROW_BINS 1024
 #define WROW_LIST 512  // threshold-bin candidates ranked exactly; the list reuses the histogram's 4 KB
+#define WROW_SLOTS 544  // 8-byte slots of a wavefront's histogram with the 64 places in front (list), before the staged output
 #define WROW_FEW 64    // up to here at once (each lane reads the whole list: 230 candidates took 50 us)
+
+// (pointers that say they are into LDS: functions of their own would take generic ones, whose offsets the compiler may fold so that the address in the registers lies below the
+// memory's window, where the hardware finds the window by that address alone)
+typedef __attribute__((address_space(3))) unsigned long long LdsKey;
+typedef __attribute__((address_space(3))) int LdsInt;
+typedef __attribute__((address_space(3))) intx4 LdsInt4;
 
 __device__ __forceinline__ unsigned long long staged_to_key(unsigned long long st) {
     return ((unsigned long long)score_key(__uint_as_float((uint32_t)(st >> 32))) << 32) | (st & 0xFFFFFFFFull);
@@ -512,17 +519,20 @@ __device__ __forceinline__ unsigned long long staged_to_key(unsigned long long s
 
 // token held in register i of a lane: piece i / E of the lane, element i % E of the piece
 template <int E> __device__ __forceinline__ int wave_tok(int i, int lane) { return ((i / E) * 64 + lane) * E + (i % E); }
+// whether it is one of the row's: V % E == 0, so a piece is in or out as a whole.  (One mask to a piece: a mask to a token, kept over the rows, filled the scalar registers and was put away in
+// vector registers before the first row, and a wavefront often has only one: 36 to 206 of them, now 16 to 72.)
+template <int E> __device__ __forceinline__ bool wave_has(int i, int lane, int V) { return ((i / E) * 64 + lane) * E < V; }
 
 // exact fallback on the registers of one wavefront: radix selection on the score keys, two bits per step (ALONE: a function for each kernel that calls
 // it, or all of them get the registers of the one with the most)
 template <int VEC, int E, bool ALONE>
-__device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], int V, int m, uint32_t flat0, unsigned long long *stage, bool tied, uint32_t tie,
+__device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], int V, int m, uint32_t flat0, LdsKey *stage, bool tied, uint32_t tie,
                                                    int tie_krem) {
     const int lane = threadIdx.x % 64;
     uint32_t k_and = 0xFFFFFFFFu, k_or = 0u;
 #pragma unroll
     for (int i = 0; i < VEC * 4; i++)
-        if (wave_tok<E>(i, lane) < V) { const uint32_t k = score_key(sc[i]); k_and &= k; k_or |= k; }
+        if (wave_has<E>(i, lane, V)) { const uint32_t k = score_key(sc[i]); k_and &= k; k_or |= k; }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { k_and &= __shfl_xor(k_and, o, 64); k_or |= __shfl_xor(k_or, o, 64); }
     const uint32_t diff = k_and ^ k_or;
@@ -541,7 +551,7 @@ __device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], i
             for (int i = 0; i < VEC * 4; i++) {
                 const uint32_t k = score_key(sc[i]);
                 const uint32_t d = (k >> shb) & 3u;
-                const uint32_t act = (((k ^ prefix) & decided) == 0u && wave_tok<E>(i, lane) < V) ? 1u : 0u;
+                const uint32_t act = (((k ^ prefix) & decided) == 0u && wave_has<E>(i, lane, V)) ? 1u : 0u;
                 c12 += (d >= 1u ? act : 0u) + (d >= 2u ? (act << 16) : 0u);
                 c3 += d >= 3u ? act : 0u;
             }
@@ -593,87 +603,102 @@ __device__ __noinline__ void select_row_radix_wave(const float (&sc)[VEC * 4], i
     }
 }
 
-// The row's own top-m cut.  x[i]: the logit of token wave_tok<E>(i, lane), padding -inf; mx, lse: the row's maximum and
-// log-sum-exp; the m best (score, token) pairs go to dst.
-template <int VEC, bool FULL, int E, bool ALONE>
-__device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c, float mx, float lse, unsigned long long *__restrict__ dst,
-                                                   uint32_t flat0, uint32_t nflat, int V, int m, unsigned long long *list, int lane) {
-    constexpr int NX = VEC * 4;
-    // Rows of more than 2048 tokens have no registers left for another histogram (77 x 338 listed rows of 7016 tokens that are all masked 1048 us without, 1535 with)
-    constexpr bool AGAIN = VEC <= 8;
-    int *hist = (int *)list;
-    unsigned long long *stage = list + 512;
-    // scores from here on (padding stays -inf)
-    float mn = INFINITY;
+// The scores' bins, monotone in the score: WROW_LOW and up to WROW_BINS - 1 more; what lies below them all is in bin WROW_LOW - 1.
+#define WROW_LOW 64
+__device__ __forceinline__ uint32_t mid_u(uint32_t v, uint32_t lo, uint32_t hi) { return min(max(v, lo), hi); }
+__device__ __forceinline__ int score_bin(float x, float inv_w, float k0) {
+    return (int)mid_u((uint32_t)__builtin_fmaf(x, inv_w, k0), WROW_LOW - 1, WROW_LOW + WROW_BINS - 1);  // negative and NaN convert to 0
+}
+// The bin T of the m-th best score, by one wavefront: krem of its cnt scores are among the m best.  Scores below the bins are counted in a place per lane in front of them and are what
+// the bins leave of the row's V (masked tokens in one bin would be served one after the other: 64 x 64 rows of 1024 half-precision logits, 70 % of them masked, 25.2 us a selection, now 17.6).
+struct RowCut { int T, krem, cnt; };
+template <int VEC, bool FULL, int E>
+__device__ __forceinline__ RowCut find_cut(const float (&x)[VEC * 4], float inv_w, float k0, int V, int m, LdsInt *hist, int lane) {
 #pragma unroll
-    for (int i = 0; i < NX; i++) {
-        x[i] = wave_score<AGAIN>(c, x[i] - lse);
-        mn = fminf(mn, ((FULL || wave_tok<E>(i, lane) < V) && (!AGAIN || x[i] > -INFINITY)) ? x[i] : INFINITY);
+    for (int i = 0; i < WROW_BINS / 256; i++) ((LdsInt4 *)(hist + WROW_LOW))[i * 64 + lane] = (intx4){0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < VEC * 4; i++) {
+        const uint32_t at = mid_u((uint32_t)__builtin_fmaf(x[i], inv_w, k0), (uint32_t)lane, WROW_LOW + WROW_BINS - 1);
+        if (FULL || wave_has<E>(i, lane, V)) __hip_atomic_fetch_add(&hist[at], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    if (m >= V) {  // nothing to cut: every token is a candidate
+    // lane l owns the bins 1023-16l .. 1008-16l; inclusive scan from the top bin down
+    const LdsInt *own = hist + WROW_LOW + WROW_BINS - 16 - 16 * lane;
+    int h[16];
 #pragma unroll
-        for (int i = 0; i < NX; i++) {
-            const int v = wave_tok<E>(i, lane);
-            if (FULL || v < V) dst[v] = pack_candidate(x[i], flat0 + (uint32_t)v);
+    for (int i = 0; i < 4; i++) { const intx4 t = ((const LdsInt4 *)own)[i]; h[4 * i] = t[0]; h[4 * i + 1] = t[1]; h[4 * i + 2] = t[2]; h[4 * i + 3] = t[3]; }
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < 16; i++) mine += h[i];
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
+    int above = incl - mine, selT = WROW_LOW - 1, selK = m - incl, selC = 0;
+    const bool owner = above < m && incl >= m;
+    if (owner) {
+#pragma unroll
+        for (int i = 15; i >= 0; i--) {  // h[15] is this lane's top bin
+            if (selC == 0 && above + h[i] >= m) { selT = WROW_LOW + WROW_BINS - 16 - 16 * lane + i; selK = m - above; selC = h[i]; }
+            if (selC == 0) above += h[i];
         }
-        return;
+    } else {
+        selC = V - incl;
     }
-    // 1. histogram of the scores over equal-width bins of [lo, hi] (AGAIN: lo is the least that is not -inf, which a masked token has); the bin index is monotone in the score
-    float lo = -wave_max(-mn), hi = c + (mx - lse);
-    float inv_w = (hi > lo) ? ((float)WROW_BINS - 0.01f) / (hi - lo) : 0.0f;
-    float k0 = -lo * inv_w;
-    int T, krem, cntT;
+    const unsigned long long owners = __ballot(owner);
+    const int src_lane = owners ? __ffsll((long long)owners) - 1 : 63;  // (nobody's: below the bins, as lane 63 has it)
+    return {__shfl(selT, src_lane, 64), __shfl(selK, src_lane, 64), __shfl(selC, src_lane, 64)};
+}
+// bins above the cut's go straight to the staged output, its bin to the list (over the dead histogram) for exact ranking
+template <int VEC, bool FULL, int E>
+__device__ __forceinline__ void stage_cut(const float (&x)[VEC * 4], const RowCut &cut, float inv_w, float k0, uint32_t nflat, int V, int m, LdsKey *list,
+                                          LdsKey *stage, int lane) {
+    const int n_gt = m - cut.krem;
+    int base_gt = 0, base_eq = 0;
+    // The bins are recomputed, not kept: opaque copies of the two constants stop the compiler from holding
+    // all bin indices of the histogram pass in registers until here.
+    float inv_w2 = inv_w, k02 = k0;
+    asm volatile("" : "+v"(inv_w2), "+v"(k02));
+#pragma unroll
+    for (int i = 0; i < VEC * 4; i++) {
+        const int bi = score_bin(x[i], inv_w2, k02);
+        const bool ok = FULL || wave_has<E>(i, lane, V);
+        const bool gt = ok && bi > cut.T, eq = ok && bi == cut.T;
+        const unsigned long long mg = __ballot(gt), me = __ballot(eq);
+        const unsigned long long st = ((unsigned long long)__float_as_uint(x[i] + 0.0f) << 32) | (nflat - (uint32_t)((i / E) * 64 * E + (i % E)));
+        if (gt) stage[base_gt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0))] = st;
+        base_gt += __popcll(mg);
+        if (me != 0) {
+            if (eq) list[base_eq + __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0))] = st;
+            base_eq += __popcll(me);
+        }
+    }
+    // rank every listed candidate among the listed ones; the krem best go out
+    for (int i = lane; i < cut.cnt; i += 64) {
+        const unsigned long long st = list[i], key = staged_to_key(st);
+        int rank = 0;
+        for (int q = 0; q < cut.cnt; q++) rank += staged_to_key(list[q]) > key ? 1 : 0;
+        if (rank < cut.krem) stage[n_gt + rank] = st;
+    }
+}
+
+// A crowded bin: equal scores go by their tokens, others take another histogram over the span of this bin's alone, then an exact ranking.  numbers: the row's best score is below +inf, so all
+// are numbers or -inf.  Otherwise - a NaN logit or log-sum-exp, a cumulative score of +inf over masked tokens - some may be NaN, which minima and maxima pass over, and equal extremes would
+// not mean equal scores: the ranking at once.  In a function of its own
+// on scores in memory: in line it cost the other rows registers (172 for up to 2048 tokens, two wavefronts to a SIMD, now 157 and three).  Whole selections in us, in line with a mask to a
+// token / now: 326 requests of 329 rows of 8 tokens, k = 10 74.2 / 69.6; 138 of 606 rows of 56 76.1 / 68.9; 546 of 15 rows of 1760, half of them without a number 130.6 / 121.9.
+template <int VEC, int E>
+__device__ __noinline__ void select_row_crowded(const float (&sc)[VEC * 4], RowCut cut, float inv_w, float k0, bool numbers, uint32_t flat0, int V, int m,
+                                                LdsKey *list, LdsKey *stage) {
+    const int lane = threadIdx.x % 64;
     bool tied = false;
     float tie = 0.0f;
-    for (int zoom = 0;; zoom++) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) ((int4 *)hist)[i * 64 + lane] = make_int4(0, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < NX; i++) {
-            const uint32_t bi = min((uint32_t)__builtin_fmaf(x[i], inv_w, k0), (uint32_t)(WROW_BINS - 1));  // negative and NaN convert to 0
-            if (FULL || wave_tok<E>(i, lane) < V) atomicAdd(&hist[bi], 1);
-        }
-        // 2. lane l owns bins 1023-16l .. 1008-16l; inclusive scan from the top bin down finds the bin T of the m-th best score
-        int h[16];
-        {
-            const int4 *hp = (const int4 *)(hist + WROW_BINS - 16 - 16 * lane);
-#pragma unroll
-            for (int i = 0; i < 4; i++) { const int4 t = hp[i]; h[4 * i] = t.x; h[4 * i + 1] = t.y; h[4 * i + 2] = t.z; h[4 * i + 3] = t.w; }
-        }
-        int mine = 0;
-#pragma unroll
-        for (int i = 0; i < 16; i++) mine += h[i];
-        int incl = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
-        int above = incl - mine, selT = 0, selK = 0, selC = 0;
-        const bool owner = above < m && incl >= m;
-        if (owner) {
-#pragma unroll
-            for (int i = 15; i >= 0; i--) {  // h[15] is this lane's top bin
-                if (selC == 0 && above + h[i] >= m) { selT = WROW_BINS - 16 - 16 * lane + i; selK = m - above; selC = h[i]; }
-                if (selC == 0) above += h[i];
-            }
-        }
-        const int src_lane = __ffsll((long long)__ballot(owner)) - 1;
-        T = __shfl(selT, src_lane, 64);
-        krem = __shfl(selK, src_lane, 64);
-        cntT = __shfl(selC, src_lane, 64);
-        // (hi not below +inf: some score may be NaN - a NaN logit or log-sum-exp, a cumulative score of +inf over masked tokens - which the minima and maxima
-        // below pass over, so equal extremes would not mean equal scores.  With hi below +inf all scores are numbers or -inf.)
-        if (!AGAIN || cntT <= WROW_FEW || !(hi < INFINITY)) break;
-        // Crowded (masked tokens, or low finite masks that press the other scores into a few bins): equal scores go by their tokens, others take another
-        // histogram over the span of this bin's alone
+    for (int zoom = 0; zoom < 3 && numbers && cut.cnt > WROW_FEW; zoom++) {
         float lo_t = INFINITY, hi_t = -INFINITY, least = INFINITY;  // least: that is not -inf
-        float inv_w2 = inv_w, k02 = k0;
-        asm volatile("" : "+v"(inv_w2), "+v"(k02));
 #pragma unroll
-        for (int i = 0; i < NX; i++) {
-            const int bi = (int)min((uint32_t)__builtin_fmaf(x[i], inv_w2, k02), (uint32_t)(WROW_BINS - 1));
-            if (bi == T && (FULL || wave_tok<E>(i, lane) < V)) {
-                lo_t = fminf(lo_t, x[i]);
-                hi_t = fmaxf(hi_t, x[i]);
-                least = fminf(least, x[i] > -INFINITY ? x[i] : INFINITY);
+        for (int i = 0; i < VEC * 4; i++) {
+            if (score_bin(sc[i], inv_w, k0) == cut.T && wave_has<E>(i, lane, V)) {
+                lo_t = fminf(lo_t, sc[i]);
+                hi_t = fmaxf(hi_t, sc[i]);
+                least = fminf(least, sc[i] > -INFINITY ? sc[i] : INFINITY);
             }
         }
         lo_t = -wave_max(-lo_t);
@@ -681,46 +706,57 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
         least = -wave_max(-least);
         tied = lo_t == hi_t;
         tie = hi_t;
-        if (tied || zoom == 3 || !(hi_t >= least)) break;
+        if (tied || !(hi_t >= least)) break;
         const float finer = hi_t > least ? (float)(WROW_BINS - 3) / (hi_t - least) : 1.0f;
-        if (!(finer < INFINITY)) break;  // (T, krem and cntT stand for the bins of inv_w and k0)
+        if (!(finer < INFINITY)) break;  // (the cut stands for the bins of inv_w and k0)
         inv_w = finer;
-        k0 = 1.5f - least * inv_w;  // (-inf alone in bin 0)
+        k0 = (float)WROW_LOW + 0.5f - least * inv_w;  // (-inf below the bins)
+        cut = find_cut<VEC, false, E>(sc, inv_w, k0, V, m, (LdsInt *)list, lane);
     }
-    if (tied || cntT > WROW_LIST) {  // ties, or exact radix selection
+    if (tied || cut.cnt > WROW_LIST) select_row_radix_wave<VEC, E, false>(sc, V, m, flat0, stage, tied, score_key(tie), cut.krem);
+    else stage_cut<VEC, false, E>(sc, cut, inv_w, k0, 0xFFFFFFFFu - flat0 - (uint32_t)lane * (uint32_t)E, V, m, list, stage, lane);
+}
+
+// The row's own top-m cut.  x[i]: the logit of token wave_tok<E>(i, lane), padding -inf; mx, lse: the row's maximum and
+// log-sum-exp; the m best (score, token) pairs go to dst.
+template <int VEC, bool FULL, int E, bool ALONE>
+__device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c, float mx, float lse, unsigned long long *__restrict__ dst,
+                                                   uint32_t flat0, uint32_t nflat, int V, int m, LdsKey *list, int lane) {
+    constexpr int NX = VEC * 4;
+    // Rows of more than 2048 tokens have no registers left for another histogram (77 x 338 listed rows of 7016 tokens that are all masked 1048 us without, 1535 with)
+    constexpr bool AGAIN = VEC <= 8;
+    LdsInt *hist = (LdsInt *)list;
+    LdsKey *stage = list + WROW_SLOTS;
+    // scores from here on (padding stays -inf)
+    float mn = INFINITY;
+#pragma unroll
+    for (int i = 0; i < NX; i++) {
+        x[i] = wave_score<AGAIN>(c, x[i] - lse);
+        mn = fminf(mn, ((FULL || wave_has<E>(i, lane, V)) && (!AGAIN || x[i] > -INFINITY)) ? x[i] : INFINITY);
+    }
+    if (m >= V) {  // nothing to cut: every token is a candidate
+#pragma unroll
+        for (int i = 0; i < NX; i++) {
+            const int v = wave_tok<E>(i, lane);
+            if (FULL || wave_has<E>(i, lane, V)) dst[v] = pack_candidate(x[i], flat0 + (uint32_t)v);
+        }
+        return;
+    }
+    // A histogram of the scores over equal-width bins of [lo, hi] finds the bin of the m-th best; the bin index is monotone in the score.  (AGAIN: lo is the least that is not -inf, which a
+    // masked token has, and at most 64 below the best: a low finite mask would press the other scores into a few bins: 16 requests of 128 rows of 2048, k = 32 35.5 us, now 16.5)
+    float lo = -wave_max(-mn), hi = c + (mx - lse);
+    if (AGAIN) lo = fmaxf(lo, hi - 64.0f);
+    const float inv_w = (hi > lo) ? ((float)WROW_BINS - 0.01f) / (hi - lo) : 0.0f;
+    const float k0 = (float)WROW_LOW - lo * inv_w;
+    const RowCut cut = find_cut<VEC, FULL, E>(x, inv_w, k0, V, m, hist, lane);
+    if (cut.cnt > (AGAIN ? WROW_FEW : WROW_LIST)) {  // crowded (e.g. all logits equal)
         float sc[NX];  // a copy, so that only this branch keeps the scores in addressable memory
 #pragma unroll
         for (int i = 0; i < NX; i++) sc[i] = x[i];
-        select_row_radix_wave<VEC, E, ALONE>(sc, V, m, flat0, stage, tied, score_key(tie), krem);
+        if constexpr (AGAIN) select_row_crowded<VEC, E>(sc, cut, inv_w, k0, hi < INFINITY, flat0, V, m, list, stage);
+        else select_row_radix_wave<VEC, E, ALONE>(sc, V, m, flat0, stage, false, 0u, 0);
     } else {
-        // 3. bins above T go straight to the staged output, bin T to the list (over the dead histogram) for exact ranking
-        const int n_gt = m - krem;
-        int base_gt = 0, base_eq = 0;
-        // The bins are recomputed, not kept: opaque copies of the two constants stop the compiler from holding
-        // all NX bin indices of the histogram pass in registers until here.
-        float inv_w2 = inv_w, k02 = k0;
-        asm volatile("" : "+v"(inv_w2), "+v"(k02));
-#pragma unroll
-        for (int i = 0; i < NX; i++) {
-            const int bi = (int)min((uint32_t)__builtin_fmaf(x[i], inv_w2, k02), (uint32_t)(WROW_BINS - 1));
-            const bool ok = FULL || wave_tok<E>(i, lane) < V;
-            const bool gt = ok && bi > T, eq = ok && bi == T;
-            const unsigned long long mg = __ballot(gt), me = __ballot(eq);
-            const unsigned long long st = ((unsigned long long)__float_as_uint(x[i] + 0.0f) << 32) | (nflat - (uint32_t)((i / E) * 64 * E + (i % E)));
-            if (gt) stage[base_gt + __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0))] = st;
-            base_gt += __popcll(mg);
-            if (me != 0) {
-                if (eq) list[base_eq + __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0))] = st;
-                base_eq += __popcll(me);
-            }
-        }
-        // rank every listed candidate among the cntT listed ones; the krem best go out
-        for (int i = lane; i < cntT; i += 64) {
-            const unsigned long long st = list[i], key = staged_to_key(st);
-            int rank = 0;
-            for (int q = 0; q < cntT; q++) rank += staged_to_key(list[q]) > key ? 1 : 0;
-            if (rank < krem) stage[n_gt + rank] = st;
-        }
+        stage_cut<VEC, FULL, E>(x, cut, inv_w, k0, nflat, V, m, list, stage, lane);
     }
     for (int i = lane; i < m; i += 64) dst[i] = staged_to_key(stage[i]);
 }
@@ -736,11 +772,11 @@ __global__ __launch_bounds__(256, ALONE ? 1 : 2) void select_rows_wave(const LT 
                                                           int m, unsigned long long *__restrict__ cand, const int2 *__restrict__ todo,
                                                           const int *__restrict__ todo_count, bool numbers_first) {
     constexpr int E = LogitPiece<LT>::E, NX = VEC * 4, G = NX / E;
-    extern __shared__ unsigned long long wave_lds[];  // per wavefront: 512 slots of histogram / list, then m slots of staged output
+    extern __shared__ unsigned long long wave_lds[];  // per wavefront: WROW_SLOTS of histogram / list, then m slots of staged output
     const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     const int64_t count = todo ? (int64_t)*todo_count : rows;
-    unsigned long long *list = wave_lds + (size_t)wv * ((512 + m + 1) & ~1);  // even number of 8-byte slots: 16-byte accesses stay aligned
+    LdsKey *list = (LdsKey *)wave_lds + (size_t)wv * ((WROW_SLOTS + m + 1) & ~1);  // even number of 8-byte slots: 16-byte accesses stay aligned
     // whole wavefronts leave the loop; nothing below synchronises across wavefronts
     for (int64_t at = (int64_t)blockIdx.x * 4 + wv; at < count; at += nwaves) {
         int64_t vrow = at, dst_at = -1;
@@ -1464,10 +1500,10 @@ static int launch_rows_wave_as(const RowsLaunch &a, int64_t rows, int mode) {
     auto kern = select_rows_wave<VEC, FULL, ALONE, LT>;
     static bool attr_done = false;
     if (!attr_done) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (512 + GR4AD_MAX_BEAM + 2) * 8) != hipSuccess) return GR4AD_EHIP;
+        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (WROW_SLOTS + GR4AD_MAX_BEAM + 2) * 8) != hipSuccess) return GR4AD_EHIP;
         attr_done = true;
     }
-    const size_t lds = 4 * (size_t)((512 + a.m + 1) & ~1) * sizeof(unsigned long long);  // <= 4 * (4 KB + 32 KB)
+    const size_t lds = 4 * (size_t)((WROW_SLOTS + a.m + 1) & ~1) * sizeof(unsigned long long);  // <= 4 * (4.25 KB + 32 KB)
     int64_t grid = ceil_div64(rows, 4);  // one wavefront per row, four rows per workgroup
     if (mode == 1) {  // the list is short as a rule: a few workgroups per compute unit walk it
         const int n_cu = compute_units();

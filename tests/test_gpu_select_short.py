@@ -16,6 +16,8 @@ def logits(kind, B, n, V, g):
         z[:, :, : V // 3] = -1e9
     if kind == "tied":         # more equal scores than survive
         z = torch.round(z)
+    if kind == "wide":         # scores over some hundreds
+        z = z * 40
     return z
 
 
@@ -24,7 +26,7 @@ def logits(kind, B, n, V, g):
 @pytest.mark.parametrize("B,n,V,k", [(3, 1, 1, 1), (2, 1, 256, 256), (2, 1, 260, 16), (2, 1, 1024, 700), (2, 1, 4096, 1), (2, 1, 4100, 512), (2, 1, 8192, 4096), (2, 1, 5001, 600), (1, 1, 16384, 4096),
                                      (512, 1, 264, 3), (513, 1, 264, 3), (4, 16, 256, 16), (2, 65, 1024, 64), (64, 64, 1024, 64), (3, 3, 2048, 1500), (1, 128, 72, 64), (1, 129, 72, 64),
                                      (2, 4, 8, 8)])
-@pytest.mark.parametrize("kind", ["plain", "masked", "low", "tied"])
+@pytest.mark.parametrize("kind", ["plain", "masked", "low", "tied", "wide"])
 def test_short_selections(B, n, V, k, kind):
     g = torch.Generator().manual_seed(B + n * 7 + V + k)
     z, cum = logits(kind, B, n, V, g), -torch.sort(torch.rand(B, n, generator=g) * 6 + 3, dim=1).values
@@ -38,10 +40,11 @@ def test_short_selections(B, n, V, k, kind):
         kth = ref[b][order[k - 1]]
         got = ref[b][flat]
         fin = np.isfinite(got)
-        # float32 scores: a few roundings of numbers below 32; four half units in the last place of a score of about -1e9
-        tol = 1e-5 + 2.0**-22 * np.abs(got[fin]) * (np.abs(got[fin]) > 32)
-        assert np.array_equal(fin, np.isfinite(score[b])) and (np.abs(got[fin] - score[b][fin]) <= tol).all()
-        assert (got >= kth - (1e-5 + (2.0**-22 * abs(kth) if 32 < abs(kth) < np.inf else 0.0))).all() and (np.diff(score[b][fin]) <= 0).all()
+        # float32 scores: a few roundings of numbers below 32; four half units in the last place of larger ones, of the score or, in wide rows, of the log-sum-exp (about the best logit,
+        # up to 200: its own rounding, the difference's and the sum's)
+        unit = lambda x: 2.0**-22 * ((np.abs(x) * (np.abs(x) > 32)) + (abs(float(z[b].max())) if kind == "wide" else 0.0))
+        assert np.array_equal(fin, np.isfinite(score[b])) and (np.abs(got[fin] - score[b][fin]) <= 1e-5 + unit(got[fin])).all()
+        assert (got >= kth - (1e-5 + unit(kth) if np.isfinite(kth) else 0.0)).all() and (np.diff(score[b][fin]) <= 0).all()
         if kind == "low":  # every token that is not masked comes before those that are
             low = z[b].reshape(-1).numpy()[flat] < -1e8
             live = min(k, int((z[b] > -1e8).sum()))
