@@ -1232,7 +1232,14 @@ template <typename EACH> __device__ __forceinline__ void select_radix(EACH each,
         for (int i = tid; i < 2048; i += SELB_THREADS) sh.hist[i] = 0;
         __syncthreads();
         each([&](unsigned long long key) {
-            if (pass == 0 || (key >> shift) == prefix) atomicAdd(&sh.hist[(int)((key >> nshift) & ((1u << w) - 1))], 1);
+            if (pass == 0 || (key >> shift) == prefix) {
+                // (keys that share a digit throughout a wavefront - a row without a number, one score - count at once: one after the other: 341 requests of one
+                // row of 7560 such keys 102.9 us a selection, now 54.5)
+                const int d = (int)((key >> nshift) & ((1u << w) - 1)), first = __builtin_amdgcn_readfirstlane(d);
+                const unsigned long long here = __ballot(1);
+                if (__ballot(d != first)) atomicAdd(&sh.hist[d], 1);
+                else if (lane == __ffsll((long long)here) - 1) atomicAdd(&sh.hist[first], __popcll(here));
+            }
         });
         __syncthreads();
         // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
