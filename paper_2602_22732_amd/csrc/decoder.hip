@@ -838,7 +838,8 @@ int gr4ad_decode_batch(gr4ad_decoder *dec, const void *ctx, const int32_t *ctx_l
             else OP_TRY(dec, gemm(xn, rows, lw.wqkv_s, 3 * d, d, reads_norm(plain_epilogue(qkv_lvl(t, a), 3 * d))), "self-attention qkv");
             distinct = nullptr;  // from here on: every beam
             prof_rows(nullptr, 0, st);
-            // The first level has one position: the softmax of its one score is 1, the output its value, which the output projection reads in place
+            // The first level has one position: the softmax of its one score is 1 (of a score that is a number: query or key weights that hold NaN or infinities show from the second level
+            // on), the output its value, which the output projection reads in place
             // (a launch of 2 to 3 us per layer where they are short).
             const bool one = t == 0 && !f8;
             if (!one)

@@ -764,7 +764,7 @@ __device__ __forceinline__ void select_row_own_cut(float (&x)[VEC * 4], float c,
 // FULL: V == VEC*256, every register holds a token (the validity tests fold away).
 // todo / todo_count (both or neither): the launch visits only the listed rows {row, slot}; each gets its
 // own cut, written at slot `slot` of its request's segment.  Wavefronts walk their rows with the launch's stride.
-// The row and the cut's state need 105 (VEC 4) to 512 registers (VEC 32): with the 168 of three wavefronts per SIMD most of a row of 4096 and
+// The row and the cut's state need 119 (VEC 4) to 511 registers (VEC 32): with the 168 of three wavefronts per SIMD most of a row of 4096 and
 // 8192 tokens lived in scratch.  ALONE: one wavefront per SIMD, the shortest time of a row of 8192 tokens (m = 256: a few listed rows 17.7 us, 21.8 with two wavefronts
 // per SIMD, 22.2 with three).  Otherwise two: what a long list takes (32768 rows all listed 318 us with one, 206 with two, 226 with three).
 template <int VEC, bool FULL, bool ALONE, typename LT>
