@@ -1232,14 +1232,7 @@ template <typename EACH> __device__ __forceinline__ void select_radix(EACH each,
         for (int i = tid; i < 2048; i += SELB_THREADS) sh.hist[i] = 0;
         __syncthreads();
         each([&](unsigned long long key) {
-            if (pass == 0 || (key >> shift) == prefix) {
-                // (keys that share a digit throughout a wavefront - a row without a number, one score - count at once: one after the other: 341 requests of one
-                // row of 7560 such keys 102.9 us a selection, now 54.5)
-                const int d = (int)((key >> nshift) & ((1u << w) - 1)), first = __builtin_amdgcn_readfirstlane(d);
-                const unsigned long long here = __ballot(1);
-                if (__ballot(d != first)) atomicAdd(&sh.hist[d], 1);
-                else if (lane == __ffsll((long long)here) - 1) atomicAdd(&sh.hist[first], __popcll(here));
-            }
+            if (pass == 0 || (key >> shift) == prefix) atomicAdd(&sh.hist[(int)((key >> nshift) & ((1u << w) - 1))], 1);
         });
         __syncthreads();
         // thread t owns digits 2047-2t (hi) and 2046-2t (lo); scan from the top digit down
@@ -1360,7 +1353,8 @@ __global__ __launch_bounds__(SELB_THREADS) void select_request(const unsigned lo
 // The row's cut and the request's sort were two launches, the first of a single wavefront (or of 256 threads) per request.  Here 1024 threads hold the row, PER logits each:
 // maximum, exponentials and keys are formed side by side, and only the sum of the exponentials, whose order decides the last bit of every score, is
 // added up as the row kernels add it (ORDER_WAVE: select_rows_wave, a lane walks its pieces; else select_rows, a thread walks every 256th token), from LDS.
-template <int PER, bool ORDER_WAVE, typename LT>
+// LOG_P_FIRST: the operand order of wave_score<true>
+template <int PER, bool ORDER_WAVE, bool LOG_P_FIRST, typename LT>
 __global__ __launch_bounds__(SELB_THREADS) void select_single(const LT *__restrict__ logits, const float *__restrict__ cum, int V, int k, Survivors out) {
     constexpr int E = ORDER_WAVE ? LogitPiece<LT>::E : 1, J = PER / E;  // tokens of a load; loads of a thread
     __shared__ SelbShared sh;
@@ -1433,8 +1427,7 @@ __global__ __launch_bounds__(SELB_THREADS) void select_single(const LT *__restri
     uint32_t hi = 0u, lo = 0xFFFFFFFFu;
 #pragma unroll
     for (int i = 0; i < PER; i++) {
-        const float log_p = x[i] - lse, first = sum_a_first(c, log_p);
-        key[i] = token(i) < V ? pack_candidate(ORDER_WAVE && V <= 2048 ? wave_score<true>(c, log_p) : first, (uint32_t)token(i)) : 0ull;
+        key[i] = token(i) < V ? pack_candidate(wave_score<LOG_P_FIRST>(c, x[i] - lse), (uint32_t)token(i)) : 0ull;
         if (i == 0 && key[i]) hi = lo = (uint32_t)(key[i] >> 32);
     }
     int kp = 1;
@@ -1454,14 +1447,31 @@ __global__ __launch_bounds__(SELB_THREADS) void select_single(const LT *__restri
         __syncthreads();
         bitonic_sort_desc(sh.skeys, np);
     } else if (!select_binned<PER>(key, true, each, hi, lo, k, sh)) {
-        select_radix(each, k, kp, sh);
+        // (a row without a number, or of one score: its first tokens.  Counted digit by digit, one after the other, 341 requests of 7560 such tokens took 102.9 us, now 25.1)
+        hi = 0u, lo = 0xFFFFFFFFu;
+        each([&](unsigned long long ky) {
+            hi = max(hi, (uint32_t)(ky >> 32));
+            lo = min(lo, (uint32_t)(ky >> 32));
+        });
+        hi = wave_max_u(hi);
+        lo = ~wave_max_u(~lo);
+        if (lane == 0) { sh.span_hi[wv] = hi; sh.span_lo[wv] = lo; }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < SELB_THREADS / 64; q++) { hi = max(hi, sh.span_hi[q]); lo = min(lo, sh.span_lo[q]); }
+        if (hi == lo) {
+            for (int i = tid; i < k; i += SELB_THREADS) sh.skeys[i] = (unsigned long long)hi << 32 | (0xFFFFFFFFu - (uint32_t)i);
+            __syncthreads();
+        } else {
+            select_radix(each, k, kp, sh);
+        }
     }
     write_survivors(out, sh.skeys, b, 1, V, k);
 }
 
-template <int PER, bool ORDER_WAVE, typename LT>
+template <int PER, bool ORDER_WAVE, bool LOG_P_FIRST, typename LT>
 static int launch_select_single(const void *logits, const float *cum, int B, int V, int k, const Survivors &out, hipStream_t st) {
-    auto kern = select_single<PER, ORDER_WAVE, LT>;
+    auto kern = select_single<PER, ORDER_WAVE, LOG_P_FIRST, LT>;
     static bool attr_done = false;
     if (!attr_done) {
         if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PER * SELB_THREADS * (int)sizeof(float)) != hipSuccess) return GR4AD_EHIP;
@@ -1659,11 +1669,13 @@ int launch_select(const void *logits_any, int logits_f16, const float *cum, int 
     // (in one round of workgroups, of which two share a compute unit up to 8192 tokens; us, two launches / one: 64 requests of 256 tokens, k = 16 10.4 / 7.7; of 4096, k = 128
     // 15.8 / 9.0; of 8192, k = 256 23.4 / 11.5; of 16384, k = 128 21.1 / 13.8; but 1024 requests of 256 tokens 15.8 / 20.0, of 8192 36.8 / 41.2)
     if (n == 1 && B <= (wave_path ? 512 : 256)) {
-        if (wave_path && logits_f16) return launch_select_single<8, true, _Float16>(logits_any, cum, B, V, k, out, st);
-        if (wave_path && V <= 4096) return launch_select_single<4, true, float>(logits_any, cum, B, V, k, out, st);
-        if (wave_path) return launch_select_single<8, true, float>(logits_any, cum, B, V, k, out, st);
-        if (V <= 4096) return launch_select_single<4, false, float>(logits_any, cum, B, V, k, out, st);
-        return launch_select_single<16, false, float>(logits_any, cum, B, V, k, out, st);
+        if (wave_path && V <= 2048)
+            return logits_f16 ? launch_select_single<8, true, true, _Float16>(logits_any, cum, B, V, k, out, st) : launch_select_single<4, true, true, float>(logits_any, cum, B, V, k, out, st);
+        if (wave_path && logits_f16) return launch_select_single<8, true, false, _Float16>(logits_any, cum, B, V, k, out, st);
+        if (wave_path && V <= 4096) return launch_select_single<4, true, false, float>(logits_any, cum, B, V, k, out, st);
+        if (wave_path) return launch_select_single<8, true, false, float>(logits_any, cum, B, V, k, out, st);
+        if (V <= 4096) return launch_select_single<4, false, false, float>(logits_any, cum, B, V, k, out, st);
+        return launch_select_single<16, false, false, float>(logits_any, cum, B, V, k, out, st);
     }
     // Request-level bound (several rows per request, a cut smaller than the row): see row_bounds.  One row per request is its own cut: a bound would only
     // read the row twice.
